@@ -15,7 +15,7 @@
 #include "exat_mode12_v2.h"
 #include "exat_mode12_v3.h"
 #include "exat_mode12_v4.h"
-#include "exat_mode12_split.h"
+#include "exat_mode12_mp.h"
 
 using namespace exat;
 
@@ -35,7 +35,9 @@ struct exat_plan_s {
     void *Vfragz = nullptr; // bf16 plans: V in the fragment order of mode2_direct_bf16 (k_pack_v_frag with perm = 1)
     void *Vfrag = nullptr;  // bf16 plans: V in bf16 MFMA fragment order (k_pack_v_frag); fp32 plans: V in the order
                             // mode2_direct consumes (k_pack_v_direct)
-    _Float16 *Ufh = nullptr, *Ufl = nullptr, *Vfh = nullptr, *Vfl = nullptr;  // split plans: fp16 pieces in fragment order
+    void *Ump = nullptr, *Vmp = nullptr;   // fp32 plans: three bf16 pieces of U and V (MpParams)
+    void *Usp = nullptr, *Vsp = nullptr;   // split plans: two fp16 pieces
+    uint32_t *ranges = nullptr;            // value ranges noted by the pack kernels and k_mode12_mp (MPF_*)
     float *Vpack = nullptr, *Wpack = nullptr, *Q = nullptr;
     bool factors_set = false;
     // block-streamed state
@@ -127,7 +129,7 @@ int launch_mode12_inst(const Mode12Params &mp, int nk, hipStream_t st)
     }
     const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), cfg::LDS_BYTES, st, mp);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(mp.guard && grid > 512 ? 512 : grid)), dim3(256), cfg::LDS_BYTES, st, mp);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
@@ -193,29 +195,6 @@ int launch_v3_inst(const Mode12Params &mp, const GenSplitParams &gs, const UFrag
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
-// materialised source: fp32 stages are long (fp32 MFMA), two register sets suffice; bf16 stages are 16 times
-// shorter and want the tiles requested further ahead
-template <typename T, int NW, int RT, bool TAB = false>
-int launch_v3_mat(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int nk, hipStream_t st)
-{
-    constexpr int D = sizeof(T) == 2 ? 3 : 2, DXV = sizeof(T) == 2 ? 3 : 1;
-    return launch_v3_inst<T, NW, RT, SRC_MATERIALISED, 1, false, D, DXV, (NW + 3) / 4, false, TAB>(mp, gs, uf, nk, st);
-}
-
-// fp32 materialised source with mode 2 straight from the (transposed) accumulators; needs L % 32 == 0
-template <int NW, int RT>
-int launch_v3_mat_zt(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int nk, hipStream_t st)
-{
-    return launch_v3_inst<float, NW, RT, SRC_MATERIALISED, 1, false, 2, 1, (NW + 3) / 4, true>(mp, gs, uf, nk, st);
-}
-
-// the same over a slab of separate blocks (Mode12Params::xtab)
-template <int NW, int RT>
-int launch_v3_mat_zt_tab(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int nk, hipStream_t st)
-{
-    return launch_v3_inst<float, NW, RT, SRC_MATERIALISED, 1, false, 2, 1, (NW + 3) / 4, true, true>(mp, gs, uf, nk, st);
-}
-
 // bf16 generated source, 4 waves
 template <int RT>
 int launch_v3_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int ks, bool boxed, int nk, hipStream_t st)
@@ -245,12 +224,12 @@ int launch_v4_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const U
     return boxed ? launch_v4_inst<true>(mp, gs, uf, nk, st) : launch_v4_inst<false>(mp, gs, uf, nk, st);
 }
 
-// fp32 data on the fp16 matrix cores (two-piece split), materialised source, 4 waves x RT row tiles
-template <int RT, bool TAB = false>
-int launch_split(const Mode12Params &mp, const SplitParams &sp, int nk, hipStream_t st)
+template <int NP, int NWC, bool PTR>
+int launch_mp_inst(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
 {
-    typedef Mode12SplitCfg<4, RT> cfg;
-    auto kern = k_mode12_split<4, RT, 2, 4, TAB>;
+    typedef Mode12MpCfg<NP, NWC> cfg;
+    auto kern = k_mode12_mp<NP, NWC, PTR>;
+    static_assert(cfg::LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, cfg::LDS_BYTES) != hipSuccess) return EXAT_ERR_HIP;
@@ -258,44 +237,134 @@ int launch_split(const Mode12Params &mp, const SplitParams &sp, int nk, hipStrea
     }
     const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), cfg::LDS_BYTES, st, mp, sp);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), cfg::LDS_BYTES, st, mp, q);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
+}
+template <int NP, int NWC>
+int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
+{
+    // 32-bit offsets within a chunk of 128 fibres, unless X is a set of blocks or its fibres are millions of values long
+    const bool ptr = mp.xtab || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
+    return ptr ? launch_mp_inst<NP, NWC, true>(mp, q, nk, st) : launch_mp_inst<NP, NWC, false>(mp, q, nk, st);
+}
+template <int NP>
+int launch_mp(const Mode12Params &mp, const MpParams &q, int nwc, int nk, hipStream_t st)
+{
+    switch (nwc) {
+    case 4: return launch_mp_nwc<NP, 4>(mp, q, nk, st);
+    case 2: return launch_mp_nwc<NP, 2>(mp, q, nk, st);
+    default: return launch_mp_nwc<NP, 1>(mp, q, nk, st);
+    }
+}
+
+// Number of row groups of k_mode12_mp for T4 quads of row tiles and nk slices: a workgroup holds two to four quads, the
+// groups take the quads as evenly as they go, and a compute unit runs one workgroup at a time.
+int choose_groups(int T4, int64_t nk)
+{
+    int best = 1;
+    double cost = 0.0;
+    for (int G = (T4 + 3) / 4; G <= (T4 + 1) / 2; G++) {
+        // rounds of the chip x (the quads of a group + about half a quad's time for what a group costs by itself)
+        const double c = std::max((double)((nk * G + 255) / 256), (double)nk * G / 256.0) * ((double)T4 / G + 0.5);
+        if (G == (T4 + 3) / 4 || c < 0.97 * cost) { best = G; cost = c; }
+    }
+    return best;
+}
+
+// mode 3 over the slices of a call whose mode-1/2 launches left 2^kshift partial Q per slice
+int run_mode3(exat_plan_s *pl, const Mode12Params &mp, int kshift, float *Yout, int accumulate, unsigned char *flag, hipStream_t st)
+{
+    Mode3Params m3;
+    m3.kshift = kshift; m3.ranges = pl->ranges;
+    m3.Q = pl->Q; m3.W = pl->Wpack; m3.Y = Yout;
+    m3.L = pl->d.L; m3.M = pl->d.M; m3.N = pl->d.N; m3.PL = pl->PL; m3.PLpad = pl->PLpad >> kshift; m3.Mpad = pl->Mpad;
+    m3.Npad = pl->Npad;
+    m3.K = pl->d.K; m3.k0 = mp.k0; m3.k1 = mp.k1; m3.accumulate = accumulate; m3.flag = flag;
+    const int64_t ntile = ((int64_t)pl->PL * pl->Mpad + 31) / 32;
+    dim3 grid((unsigned)ntile, (unsigned)((pl->Npad + 63) / 64));
+    const bool longk = ((m3.k1 - m3.k0) << kshift) > 512LL * M3_WAVES - 8;   // a wave's slab (rounded up to even) may exceed 512
+    if (pl->Npad % 64 == 0) {
+        if (longk) hipLaunchKernelGGL((k_mode3<2, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
+        else hipLaunchKernelGGL((k_mode3<2, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
+    } else {  // 32-column tiles, so that no launch carries an idle second tile
+        grid.y = (unsigned)(pl->Npad / 32);
+        if (longk) hipLaunchKernelGGL((k_mode3<1, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
+        else hipLaunchKernelGGL((k_mode3<1, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
+    }
+    if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
+    if (pl->timing) {
+        if (hipEventRecord(pl->evr[pl->timed_calls % exat_plan_s::kTimeRing][2], st) != hipSuccess) return EXAT_ERR_HIP;
+        pl->timed_calls++;
+    }
+    return EXAT_OK;
+}
+
+// materialised X: modes 1 and 2 (k_mode12_mp, and behind it the generic kernel for values outside the ranges of the piece sums),
+// then mode 3
+int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yout, int accumulate, hipStream_t st, unsigned char *flag)
+{
+    const bool bf = pl->d.in_dtype == EXAT_BF16;
+    const int64_t nk = mp.k1 - mp.k0;
+    mp.U = pl->Upack; mp.V = pl->Vpack; mp.Q = pl->Q;
+    mp.I = pl->d.I; mp.Ipad = pl->Ipad; mp.Jpad = pl->Jpad;
+    mp.L = pl->d.L; mp.PL = pl->PL; mp.PLpad = pl->PLpad; mp.Mpad = pl->Mpad; mp.MT = pl->MT;
+    hipEvent_t *ev = pl->evr[pl->timed_calls % exat_plan_s::kTimeRing];
+    if (pl->timing && hipEventRecord(ev[0], st) != hipSuccess) return EXAT_ERR_HIP;
+    int rc = EXAT_OK, kshift = 0;
+    if (pipelined) {
+        // split-precision plans take the fp16 pieces for aligned tensors and blocks with whole 32-value stages of i, and the
+        // fp32 path's pieces (no range limit) for the rest
+        const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
+        const int T = (pl->PL + 31) / 32;
+        const int nwc = T <= 4 ? 4 : (T <= 8 ? 2 : 1);
+        kshift = nwc == 4 ? 2 : (nwc == 2 ? 1 : 0);
+        MpParams q;
+        q.nig = pl->Ipad / 16; q.T4 = (T + 3) / 4;
+        q.Uf = bf ? pl->Ufrag : (split ? pl->Usp : pl->Ump);
+        q.Vf = bf ? pl->Vfragz : (split ? pl->Vsp : pl->Vmp);
+        q.vmt = bf ? 2 : pl->MT;
+        q.flags = split ? nullptr : pl->ranges;
+        // chunks of 128 fibres from j0 down to a multiple of 16, as long as V's padding covers the last one
+        q.ja0 = mp.j0 & ~(int64_t)15;
+        if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
+        mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk);
+        rc = bf ? launch_mp<1>(mp, q, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, nwc, (int)nk, st) : launch_mp<3>(mp, q, nwc, (int)nk, st));
+        if (rc != EXAT_OK) return rc;
+        mp.guard = q.flags;
+        mp.qzero0 = pl->PLpad >> kshift;
+    }
+    if (!pipelined || mp.guard) {
+        const int rt = choose_rt(pl, false);
+        mp.G = (pl->PL + 128 * rt - 1) / (128 * rt);
+        rc = bf ? launch_mode12_bf16<SRC_MATERIALISED>(rt, mp, (int)nk, st) : launch_mode12_f32<SRC_MATERIALISED>(rt, mp, (int)nk, st);
+        if (rc != EXAT_OK) return rc;
+    }
+    if (pl->timing && hipEventRecord(ev[1], st) != hipSuccess) return EXAT_ERR_HIP;
+    return run_mode3(pl, mp, kshift, Yout, accumulate, flag, st);
 }
 
 // fills the plan-dependent part of the parameters and launches mode 1+2 followed by mode 3
 int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int accumulate, hipStream_t st, unsigned char *flag = nullptr)
 {
-    // The pipelined kernels need whole 64-byte stages of i inside the box (materialised source) or a factor
-    // rank that fits their generator (generated source); everything else takes the generic kernel.
-    // EXAT_PIPELINED=0 forces the generic kernel (a testing aid).
+    // Materialised sources run k_mode12_mp at any size and alignment.  Generated sources run the pipelined kernels if the factor
+    // rank fits their generator, else the generic kernel.  EXAT_PIPELINED=0 forces the generic kernel (a testing aid).
     const bool bf = pl->d.in_dtype == EXAT_BF16;
-    const int ei = bf ? 32 : 16;
     bool pipelined = env_int("EXAT_PIPELINED", 1) != 0;
-    if (generated) pipelined = pipelined && mp.R <= 64;
-    else pipelined = pipelined && mp.x_vec && (mp.i0 % ei == 0) && ((mp.i1 - mp.i0) % ei == 0);
-    // only k_mode12_v3<..., TAB> and k_mode12_split<..., TAB> read the block table
-    if (mp.xtab && (generated || (pl->d.in_dtype == EXAT_F32_SPLIT ? (mp.i0 % 32 != 0 || (mp.i1 - mp.i0) % 32 != 0) : !pipelined))) return EXAT_ERR_STATE;
+    if (!generated) return run_materialised(pl, mp, pipelined, Yout, accumulate, st, flag);
+    pipelined = pipelined && mp.R <= 64;
     int rt = choose_rt(pl, generated);
     if (pipelined) {
         // rt = 128-row units of the workgroup tile: 2 = 4 waves x 2 row tiles, 3 = 4 waves x 3, 4 = 8 waves x 2
         const int forced = env_int("EXAT_RT", 0);
         rt = (forced == 2 || forced == 4) ? forced : (pl->PL > 256 ? 4 : 2);
-        // bf16 generated source: 4 waves x 3 row tiles (384 stacked rows), one wave per SIMD, unless told otherwise
-        if (bf && generated && pl->PL > 256 && forced != 2 && forced != 4) rt = 3;
-        // the bf16 generator has no 8-wave build
-        if (bf && generated && rt == 4) rt = 3;
-        // bf16 materialised source: the 8-wave build spills around its mode-2 phase and measured 2.5 times slower than the
-        // 4-wave one on a 10000 x 10000 x 256 slab (621 against 251 ms)
-        if (bf && !generated && forced == 0) rt = 2;
-        // a small box (one streamed block) with 512-row groups would not give every compute unit a workgroup
-        if (!generated && rt == 4 && forced == 0 && (mp.k1 - mp.k0) * ((pl->PL + 511) / 512) < 256) rt = 2;
+        // bf16: 4 waves x 3 row tiles (384 stacked rows), one wave per SIMD, unless told otherwise; there is no 8-wave build
+        if (bf && pl->PL > 256 && forced != 2 && forced != 4) rt = 3;
+        if (bf && rt == 4) rt = 3;
     }
     // the LDS-staged fp32 generator kernel (k_mode12_v2) addresses its U tile with 32-bit element offsets of up to
     // 255 rows: beyond 2^23 padded columns the generic kernel takes over
     const bool f32_gen_v3 = rt == 4 && pl->d.L % 32 == 0 && env_int("EXAT_F32_GEN_V3", 1);
-    if (pipelined && generated && !bf && !f32_gen_v3 && pl->Ipad > (1LL << 23)) { pipelined = false; rt = choose_rt(pl, generated); }
-    // fp32 data on the fp16 matrix cores: materialised sources with whole 32-value stages of i inside the box
-    const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && !generated && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
+    if (pipelined && !bf && !f32_gen_v3 && pl->Ipad > (1LL << 23)) { pipelined = false; rt = choose_rt(pl, generated); }
     const int rows = 128 * rt;
     mp.U = pl->Upack; mp.V = pl->Vpack; mp.Q = pl->Q;
     mp.Vd = pl->d.in_dtype == EXAT_BF16 ? nullptr : (const float *)pl->Vfrag;
@@ -306,7 +375,7 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
     int rc;
     GenSplitParams gs;
     gs.Asp = pl->Asplit; gs.Irows = pl->Ipad; gs.Rpad = 32 * ((mp.R + 31) / 32);
-    if (pipelined && generated) {
+    if (pipelined) {
         const int64_t n = gs.Irows * gs.Rpad;
         if (bf) hipLaunchKernelGGL(k_split_a<__bf16>, dim3(grid_for(n)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
         else hipLaunchKernelGGL(k_split_a<float>, dim3(grid_for(n)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
@@ -314,34 +383,12 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
     }
     hipEvent_t *ev = pl->evr[pl->timed_calls % exat_plan_s::kTimeRing];
     if (pl->timing && hipEventRecord(ev[0], st) != hipSuccess) return EXAT_ERR_HIP;
-    if (split) {
-        SplitParams sp;
-        sp.Ufh = pl->Ufh; sp.Ufl = pl->Ufl; sp.nig = pl->Ipad / 16; sp.Vfh = pl->Vfh; sp.Vfl = pl->Vfl;
-        // 256-row groups (one wave per SIMD, 2 row tiles; measured a little faster than 384-row groups); a
-        // remainder of at most 128 rows gets a launch of its own with one row tile per wave
-        const int full = pl->PL / 256, rem = pl->PL - 256 * full;
-        rc = EXAT_OK;
-        if (full > 0 || rem > 128) { mp.G = rem > 128 ? full + 1 : full; rc = mp.xtab ? launch_split<2, true>(mp, sp, nk, st) : launch_split<2>(mp, sp, nk, st); }
-        if (rc == EXAT_OK && rem > 0 && rem <= 128) {
-            mp.row_base = 256 * full; mp.G = 1;
-            rc = mp.xtab ? launch_split<1, true>(mp, sp, nk, st) : launch_split<1>(mp, sp, nk, st);
-        }
-    } else if (pipelined) {
-        const bool boxed = generated && (mp.i0 != 0 || mp.i1 != pl->d.I);
+    if (pipelined) {
+        const bool boxed = (mp.i0 != 0 || mp.i1 != pl->d.I);
         const int ks = gs.Rpad / 32;
         UFragParams uf;
         uf.Uf = pl->Ufrag; uf.nig = pl->Ipad / (bf ? 16 : 8); uf.Vf = pl->Vfrag; uf.Vz = pl->Vfragz;
-        if (!generated) {
-            if (mp.xtab) {   // a slab of blocks (exat_compress_blocks has checked that these kernels apply)
-                if (bf) rc = rt == 4 ? launch_v3_mat<__bf16, 8, 2, true>(mp, gs, uf, nk, st) : launch_v3_mat<__bf16, 4, 2, true>(mp, gs, uf, nk, st);
-                else if (pl->d.L % 32 == 0 && env_int("EXAT_ZT", 1))
-                    rc = rt == 4 ? launch_v3_mat_zt_tab<8, 2>(mp, gs, uf, nk, st) : launch_v3_mat_zt_tab<4, 2>(mp, gs, uf, nk, st);
-                else rc = rt == 4 ? launch_v3_mat<float, 8, 2, true>(mp, gs, uf, nk, st) : launch_v3_mat<float, 4, 2, true>(mp, gs, uf, nk, st);
-            } else if (bf) rc = rt == 4 ? launch_v3_mat<__bf16, 8, 2>(mp, gs, uf, nk, st) : launch_v3_mat<__bf16, 4, 2>(mp, gs, uf, nk, st);
-            else if (pl->d.L % 32 == 0 && env_int("EXAT_ZT", 1))
-                rc = rt == 4 ? launch_v3_mat_zt<8, 2>(mp, gs, uf, nk, st) : launch_v3_mat_zt<4, 2>(mp, gs, uf, nk, st);
-            else rc = rt == 4 ? launch_v3_mat<float, 8, 2>(mp, gs, uf, nk, st) : launch_v3_mat<float, 4, 2>(mp, gs, uf, nk, st);
-        } else if (bf && pl->PL > 256 && ks == 1 && env_int("EXAT_RT", 0) == 0 && pl->Ipad < (1LL << 21)) {
+        if (bf && pl->PL > 256 && ks == 1 && env_int("EXAT_RT", 0) == 0 && pl->Ipad < (1LL << 21)) {
             // 512-row groups, two waves per SIMD (k_mode12_v4): the tile is generated once per group, so large groups
             // are what keeps the generator's vector work below the MFMA work.  Factor ranks above 32 would need twice
             // the generator registers, which this build does not have: they take the 384-row kernel below.  The kernel
@@ -381,38 +428,22 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
             rc = launch_v2_gen_f32<4, 2>(mp, gs, ks, boxed, nk, st);
         }
     } else if (pl->d.in_dtype == EXAT_BF16)
-        rc = generated ? launch_mode12_bf16<SRC_GENERATED>(rt, mp, nk, st) : launch_mode12_bf16<SRC_MATERIALISED>(rt, mp, nk, st);
+        rc = launch_mode12_bf16<SRC_GENERATED>(rt, mp, nk, st);
     else
-        rc = generated ? launch_mode12_f32<SRC_GENERATED>(rt, mp, nk, st) : launch_mode12_f32<SRC_MATERIALISED>(rt, mp, nk, st);
+        rc = launch_mode12_f32<SRC_GENERATED>(rt, mp, nk, st);
     if (rc != EXAT_OK) return rc;
     if (pl->timing && hipEventRecord(ev[1], st) != hipSuccess) return EXAT_ERR_HIP;
-    Mode3Params m3;
-    m3.Q = pl->Q; m3.W = pl->Wpack; m3.Y = Yout;
-    m3.L = pl->d.L; m3.M = pl->d.M; m3.N = pl->d.N; m3.PL = pl->PL; m3.PLpad = pl->PLpad; m3.Mpad = pl->Mpad;
-    m3.Npad = pl->Npad;
-    m3.K = pl->d.K; m3.k0 = mp.k0; m3.k1 = mp.k1; m3.accumulate = accumulate; m3.flag = flag;
-    const int64_t ntile = ((int64_t)pl->PL * pl->Mpad + 31) / 32;
-    dim3 grid((unsigned)ntile, (unsigned)((pl->Npad + 63) / 64));
-    const bool longk = (m3.k1 - m3.k0) > 512LL * M3_WAVES - 8;   // a wave's slab (rounded up to even) may exceed 512
-    if (pl->Npad % 64 == 0) {
-        if (longk) hipLaunchKernelGGL((k_mode3<2, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-        else hipLaunchKernelGGL((k_mode3<2, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-    } else {  // 32-column tiles, so that no launch carries an idle second tile
-        grid.y = (unsigned)(pl->Npad / 32);
-        if (longk) hipLaunchKernelGGL((k_mode3<1, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-        else hipLaunchKernelGGL((k_mode3<1, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-    }
-    if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
-    if (pl->timing) {
-        if (hipEventRecord(ev[2], st) != hipSuccess) return EXAT_ERR_HIP;
-        pl->timed_calls++;
-    }
-    return EXAT_OK;
+    return run_mode3(pl, mp, 0, Yout, accumulate, flag, st);
 }
 
 __global__ void k_clear_flags(unsigned char *flags, int n)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) flags[i] = 0;
+}
+
+__global__ void k_clear_words(uint32_t *w, int n)
+{
+    if ((int)threadIdx.x < n) w[threadIdx.x] = 0;
 }
 
 // up to 32 entries of the block-pointer table per launch, carried in the kernel arguments
@@ -481,9 +512,11 @@ int exat_plan_create(exat_plan_t *plan, const exat_desc_t *desc)
         (desc->in_dtype == EXAT_BF16 && (hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess ||
                                          hipMalloc(&pl->Vfragz, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess)) ||
         (desc->in_dtype != EXAT_BF16 && hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess) ||
-        (desc->in_dtype == EXAT_F32_SPLIT &&
-         (hipMalloc((void **)&pl->Ufh, (size_t)pl->PLpad * pl->Ipad * 2) != hipSuccess || hipMalloc((void **)&pl->Ufl, (size_t)pl->PLpad * pl->Ipad * 2) != hipSuccess ||
-          hipMalloc((void **)&pl->Vfh, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess || hipMalloc((void **)&pl->Vfl, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess)) || hipMalloc((void **)&pl->Vpack, vb) != hipSuccess ||
+        (desc->in_dtype != EXAT_BF16 && (hipMalloc(&pl->Ump, (size_t)pl->PLpad * pl->Ipad * 6) != hipSuccess ||
+                                         hipMalloc(&pl->Vmp, (size_t)desc->P * pl->Mpad * pl->Jpad * 6) != hipSuccess)) ||
+        (desc->in_dtype == EXAT_F32_SPLIT && (hipMalloc(&pl->Usp, (size_t)pl->PLpad * pl->Ipad * 4) != hipSuccess ||
+                                              hipMalloc(&pl->Vsp, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess)) ||
+        hipMalloc((void **)&pl->ranges, MPF_WORDS * sizeof(uint32_t)) != hipSuccess || hipMalloc((void **)&pl->Vpack, vb) != hipSuccess ||
         hipMalloc((void **)&pl->Wpack, wb) != hipSuccess || hipMalloc((void **)&pl->Q, qb) != hipSuccess) {
         (void)hipGetLastError();
         exat_plan_destroy(pl);
@@ -507,7 +540,7 @@ int exat_plan_destroy(exat_plan_t pl)
     }
     if (!pl) return EXAT_OK;
     (void)hipFree(pl->Upack); (void)hipFree(pl->Ufrag); (void)hipFree(pl->Vfrag); (void)hipFree(pl->Vfragz);
-    (void)hipFree(pl->Ufh); (void)hipFree(pl->Ufl); (void)hipFree(pl->Vfh); (void)hipFree(pl->Vfl); (void)hipFree(pl->Vpack); (void)hipFree(pl->Wpack); (void)hipFree(pl->Q);
+    (void)hipFree(pl->Ump); (void)hipFree(pl->Vmp); (void)hipFree(pl->Usp); (void)hipFree(pl->Vsp); (void)hipFree(pl->ranges); (void)hipFree(pl->Vpack); (void)hipFree(pl->Wpack); (void)hipFree(pl->Q);
     (void)hipFree(pl->slots); (void)hipFree(pl->used_dev); (void)hipFree(pl->Asplit); (void)hipFree((void *)pl->xtab);
     for (auto &tr : pl->evr)
         for (hipEvent_t e : tr) if (e) (void)hipEventDestroy(e);
@@ -523,6 +556,7 @@ int exat_set_factors(exat_plan_t pl, const float *U, int64_t ldU, const float *V
     if (ldU < d.I || ldV < d.J || ldW < d.K) return EXAT_ERR_SHAPE;
     hipStream_t st = (hipStream_t)stream;
     const int64_t nu = (int64_t)pl->PLpad * pl->Ipad, nv = (int64_t)d.P * pl->Mpad * pl->Jpad, nw = (int64_t)d.P * d.K * pl->Npad;
+    hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, st, pl->ranges, (int)MPF_WORDS);
     if (d.in_dtype == EXAT_BF16) {
         hipLaunchKernelGGL(k_pack_u<__bf16>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (__bf16 *)pl->Upack, pl->PLpad, pl->Ipad);
         hipLaunchKernelGGL(k_pack_u_frag<__bf16>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (__bf16 *)pl->Ufrag, pl->PLpad / 32, pl->Ipad / 16);
@@ -531,9 +565,12 @@ int exat_set_factors(exat_plan_t pl, const float *U, int64_t ldU, const float *V
         hipLaunchKernelGGL(k_pack_v<__bf16>, dim3(grid_for(nv)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, pl->Vpack, pl->Mpad, pl->Jpad);
         hipLaunchKernelGGL(k_pack_w<__bf16>, dim3(grid_for(nw)), dim3(256), 0, st, W, ldW, d.P, d.N, d.K, pl->Wpack, pl->Npad);
     } else {
+        const int64_t nig = pl->Ipad / 16, nj16 = pl->Jpad / 16, nu8 = (int64_t)(pl->PLpad / 32) * nig * 64, nv8 = (int64_t)d.P * nj16 * pl->MT * 64;
+        hipLaunchKernelGGL(k_pack_u_mp<3>, dim3(grid_for(nu8)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (u32x4 *)pl->Ump, pl->PLpad / 32, nig, pl->ranges);
+        hipLaunchKernelGGL(k_pack_v_mp<3>, dim3(grid_for(nv8)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (u32x4 *)pl->Vmp, pl->MT, nj16, pl->ranges);
         if (d.in_dtype == EXAT_F32_SPLIT) {
-            hipLaunchKernelGGL(k_pack_u_split, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, pl->Ufh, pl->Ufl, pl->PLpad / 32, pl->Ipad / 16);
-            hipLaunchKernelGGL(k_pack_v_split, dim3(grid_for((int64_t)d.P * pl->Jpad * 64)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, pl->Vfh, pl->Vfl, pl->Jpad);
+            hipLaunchKernelGGL(k_pack_u_mp<2>, dim3(grid_for(nu8)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (u32x4 *)pl->Usp, pl->PLpad / 32, nig, (uint32_t *)nullptr);
+            hipLaunchKernelGGL(k_pack_v_mp<2>, dim3(grid_for(nv8)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (u32x4 *)pl->Vsp, pl->MT, nj16, (uint32_t *)nullptr);
         }
         hipLaunchKernelGGL(k_pack_u<float>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (float *)pl->Upack, pl->PLpad, pl->Ipad);
         hipLaunchKernelGGL(k_pack_u_frag<float>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (float *)pl->Ufrag, pl->PLpad / 32, pl->Ipad / 8);
@@ -629,7 +666,7 @@ int exat_compress_blocks(exat_plan_t pl, const void *const *Xblk, int32_t bj0, i
         for (int64_t bj = bj0; bj < bj1; bj++)
             for (int64_t bi = 0; bi < nbi; bi++)
                 if (pl->submitted[(size_t)(bi + nbi * (bj + nbj * bk))]) return EXAT_ERR_STATE;
-    // One launch over the slab needs the kernels that read X through a table of block pointers: whole stages of i
+    // One launch over the slab reads X through a table of block pointers: whole stages of i
     // (16 values for fp32 plans, 32 for bf16 and split-fp16 plans) and whole 128-fibre chunks inside every block,
     // 16-byte aligned blocks.  Any other slab is compressed block by block.
     const int ei = d.in_dtype == EXAT_F32 ? 16 : 32;

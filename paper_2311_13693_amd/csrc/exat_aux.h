@@ -1,7 +1,7 @@
 // Small kernels around the fused mode-1/2 kernel: operand packing (stacking, padding,
 // bf16 rounding), the mode-3 contraction, the block merge and the stand-alone block generator.
 #pragma once
-#include "exat_device.h"
+#include "exat_common.h"
 
 namespace exat {
 
@@ -53,12 +53,14 @@ __global__ void k_pack_w(const float *src, int64_t ld, int P, int N, int64_t K, 
 // sums into fp64 totals every KFLUSH values of k so that the summation error does not grow
 // with the extent of K.
 struct Mode3Params {
-    const float *Q;  // [nk][PLpad][Mpad]
+    const float *Q;  // [nk << kshift][PLpad][Mpad]
     const float *W;  // [P][K][Npad]
     float *Y;        // Y[l + L*(m + M*(n + N*p))]
     int L, M, N, PL, PLpad, Mpad, Npad;
     int64_t K, k0, k1;
     int accumulate;
+    int kshift;           // slice k left 2^kshift partial Q, which follow each other
+    uint32_t *ranges;     // if not null, the MPF_CALL_WORDS first words are cleared for the next call
     unsigned char *flag;  // if not null, set to 1 by the launch (block streaming: "this slot holds a partial result")
 };
 
@@ -77,18 +79,19 @@ __global__ __launch_bounds__(64 * M3_WAVES, LONGK ? 1 : 2) void k_mode3(const Mo
     __shared__ float part[M3_WAVES - 1][NT][16][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     if (p.flag != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.flag = 1;
+    if (p.ranges != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < MPF_CALL_WORDS) p.ranges[threadIdx.x] = 0;
     const int64_t pos0 = (int64_t)blockIdx.x * 32;
     if (pos0 >= (int64_t)p.PL * p.Mpad) return;  // whole workgroup
     const int q = (int)(pos0 / p.Mpad), m0 = (int)(pos0 % p.Mpad);
     if (m0 >= p.M) return;                       // a tile made of padding columns only (whole workgroup)
     const int pr = q / p.L, l = q % p.L;
     const int n0 = blockIdx.y * 32 * NT;
-    const int64_t nkall = p.k1 - p.k0, qs = (int64_t)p.PLpad * p.Mpad;
+    const int64_t nkall = (p.k1 - p.k0) << p.kshift, qs = (int64_t)p.PLpad * p.Mpad;
     const int64_t slab = (((nkall + M3_WAVES - 1) / M3_WAVES) + 1) & ~(int64_t)1;  // even: lanes 32..63 take odd k
     const int64_t kbeg = wave * slab;
     const int64_t nk = (kbeg >= nkall) ? 0 : ((kbeg + slab < nkall) ? slab : nkall - kbeg);
     const float *qp = p.Q + kbeg * qs + pos0 + l32;                                    // + kk*qs
-    const float *wp = p.W + ((int64_t)pr * p.K + p.k0 + kbeg) * p.Npad + n0 + l32;     // + kk*Npad (+32 for tile 1)
+    const float *wp = p.W + ((int64_t)pr * p.K + p.k0) * p.Npad + n0 + l32;     // + ((kbeg + kk) >> kshift)*Npad (+32 for tile 1)
     double totl[LONGK ? NT : 1][16];   // LONGK only
     f32x16 acc[NT];
 #pragma unroll
@@ -110,8 +113,9 @@ __global__ __launch_bounds__(64 * M3_WAVES, LONGK ? 1 : 2) void k_mode3(const Mo
                 const int64_t kx = kk + 2 * t + hi;
                 const bool ok = kx < kend;
                 a[t] = ok ? qp[kx * qs] : 0.0f;
-                b0[t] = ok ? wp[kx * p.Npad] : 0.0f;
-                if (NT == 2) b1[t] = ok ? wp[kx * p.Npad + 32] : 0.0f;
+                const int64_t kw = ((kbeg + kx) >> p.kshift) * p.Npad;
+                b0[t] = ok ? wp[kw] : 0.0f;
+                if (NT == 2) b1[t] = ok ? wp[kw + 32] : 0.0f;
             }
         };
         auto mma_batch = [&](const float *a, const float *b0, const float *b1) {

@@ -28,7 +28,26 @@ struct Mode12Params {
     int L, PL, PLpad, Mpad, MT, G;
     int row_base;  // first stacked row of row group 0 of this launch (k_mode12_v3; a multiple of 32, else 0)
     int64_t i0, i1, j0, j1, k0, k1;
+    // k_mode12 behind k_mode12_mp: it computes the call only if the noted value ranges say so (mp_out_of_range), and then
+    // also clears the rows from qzero0 on of every slice's part of Q (the other wave columns' partial results)
+    const uint32_t *guard;
+    int qzero0;
 };
+
+// value ranges inside which the piece sums of k_mode12_mp hold; words of MpParams::flags
+enum { MPF_XBIG = 0, MPF_XNORM, MPF_XNZ, MPF_ZBIG, MPF_ZNORM, MPF_ZNZ, MPF_CALL_WORDS,   // of one call: cleared by mode 3
+       MPF_UBIG = 8, MPF_UNORM, MPF_UNZ, MPF_VBIG, MPF_VNORM, MPF_VNZ, MPF_WORDS = 16 }; // of the factors
+constexpr float MP_XMAX = 0x1p60f, MP_XMIN = 0x1p-40f, MP_UMAX = 0x1p40f, MP_UMIN = 0x1p-20f, MP_VMAX = 0x1p20f, MP_VMIN = 0x1p-20f,
+                MP_ZMAX = 0x1p104f, MP_ZMIN = 0x1p-70f;
+
+// true if the products of the call have to be formed in fp32
+__device__ __forceinline__ bool mp_out_of_range(const uint32_t *f)
+{
+    const bool big = f[MPF_XBIG] | f[MPF_ZBIG] | f[MPF_UBIG] | f[MPF_VBIG];
+    const bool tiny = (f[MPF_XNZ] && !f[MPF_XNORM]) || (f[MPF_ZNZ] && !f[MPF_ZNORM]) || (f[MPF_UNZ] && !f[MPF_UNORM]) ||
+                      (f[MPF_VNZ] && !f[MPF_VNORM]);
+    return big || tiny;
+}
 
 enum { SRC_MATERIALISED = 0, SRC_GENERATED = 1 };
 

@@ -34,6 +34,15 @@ struct Mode12Cfg {
     static constexpr int LDS_BYTES = STAGE_BYTES > EPI_BYTES ? STAGE_BYTES : EPI_BYTES;
 };
 
+// element (i, j, k) of an X that is held as separate blocks
+template <typename T>
+__device__ __forceinline__ T x_of_table(const Mode12Params &p, int64_t i, int64_t j, int64_t k)
+{
+    const int64_t bi = i / p.x_dI, bj = j / p.x_dJ, bk = k / p.x_dK, jb0 = bj * p.x_dJ;
+    const int64_t djb = (p.j1 - jb0 < p.x_dJ) ? p.j1 - jb0 : p.x_dJ;
+    return ((const T *)p.xtab[(bk * p.tab_nbj + bj) * p.tab_nbi + bi])[(i - bi * p.x_dI) + p.x_dI * ((j - jb0) + djb * (k - bk * p.x_dK))];
+}
+
 // Slow, fully guarded staging of the X tile straight into LDS (box edges, unaligned tensors).
 template <typename T, int COLS, int ROWB>
 __device__ __forceinline__ void stage_x_guarded(const Mode12Params &p, unsigned char *Xs, int64_t ib, int64_t jc, int64_t k, int tid)
@@ -44,7 +53,7 @@ __device__ __forceinline__ void stage_x_guarded(const Mode12Params &p, unsigned 
         const int64_t j = jc + c, i = ib + e;
         T v = elem<T>::from_f32(0.0f);
         if (j >= p.j0 && j < p.j1 && i >= p.i0 && i < p.i1)
-            v = Xp[(i - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk];
+            v = p.xtab ? x_of_table<T>(p, i, j, k) : Xp[(i - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk];
         ((T *)(Xs + c * ROWB))[e] = v;
     }
 }
@@ -118,15 +127,21 @@ __global__ __launch_bounds__(256) void k_mode12(const Mode12Params p)
     unsigned char *Xs = smem + ROWS * ROWB;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-    // unit decode: consecutive workgroup ids go round-robin over the 8 XCDs, so the G row
-    // groups that read the same slice k land on the same XCD (and share its L2).
+    if (p.guard && !mp_out_of_range(p.guard)) return;
+    // A unit is one slice and one row group.  Consecutive units go round-robin over the 8 XCDs, so the G row groups that read
+    // the same slice k land on the same XCD (and share its L2).  A launch behind a guard has fewer workgroups than units (it
+    // mostly ends right here), hence the loop.
     const int nk = (int)(p.k1 - p.k0);
-    const int bid = blockIdx.x, xcd = bid & 7, t = bid >> 3;
+    const int64_t nunit = 8LL * ((nk + 7) / 8) * p.G;
+    for (int64_t unit = blockIdx.x; unit < nunit; unit += gridDim.x) {
+    const int xcd = (int)(unit & 7), t = (int)(unit >> 3);
     const int g = t % p.G, kidx = (t / p.G) * 8 + xcd;
-    if (kidx >= nk) return;
+    if (kidx >= nk) continue;
     const int64_t k = p.k0 + kidx;
     const int row0 = g * ROWS;
     const int wrow0 = row0 + wave * (RT * 32);
+    if (p.guard && g == 0)
+        for (int64_t e = (int64_t)p.qzero0 * p.Mpad + tid; e < (int64_t)p.PLpad * p.Mpad; e += 256) p.Q[(int64_t)kidx * p.PLpad * p.Mpad + e] = 0.0f;
     const int64_t ia0 = p.i0 & ~(int64_t)(EI - 1);
     const int nstage = (int)((p.i1 - ia0 + EI - 1) / EI);
     const int64_t ja0 = (p.j0 / COLS) * COLS;
@@ -247,6 +262,7 @@ __global__ __launch_bounds__(256) void k_mode12(const Mode12Params p)
         const bool first_chunk = (jc == ja0);
         if (p.MT == 2) mode2_chunk<RT, CT, 2, VM_F32, 4>(p, nullptr, Zs, acc, wrow0, kidx, jc, first_chunk, lane);
         else mode2_chunk<RT, CT, 1, VM_F32, 4>(p, nullptr, Zs, acc, wrow0, kidx, jc, first_chunk, lane);
+    }
     }
 }
 

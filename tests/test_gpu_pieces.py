@@ -1,0 +1,156 @@
+"""The piece-sum kernel of modes 1 and 2 (materialised X, any size and alignment) against plain fp64 torch at the sizes where
+it can go wrong, and against the generic fp32 kernel (EXAT_PIPELINED=0) on values outside the range of the piece sums, which
+the library hands to that kernel.
+
+Tolerance: three bf16 pieces hold an fp32 value exactly and the products left out are 2^-26, so what remains is the rounding
+of the fp32 running sums, as in the fp32 kernels: relative rms error about 2^-24 sqrt(n) / 2.4 per mode, below 1e-6 for the
+extents here; two fp16 pieces carry 21 bits (2^-22 per operand and mode).  2e-6 covers both."""
+import os
+
+import pytest
+import torch
+
+from paper_2311_13693_amd import exat
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-6
+DT = {"f32": exat.EXAT_F32, "bf16": exat.EXAT_BF16, "f32s": exat.EXAT_F32_SPLIT}
+
+
+def _problem(I, J, K, L, M, N, P, dtype, seed=5):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X = rn(K, J, I)
+    return (X.to(torch.bfloat16) if dtype == "bf16" else X), rn(P * L, I) * L ** -0.5, rn(P * M, J) * M ** -0.5, rn(P * N, K) * N ** -0.5
+
+
+def _plan(I, J, K, L, M, N, P, dtype, U, V, W, d=None):
+    d = d or (I, J, K)
+    plan = exat.Plan(exat.make_desc(I, J, K, L, M, N, P, *d, DT[dtype]))
+    plan.set_factors(U, V, W)
+    return plan
+
+
+def _ref(X, U, V, W, L, M, N, P, dtype):
+    r = (lambda t: t.to(torch.bfloat16).double()) if dtype == "bf16" else (lambda t: t.double())
+    X, U, V, W = X.double(), r(U), r(V), r(W)
+    K, J, I = X.shape
+    Z = (X.reshape(-1, I) @ U.T).view(K, J, P * L)
+    Y = [W[p * N:(p + 1) * N] @ torch.matmul(V[p * M:(p + 1) * M], Z[:, :, p * L:(p + 1) * L].contiguous()).view(K, M * L) for p in range(P)]
+    return torch.stack(Y).view(-1)
+
+
+def _err(Y, R):
+    return float((Y.double() - R).norm() / R.norm())
+
+
+# stacked rows around the tile, quad, wave-column and group boundaries; replicas inside a tile, straddling tiles, whole tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f32s"])
+@pytest.mark.parametrize("P,L", [(1, 1), (2, 16), (3, 33), (8, 16), (9, 16), (5, 50), (16, 16), (17, 16), (11, 50), (16, 32), (33, 16), (21, 50), (20, 64)])
+def test_row_groups(dtype, P, L):
+    I, J, K, M, N = 96, 130, 9, 7, 5
+    print("case", dtype, P, L, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+# stages, ring slots and chunks: one stage and less, the ring length and around it, fibres around a chunk
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f32s"])
+@pytest.mark.parametrize("I,J,M", [(1, 1, 1), (8, 127, 32), (31, 128, 33), (32, 129, 64), (33, 40, 50), (64, 257, 20), (127, 16, 64), (128, 15, 32),
+                                   (129, 300, 50), (250, 250, 50), (257, 33, 64), (511, 130, 17)])
+@pytest.mark.parametrize("P", [2, 7, 13])   # 4, 2 and 1 wave columns
+def test_extents(dtype, I, J, M, P):
+    K, L, N = 6, 40, 9
+    print("case", dtype, I, J, M, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+# blocks whose edges are multiples of nothing, one by one; a slab of blocks of half stages in one launch; X not 16-byte aligned
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [(50, 45, 7), (37, 128, 4), (100, 33, 13)])
+def test_odd_blocks(dtype, d):
+    I, J, K, L, M, N, P = 115, 140, 13, 50, 50, 20, 13
+    print("case", dtype, d, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W, d)
+    for k in range(0, K, d[2]):
+        for j in range(0, J, d[1]):
+            for i in range(0, I, d[0]):
+                plan.compress_block(X[k:k + d[2], j:j + d[1], i:i + d[0]].contiguous(), i // d[0], j // d[1], k // d[2])
+    assert _err(plan.finalize(), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+@pytest.mark.parametrize("dtype,dI", [("f32", 16), ("f32", 48), ("bf16", 32), ("f32s", 32)])
+@pytest.mark.parametrize("P", [2, 6, 13])
+def test_slab_blocks(dtype, dI, P):
+    I, J, K, L, M, N = 144 if dI != 32 else 160, 300, 10, 40, 50, 20
+    d = (dI, 128, 4)
+    print("case", dtype, dI, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W, d)
+    blocks = [X[k:k + 4, j:j + 128, i:i + dI].contiguous() for k in range(0, K, 4) for j in range(0, J, 128) for i in range(0, I, dI)]
+    plan.compress_blocks(blocks, 0, 3, 0, 3)
+    assert _err(plan.finalize(), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+@pytest.mark.parametrize("dtype,off", [("f32", 1), ("f32", 3), ("bf16", 1), ("bf16", 4), ("f32s", 2)])
+def test_unaligned_tensor(dtype, off):
+    I, J, K, L, M, N, P = 96, 130, 5, 50, 33, 20, 12
+    print("case", dtype, off, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    buf = torch.full((X.numel() + 8,), float("nan"), dtype=X.dtype, device="cuda")
+    buf[off:off + X.numel()] = X.view(-1)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    assert _err(plan.compress(buf[off:]), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+# values outside the range of the piece sums: the call is computed with fp32 products, as the generic kernel does
+RANGES = {
+    "x_tiny": (1e-36, 1.0, 1.0), "x_huge": (1e30, 1.0, 1.0), "u_tiny": (1.0, 1e-30, 1.0), "u_huge": (1.0, 1e15, 1.0), "v_tiny": (1.0, 1.0, 1e-25),
+    "v_huge": (1.0, 1.0, 1e10), "z_tiny": (1e-11, 1e-5, 1.0),
+}
+
+
+@pytest.mark.parametrize("P", [2, 7, 13])
+@pytest.mark.parametrize("case", list(RANGES) + ["x_inf", "x_max", "x_zero", "one_huge", "bf16_inf"])
+def test_value_ranges(case, P):
+    I, J, K, L, M, N = 70, 140, 6, 40, 50, 20
+    dtype = "bf16" if case.startswith("bf16") else "f32"
+    print("case", case, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    sx, su, sv = RANGES.get(case, (1.0, 1.0, 1.0))
+    X, U, V = X * sx, U * su, V * sv
+    if case in ("x_inf", "bf16_inf"):
+        X[3, 100, 17] = float("inf")
+    elif case == "x_max":
+        X[3, 100, 17] = torch.finfo(torch.float32).max / 64
+        V.clamp_(-0.5, 0.5)
+    elif case == "x_zero":
+        X.zero_()
+    elif case == "one_huge":
+        X[0, 0, 0] = 1e25
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    Y = plan.compress(X)
+    os.environ["EXAT_PIPELINED"] = "0"
+    try:
+        G = plan.compress(X)
+    finally:
+        os.environ.pop("EXAT_PIPELINED")
+    if case == "z_tiny":   # inside the ranges of X and U, and Z as small as they make it: either route
+        assert _err(Y, G.double()) <= 2 * TOL
+    else:
+        assert torch.equal(torch.isnan(Y), torch.isnan(G)) and torch.equal(torch.isinf(Y), torch.isinf(G))
+        fin = torch.isfinite(G)
+        assert torch.equal(Y[~fin].nan_to_num(0), G[~fin].nan_to_num(0))
+        if P == 13:
+            assert torch.equal(Y[fin], G[fin])
+        else:   # several wave columns: mode 3 adds the same partial results (and zeros) in another order
+            assert float((Y[fin].double() - G[fin].double()).norm()) <= TOL * float(G[fin].double().norm())
+    # the next call starts with a clean record
+    X2, _, _, _ = _problem(I, J, K, L, M, N, P, dtype, seed=6)
+    if case in ("x_tiny", "x_huge", "x_inf", "x_max", "x_zero", "one_huge", "bf16_inf"):
+        assert _err(plan.compress(X2), _ref(X2, U, V, W, L, M, N, P, dtype)) <= TOL
