@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -224,11 +225,11 @@ int launch_v4_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const U
     return boxed ? launch_v4_inst<true>(mp, gs, uf, nk, st) : launch_v4_inst<false>(mp, gs, uf, nk, st);
 }
 
-template <int NP, int NWC, bool PTR>
+template <int NP, int NW, int NWC, bool PTR>
 int launch_mp_inst(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
 {
-    typedef Mode12MpCfg<NP, NWC> cfg;
-    auto kern = k_mode12_mp<NP, NWC, PTR>;
+    typedef Mode12MpCfg<NP, NW, NWC> cfg;
+    auto kern = k_mode12_mp<NP, NW, NWC, PTR>;
     static_assert(cfg::LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
     static bool attr_done = false;
     if (!attr_done) {
@@ -237,36 +238,34 @@ int launch_mp_inst(const Mode12Params &mp, const MpParams &q, int nk, hipStream_
     }
     const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), cfg::LDS_BYTES, st, mp, q);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), cfg::LDS_BYTES, st, mp, q);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
-template <int NP, int NWC>
+template <int NP, int NW, int NWC>
 int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
 {
-    // 32-bit offsets within a chunk of 128 fibres, unless X is a set of blocks or its fibres are millions of values long
-    const bool ptr = mp.xtab || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
-    return ptr ? launch_mp_inst<NP, NWC, true>(mp, q, nk, st) : launch_mp_inst<NP, NWC, false>(mp, q, nk, st);
+    // the lean build unless X is a set of blocks, the box has odd ends in i, or the fibres are millions of values long
+    const bool ptr = mp.xtab || mp.i0 % 8 != 0 || mp.i1 % 8 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
+    return ptr ? launch_mp_inst<NP, NW, NWC, true>(mp, q, nk, st) : launch_mp_inst<NP, NW, NWC, false>(mp, q, nk, st);
 }
 template <int NP>
-int launch_mp(const Mode12Params &mp, const MpParams &q, int nwc, int nk, hipStream_t st)
+int launch_mp(const Mode12Params &mp, const MpParams &q, int nw, int nwc, int nk, hipStream_t st)
 {
-    switch (nwc) {
-    case 4: return launch_mp_nwc<NP, 4>(mp, q, nk, st);
-    case 2: return launch_mp_nwc<NP, 2>(mp, q, nk, st);
-    default: return launch_mp_nwc<NP, 1>(mp, q, nk, st);
-    }
+    if (nwc == 4) return launch_mp_nwc<NP, 8, 4>(mp, q, nk, st);
+    return nw == 8 ? launch_mp_nwc<NP, 8, 1>(mp, q, nk, st) : launch_mp_nwc<NP, 4, 1>(mp, q, nk, st);
 }
 
 // Number of row groups of k_mode12_mp for T4 quads of row tiles and nk slices: a workgroup holds two to four quads, the
 // groups take the quads as evenly as they go, and a compute unit runs one workgroup at a time.
-int choose_groups(int T4, int64_t nk)
+int choose_groups(int T4, int64_t nk, int nw)
 {
     int best = 1;
     double cost = 0.0;
-    for (int G = (T4 + 3) / 4; G <= (T4 + 1) / 2; G++) {
-        // rounds of the chip x (the quads of a group + about half a quad's time for what a group costs by itself)
-        const double c = std::max((double)((nk * G + 255) / 256), (double)nk * G / 256.0) * ((double)T4 / G + 0.5);
-        if (G == (T4 + 3) / 4 || c < 0.97 * cost) { best = G; cost = c; }
+    const int mx = nw / 2, mn = nw / 4;
+    const double slots = nw == 8 ? 256 : 512;
+    for (int G = (T4 + mx - 1) / mx; G <= (T4 + mn - 1) / mn; G++) {
+        const double c = std::max(std::ceil((double)nk * G / slots), (double)nk * G / slots) * ((double)T4 / G + 0.5);
+        if (G == (T4 + mx - 1) / mx || c < 0.97 * cost) { best = G; cost = c; }
     }
     return best;
 }
@@ -316,8 +315,10 @@ int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yo
         // fp32 path's pieces (no range limit) for the rest
         const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
         const int T = (pl->PL + 31) / 32;
-        const int nwc = T <= 4 ? 4 : (T <= 8 ? 2 : 1);
-        kshift = nwc == 4 ? 2 : (nwc == 2 ? 1 : 0);
+        // up to 4 row tiles: 8 waves, four of which share a tile's fibres; up to 8: two 4-wave workgroups per compute unit; else
+        // groups of 8 to 16 tiles, one 8-wave workgroup per compute unit
+        const int nwc = T <= 4 ? 4 : 1, nw = T > 4 && T <= 8 ? 4 : 8;
+        kshift = nwc == 4 ? 2 : 0;
         MpParams q;
         q.nig = pl->Ipad / 16; q.T4 = (T + 3) / 4;
         q.Uf = bf ? pl->Ufrag : (split ? pl->Usp : pl->Ump);
@@ -327,8 +328,8 @@ int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yo
         // chunks of 128 fibres from j0 down to a multiple of 16, as long as V's padding covers the last one
         q.ja0 = mp.j0 & ~(int64_t)15;
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
-        mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk);
-        rc = bf ? launch_mp<1>(mp, q, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, nwc, (int)nk, st) : launch_mp<3>(mp, q, nwc, (int)nk, st));
+        mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
+        rc = bf ? launch_mp<1>(mp, q, nw, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, nw, nwc, (int)nk, st) : launch_mp<3>(mp, q, nw, nwc, (int)nk, st));
         if (rc != EXAT_OK) return rc;
         mp.guard = q.flags;
         mp.qzero0 = pl->PLpad >> kshift;
@@ -508,13 +509,13 @@ int exat_plan_create(exat_plan_t *plan, const exat_desc_t *desc)
     const size_t qb = (size_t)desc->K * pl->PLpad * pl->Mpad * 4;
     pl->ub = ub; pl->vb = vb; pl->qb = qb; pl->ab = (size_t)3 * pl->Ipad * 64 * 2;
     if (hipMalloc((void **)&pl->Asplit, pl->ab) != hipSuccess ||
-        hipMalloc(&pl->Upack, ub) != hipSuccess || hipMalloc(&pl->Ufrag, ub) != hipSuccess ||
+        hipMalloc(&pl->Upack, ub) != hipSuccess || hipMalloc(&pl->Ufrag, ub + MP_UPAD) != hipSuccess ||
         (desc->in_dtype == EXAT_BF16 && (hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess ||
                                          hipMalloc(&pl->Vfragz, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess)) ||
         (desc->in_dtype != EXAT_BF16 && hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess) ||
-        (desc->in_dtype != EXAT_BF16 && (hipMalloc(&pl->Ump, (size_t)pl->PLpad * pl->Ipad * 6) != hipSuccess ||
+        (desc->in_dtype != EXAT_BF16 && (hipMalloc(&pl->Ump, (size_t)pl->PLpad * pl->Ipad * 6 + MP_UPAD) != hipSuccess ||
                                          hipMalloc(&pl->Vmp, (size_t)desc->P * pl->Mpad * pl->Jpad * 6) != hipSuccess)) ||
-        (desc->in_dtype == EXAT_F32_SPLIT && (hipMalloc(&pl->Usp, (size_t)pl->PLpad * pl->Ipad * 4) != hipSuccess ||
+        (desc->in_dtype == EXAT_F32_SPLIT && (hipMalloc(&pl->Usp, (size_t)pl->PLpad * pl->Ipad * 4 + MP_UPAD) != hipSuccess ||
                                               hipMalloc(&pl->Vsp, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess)) ||
         hipMalloc((void **)&pl->ranges, MPF_WORDS * sizeof(uint32_t)) != hipSuccess || hipMalloc((void **)&pl->Vpack, vb) != hipSuccess ||
         hipMalloc((void **)&pl->Wpack, wb) != hipSuccess || hipMalloc((void **)&pl->Q, qb) != hipSuccess) {

@@ -34,6 +34,8 @@
 
 namespace exat {
 
+constexpr size_t MP_UPAD = 64 << 10;   // the U fragments of up to UNR + DU stages past the last one are requested (and not used)
+
 struct MpParams {
     const void *Uf;    // [PLpad/32][nig][NP][64 lanes][8]: lane l of fragment (rt, ig, piece) holds row 32*rt + l%32,
                        // i = 16*ig + 8*(l/32) .. +7
@@ -83,14 +85,15 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
             w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a - (float)h[0], b - (float)h[1]));
         } else {
             typedef _Float16 g2 __attribute__((ext_vector_type(2)));
-            const g2 h = {(_Float16)a, (_Float16)b}, l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
+            typedef float f2 __attribute__((ext_vector_type(2)));
+            const g2 h = __builtin_convertvector((f2{a, b}), g2), l = __builtin_convertvector((f2{a - (float)h[0], b - (float)h[1]}), g2);
             w[0] = __builtin_bit_cast(uint32_t, h); w[1] = __builtin_bit_cast(uint32_t, l);
         }
     } else {
 #pragma unroll
         for (int q = 0; q < NP; q++) {
-            const bf16x2 h = {(__bf16)a, (__bf16)b};
-            w[q] = __builtin_bit_cast(uint32_t, h);
+            typedef float f2 __attribute__((ext_vector_type(2)));
+            w[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf16x2));   // one packed conversion
             if (q + 1 < NP) {   // the residual of a rounding to bf16 is exact in fp32
                 a -= __builtin_bit_cast(float, w[q] << 16);
                 b -= __builtin_bit_cast(float, w[q] & 0xffff0000u);
@@ -99,15 +102,19 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
     }
 }
 
-template <int NP, int NWC>
+template <int NP, int NW, int NWC>
 struct Mode12MpCfg {
-    static constexpr int NW = 8, NWR = NW / NWC, RT = 2, CT = 4 / NWC, COLS = 128, EI = 32;
+    static constexpr int NWR = NW / NWC, RT = 2, CT = 4 / NWC, COLS = 128, EI = 32;
+    static constexpr int XPT = 512 / (64 * NW);                 // runs of 8 values of the X tile per thread
     static constexpr int ROWB = 80, XBUF = COLS * ROWB, SLOT = NP * XBUF;
-    static constexpr int NSLOT = NP == 1 ? 8 : 4, H = NSLOT / 2;
+    static constexpr int NSLOT = NP == 1 ? 8 : (NP == 3 && NW == 4 ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
     static constexpr int LDS_BYTES = NSLOT * SLOT;
-    static constexpr int DU = NP == 1 ? 2 : 1;                  // register sets of U fragments
-    static constexpr int DX = NP == 1 ? 4 : (NP == 2 ? 2 : 1);  // register sets of the X tile in flight
-    static constexpr int XD = NP == 1 ? 4 : 2;                  // register sets of X fragments read from LDS
+    static constexpr int DU = NP == 1 ? 2 : 1;   // register sets of U fragments
+    static constexpr int DX = NP == 1 ? 4 : 1;   // register sets of the X tile in flight
+    static constexpr int XD = NP == 1 ? 4 : 2;   // register sets of X fragments read from LDS
+    static constexpr int UNR = DX;               // stages per pass of the stage loop (register sets are addressed statically)
+    static_assert(H <= 2 || H % UNR == 0 || UNR % H == 0, "");
+    static_assert(UNR % DU == 0 && UNR % DX == 0 && (UNR % H == 0 || H % UNR == 0), "");
 };
 
 // Mode 2 from the accumulators (acc holds Z^T: rows 32 fibres j, columns 32 stacked rows q; see mode2_direct_bf16 for the
@@ -115,7 +122,7 @@ struct Mode12MpCfg {
 // replicas is multiplied with each one's V, and a lane keeps the product of its row's replica.  Q[row][m] += Q^T[m][row];
 // Qk points to the rows of this slice (and wave column).
 template <int NP, int RT, int CT, int MTC, int RSTRIDE>
-__device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &mp, float *Qk, const f32x16 (&acc)[RT][CT], int wrow0, int ntile,
+__device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &mp, float *Qk, f32x16 (&acc)[RT][CT], int wrow0, int ntile,
                                          int64_t jc, bool first_chunk, int lane)
 {
     constexpr bool F16 = NP == 2;
@@ -134,28 +141,40 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
             float *Qt = Qk + (int64_t)q * MP + 4 * hi;   // + 32*mt + 8*b
             for (int pp = pfirst; pp <= plast; pp++) {
                 const bool mine = q >= pp * p.L && q < (pp + 1) * p.L && q < p.PL;
-                // fragment (ct, t, mt, piece) of this chunk: j16 = jc/16 + 2 ct + t.  Step u = (2 ct + t) * MTC + mt multiplies
-                // with one 32-row tile of V; its fragments are requested AHEAD steps before.
+                // Step st = 2 ct + t multiplies 16 fibres: Z split into pieces (during the step before) times the fragments of V,
+                // requested VA steps before.  Consecutive MFMAs go to two accumulators (with one 32-row tile of V the products
+                // alternate between two partial sums): one that adds to the result of the MFMA before it waits for that result.
                 const u32x4 *vz = (const u32x4 *)mp.Vf + ((int64_t)pp * (p.Jpad / 16) + jc / 16) * mp.vmt * NV * 64 + ln;
-                constexpr int NU = 2 * CT * MTC, AHEAD = 2;
-                u32x4 v[AHEAD + 1][NV], z[NZ];
-                f32x16 d[MTC];
+                constexpr int NS = 2 * CT, VA = MTC == 2 && NV > 1 ? 1 : 2;
+                u32x4 v[VA + 1][MTC][NV], z[2][NZ];
+                f32x16 d[2];
 #pragma unroll
-                for (int mt = 0; mt < MTC; mt++)
+                for (int m = 0; m < 2; m++)
 #pragma unroll
-                    for (int e = 0; e < 16; e++) d[mt][e] = 0.0f;
-                auto load_v = [&](int u) __attribute__((always_inline)) {
+                    for (int e = 0; e < 16; e++) d[m][e] = 0.0f;
+                auto load_v = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int c = 0; c < NV; c++) v[u % (AHEAD + 1)][c] = vz[((u / MTC) * mp.vmt + u % MTC) * (NV * 64) + c * 64];
+                    for (int m = 0; m < MTC; m++)
+#pragma unroll
+                        for (int c = 0; c < NV; c++) v[st % (VA + 1)][m][c] = vz[(st * mp.vmt + m) * (NV * 64) + c * 64];
+                };
+                auto split_z = [&](int st, int e) __attribute__((always_inline)) {   // registers 8t+2e, 8t+2e+1 of the tile
+                    uint32_t w[NZ];
+                    float za = acc[rt][st >> 1][8 * (st & 1) + 2 * e], zb = acc[rt][st >> 1][8 * (st & 1) + 2 * e + 1];
+                    asm volatile("" : "+v"(za), "+v"(zb));   // opaque: or every split is formed ahead of the loop over pp, and spilled
+                    mp_split2<NZ, F16>(za, zb, w);
+#pragma unroll
+                    for (int c = 0; c < NZ; c++) z[st & 1][c][e] = w[c];
                 };
 #pragma unroll
-                for (int u = 0; u < AHEAD && u < NU; u++) load_v(u);
-                f32x4 qold[MTC][4];
+                for (int st = 0; st < VA && st < NS; st++) load_v(st);
 #pragma unroll
-                for (int u = 0; u < NU; u++) {
-                    const int ct = u / (2 * MTC), t = (u / MTC) & 1, mt = u % MTC;
-                    if (u + AHEAD < NU) load_v(u + AHEAD);
-                    if (u == NU - 1 - AHEAD / 2) {
+                for (int e = 0; e < 4; e++) split_z(0, e);
+                f32x4 qold[MTC][4];
+                static_for<NS>([&](auto sc) {
+                    constexpr int st = decltype(sc)::value, NM = terms::N * MTC;
+                    if constexpr (st + VA < NS) load_v(st + VA);
+                    if constexpr (st == NS - 1) {   // the fragments' registers are free now
 #pragma unroll
                         for (int m = 0; m < MTC; m++)
 #pragma unroll
@@ -165,30 +184,26 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
                             }
                     }
                     __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the MFMAs
-                    if (mt == 0) {
-#pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            uint32_t w[NZ];
-                            // opaque: or the pieces of all accumulators are formed ahead of the loop over the replicas and spilled
-                            float za = acc[rt][ct][8 * t + 2 * e], zb = acc[rt][ct][8 * t + 2 * e + 1];
-                            asm volatile("" : "+v"(za), "+v"(zb));
-                            mp_split2<NZ, F16>(za, zb, w);
-#pragma unroll
-                            for (int c = 0; c < NZ; c++) z[c][e] = w[c];
+                    static_for<NM>([&](auto nc) {
+                        constexpr int i = decltype(nc)::value, n = i / MTC, m = i % MTC, dm = MTC == 2 ? m : n & 1;
+                        d[dm] = mp_mma<F16>(v[st % (VA + 1)][m][terms::U[n]], z[st & 1][terms::X[n]], d[dm]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (st + 1 < NS) {   // the next step's split, dealt out behind the MFMAs
+                            static_for<(i + 1) * 4 / NM - i * 4 / NM>([&](auto ec) { split_z(st + 1, i * 4 / NM + decltype(ec)::value); });
+                            __builtin_amdgcn_sched_barrier(0);
                         }
-                    }
-#pragma unroll
-                    for (int n = 0; n < terms::N; n++) d[mt] = mp_mma<F16>(v[u % (AHEAD + 1)][terms::U[n]], z[terms::X[n]], d[mt]);
-                }
+                    });
+                });
+                if (MTC == 1) d[0] += d[1];
                 if (mine) {
 #pragma unroll
-                    for (int mt = 0; mt < MTC; mt++)
+                    for (int m = 0; m < MTC; m++)
 #pragma unroll
                         for (int b = 0; b < 4; b++) {
                             f32x4 o;
 #pragma unroll
-                            for (int r = 0; r < 4; r++) o[r] = d[mt][4 * b + r] + qold[mt][b][r];
-                            *(f32x4 *)(Qt + 32 * mt + 8 * b) = o;
+                            for (int r = 0; r < 4; r++) o[r] = d[m][4 * b + r] + qold[m][b][r];
+                            *(f32x4 *)(Qt + 32 * m + 8 * b) = o;
                         }
                 }
             }
@@ -201,17 +216,19 @@ typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
 // PTR = false: a fibre of X is addressed by a wave-uniform base and a 32-bit offset of the lane (128 fibres of X are less than
-// 2^31 bytes apart).  PTR = true: by a 64-bit pointer of the lane, which may come from the table of blocks of a slab.
-template <int NP, int NWC, bool PTR>
-__global__ __launch_bounds__(512, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp)
+// 2^31 bytes apart), and the box begins and ends at multiples of 8 in i.  PTR = true: any box; a fibre is addressed by a 64-bit
+// pointer of the lane, which may come from the table of blocks of a slab.
+template <int NP, int NW, int NWC, bool PTR>
+__global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp)
 {
-    typedef Mode12MpCfg<NP, NWC> cfg;
+    typedef Mode12MpCfg<NP, NW, NWC> cfg;
     typedef std::conditional_t<NP == 1, __bf16, float> T;
     typedef mp_terms<NP> terms;
     constexpr bool F16 = NP == 2;
     constexpr int NWR = cfg::NWR, RT = cfg::RT, CT = cfg::CT, EI = cfg::EI, COLS = cfg::COLS, ROWB = cfg::ROWB, XBUF = cfg::XBUF;
     constexpr int SLOT = cfg::SLOT, NSLOT = cfg::NSLOT, H = cfg::H, DU = cfg::DU, DX = cfg::DX, XD = cfg::XD, NF = 2 * CT;
-    constexpr int UNR = lcm_i(lcm_i(NSLOT, DU), DX);
+    constexpr int XPT = cfg::XPT, XC = COLS / XPT, XW = NP == 1 ? 1 : 2;   // run u of a thread belongs to fibre col + u*XC
+    constexpr int UNR = cfg::UNR;
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -234,38 +251,156 @@ __global__ __launch_bounds__(512, 2) void k_mode12_mp(const Mode12Params p, cons
     const int nstage = (int)((p.i1 - ia0 + EI - 1) / EI);
     const int64_t u_tile = mp.nig * (NP * 1024);   // bytes of one row tile of Uf
 
+    const int nst = (nstage + UNR - 1) / UNR * UNR;   // stages per chunk: those past the end of the box hold zeros
+
+    const int s_lo = p.i0 > ia0 ? 1 : 0, s_hi = (int)((p.i1 - ia0) / EI);   // stages that lie inside the box: s_lo .. s_hi - 1
+
     u32x4 ufr[DU][2][RT][NP];
-    u32x4 xr[DX][NP == 1 ? 1 : 2];
+    u32x4 xr[DX][XPT][XW];
     float xmax = 0.0f, zmax = 0.0f;
 
+    // ---- the producing side: tiles follow each other through all chunks.  State of the tile that is requested next: chunk
+    //      start pj, stage ps, the lane's addresses in that chunk ----
+    int64_t pj = mp.ja0;
+    int ps = 0;
+    int so = 0, sw = H * SLOT;   // ring slots, in bytes: of the tile that is multiplied next, of the tile that is written next
     for (int64_t jc = mp.ja0; jc < p.j1; jc += COLS) {
         int tidc = tid;
         asm volatile("" : "+v"(tidc));   // per-lane offsets are derived again in every chunk (not kept live over mode 2)
         const int lane = tidc & 63, l32 = lane & 31, hi = lane >> 5;
-        const int col = tidc >> 2, part = tidc & 3;        // this thread's piece of the X tile: 8 values of i of one fibre
-        const int xs_w = col * ROWB + part * 16;
-        const int xs_r = (wc * CT * 32 + l32) * ROWB + hi * 16;   // + ct*32*ROWB + g2*32 + piece*XBUF
-        const bool full = jc >= p.j0 && jc + COLS <= p.j1;
-        const bool cok = jc + col >= p.j0 && jc + col < p.j1;
-        const int64_t jb = jc > p.j0 ? jc : p.j0, j = cok ? jc + col : jb;   // a lane outside the box reads the chunk's first fibre
-        // the thread's values of the stage that starts at i: plain layout at xu + (i - ia0) + xo
-        const T *xu = nullptr;       // wave-uniform
-        unsigned xo = 0;             // bytes
-        const T *xp = nullptr;       // PTR: the lane's pointer for i = ia0
-        int64_t tab_end = 0, tab_in = 0;   // table: first i beyond the current block; offset of the fibre inside a block
-        const void *const *tabrow = nullptr;
-        if constexpr (PTR) {
-            if (p.xtab) {
-                const int64_t bj = j / p.x_dJ, bk = k / p.x_dK, jb0 = bj * p.x_dJ, djb = (p.j1 - jb0 < p.x_dJ) ? p.j1 - jb0 : p.x_dJ;
-                tabrow = p.xtab + (bk * p.tab_nbj + bj) * p.tab_nbi;
-                tab_in = (j - jb0) * p.x_dI + (k - bk * p.x_dK) * p.x_dI * djb;
-            } else
-                xp = (const T *)p.X + (ia0 + 8 * part - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
-        } else {
-            xu = (const T *)p.X + (ia0 - p.xo_i) + (jb - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
-            xo = ((unsigned)(j - jb) * (unsigned)p.x_sj + 8u * (unsigned)part) * (unsigned)sizeof(T);
-        }
+        const int col = tidc >> 2, part = tidc & 3;                 // this thread's runs of the X tile: 8 values of i of a fibre
+        const int xs_w = col * ROWB + part * 16;                  // + slot + u*XC*ROWB + piece*XBUF
+        const int xs_r = (wc * CT * 32 + l32) * ROWB + hi * 16;   // + slot + ct*32*ROWB + g2*32 + piece*XBUF
+        const T *xu = nullptr;           // plain layout, wave-uniform: element (first i of the stage, first fibre of the chunk inside the box, k)
+        bool jin = false;                // all fibres of the chunk lie inside the box
+        unsigned xo[XPT];                // the lane's offset from it in bytes
+        const T *xp[XPT];                // PTR: the lane's pointer for i = ia0 (in the current block)
+        int64_t tab_end = 0, tab_in[XPT];   // table: first i beyond the current block; offset of the fibre inside a block
+        const void *const *tabrow[XPT];
+        auto chunk_state = [&]() __attribute__((always_inline)) {
+            const int64_t jb = pj > p.j0 ? pj : p.j0;
+            tab_end = 0;
+            jin = pj >= p.j0 && pj + COLS <= p.j1;
+#pragma unroll
+            for (int u = 0; u < XPT; u++) {
+                int64_t j = pj + col + u * XC;
+                j = (j >= jb && j < p.j1) ? j : jb;   // a lane outside the box reads the chunk's first fibre
+                if constexpr (PTR) {
+                    if (p.xtab) {
+                        const int64_t bj = j / p.x_dJ, bk = k / p.x_dK, jb0 = bj * p.x_dJ, djb = (p.j1 - jb0 < p.x_dJ) ? p.j1 - jb0 : p.x_dJ;
+                        tabrow[u] = p.xtab + (bk * p.tab_nbj + bj) * p.tab_nbi;
+                        tab_in[u] = (j - jb0) * p.x_dI + (k - bk * p.x_dK) * p.x_dI * djb;
+                    } else
+                        xp[u] = (const T *)p.X + (ia0 + 8 * part - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
+                } else
+                    xo[u] = ((unsigned)(j - jb) * (unsigned)p.x_sj + 8u * (unsigned)part) * (unsigned)sizeof(T);
+            }
+            if constexpr (!PTR) xu = (const T *)p.X + (ia0 + (int64_t)ps * EI - p.xo_i) + (jb - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
+        };
+        chunk_state();
+        // requests this thread's runs of the next tile; goes on to the tile after it if `go` is set
+        auto request_x = [&](u32x4 (&dst)[XPT][XW], bool go) __attribute__((always_inline)) {
+            const int64_t ib = ia0 + (int64_t)ps * EI;
+            if constexpr (PTR) {
+                if (p.xtab) {
+                    int64_t i = ib + 8 * part;
+                    i = i < p.i1 ? i : p.i1 - 1;
+                    if (__any(i >= tab_end)) {   // a block boundary: dI is a multiple of 16, a thread's 8 values lie in one block
+                        const int64_t bi = i / p.x_dI;
+#pragma unroll
+                        for (int u = 0; u < XPT; u++) xp[u] = (const T *)tabrow[u][bi] + tab_in[u] + (8 * part - bi * p.x_dI);
+                        tab_end = (bi + 1) * p.x_dI;
+                    }
+                }
+            }
+            const bool inside = jin && ps >= s_lo && ps < s_hi;
+            typedef const __attribute__((address_space(1))) T *gp;   // X is device memory whatever the pointer's origin
+            auto load_run = [&](const T *a, u32x4 (&d)[XW]) __attribute__((always_inline)) {
+                if constexpr (NP == 1) d[0] = *(const __attribute__((address_space(1))) u32x4_a2 *)(gp)a;
+                else {
+                    d[0] = *(const __attribute__((address_space(1))) u32x4_a4 *)(gp)a;
+                    d[1] = *(const __attribute__((address_space(1))) u32x4_a4 *)(gp)(a + 4);
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < XPT; u++) {
+                const T *a;
+                if constexpr (PTR) a = xp[u] + (ib - ia0);
+                else a = (const T *)((const char *)xu + xo[u]);
+                if (__builtin_expect(inside, 1)) load_run(a, dst[u]);
+                else {   // a tile that is not filled by the box: zero outside
+#pragma unroll
+                    for (int c = 0; c < XW; c++) dst[u][c] = u32x4{0u, 0u, 0u, 0u};
+                    if constexpr (!PTR) {   // whole runs only: i0 and i1 are multiples of 8
+                        const int lo = (int)(p.i0 - ib), hi_ = p.i1 - ib < EI ? (int)(p.i1 - ib) : EI;
+                        const int jl = (int)(p.j0 - pj), jh = p.j1 - pj < COLS ? (int)(p.j1 - pj) : COLS;
+                        const int c = col + u * XC;
+                        if (8 * part >= lo && 8 * part < hi_ && c >= jl && c < jh) load_run(a, dst[u]);
+                    } else {
+                        const int64_t i = ib + 8 * part, j = pj + col + u * XC;
+                        const bool jok = j >= p.j0 && j < p.j1;
+                        if (jok && i >= p.i0 && i + 8 <= p.i1) load_run(a, dst[u]);
+                        else if (jok && i + 8 > p.i0 && i < p.i1) {   // value by value
+#pragma unroll
+                            for (int e = 0; e < 8; e++)
+                                if (i + e >= p.i0 && i + e < p.i1) {
+                                    if constexpr (NP == 1) dst[u][0][e >> 1] |= (uint32_t)*(const __attribute__((address_space(1))) uint16_t *)(gp)(a + e) << (16 * (e & 1));
+                                    else dst[u][e >> 2][e & 3] = *(const __attribute__((address_space(1))) uint32_t *)(gp)(a + e);
+                                }
+                        }
+                    }
+                }
+            }
+            if (!go) return;
+            if constexpr (!PTR) xu += EI;
+            if (++ps == nst) {   // the first tile of the next chunk (of the same one again behind the last)
+                ps = 0;
+                if (pj + COLS < p.j1) pj += COLS;
+                chunk_state();
+            }
+        };
+        uint32_t xw[4][NP];   // the pieces of a run on its way to LDS
+        // splits values 2e, 2e+1 of a requested run
+        auto split_pair = [&](int e, const u32x4 (&src)[XW]) __attribute__((always_inline)) {
+            if constexpr (NP > 1) {
+                const uint32_t ua = src[e >> 1][2 * (e & 1)], ub = src[e >> 1][2 * (e & 1) + 1];
+                const float a = __builtin_bit_cast(float, ua), b = __builtin_bit_cast(float, ub);
+                if (NP == 3) xmax = fmaxf(fmaxf(xmax, fabsf(a)), fabsf(b));
+                mp_split2<NP, F16, true>(a, b, xw[e]);
+            }
+        };
+        auto store_x = [&](unsigned char *base, int u, const u32x4 (&src)[XW]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < NP; c++) {
+                u32x4 v;
+                if constexpr (NP == 1) v = src[0];
+                else v = u32x4{xw[0][c], xw[1][c], xw[2][c], xw[3][c]};
+                *(u32x4 *)(base + c * XBUF + xs_w + u * XC * ROWB) = v;
+            }
+        };
+        auto load_u = [&](int rt, int s, int g2, u32x4 *dst) __attribute__((always_inline)) {   // (Uf is padded by MP_UPAD bytes)
+            const char *b = (const char *)mp.Uf + (int64_t)((wrow0 >> 5) + rt * NWR) * u_tile + ((ia0 >> 4) + 2 * (int64_t)s + g2) * (NP * 1024);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, NP * 1024, 0x00020000);
+#pragma unroll
+            for (int c = 0; c < NP; c++) dst[c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, c * 1024, 0));
+        };
 
+        // tiles 0 .. H-1 into the ring.  (What a chunk hands to the next across its mode 2 lies in the ring; nothing is in flight in
+        // registers then, which mode 2 needs.)
+        if (jc == mp.ja0) {
+            u32x4 x0[H][XPT][XW];
+#pragma unroll
+            for (int d = 0; d < H; d++) request_x(x0[d], true);
+#pragma unroll
+            for (int d = 0; d < H; d++)
+#pragma unroll
+                for (int u = 0; u < XPT; u++) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) split_pair(e, x0[d][u]);
+                    store_x(smem + d * SLOT, u, x0[d][u]);
+                }
+            __syncthreads();
+        }
         f32x16 acc[RT][CT];
         float zero = 0.0f;
         asm volatile("" : "+v"(zero));   // a zero the compiler cannot keep as a 16-register vector across the chunks
@@ -276,90 +411,25 @@ __global__ __launch_bounds__(512, 2) void k_mode12_mp(const Mode12Params p, cons
 #pragma unroll
                 for (int e = 0; e < 16; e++) acc[rt][ct][e] = zero;
 
-        // requests this thread's 8 values of stage s (calls come in the order of the stages)
-        auto request_x = [&](int s, u32x4 *dst) __attribute__((always_inline)) {
-            s = s < nstage ? s : nstage - 1;
-            const int64_t ib = ia0 + (int64_t)s * EI;
-            const T *a;
-            if constexpr (PTR) {
-                if (p.xtab) {
-                    int64_t i = ib + 8 * part;
-                    i = i < p.i1 ? i : p.i1 - 1;
-                    if (__any(i >= tab_end)) {   // a block boundary: dI is a multiple of 16, a thread's 8 values lie in one block
-                        const int64_t bi = i / p.x_dI;
-                        xp = (const T *)tabrow[bi] + tab_in + (8 * part - bi * p.x_dI);
-                        tab_end = (bi + 1) * p.x_dI;
-                    }
-                }
-                a = xp + (ib - ia0);
-            } else
-                a = (const T *)((const char *)(xu + (ib - ia0)) + xo);
-            typedef const __attribute__((address_space(1))) T *gp;   // X is device memory whatever the pointer's origin
-            if (__builtin_expect(ib >= p.i0 && ib + EI <= p.i1, 1)) {
-                if constexpr (NP == 1) dst[0] = *(const __attribute__((address_space(1))) u32x4_a2 *)(gp)a;
-                else {
-                    dst[0] = *(const __attribute__((address_space(1))) u32x4_a4 *)(gp)a;
-                    dst[1] = *(const __attribute__((address_space(1))) u32x4_a4 *)(gp)(a + 4);
-                }
-            } else {   // first or last stage of a box that does not fill it: value by value, zero outside
-                const int64_t i = ib + 8 * part;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const bool ok = i + e >= p.i0 && i + e < p.i1;
-                    if constexpr (NP == 1) {
-                        const uint32_t v = ok ? (uint32_t)*(const __attribute__((address_space(1))) uint16_t *)(gp)(a + e) : 0u;
-                        dst[0][e >> 1] = (e & 1) ? (dst[0][e >> 1] | (v << 16)) : v;
-                    } else
-                        dst[e >> 2][e & 3] = ok ? *(const __attribute__((address_space(1))) uint32_t *)(gp)(a + e) : 0u;
-                }
-            }
-        };
-        uint32_t xw[4][NP];   // the pieces of the tile on its way to LDS
-        // splits values 2e, 2e+1 of the requested tile
-        auto split_pair = [&](int e, const u32x4 *src) __attribute__((always_inline)) {
-            if constexpr (NP > 1) {
-                const uint32_t ua = src[e >> 1][2 * (e & 1)], ub = src[e >> 1][2 * (e & 1) + 1];
-                const float a = __builtin_bit_cast(float, ua), b = __builtin_bit_cast(float, ub);
-                if (NP == 3) xmax = fmaxf(fmaxf(xmax, fabsf(a)), fabsf(b));
-                mp_split2<NP, F16, true>(a, b, xw[e]);
-            }
-        };
-        auto store_x = [&](unsigned char *base, const u32x4 *src) __attribute__((always_inline)) {
-#pragma unroll
-            for (int c = 0; c < NP; c++) {
-                u32x4 v;
-                if constexpr (NP == 1) v = src[0];
-                else v = u32x4{xw[0][c], xw[1][c], xw[2][c], xw[3][c]};
-                if (!full) v = cok ? v : u32x4{0u, 0u, 0u, 0u};
-                *(u32x4 *)(base + c * XBUF + xs_w) = v;
-            }
-        };
-        const int u_lane = lane * 16;
-        auto load_u = [&](int rt, int s, int g2, u32x4 *dst) __attribute__((always_inline)) {
-            s = s < nstage ? s : nstage - 1;
-            const char *b = (const char *)mp.Uf + (int64_t)((wrow0 >> 5) + rt * NWR) * u_tile + ((ia0 >> 4) + 2 * (int64_t)s + g2) * (NP * 1024);
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, NP * 1024, 0x00020000);
-#pragma unroll
-            for (int c = 0; c < NP; c++) dst[c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, u_lane, c * 1024, 0));
-        };
-
-        // One stage: the MFMAs of stage s, the tile of stage s+H split and written to its slot, the requests of later stages
+        // One stage: the MFMAs of stage s, the tile H stages ahead split and written to its slot, the requests of later stages
         auto stage = [&](auto sic, auto rac, int s) __attribute__((always_inline)) {
             constexpr int SI = decltype(sic)::value, RA = decltype(rac)::value;
             constexpr int US = SI % DU, XS = (SI + H) % DX;
-            const unsigned char *cur = smem + (SI % NSLOT) * SLOT;
-            unsigned char *oth = smem + ((SI + H) % NSLOT) * SLOT;
-            constexpr int NSP = NF < 4 ? NF : 4;   // fragments behind which the split of the tile is dealt out
+            const unsigned char *cur = smem + so + xs_r;
+            unsigned char *oth = smem + sw;
+            // The tile is split behind the last fragments, a run at a time: its request is a stage old, in a chunk's first stage
+            // younger (it follows mode 2).
+            constexpr int NPAIR = 4 * XPT, NSP = NF < XPT ? NF : XPT, FSP = NF - NSP;
             u32x4 bx[XD][NP];
-            auto load_bx = [&](int f, u32x4 *dst) __attribute__((always_inline)) {
+            auto load_bx = [&](int f) __attribute__((always_inline)) {
 #pragma unroll
-                for (int c = 0; c < NP; c++) dst[c] = *(const u32x4 *)(cur + c * XBUF + xs_r + (f % CT) * 32 * ROWB + (f / CT) * 32);
+                for (int c = 0; c < NP; c++) bx[f % XD][c] = *(const u32x4 *)(cur + c * XBUF + (f % CT) * 32 * ROWB + (f / CT) * 32);
             };
 #pragma unroll
-            for (int f = 0; f < XD - 1 && f < NF; f++) load_bx(f, bx[f]);
+            for (int f = 0; f < XD - 1 && f < NF; f++) load_bx(f);
             static_for<NF>([&](auto fc) {
                 constexpr int f = decltype(fc)::value, g2 = f / CT, ct = f % CT;
-                if constexpr (f + XD - 1 < NF) load_bx(f + XD - 1, bx[(f + XD - 1) % XD]);
+                if constexpr (f + XD - 1 < NF) load_bx(f + XD - 1);
                 __builtin_amdgcn_sched_barrier(0);
                 static_for<terms::N>([&](auto nc) {
                     constexpr int n = decltype(nc)::value;
@@ -371,52 +441,43 @@ __global__ __launch_bounds__(512, 2) void k_mode12_mp(const Mode12Params p, cons
                     for (int rt = 0; rt < RA; rt++) load_u(rt, s + DU, g2, ufr[US][g2][rt]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (f < NSP) {
-#pragma unroll
-                    for (int e = f * 4 / NSP; e < (f + 1) * 4 / NSP; e++) split_pair(e, xr[XS]);
-                    if constexpr (f == NSP - 1) {
-                        store_x(oth, xr[XS]);
-                        request_x(s + H + DX, xr[XS]);
-                    }
+                if constexpr (f >= FSP && f < FSP + NSP) {
+                    static_for<NPAIR / NSP>([&](auto ec) {
+                        constexpr int e = (f - FSP) * (NPAIR / NSP) + decltype(ec)::value;
+                        split_pair(e % 4, xr[XS][e / 4]);
+                        if constexpr (e % 4 == 3) store_x(oth, e / 4, xr[XS][e / 4]);
+                        // (in the last stages the request is made once more after mode 2; without a request here the registers would be
+                        // copied at the end of the stage, behind a wait for everything in flight)
+                        if constexpr (e == NPAIR - 1) {
+                            if (NP == 3) asm volatile("" : "+v"(xmax));   // here, and not behind the request, which takes the registers over
+                            request_x(xr[XS], s + DX < nst);
+                        }
+                    });
                     __builtin_amdgcn_sched_barrier(0);
                 }
             });
+            so = so == (NSLOT - 1) * SLOT ? 0 : so + SLOT;
+            sw = sw == (NSLOT - 1) * SLOT ? 0 : sw + SLOT;
+            if constexpr (H % UNR == 0) { if (H == 1 || so == 0 || sw == 0) __syncthreads(); }
+            else if constexpr ((SI + 1) % H == 0) __syncthreads();
         };
-
         auto run = [&](auto rac) __attribute__((always_inline)) {
             constexpr int RA = decltype(rac)::value;
-            // prologue: tiles 0 .. H-1 into the ring, tiles H .. H+DX-1 requested, U of the first stages requested
-            {
-                u32x4 x0[H][NP == 1 ? 1 : 2];
 #pragma unroll
-                for (int d = 0; d < H; d++) request_x(d, x0[d]);
+            for (int d = 0; d < DX; d++) request_x(xr[(H + d) % DX], true);
 #pragma unroll
-                for (int d = 0; d < DU; d++)
+            for (int d = 0; d < DU; d++)
 #pragma unroll
-                    for (int g2 = 0; g2 < 2; g2++)
+                for (int g2 = 0; g2 < 2; g2++) {
+                    // in this order: the compiler takes the wait in front of a stage's MFMAs from the smaller of the two counts of
+                    // requests behind the fragments they read, the one on the way in from here and the one around the loop
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int rt = 0; rt < RA; rt++) load_u(rt, d, g2, ufr[d][g2][rt]);
-#pragma unroll
-                for (int d = 0; d < DX; d++) request_x(H + d, xr[(H + d) % DX]);
-                __syncthreads();   // every wave is done with the slots of the previous chunk
-#pragma unroll
-                for (int d = 0; d < H; d++) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) split_pair(e, x0[d]);
-                    store_x(smem + d * SLOT, x0[d]);
+                    for (int rt = 0; rt < RA; rt++) load_u(rt, d, g2, ufr[d][g2][rt]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __syncthreads();
-            }
-            int s = 0;
-            auto chain = [&](auto self, auto cc) __attribute__((always_inline)) -> bool {
-                constexpr int c = decltype(cc)::value;
-                stage(cc, rac, s);
-                if (++s >= nstage) return false;
-                if constexpr ((c + 1) % H == 0) __syncthreads();
-                if constexpr (c + 1 < UNR) return self(self, ic<c + 1>());
-                else return true;
-            };
-            while (chain(chain, ic<0>())) {}
+            for (int s = 0; s < nst; s += UNR)
+                static_for<UNR>([&](auto c) { stage(c, rac, s + decltype(c)::value); });
         };
         if (RT == 2 && two) run(ic<2>()); else run(ic<1>());
 
