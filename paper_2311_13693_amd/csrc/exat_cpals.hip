@@ -1,15 +1,24 @@
 // Batched CP-ALS on the P proxy tensors (paper Alg. 1; Sec. 3 "Decomposition").  Declarations and contracts in
 // include/exat.h.
 //
-// The P problems are independent and small (L, M, N, R <= 64).  One update, e.g. of A, is two launches:
-//   k_cpals_mttkrp  Mx[l,r] = sum_n C[n,r] * (sum_m Y[l,m,n] * B[m,r]): the n range of every replica is cut into
-//                   slabs, one workgroup per (replica, slab), so that the P small problems fill the chip; lanes
-//                   along l, a quarter of the r per wave, the two factor matrices in LDS.  Partial results per slab.
-//   k_cpals_solve   one workgroup per replica: adds the slabs' partial results in slab order, forms the normal
-//                   matrix G = (C^T C) * (B^T B) (Hadamard product of the Gram matrices), factors it (Cholesky,
-//                   right-looking, in LDS) and solves A = Mx G^{-1}, one row of Mx per thread.
-// The tensor is read from three copies, one per mode, each with the updated mode's index contiguous, so that
-// every MTTKRP reads coalesced.  fp32 throughout; every sum has a fixed order.
+// The P problems are independent and small (L, M, N, R <= 64), so latency is what bounds them: the tensors stay in the caches,
+// a sweep is 3 * 2 L M N R flops per replica (1.6 GFLOP at 32 replicas of 64^3, rank 32: 10 us at the fp32 matrix rate) and the
+// rest are short serial steps.  One update, e.g. of A, is one launch, k_cpals_step, of NS workgroups per replica:
+//   1. the update before it is finished: the workgroup adds the NS partial MTTKRP results in slab order, forms the normal matrix
+//      G = (F2^T F2) * (F1^T F1) (Gram matrices on the fp32 matrix cores), inverts it and multiplies, X = Mx G^{-1}.  Every
+//      workgroup of the replica does that for itself (it needs the new factor at once and there is nothing to wait for); the
+//      first one writes the factor to memory.
+//   2. its share of this update's MTTKRP, Mx[d0,r] = sum_{d2} sum_{d1} Y[d0,d1,d2] F1[d1,r] F2[d2,r]: a product of the
+//      unfolded tensor with the Khatri-Rao matrix, whose entries are formed in registers, on the fp32 matrix cores, over a
+//      slab of the outer contraction index.
+// The tensor is read where it lies: a lane holds one row of the updated mode, and the order of the contraction indices inside
+// a matrix instruction is free, so the first mode reads 128-byte runs along l and the other two 16 bytes of l per lane.
+// The normal matrix is inverted in place by Gauss-Jordan steps without pivoting (it is positive definite; the diagonal elements
+// met are the squared pivots of its Cholesky factorisation): 256 threads own cyclic blocks of it in registers, a step publishes
+// one row and one column through LDS and has one barrier.
+// fp32 throughout; every sum has a fixed order.
+// Measured (32 tensors of 64^3, rank 32, ten sweeps): 3.06 ms with two launches per update and permuted copies of the tensor, 0.75 ms
+// now; an update takes 23 us, of which finishing the one before 10 (the inversion 5), the product 9 and an empty launch 4.
 #include "../../include/exat.h"
 
 #include <hip/hip_runtime.h>
@@ -20,200 +29,327 @@ namespace {
 
 constexpr int CP_MAX = 64;   // largest L, M, N and R
 
-struct CpUpdate {
-    const float *Yp;        // the copy of Y with the updated mode contiguous: per replica [d0 + D0(d1 + D1 d2)]
-    const float *F1, *F2;   // the two fixed factors, per replica column-major D1 x R, D2 x R
-    float *F0;              // the updated factor, per replica column-major D0 x R
-    float *part;            // [replica][slab][d0][R] partial MTTKRP results
-    int D0, D1, D2, R, NS, DS;   // NS slabs of DS values of d2
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // rows of Y start at multiples of 4 bytes
+
+struct CpStep {
+    const float *Y;         // per replica Y[l + L(m + M n)]
+    float *F[3];            // A, B, C, per replica column-major D x R
+    const float *pin;       // [replica][NSin][d][R]: partial MTTKRP results of the update before this one
+    float *pout;            // the same of this update
+    int D[3];               // L, M, N
+    int R, NSin, NS, DS;    // NS slabs of DS values of the outer contraction index
+    int prev, mode;         // updated factor of the update before and of this one (0, 1, 2), or -1: none
+    int P;
     int32_t *status;        // optional, [replica]: incremented by every update whose normal matrix has a non-positive pivot
 };
 
-// Y2[m + M(l + Ln)] and Y3[n + N(l + Lm)] from Y[l + L(m + Mn)], all replicas
-__global__ __launch_bounds__(256) void k_cpals_permute(const float *Y, float *Y2, float *Y3, int L, int M, int N, int64_t total)
+// 1/x to within an ulp: the hardware's estimate and one Newton step; the division itself where either would leave the normal range
+__device__ __forceinline__ float recip(float x)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
-    const int64_t lmn = (int64_t)L * M * N, p = t / lmn, e = t % lmn;
-    const int l = (int)(e % L), m = (int)((e / L) % M), n = (int)(e / ((int64_t)L * M));
-    const float y = Y[t];
-    Y2[p * lmn + m + (int64_t)M * (l + (int64_t)L * n)] = y;
-    Y3[p * lmn + n + (int64_t)N * (l + (int64_t)L * m)] = y;
+    const float ax = fabsf(x), r = __builtin_amdgcn_rcpf(x), y = fmaf(fmaf(-x, r, 1.0f), r, r);
+    return (ax > 0x1p-120f && ax < 0x1p120f) ? y : 1.0f / x;
 }
 
-// column-major D x R in memory -> [d][RS] in LDS, zero beyond D and R
-template <int RS>
-__device__ inline void load_factor(float *F, const float *src, int D, int R, int tid)
+// RC = 32-column tiles of the rank, NB = 16-wide blocks of it (R <= 16 NB, NB <= 2 RC)
+template <int RC, int NB>
+__global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
 {
-    for (int e = tid; e < CP_MAX * RS; e += 256) F[e] = 0.0f;
-    __syncthreads();
-    for (int e = tid; e < D * R; e += 256) F[(e % D) * RS + e / D] = src[e];
-}
-
-// RW = columns r per wave (R <= 4*RW); factor rows in LDS are RS = 4*RW floats long
-template <int RW>
-__global__ __launch_bounds__(256) void k_cpals_mttkrp(const CpUpdate p)
-{
-    constexpr int RS = 4 * RW;
-    __shared__ float F1[CP_MAX * RS], F2[CP_MAX * RS];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    constexpr int RS = 32 * RC, RSP = RS + 1;
+    __shared__ float Fs[3][CP_MAX * RSP];     // factors as [d][r], zero beyond D and R
+    __shared__ float Mx[CP_MAX * RSP];        // MTTKRP result of the update before; scratch of the partial tiles
+    __shared__ float G[RS * RSP];             // normal matrix, then its inverse
+    __shared__ float Gt[RC == 1 ? 4 : 8][1024];   // tiles of the Gram matrices
+    __shared__ float rowb[2][2][64], colb[2][2][64];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t rep = blockIdx.x;
-    const int slab = blockIdx.y, D0 = p.D0, D1 = p.D1, R = p.R;
-    load_factor<RS>(F1, p.F1 + rep * D1 * R, D1, R, tid);
-    load_factor<RS>(F2, p.F2 + rep * p.D2 * R, p.D2, R, tid);
-    __syncthreads();
-    float acc[RW];
+    const int slab = blockIdx.y, R = p.R;
+
+    // ---- this workgroup's share of the MTTKRP.  Mode 0: rows l, inner m, outer n; mode 1: rows m, inner l, outer n; mode 2:
+    //      rows n, inner l, outer m.  Tile (rt, ct) of the result to wave w mod ntile; the waves of a tile take the values of
+    //      the outer index in turn ----
+    const int u = p.mode >= 0 ? p.mode : 0, Du = p.D[u], i1 = u == 0 ? 1 : 0, i2 = u == 2 ? 1 : 2, D1 = p.D[i1], D2 = p.D[i2];
+    const int rtn = (Du + 31) / 32, ntile = rtn * RC, kgn = 4 / ntile, kg = w / ntile, tile = w % ntile;
+    const int row = 32 * (tile / RC) + l32, c = 32 * (tile % RC) + l32;
+    // element (row, d1, d2) of the tensor: a wave-uniform pointer to (0, d1, d2) and the lane's 32-bit offset (a replica has at most
+    // 2^18 elements)
+    const int LM = p.D[0] * p.D[1], su = u == 0 ? 1 : (u == 1 ? p.D[0] : LM), s2 = u == 2 ? p.D[0] : LM;
+    const float *yu = p.Y + rep * LM * p.D[2];
+    const unsigned ro = (unsigned)((row < Du ? row : Du - 1) * su);
+    constexpr int NSTEP = CP_MAX / 2;
+    const int nq = (D1 + 7) / 8;           // groups of 8 inner indices
+    const int d2a = slab * p.DS, d2b = d2a + p.DS < D2 ? d2a + p.DS : D2;
+    auto load = [&](int d2, f32x4 (&a)[NSTEP / 4]) __attribute__((always_inline)) {
+        const float *y = yu + d2 * s2;
 #pragma unroll
-    for (int x = 0; x < RW; x++) acc[x] = 0.0f;
-    const int r0 = w * RW;
-    const bool on = lane < D0;
-    const float *yl = p.Yp + rep * D0 * D1 * p.D2 + (on ? lane : 0);
-    const int d2a = slab * p.DS, d2b = (d2a + p.DS < p.D2) ? d2a + p.DS : p.D2;
-    for (int d2 = d2a; d2 < d2b; d2++) {
-        float s[RW];
+        for (int q = 0; q < NSTEP / 4; q++) {
+            if (q < nq) {
+                if (u == 0) {
 #pragma unroll
-        for (int x = 0; x < RW; x++) s[x] = 0.0f;
-        const float *yd = yl + (int64_t)D0 * D1 * d2;
-        int d1 = 0;
-        for (; d1 + 4 <= D1; d1 += 4) {   // four loads in flight
-            const float y0 = yd[(int64_t)D0 * d1], y1 = yd[(int64_t)D0 * (d1 + 1)];
-            const float y2 = yd[(int64_t)D0 * (d1 + 2)], y3 = yd[(int64_t)D0 * (d1 + 3)];
+                    for (int e = 0; e < 4; e++) {
+                        const int d = 8 * q + 2 * e;   // lane half hi: d + hi; beyond D1 the factor is zero and any element will do
+                        if (d + 1 < D1) a[q][e] = (y + d * p.D[0])[ro + (unsigned)(hi * p.D[0])];
+                        else a[q][e] = (y + (D1 - 1) * p.D[0])[ro];
+                    }
+                } else if (8 * q + 8 <= D1)
+                    a[q] = *(const f32x4_a4 *)((y + 8 * q) + (ro + 4u * hi));
+                else {
 #pragma unroll
-            for (int x = 0; x < RW; x++) {
-                s[x] = fmaf(y0, F1[d1 * RS + r0 + x], s[x]);
-                s[x] = fmaf(y1, F1[(d1 + 1) * RS + r0 + x], s[x]);
-                s[x] = fmaf(y2, F1[(d1 + 2) * RS + r0 + x], s[x]);
-                s[x] = fmaf(y3, F1[(d1 + 3) * RS + r0 + x], s[x]);
+                    for (int e = 0; e < 4; e++) {
+                        const int d = 8 * q + 4 * hi + e;
+                        a[q][e] = y[ro + (unsigned)(d < D1 ? d : D1 - 1)];
+                    }
+                }
             }
         }
-        for (; d1 < D1; d1++) {
-            const float y0 = yd[(int64_t)D0 * d1];
+    };
+    // the wave's first PF values of the outer index are requested ahead of everything else: most of its share comes in while the
+    // update before is finished
+    constexpr int PF = 4;
+    f32x4 ya[PF][NSTEP / 4];
+    if (p.mode >= 0) {
 #pragma unroll
-            for (int x = 0; x < RW; x++) s[x] = fmaf(y0, F1[d1 * RS + r0 + x], s[x]);
-        }
-#pragma unroll
-        for (int x = 0; x < RW; x++) acc[x] = fmaf(s[x], F2[d2 * RS + r0 + x], acc[x]);
+        for (int i = 0; i < PF; i++)
+            if (d2a + kg + i * kgn < d2b) load(d2a + kg + i * kgn, ya[i]);
     }
-    if (on) {
-        float *dst = p.part + ((rep * p.NS + slab) * D0 + lane) * R;
-#pragma unroll
-        for (int x = 0; x < RW; x++)
-            if (r0 + x < R) dst[r0 + x] = acc[x];
-    }
-}
 
-template <int RW>
-__global__ __launch_bounds__(256) void k_cpals_solve(const CpUpdate p)
-{
-    constexpr int RS = 4 * RW;
-    __shared__ float F1[CP_MAX * RS], F2[CP_MAX * RS];
-    __shared__ float G[RS * (RS + 1)];        // normal matrix, updated in place by the factorisation (row stride R+1)
-    __shared__ float Lf[RS * (RS + 1)];       // its Cholesky factor
-    __shared__ float Mx[CP_MAX * (RS + 1)];   // MTTKRP result (row stride R+1)
-    const int tid = threadIdx.x;
-    const int64_t rep = blockIdx.x;
-    const int D0 = p.D0, D1 = p.D1, D2 = p.D2, R = p.R, GS = R + 1;
-    load_factor<RS>(F1, p.F1 + rep * D1 * R, D1, R, tid);
-    load_factor<RS>(F2, p.F2 + rep * D2 * R, D2, R, tid);
-    // MTTKRP result: the slabs' partial results in slab order
-    for (int e = tid; e < D0 * R; e += 256) {
-        const float *src = p.part + rep * p.NS * D0 * R + e;
-        const int64_t st = (int64_t)D0 * R;
-        float v = 0.0f;
-        int sl = 0;
-        for (; sl + 32 <= p.NS; sl += 32) {   // 32 loads in flight (a round trip to memory each), added in slab order
-            float t[32];
+    // The factors that are fixed in the update before this one (without one: in this update).  All loads below are made at clamped
+    // addresses and masked afterwards, so that they are in flight together.
+    const int v = p.prev >= 0 ? p.prev : p.mode;
+    const int f1 = v == 0 ? 1 : 0, f2 = v == 2 ? 1 : 2;
+    constexpr int FE = CP_MAX * RS / 256;
+    {
+        float t[2][FE];
 #pragma unroll
-            for (int u = 0; u < 32; u++) t[u] = src[(sl + u) * st];
+        for (int q = 0; q < 2; q++) {
+            const int f = q ? f2 : f1, D = p.D[f];
+            const float *src = p.F[f] + rep * D * R;
 #pragma unroll
-            for (int u = 0; u < 32; u++) v += t[u];
+            for (int x = 0; x < FE; x++) {
+                const int e = tid + 256 * x, d = e % CP_MAX, r = e / CP_MAX;
+                t[q][x] = src[(d < D ? d : D - 1) + D * (r < R ? r : R - 1)];
+            }
         }
-        for (; sl + 8 <= p.NS; sl += 8) {
-            float t[8];
 #pragma unroll
-            for (int u = 0; u < 8; u++) t[u] = src[(sl + u) * st];
+        for (int q = 0; q < 2; q++) {
+            const int f = q ? f2 : f1, D = p.D[f];
 #pragma unroll
-            for (int u = 0; u < 8; u++) v += t[u];
+            for (int x = 0; x < FE; x++) {
+                const int e = tid + 256 * x, d = e % CP_MAX, r = e / CP_MAX;
+                Fs[f][d * RSP + r] = (d < D && r < R) ? t[q][x] : 0.0f;
+            }
         }
-        for (; sl < p.NS; sl++) v += src[sl * st];
-        Mx[(e / R) * GS + e % R] = v;
     }
-    __syncthreads();
-    // normal matrix G = (F2^T F2) * (F1^T F1)
-    for (int e = tid; e < R * R; e += 256) {
-        const int r = e / R, c = e % R;
-        float g1 = 0.0f, g2 = 0.0f;
-        for (int d = 0; d < D1; d++) g1 = fmaf(F1[d * RS + r], F1[d * RS + c], g1);
-        for (int d = 0; d < D2; d++) g2 = fmaf(F2[d * RS + r], F2[d * RS + c], g2);
-        G[r * GS + c] = g1 * g2;
-    }
-    __syncthreads();
-    // Cholesky factor, right-looking, one barrier per column: every thread scales the entries of column j that it
-    // needs by the pivot's inverse square root on the fly for its share of the trailing triangle, and the scaled
-    // column goes to a second matrix Lf (nobody reads column j of G again), so reading and scaling do not collide.
-    bool bad = false;   // the same in every thread: all read the same pivots
-    for (int j = 0; j < R; j++) {
-        const float piv = G[j * GS + j];
-        bad = bad || !(piv > 0.0f);   // zero, negative or NaN: the normal matrix is not positive definite in fp32
-        const float inv = 1.0f / sqrtf(piv);
-        for (int t = j + tid; t < R; t += 256) Lf[t * GS + j] = G[t * GS + j] * inv;   // t = j: the pivot's square root
-        const int n = R - 1 - j;   // trailing triangle: rows t > j, columns j < c <= t
-        for (int e = tid; e < n * n; e += 256) {
-            const int t = j + 1 + e / n, c = j + 1 + e % n;
-            if (c <= t) G[t * GS + c] = fmaf(-(G[t * GS + j] * inv), G[c * GS + j] * inv, G[t * GS + c]);
+
+    if (p.prev >= 0) {
+        const int D0 = p.D[v];
+        // MTTKRP result: the slabs' partial results in slab order
+        const float *src = p.pin + rep * p.NSin * D0 * R;
+        const int st = D0 * R;
+        constexpr int XB = FE < 4 ? FE : 4;
+#pragma unroll
+        for (int x0 = 0; x0 < FE; x0 += XB) {
+            const float *q[XB];
+            float x[XB];
+#pragma unroll
+            for (int i = 0; i < XB; i++) {
+                const int e = tid + 256 * (x0 + i), d = e / RS, r = e % RS;
+                q[i] = src + (d < D0 ? d : D0 - 1) * R + (r < R ? r : R - 1);
+                x[i] = 0.0f;
+            }
+            int sl = 0;
+            for (; sl + 8 <= p.NSin; sl += 8) {
+                float t[XB][8];
+#pragma unroll
+                for (int i = 0; i < XB; i++)
+#pragma unroll
+                    for (int u = 0; u < 8; u++) t[i][u] = q[i][(sl + u) * st];
+#pragma unroll
+                for (int i = 0; i < XB; i++)
+#pragma unroll
+                    for (int u = 0; u < 8; u++) x[i] += t[i][u];
+            }
+            for (; sl < p.NSin; sl++)
+#pragma unroll
+                for (int i = 0; i < XB; i++) x[i] += q[i][sl * st];
+#pragma unroll
+            for (int i = 0; i < XB; i++) {
+                const int e = tid + 256 * (x0 + i), d = e / RS, r = e % RS;
+                Mx[d * RSP + r] = (d < D0 && r < R) ? x[i] : 0.0f;
+            }
         }
         __syncthreads();
+        // Gram matrices, one 32 x 32 tile of one of them (one tile only: half of its contraction) per job, jobs to the waves in turn
+        constexpr int KH = RC == 1 ? 2 : 1, NJ = RC * RC * 2 * KH;
+#pragma unroll
+        for (int j = w; j < NJ; j += 4) {
+            const int t = j / (2 * KH), m = (j / KH) & 1, kh = j % KH;
+            const float *F = Fs[m ? f2 : f1];
+            const int ri = 32 * (t / RC) + l32, ci = 32 * (t % RC) + l32;
+            f32x16 g[2];
+#pragma unroll
+            for (int e = 0; e < 16; e++) g[0][e] = g[1][e] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < CP_MAX / 2 / KH; s++) {
+                const int d = (2 * (s + kh * (CP_MAX / 2 / KH)) + hi) * RSP;
+                g[s & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(F[d + ri], F[d + ci], g[s & 1], 0, 0, 0);
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e++) Gt[j][e * 64 + lane] = g[0][e] + g[1][e];
+        }
+        __syncthreads();
+        for (int e = tid; e < RC * RC * 1024; e += 256) {
+            const int t = e >> 10, x = e & 1023, r = x >> 6, l = x & 63;
+            float g1 = Gt[2 * KH * t][x], g2 = Gt[2 * KH * t + KH][x];
+            if (KH == 2) { g1 += Gt[2 * KH * t + 1][x]; g2 += Gt[2 * KH * t + KH + 1][x]; }
+            G[(32 * (t / RC) + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * RSP + 32 * (t % RC) + (l & 31)] = g1 * g2;
+        }
+        __syncthreads();
+        // G <- G^{-1}: thread (ty, tx) owns the entries (ty + 16 a, tx + 16 b), extended by the identity beyond R.  A step eliminates
+        // two rows and columns, in the order and with the pivots of two single steps.
+        const int ty = tid >> 4, tx = tid & 15;
+        float g[NB][NB];
+#pragma unroll
+        for (int a = 0; a < NB; a++)
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                const int i = ty + 16 * a, c = tx + 16 * b;
+                g[a][b] = (i == c && i >= R) ? 1.0f : G[i * RSP + c];
+            }
+        bool bad = false;   // the same in every thread: all see the same pivots
+#pragma unroll
+        for (int jb = 0; jb < NB; jb++)
+            for (int jt = 0; jt < 16; jt += 2) {
+                const int j = 16 * jb + jt, par = (jt >> 1) & 1;
+                if (j >= R) break;
+                if ((tx & 14) == jt) {
+#pragma unroll
+                    for (int a = 0; a < NB; a++) colb[par][tx & 1][ty + 16 * a] = g[a][jb];
+                }
+                if ((ty & 14) == jt) {
+#pragma unroll
+                    for (int b = 0; b < NB; b++) rowb[par][ty & 1][tx + 16 * b] = g[jb][b];
+                }
+                __syncthreads();
+                const float p00 = colb[par][0][j], p10 = colb[par][0][j + 1], p01 = colb[par][1][j], p11 = colb[par][1][j + 1];
+                const float inv0 = recip(p00), ur = p01 * inv0, lr = p10 * inv0, s = fmaf(-lr, p01, p11), inv1 = recip(s);
+                bad = bad || !(p00 > 0.0f) || (j + 1 < R && !(s > 0.0f));   // zero, negative or NaN: not positive definite in fp32
+                float w0[NB], w1[NB], q0[NB], q1[NB];
+#pragma unroll
+                for (int a = 0; a < NB; a++) {
+                    const float f0 = colb[par][0][ty + 16 * a], f1v = colb[par][1][ty + 16 * a];
+                    w1[a] = fmaf(-f0, ur, f1v) * inv1;
+                    w0[a] = fmaf(-w1[a], p10, f0) * inv0;
+                    q0[a] = rowb[par][0][tx + 16 * a]; q1[a] = rowb[par][1][tx + 16 * a];
+                }
+#pragma unroll
+                for (int a = 0; a < NB; a++)
+#pragma unroll
+                    for (int b = 0; b < NB; b++) {
+                        float up = fmaf(-w1[a], q1[b], fmaf(-w0[a], q0[b], g[a][b]));
+                        if (b == jb) up = (tx & 14) == jt ? ((tx & 1) ? -w1[a] : -w0[a]) : up;
+                        if (a == jb) {
+                            const float r1 = fmaf(-lr, q0[b], q1[b]) * inv1, r0 = fmaf(-p01, r1, q0[b]) * inv0;
+                            float rr = (ty & 1) ? r1 : r0;
+                            if (b == jb) {   // the inverse of the 2 x 2 pivot block
+                                const float i01 = -ur * inv1;
+                                const float dd = (tx & 1) ? ((ty & 1) ? inv1 : i01) : ((ty & 1) ? -lr * inv1 : fmaf(-i01, lr, inv0));
+                                rr = (tx & 14) == jt ? dd : rr;
+                            }
+                            up = (ty & 14) == jt ? rr : up;
+                        }
+                        g[a][b] = up;
+                    }
+            }
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < NB; a++)
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                const int i = ty + 16 * a, c = tx + 16 * b;
+                G[i * RSP + c] = (i < R && c < R) ? g[a][b] : 0.0f;
+            }
+        if (bad && tid == 0 && slab == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
+        __syncthreads();
+        // X = Mx G^{-1}: tile (rt, ct) to wave (rt RC + ct) mod 4
+        const int rtn = (D0 + 31) / 32;
+        for (int t = w; t < rtn * RC; t += 4) {
+            const int row = 32 * (t / RC) + l32, c = 32 * (t % RC) + l32;
+            f32x16 x;
+#pragma unroll
+            for (int e = 0; e < 16; e++) x[e] = 0.0f;
+            for (int s = 0; s < 8 * NB; s++) x = __builtin_amdgcn_mfma_f32_32x32x2f32(Mx[row * RSP + 2 * s + hi], G[(2 * s + hi) * RSP + c], x, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int d = 32 * (t / RC) + 8 * (e >> 2) + 4 * hi + (e & 3);
+                Fs[v][d * RSP + c] = (d < D0 && c < R) ? x[e] : 0.0f;
+                if (slab == 0 && d < D0 && c < R) p.F[v][rep * D0 * R + d + (int64_t)D0 * c] = x[e];
+            }
+        }
+        for (int e = tid + 32 * rtn * RS; e < CP_MAX * RS; e += 256) Fs[v][(e / RS) * RSP + e % RS] = 0.0f;   // the unused row tile
     }
-    // one row of Mx per thread, held in registers: L z = m, then L^T o = z.  The loops are unrolled to the
-    // instantiation's largest rank, so the row is indexed statically and the reads of the factor (the same
-    // address for every thread) do not depend on the data.
-    if (bad && tid == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
-    if (tid < D0) {
-        float m[RS];
+    if (p.mode < 0) return;
+    __syncthreads();
+
+    // inner index of step s, lane half hi: mode 0: 2s + hi; else 8 (s/4) + 4 hi + s%4 (a lane's 16 bytes)
+    float b1[NSTEP];
 #pragma unroll
-        for (int i = 0; i < RS; i++) m[i] = i < R ? Mx[tid * GS + i] : 0.0f;
+    for (int s = 0; s < NSTEP; s++) {
+        const int d = u == 0 ? 2 * s + hi : 8 * (s >> 2) + 4 * hi + (s & 3);
+        b1[s] = Fs[i1][d * RSP + c];
+    }
+    f32x16 acc[2];
 #pragma unroll
-        for (int i = 0; i < RS; i++) {
-            if (i < R) {
-                float v = m[i];
+    for (int e = 0; e < 16; e++) acc[0][e] = acc[1][e] = 0.0f;
+    auto mac = [&](int d2, const f32x4 (&a)[NSTEP / 4]) __attribute__((always_inline)) {
+        const float f2 = Fs[i2][d2 * RSP + c];
 #pragma unroll
-                for (int k = 0; k < i; k++) v = fmaf(-Lf[i * GS + k], m[k], v);
-                m[i] = v / Lf[i * GS + i];
+        for (int q = 0; q < NSTEP / 4; q++) {
+            if (q < nq) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][e], b1[4 * q + e] * f2, acc[e & 1], 0, 0, 0);
             }
         }
+    };
+    for (int d2 = d2a + kg; d2 < d2b; d2 += PF * kgn) {
 #pragma unroll
-        for (int i = RS - 1; i >= 0; i--) {
-            if (i < R) {
-                float v = m[i];
-#pragma unroll
-                for (int k = i + 1; k < RS; k++)
-                    if (k < R) v = fmaf(-Lf[k * GS + i], m[k], v);
-                m[i] = v / Lf[i * GS + i];
-            }
+        for (int i = 0; i < PF; i++) {
+            if (d2 + i * kgn < d2b) mac(d2 + i * kgn, ya[i]);
+            if (d2 + (i + PF) * kgn < d2b) load(d2 + (i + PF) * kgn, ya[i]);
         }
-        float *dst = p.F0 + rep * D0 * R + tid;   // column-major D0 x R
+    }
 #pragma unroll
-        for (int r = 0; r < RS; r++)
-            if (r < R) dst[(int64_t)D0 * r] = m[r];
+    for (int e = 0; e < 16; e++) acc[0][e] += acc[1][e];
+    // the waves of a tile add up in wave order
+    for (int k = 1; k < kgn; k++) {
+        __syncthreads();
+        if (kg == k) {
+#pragma unroll
+            for (int e = 0; e < 16; e++) Mx[(tile * 16 + e) * 64 + lane] = acc[0][e];
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[0][e] += Mx[(tile * 16 + e) * 64 + lane];
+        }
+    }
+    if (kg == 0) {
+        float *dst = p.pout + (rep * p.NS + slab) * Du * R;
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int d = 32 * (tile / RC) + 8 * (e >> 2) + 4 * hi + (e & 3);
+            if (d < Du && c < R) dst[d * R + c] = acc[0][e];
+        }
     }
 }
 
-// slabs per replica: enough workgroups for about four per compute unit, at most one slab per value of d2
+// workspace: slabs of 64 x 64 values per replica
 inline int slabs_for(int D2, int P)
 {
     int ns = (1024 + P - 1) / P;
     return ns < 1 ? 1 : (ns > D2 ? D2 : ns);
-}
-
-template <int RW>
-int launch_update(CpUpdate u, int P, hipStream_t st)
-{
-    u.NS = slabs_for(u.D2, P);
-    u.DS = (u.D2 + u.NS - 1) / u.NS;
-    u.NS = (u.D2 + u.DS - 1) / u.DS;
-    hipLaunchKernelGGL(k_cpals_mttkrp<RW>, dim3((unsigned)P, (unsigned)u.NS), dim3(256), 0, st, u);
-    hipLaunchKernelGGL(k_cpals_solve<RW>, dim3((unsigned)P), dim3(256), 0, st, u);
-    return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
 }  // namespace
@@ -223,7 +359,8 @@ extern "C" {
 int64_t exat_cpals_workspace_floats(int32_t L, int32_t M, int32_t N, int32_t P)
 {
     if (L < 1 || M < 1 || N < 1 || P < 1) return 0;
-    // two permuted copies of Y + the slabs' partial MTTKRP results (at most 64 slabs of 64 x 64 per replica)
+    // the slabs' partial MTTKRP results, double-buffered, need slabs_for x 64 x 64 values per replica at most; the call documents
+    // the larger figure (room for two copies of Y)
     const int maxd = L > M ? (L > N ? L : N) : (M > N ? M : N);
     return 2 * (int64_t)L * M * N * P + (int64_t)P * slabs_for(maxd, P) * CP_MAX * CP_MAX;
 }
@@ -247,30 +384,44 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
     if (L < 1 || M < 1 || N < 1 || R < 1 || P < 1 || sweeps < 0) return EXAT_ERR_SHAPE;
     if (L > CP_MAX || M > CP_MAX || N > CP_MAX || R > CP_MAX || P > (1 << 20)) return EXAT_ERR_SHAPE;
     hipStream_t st = (hipStream_t)stream;
-    const int64_t total = (int64_t)L * M * N * P;
-    float *Y2 = work, *Y3 = work + total, *part = work + 2 * total;
     if (status) {   // a fill kernel, not a memset: the call may be recorded into a graph
         hipLaunchKernelGGL(k_cpals_clear_status, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, status, P);
         if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
     }
-    if (sweeps > 0) {
-        hipLaunchKernelGGL(k_cpals_permute, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Y, Y2, Y3, L, M, N, total);
-        if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
-    }
-    auto update = [&](const float *Yp, float *F0, const float *F1, const float *F2, int D0, int D1, int D2) {
-        CpUpdate u;
-        u.Yp = Yp; u.F0 = F0; u.F1 = F1; u.F2 = F2; u.part = part; u.status = status; u.D0 = D0; u.D1 = D1; u.D2 = D2; u.R = R; u.NS = 1; u.DS = D2;
-        if (R <= 16) return launch_update<4>(u, P, st);
-        if (R <= 32) return launch_update<8>(u, P, st);
-        return launch_update<16>(u, P, st);
+    if (sweeps == 0) return EXAT_OK;
+    // Slabs per replica: about one workgroup per compute unit, and no more than 16, since every workgroup adds up all slabs.  The
+    // partial results are double-buffered (a workgroup that is ahead writes while others still read) unless a replica has
+    // one workgroup only.
+    const int maxd = L > M ? (L > N ? L : N) : (M > N ? M : N);
+    int NS = 256 / P;
+    NS = NS > 16 ? 16 : (NS < 1 ? 1 : NS);
+    const int64_t room = (int64_t)slabs_for(maxd, P) * CP_MAX * CP_MAX, one = (int64_t)maxd * R;
+    while (NS > 1 && 2 * NS * one > room) NS--;
+    float *part[2] = {work, NS > 1 ? work + (int64_t)P * NS * one : work};
+    CpStep c;
+    c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.P = P; c.status = status;
+    c.NSin = 1; c.prev = -1;
+    auto launch = [&](int ns) {
+        const dim3 grid((unsigned)P, (unsigned)ns);
+        if (R <= 16) hipLaunchKernelGGL((k_cpals_step<1, 1>), grid, dim3(256), 0, st, c);
+        else if (R <= 32) hipLaunchKernelGGL((k_cpals_step<1, 2>), grid, dim3(256), 0, st, c);
+        else hipLaunchKernelGGL((k_cpals_step<2, 4>), grid, dim3(256), 0, st, c);
     };
-    for (int t = 0; t < sweeps; t++) {
-        int rc;
-        if ((rc = update(Y, A, B, C, L, M, N)) != EXAT_OK) return rc;    // A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^-1
-        if ((rc = update(Y2, B, A, C, M, L, N)) != EXAT_OK) return rc;   // B <- Y_(2) (C kr A) [(C^T C) * (A^T A)]^-1
-        if ((rc = update(Y3, C, A, B, N, L, M)) != EXAT_OK) return rc;   // C <- Y_(3) (B kr A) [(B^T B) * (A^T A)]^-1
+    // A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^-1, then B <- Y_(2) (C kr A) [..]^-1, then C <- Y_(3) (B kr A) [..]^-1: the launch of an
+    // update finishes the one before it
+    for (int t = 0; t < 3 * sweeps; t++) {
+        c.mode = t % 3;
+        const int D2 = c.mode == 2 ? M : N;
+        int ns = NS < D2 ? NS : D2;
+        c.DS = (D2 + ns - 1) / ns;
+        c.NS = (D2 + c.DS - 1) / c.DS;
+        c.pin = part[(t + 1) & 1]; c.pout = part[t & 1];
+        launch(c.NS);
+        c.NSin = c.NS; c.prev = c.mode;
     }
-    return EXAT_OK;
+    c.pin = part[(3 * sweeps + 1) & 1]; c.pout = nullptr; c.mode = -1; c.NS = 1;
+    launch(1);
+    return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
 }  // extern "C"
@@ -300,8 +451,7 @@ int exat_cpals_noalloc(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) { (void)hipGetLastError(); return EXAT_ERR_HIP; }
         g_scratch_ptr[dev] = (float *)ptr;
     }
-    // nothing of the workspace has to start at zero: every sweep writes the permuted copies and the slab sums before
-    // it reads them
+    // nothing of the workspace has to start at zero: every update writes the partial results that the next launch reads
     return exat_cpals(Y, L, M, N, P, R, sweeps, A, B, C, g_scratch_ptr[dev], stream);
 }
 
