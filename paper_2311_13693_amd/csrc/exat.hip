@@ -245,7 +245,7 @@ template <int NP, int NW, int NWC>
 int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
 {
     // the lean build unless X is a set of blocks, the box has odd ends in i, or the fibres are millions of values long
-    const bool ptr = mp.xtab || mp.i0 % 8 != 0 || mp.i1 % 8 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
+    const bool ptr = mp.xtab || mp.i0 % 4 != 0 || mp.i1 % 4 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
     return ptr ? launch_mp_inst<NP, NW, NWC, true>(mp, q, nk, st) : launch_mp_inst<NP, NW, NWC, false>(mp, q, nk, st);
 }
 template <int NP>
@@ -812,12 +812,12 @@ int exat_gen_block(const exat_desc_t *desc, const exat_gen_t *gen, int32_t bi, i
     gp.j0 = (int64_t)bj * d.dJ; gp.j1 = gp.j0 + blk_ext(d.J, d.dJ, bj);
     gp.k0 = (int64_t)bk * d.dK; gp.k1 = gp.k0 + blk_ext(d.K, d.dK, bk);
     const int64_t nq = ((gp.i1 - 1) >> 2) - (gp.i0 >> 2) + 1;
-    const int64_t n = nq * (gp.j1 - gp.j0) * (gp.k1 - gp.k0);
+    const int64_t nb = cdiv(nq, GB_Q) * cdiv(gp.j1 - gp.j0, GB_J * GB_W) * (gp.k1 - gp.k0);
+    const dim3 grid((unsigned)(nb > (1 << 22) ? (1 << 22) : nb));
+    const size_t lds = (size_t)GB_W * gp.R * GB_J * sizeof(float);   // at most 32 KiB (R <= 256)
     hipStream_t st = (hipStream_t)stream;
-    if (d.in_dtype == EXAT_BF16)
-        hipLaunchKernelGGL(k_gen_box<__bf16>, dim3(grid_for(n)), dim3(256), 0, st, gp, (__bf16 *)out);
-    else
-        hipLaunchKernelGGL(k_gen_box<float>, dim3(grid_for(n)), dim3(256), 0, st, gp, (float *)out);
+    if (d.in_dtype == EXAT_BF16) hipLaunchKernelGGL(k_gen_box<__bf16>, grid, dim3(64 * GB_W), lds, st, gp, (__bf16 *)out);
+    else hipLaunchKernelGGL(k_gen_box<float>, grid, dim3(64 * GB_W), lds, st, gp, (float *)out);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 

@@ -204,34 +204,78 @@ struct GenParams {
     int64_t i0, i1, j0, j1, k0, k1;
 };
 
+// Bound by the writes and, close behind, by the noise (39 vector instructions per four elements).  A wave owns GB_Q quads of
+// four consecutive i (one per lane) of GB_J fibres: a quad of A serves all of them, and what depends on the fibre only -- the
+// products B[j,r] C[k,r], the fibre's key -- is formed once per wave (LDS, scalar registers).  Before, a thread made one quad and
+// read A, B and C for each.  500^3, R = 5, fp32: 0.595 ms before,
+// 0.095 ms now (5.3 TB/s written).
+constexpr int GB_Q = 64, GB_J = 8, GB_W = 4;   // quads and fibres per wave, waves per workgroup
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_gen_box(const GenParams p, T *out)
+__global__ __launch_bounds__(64 * GB_W) void k_gen_box(const GenParams p, T *out)
 {
+    extern __shared__ float bcs[];   // [wave][r][GB_J]
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int64_t q0 = p.i0 >> 2, nq = ((p.i1 - 1) >> 2) - q0 + 1;
     const int64_t di = p.i1 - p.i0, dj = p.j1 - p.j0, dk = p.k1 - p.k0;
-    const int64_t n = nq * dj * dk;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t iq = q0 + idx % nq, jk = idx / nq;
-        const int64_t j = p.j0 + jk % dj, k = p.k0 + jk / dj;
-        float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int r = 0; r < p.R; r++) {
-            const float bc = p.B[j + p.ldB * r] * p.C[k + p.ldC * r];
+    const int64_t nqb = (nq + GB_Q - 1) / GB_Q, njb = (dj + GB_J * GB_W - 1) / (GB_J * GB_W), nb = nqb * njb * dk;
+    float *bc = bcs + w * p.R * GB_J;
+    typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+    typedef T out4 __attribute__((ext_vector_type(4)));
+    typedef out4 out4_u __attribute__((aligned(sizeof(T))));
+    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int64_t qb = b % nqb, jb = b / nqb % njb, k = p.k0 + b / (nqb * njb);
+        const int64_t jw = p.j0 + (jb * GB_W + w) * GB_J;   // the wave's first fibre; fibres past the box are made and not written
+        const int64_t iq = q0 + qb * GB_Q + lane, i = 4 * iq;
+        __syncthreads();   // the products of the round before have been read
+        for (int e = lane; e < p.R * GB_J; e += 64) {
+            const int r = e / GB_J;
+            const int64_t j = jw + e % GB_J < p.j1 ? jw + e % GB_J : p.j1 - 1;
+            bc[e] = p.B[j + p.ldB * r] * p.C[k + p.ldC * r];
+        }
+        __syncthreads();
+        float x[GB_J][4];
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int64_t i = 4 * iq + e;
-                if (i >= p.i0 && i < p.i1) x[e] = __builtin_fmaf(p.A[i + p.ldA * r], bc, x[e]);
+        for (int u = 0; u < GB_J; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) x[u][e] = 0.0f;
+        const bool whole = i >= p.i0 && i + 4 <= p.i1;
+        for (int r = 0; r < p.R; r++) {
+            f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
+            const float *ap = p.A + p.ldA * r;
+            if (whole) a = *(const f32x4_a4 *)(ap + i);
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (i + e >= p.i0 && i + e < p.i1) a[e] = ap[i + e];
             }
+            const f32x4 b0 = *(const f32x4 *)(bc + r * GB_J), b1 = *(const f32x4 *)(bc + r * GB_J + 4);
+#pragma unroll
+            for (int u = 0; u < GB_J; u++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[u][e] = __builtin_fmaf(a[e], u < 4 ? b0[u & 3] : b1[u & 3], x[u][e]);
         }
         if (p.amp2_ln2 != 0.0f) {
-            float z[4];
-            noise_quad(fibre_key(p.skey, (uint32_t)j, (uint32_t)k), (uint32_t)iq, p.amp2_ln2, z);
 #pragma unroll
-            for (int e = 0; e < 4; e++) x[e] += z[e];
+            for (int u = 0; u < GB_J; u++) {
+                float z[4];
+                noise_quad(fibre_key(p.skey, (uint32_t)(jw + u), (uint32_t)k), (uint32_t)iq, p.amp2_ln2, z);
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[u][e] += z[e];
+            }
         }
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int64_t i = 4 * iq + e;
-            if (i >= p.i0 && i < p.i1) out[(i - p.i0) + di * ((j - p.j0) + dj * (k - p.k0))] = elem<T>::from_f32(x[e]);
+        for (int u = 0; u < GB_J; u++) {
+            if (jw + u >= p.j1) break;   // wave-uniform
+            T *dst = out + (i - p.i0) + di * ((jw + u - p.j0) + dj * (k - p.k0));
+            if (whole) {
+                const out4 v = {elem<T>::from_f32(x[u][0]), elem<T>::from_f32(x[u][1]), elem<T>::from_f32(x[u][2]), elem<T>::from_f32(x[u][3])};
+                *(out4_u *)dst = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (i + e >= p.i0 && i + e < p.i1) dst[e] = elem<T>::from_f32(x[u][e]);
+            }
         }
     }
 }

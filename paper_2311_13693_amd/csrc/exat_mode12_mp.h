@@ -214,9 +214,11 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
 // a fibre of X starts at a multiple of the element size, not of 16 bytes
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
 
 // PTR = false: a fibre of X is addressed by a wave-uniform base and a 32-bit offset of the lane (128 fibres of X are less than
-// 2^31 bytes apart), and the box begins and ends at multiples of 8 in i.  PTR = true: any box; a fibre is addressed by a 64-bit
+// 2^31 bytes apart), and the box begins and ends at multiples of 4 in i.  PTR = true: any box; a fibre is addressed by a 64-bit
 // pointer of the lane, which may come from the table of blocks of a slab.
 template <int NP, int NW, int NWC, bool PTR>
 __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp)
@@ -331,11 +333,21 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
                 else {   // a tile that is not filled by the box: zero outside
 #pragma unroll
                     for (int c = 0; c < XW; c++) dst[u][c] = u32x4{0u, 0u, 0u, 0u};
-                    if constexpr (!PTR) {   // whole runs only: i0 and i1 are multiples of 8
+                    if constexpr (!PTR) {   // half runs of 4 values: i0 and i1 are multiples of 4
                         const int lo = (int)(p.i0 - ib), hi_ = p.i1 - ib < EI ? (int)(p.i1 - ib) : EI;
                         const int jl = (int)(p.j0 - pj), jh = p.j1 - pj < COLS ? (int)(p.j1 - pj) : COLS;
                         const int c = col + u * XC;
-                        if (8 * part >= lo && 8 * part < hi_ && c >= jl && c < jh) load_run(a, dst[u]);
+                        if (c >= jl && c < jh) {
+#pragma unroll
+                            for (int h = 0; h < 2; h++)
+                                if (8 * part + 4 * h >= lo && 8 * part + 4 * h < hi_) {
+                                    if constexpr (NP == 1) {
+                                        const u32x2_a2 v = *(const __attribute__((address_space(1))) u32x2_a2 *)(gp)(a + 4 * h);
+                                        dst[u][0][2 * h] = v[0]; dst[u][0][2 * h + 1] = v[1];
+                                    } else
+                                        dst[u][h] = *(const __attribute__((address_space(1))) u32x4_a4 *)(gp)(a + 4 * h);
+                                }
+                        }
                     } else {
                         const int64_t i = ib + 8 * part, j = pj + col + u * XC;
                         const bool jok = j >= p.j0 && j < p.j1;

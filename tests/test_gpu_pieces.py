@@ -59,7 +59,7 @@ def test_row_groups(dtype, P, L):
 # stages, ring slots and chunks: one stage and less, the ring length and around it, fibres around a chunk
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f32s"])
 @pytest.mark.parametrize("I,J,M", [(1, 1, 1), (8, 127, 32), (31, 128, 33), (32, 129, 64), (33, 40, 50), (64, 257, 20), (127, 16, 64), (128, 15, 32),
-                                   (129, 300, 50), (250, 250, 50), (257, 33, 64), (511, 130, 17)])
+                                   (129, 300, 50), (250, 250, 50), (244, 60, 20), (257, 33, 64), (511, 130, 17)])
 @pytest.mark.parametrize("P", [2, 7, 13])   # 4, 2 and 1 wave columns
 def test_extents(dtype, I, J, M, P):
     K, L, N = 6, 40, 9
@@ -71,7 +71,7 @@ def test_extents(dtype, I, J, M, P):
 
 # blocks whose edges are multiples of nothing, one by one; a slab of blocks of half stages in one launch; X not 16-byte aligned
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d", [(50, 45, 7), (37, 128, 4), (100, 33, 13)])
+@pytest.mark.parametrize("d", [(50, 45, 7), (37, 128, 4), (100, 33, 13), (52, 60, 5)])
 def test_odd_blocks(dtype, d):
     I, J, K, L, M, N, P = 115, 140, 13, 50, 50, 20, 13
     print("case", dtype, d, flush=True)
