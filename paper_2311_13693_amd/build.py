@@ -10,7 +10,7 @@ OBJDIR = os.path.join(HERE, "_build")
 _PUBLIC = os.path.join(os.path.dirname(HERE), "include", "exat.h")
 # translation unit -> the headers it includes
 UNITS = {
-    "exat.hip": ["exat_device.h", "exat_common.h", "exat_mode12.h", "exat_mode2.h", "exat_mode12_v2.h",
+    "exat.hip": ["exat_device.h", "exat_common.h", "exat_mode12.h", "exat_mode2.h", "exat_gen.h",
                  "exat_mode12_v3.h", "exat_mode12_v4.h", "exat_mode12_mp.h", "exat_aux.h"],
     "exat_stage1.hip": [],
     "exat_cpals.hip": [],

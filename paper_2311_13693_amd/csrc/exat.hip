@@ -13,7 +13,6 @@
 
 #include "exat_aux.h"
 #include "exat_mode12.h"
-#include "exat_mode12_v2.h"
 #include "exat_mode12_v3.h"
 #include "exat_mode12_v4.h"
 #include "exat_mode12_mp.h"
@@ -32,10 +31,9 @@ struct exat_plan_s {
     int PL, PLpad, Mpad, MT, Npad;
     int64_t Ipad, Jpad;
     void *Upack = nullptr;
-    void *Ufrag = nullptr;  // U in MFMA fragment order (k_pack_u_frag), same size as Upack
+    void *Ufrag = nullptr;  // bf16 plans: U in MFMA fragment order (k_pack_u_frag), same size as Upack
     void *Vfragz = nullptr; // bf16 plans: V in the fragment order of mode2_direct_bf16 (k_pack_v_frag with perm = 1)
-    void *Vfrag = nullptr;  // bf16 plans: V in bf16 MFMA fragment order (k_pack_v_frag); fp32 plans: V in the order
-                            // mode2_direct consumes (k_pack_v_direct)
+    void *Vfrag = nullptr;  // bf16 plans: V in bf16 MFMA fragment order (k_pack_v_frag)
     void *Ump = nullptr, *Vmp = nullptr;   // fp32 plans: three bf16 pieces of U and V (MpParams)
     void *Usp = nullptr, *Vsp = nullptr;   // split plans: two fp16 pieces
     uint32_t *ranges = nullptr;            // value ranges noted by the pack kernels and k_mode12_mp (MPF_*)
@@ -152,11 +150,12 @@ int launch_mode12_bf16(int rt, const Mode12Params &mp, int nk, hipStream_t st)
     }
 }
 
-template <typename T, int NW, int RT, int SRC, int KS, bool BOXED>
-int launch_v2_inst(const Mode12Params &mp, const GenSplitParams &gs, int nk, hipStream_t st)
+// bf16 generated source, 4 waves x RT row tiles
+template <int RT, int KS, bool BOXED>
+int launch_v3_inst(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int nk, hipStream_t st)
 {
-    typedef Mode12V2Cfg<NW, RT> cfg;
-    auto kern = k_mode12_v2<T, NW, RT, SRC, KS, BOXED>;
+    typedef Mode12V3Cfg<4, RT> cfg;
+    auto kern = k_mode12_v3<4, RT, KS, BOXED, 2>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, cfg::LDS_BYTES) != hipSuccess) return EXAT_ERR_HIP;
@@ -164,44 +163,14 @@ int launch_v2_inst(const Mode12Params &mp, const GenSplitParams &gs, int nk, hip
     }
     const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), cfg::LDS_BYTES, st, mp, gs);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), cfg::LDS_BYTES, st, mp, gs, uf);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
-
-// fp32 generated source (LDS-staged U)
-template <int NW, int RT>
-int launch_v2_gen_f32(const Mode12Params &mp, const GenSplitParams &gs, int ks, bool boxed, int nk, hipStream_t st)
-{
-    if (ks == 1) return boxed ? launch_v2_inst<float, NW, RT, SRC_GENERATED, 1, true>(mp, gs, nk, st) : launch_v2_inst<float, NW, RT, SRC_GENERATED, 1, false>(mp, gs, nk, st);
-    return boxed ? launch_v2_inst<float, NW, RT, SRC_GENERATED, 2, true>(mp, gs, nk, st) : launch_v2_inst<float, NW, RT, SRC_GENERATED, 2, false>(mp, gs, nk, st);
-}
-
-template <typename T, int NW, int RT, int SRC, int KS, bool BOXED, int DU, int DX, int WPS = (NW + 3) / 4, bool ZT = false, bool TAB = false>
-int launch_v3_inst(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int nk, hipStream_t st)
-{
-    typedef Mode12V3Cfg<NW, RT> cfg;
-    auto kern = k_mode12_v3<T, NW, RT, SRC, KS, BOXED, DU, DX, WPS, ZT, TAB>;
-    static bool attr_done = false;
-    constexpr int lds_max = ZT ? cfg::zt_lds_bytes(2) : cfg::LDS_BYTES;
-    static_assert(lds_max <= 160 * 1024, "LDS of a compute unit");
-    if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max) != hipSuccess) return EXAT_ERR_HIP;
-        attr_done = true;
-    }
-    const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
-    if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    if (ZT && (mp.MT < 1 || mp.MT > 2)) return EXAT_ERR_SHAPE;
-    const int lds = ZT ? cfg::zt_lds_bytes(mp.MT) : cfg::LDS_BYTES;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, mp, gs, uf);
-    return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
-}
-
-// bf16 generated source, 4 waves
 template <int RT>
 int launch_v3_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const UFragParams &uf, int ks, bool boxed, int nk, hipStream_t st)
 {
-    if (ks == 1) return boxed ? launch_v3_inst<__bf16, 4, RT, SRC_GENERATED, 1, true, 2, 1>(mp, gs, uf, nk, st) : launch_v3_inst<__bf16, 4, RT, SRC_GENERATED, 1, false, 2, 1>(mp, gs, uf, nk, st);
-    return boxed ? launch_v3_inst<__bf16, 4, RT, SRC_GENERATED, 2, true, 2, 1>(mp, gs, uf, nk, st) : launch_v3_inst<__bf16, 4, RT, SRC_GENERATED, 2, false, 2, 1>(mp, gs, uf, nk, st);
+    if (ks == 1) return boxed ? launch_v3_inst<RT, 1, true>(mp, gs, uf, nk, st) : launch_v3_inst<RT, 1, false>(mp, gs, uf, nk, st);
+    return boxed ? launch_v3_inst<RT, 2, true>(mp, gs, uf, nk, st) : launch_v3_inst<RT, 2, false>(mp, gs, uf, nk, st);
 }
 
 // bf16 generated source, 8 waves x 2 row tiles (512 stacked rows per group), k_mode12_v4
@@ -225,34 +194,37 @@ int launch_v4_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const U
     return boxed ? launch_v4_inst<true>(mp, gs, uf, nk, st) : launch_v4_inst<false>(mp, gs, uf, nk, st);
 }
 
-template <int NP, int NW, int NWC, bool PTR>
-int launch_mp_inst(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
+template <int NP, int NW, int NWC, int SRC, int KS = 1>
+int launch_mp_inst(const Mode12Params &mp, const MpParams &q, const GenSplitParams &gs, int nk, hipStream_t st)
 {
     typedef Mode12MpCfg<NP, NW, NWC> cfg;
-    auto kern = k_mode12_mp<NP, NW, NWC, PTR>;
-    static_assert(cfg::LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+    auto kern = k_mode12_mp<NP, NW, NWC, SRC, KS>;
+    constexpr int lds = cfg::lds_bytes(SRC == MP_GEN, KS);
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, cfg::LDS_BYTES) != hipSuccess) return EXAT_ERR_HIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return EXAT_ERR_HIP;
         attr_done = true;
     }
     const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), cfg::LDS_BYTES, st, mp, q);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, mp, q, gs);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 template <int NP, int NW, int NWC>
-int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, int nk, hipStream_t st)
+int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, const GenSplitParams &gs, bool generated, int nk, hipStream_t st)
 {
+    if constexpr (NP == 3)
+        if (generated) return gs.Rpad == 32 ? launch_mp_inst<NP, NW, NWC, MP_GEN, 1>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_GEN, 2>(mp, q, gs, nk, st);
     // the lean build unless X is a set of blocks, the box has odd ends in i, or the fibres are millions of values long
     const bool ptr = mp.xtab || mp.i0 % 4 != 0 || mp.i1 % 4 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
-    return ptr ? launch_mp_inst<NP, NW, NWC, true>(mp, q, nk, st) : launch_mp_inst<NP, NW, NWC, false>(mp, q, nk, st);
+    return ptr ? launch_mp_inst<NP, NW, NWC, MP_PTR>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_LEAN>(mp, q, gs, nk, st);
 }
 template <int NP>
-int launch_mp(const Mode12Params &mp, const MpParams &q, int nw, int nwc, int nk, hipStream_t st)
+int launch_mp(const Mode12Params &mp, const MpParams &q, const GenSplitParams &gs, bool generated, int nw, int nwc, int nk, hipStream_t st)
 {
-    if (nwc == 4) return launch_mp_nwc<NP, 8, 4>(mp, q, nk, st);
-    return nw == 8 ? launch_mp_nwc<NP, 8, 1>(mp, q, nk, st) : launch_mp_nwc<NP, 4, 1>(mp, q, nk, st);
+    if (nwc == 4) return launch_mp_nwc<NP, 8, 4>(mp, q, gs, generated, nk, st);
+    return nw == 8 ? launch_mp_nwc<NP, 8, 1>(mp, q, gs, generated, nk, st) : launch_mp_nwc<NP, 4, 1>(mp, q, gs, generated, nk, st);
 }
 
 // Number of row groups of k_mode12_mp for T4 quads of row tiles and nk slices: a workgroup holds two to four quads, the
@@ -298,12 +270,18 @@ int run_mode3(exat_plan_s *pl, const Mode12Params &mp, int kshift, float *Yout, 
     return EXAT_OK;
 }
 
-// materialised X: modes 1 and 2 (k_mode12_mp, and behind it the generic kernel for values outside the ranges of the piece sums),
-// then mode 3
-int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yout, int accumulate, hipStream_t st, unsigned char *flag)
+// materialised X, and generated X of fp32 plans: modes 1 and 2 (k_mode12_mp, and behind it the generic kernel for values outside the
+// ranges of the piece sums), then mode 3
+int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined, float *Yout, int accumulate, hipStream_t st, unsigned char *flag)
 {
     const bool bf = pl->d.in_dtype == EXAT_BF16;
     const int64_t nk = mp.k1 - mp.k0;
+    GenSplitParams gs;
+    gs.Asp = pl->Asplit; gs.Irows = pl->Ipad; gs.Rpad = 32 * ((mp.R + 31) / 32);
+    if (generated && pipelined) {
+        hipLaunchKernelGGL(k_split_a<float>, dim3(grid_for(gs.Irows * gs.Rpad)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
+        if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
+    }
     mp.U = pl->Upack; mp.V = pl->Vpack; mp.Q = pl->Q;
     mp.I = pl->d.I; mp.Ipad = pl->Ipad; mp.Jpad = pl->Jpad;
     mp.L = pl->d.L; mp.PL = pl->PL; mp.PLpad = pl->PLpad; mp.Mpad = pl->Mpad; mp.MT = pl->MT;
@@ -313,7 +291,7 @@ int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yo
     if (pipelined) {
         // split-precision plans take the fp16 pieces for aligned tensors and blocks with whole 32-value stages of i, and the
         // fp32 path's pieces (no range limit) for the rest
-        const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
+        const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && !generated && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
         const int T = (pl->PL + 31) / 32;
         // up to 4 row tiles: 8 waves, four of which share a tile's fibres; up to 8: two 4-wave workgroups per compute unit; else
         // groups of 8 to 16 tiles, one 8-wave workgroup per compute unit
@@ -329,46 +307,33 @@ int run_materialised(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yo
         q.ja0 = mp.j0 & ~(int64_t)15;
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
-        rc = bf ? launch_mp<1>(mp, q, nw, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, nw, nwc, (int)nk, st) : launch_mp<3>(mp, q, nw, nwc, (int)nk, st));
+        rc = bf ? launch_mp<1>(mp, q, gs, false, nw, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, gs, false, nw, nwc, (int)nk, st) : launch_mp<3>(mp, q, gs, generated, nw, nwc, (int)nk, st));
         if (rc != EXAT_OK) return rc;
         mp.guard = q.flags;
         mp.qzero0 = pl->PLpad >> kshift;
     }
     if (!pipelined || mp.guard) {
-        const int rt = choose_rt(pl, false);
+        const int rt = choose_rt(pl, generated);
         mp.G = (pl->PL + 128 * rt - 1) / (128 * rt);
-        rc = bf ? launch_mode12_bf16<SRC_MATERIALISED>(rt, mp, (int)nk, st) : launch_mode12_f32<SRC_MATERIALISED>(rt, mp, (int)nk, st);
+        if (bf) rc = launch_mode12_bf16<SRC_MATERIALISED>(rt, mp, (int)nk, st);
+        else rc = generated ? launch_mode12_f32<SRC_GENERATED>(rt, mp, (int)nk, st) : launch_mode12_f32<SRC_MATERIALISED>(rt, mp, (int)nk, st);
         if (rc != EXAT_OK) return rc;
     }
     if (pl->timing && hipEventRecord(ev[1], st) != hipSuccess) return EXAT_ERR_HIP;
     return run_mode3(pl, mp, kshift, Yout, accumulate, flag, st);
 }
 
-// fills the plan-dependent part of the parameters and launches mode 1+2 followed by mode 3
-int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int accumulate, hipStream_t st, unsigned char *flag = nullptr)
+// generated source of a bf16 plan: the pipelined generating kernels (or the generic one), then mode 3
+int run_generated_bf16(exat_plan_s *pl, Mode12Params mp, bool pipelined, float *Yout, hipStream_t st)
 {
-    // Materialised sources run k_mode12_mp at any size and alignment.  Generated sources run the pipelined kernels if the factor
-    // rank fits their generator, else the generic kernel.  EXAT_PIPELINED=0 forces the generic kernel (a testing aid).
-    const bool bf = pl->d.in_dtype == EXAT_BF16;
-    bool pipelined = env_int("EXAT_PIPELINED", 1) != 0;
-    if (!generated) return run_materialised(pl, mp, pipelined, Yout, accumulate, st, flag);
-    pipelined = pipelined && mp.R <= 64;
-    int rt = choose_rt(pl, generated);
+    int rt = choose_rt(pl, true);
     if (pipelined) {
-        // rt = 128-row units of the workgroup tile: 2 = 4 waves x 2 row tiles, 3 = 4 waves x 3, 4 = 8 waves x 2
+        // rt = 128-row units of the workgroup tile: 2 = 4 waves x 2 row tiles, 3 = 4 waves x 3 (384 stacked rows, one wave per SIMD)
         const int forced = env_int("EXAT_RT", 0);
-        rt = (forced == 2 || forced == 4) ? forced : (pl->PL > 256 ? 4 : 2);
-        // bf16: 4 waves x 3 row tiles (384 stacked rows), one wave per SIMD, unless told otherwise; there is no 8-wave build
-        if (bf && pl->PL > 256 && forced != 2 && forced != 4) rt = 3;
-        if (bf && rt == 4) rt = 3;
+        rt = forced == 2 || (forced != 4 && pl->PL <= 256) ? 2 : 3;
     }
-    // the LDS-staged fp32 generator kernel (k_mode12_v2) addresses its U tile with 32-bit element offsets of up to
-    // 255 rows: beyond 2^23 padded columns the generic kernel takes over
-    const bool f32_gen_v3 = rt == 4 && pl->d.L % 32 == 0 && env_int("EXAT_F32_GEN_V3", 1);
-    if (pipelined && !bf && !f32_gen_v3 && pl->Ipad > (1LL << 23)) { pipelined = false; rt = choose_rt(pl, generated); }
     const int rows = 128 * rt;
     mp.U = pl->Upack; mp.V = pl->Vpack; mp.Q = pl->Q;
-    mp.Vd = pl->d.in_dtype == EXAT_BF16 ? nullptr : (const float *)pl->Vfrag;
     mp.I = pl->d.I; mp.Ipad = pl->Ipad; mp.Jpad = pl->Jpad;
     mp.L = pl->d.L; mp.PL = pl->PL; mp.PLpad = pl->PLpad; mp.Mpad = pl->Mpad; mp.MT = pl->MT;
     mp.G = (pl->PL + rows - 1) / rows;
@@ -377,9 +342,7 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
     GenSplitParams gs;
     gs.Asp = pl->Asplit; gs.Irows = pl->Ipad; gs.Rpad = 32 * ((mp.R + 31) / 32);
     if (pipelined) {
-        const int64_t n = gs.Irows * gs.Rpad;
-        if (bf) hipLaunchKernelGGL(k_split_a<__bf16>, dim3(grid_for(n)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
-        else hipLaunchKernelGGL(k_split_a<float>, dim3(grid_for(n)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
+        hipLaunchKernelGGL(k_split_a<__bf16>, dim3(grid_for(gs.Irows * gs.Rpad)), dim3(256), 0, st, mp.A, pl->d.I, mp.R, pl->Asplit, gs.Irows, gs.Rpad);
         if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
     }
     hipEvent_t *ev = pl->evr[pl->timed_calls % exat_plan_s::kTimeRing];
@@ -388,8 +351,8 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
         const bool boxed = (mp.i0 != 0 || mp.i1 != pl->d.I);
         const int ks = gs.Rpad / 32;
         UFragParams uf;
-        uf.Uf = pl->Ufrag; uf.nig = pl->Ipad / (bf ? 16 : 8); uf.Vf = pl->Vfrag; uf.Vz = pl->Vfragz;
-        if (bf && pl->PL > 256 && ks == 1 && env_int("EXAT_RT", 0) == 0 && pl->Ipad < (1LL << 21)) {
+        uf.Uf = pl->Ufrag; uf.nig = pl->Ipad / 16; uf.Vf = pl->Vfrag; uf.Vz = pl->Vfragz;
+        if (pl->PL > 256 && ks == 1 && env_int("EXAT_RT", 0) == 0 && pl->Ipad < (1LL << 21)) {
             // 512-row groups, two waves per SIMD (k_mode12_v4): the tile is generated once per group, so large groups
             // are what keeps the generator's vector work below the MFMA work.  Factor ranks above 32 would need twice
             // the generator registers, which this build does not have: they take the 384-row kernel below.  The kernel
@@ -397,44 +360,38 @@ int run_chain(exat_plan_s *pl, Mode12Params mp, bool generated, float *Yout, int
             // bytes per padded column, apart): 2^21 padded columns and more take the 384-row kernel as well.
             mp.G = (pl->PL + 511) / 512;
             rc = launch_v4_gen_bf16(mp, gs, uf, boxed, nk, st);
-        } else if (bf) {
-            if (rt == 3) {
-                // 384-row groups; a remainder of at most 256 rows gets a launch of its own with a smaller tile
-                // instead of a mostly empty group (the generator's vector work per group does not shrink with
-                // the rows, the MFMA work does)
-                const int full = pl->PL / 384, rem = pl->PL - 384 * full;
-                rc = EXAT_OK;
-                if (full > 0 && (rem == 0 || rem <= 256)) {
-                    mp.G = full;
-                    rc = launch_v3_gen_bf16<3>(mp, gs, uf, ks, boxed, nk, st);
-                    if (rc == EXAT_OK && rem > 0) {
-                        mp.row_base = 384 * full; mp.G = 1;
-                        rc = rem <= 128 ? launch_v3_gen_bf16<1>(mp, gs, uf, ks, boxed, nk, st) : launch_v3_gen_bf16<2>(mp, gs, uf, ks, boxed, nk, st);
-                    }
-                } else
-                    rc = launch_v3_gen_bf16<3>(mp, gs, uf, ks, boxed, nk, st);
-            } else rc = launch_v3_gen_bf16<2>(mp, gs, uf, ks, boxed, nk, st);
-        } else if (f32_gen_v3) {
-            // fp32 generator, 8 waves x 2 row tiles, U fragments straight into registers and mode 2 straight from the
-            // accumulators (the register-hungry LDS transposition of mode 2 was what made this build spill in its stage
-            // loop); EXAT_F32_GEN_V3=0 selects the LDS-staged kernel below
-            if (ks == 1) rc = boxed ? launch_v3_inst<float, 8, 2, SRC_GENERATED, 1, true, 2, 1, 2, true>(mp, gs, uf, nk, st)
-                                    : launch_v3_inst<float, 8, 2, SRC_GENERATED, 1, false, 2, 1, 2, true>(mp, gs, uf, nk, st);
-            else rc = boxed ? launch_v3_inst<float, 8, 2, SRC_GENERATED, 2, true, 2, 1, 2, true>(mp, gs, uf, nk, st)
-                            : launch_v3_inst<float, 8, 2, SRC_GENERATED, 2, false, 2, 1, 2, true>(mp, gs, uf, nk, st);
-        } else {
-            // LDS-staged fp32 generator kernel, 4 waves x 2 row tiles (256-row groups) only: its 8-wave build is not
-            // instantiated (the bf16 build of that shape once faulted at the 10000^3 size, cause unknown)
-            mp.G = (pl->PL + 255) / 256;
-            rc = launch_v2_gen_f32<4, 2>(mp, gs, ks, boxed, nk, st);
-        }
-    } else if (pl->d.in_dtype == EXAT_BF16)
+        } else if (rt == 3) {
+            // 384-row groups; a remainder of at most 256 rows gets a launch of its own with a smaller tile
+            // instead of a mostly empty group (the generator's vector work per group does not shrink with
+            // the rows, the MFMA work does)
+            const int full = pl->PL / 384, rem = pl->PL - 384 * full;
+            rc = EXAT_OK;
+            if (full > 0 && (rem == 0 || rem <= 256)) {
+                mp.G = full;
+                rc = launch_v3_gen_bf16<3>(mp, gs, uf, ks, boxed, nk, st);
+                if (rc == EXAT_OK && rem > 0) {
+                    mp.row_base = 384 * full; mp.G = 1;
+                    rc = rem <= 128 ? launch_v3_gen_bf16<1>(mp, gs, uf, ks, boxed, nk, st) : launch_v3_gen_bf16<2>(mp, gs, uf, ks, boxed, nk, st);
+                }
+            } else
+                rc = launch_v3_gen_bf16<3>(mp, gs, uf, ks, boxed, nk, st);
+        } else
+            rc = launch_v3_gen_bf16<2>(mp, gs, uf, ks, boxed, nk, st);
+    } else
         rc = launch_mode12_bf16<SRC_GENERATED>(rt, mp, nk, st);
-    else
-        rc = launch_mode12_f32<SRC_GENERATED>(rt, mp, nk, st);
     if (rc != EXAT_OK) return rc;
     if (pl->timing && hipEventRecord(ev[1], st) != hipSuccess) return EXAT_ERR_HIP;
-    return run_mode3(pl, mp, 0, Yout, accumulate, flag, st);
+    return run_mode3(pl, mp, 0, Yout, 0, nullptr, st);
+}
+
+// Materialised sources run k_mode12_mp at any size and alignment, and so do generated sources of fp32 plans if the factor rank
+// fits the generator; generated sources of bf16 plans run kernels of their own under the same condition; everything else
+// runs the generic kernel.  EXAT_PIPELINED=0 forces the generic kernel (a testing aid).
+int run_chain(exat_plan_s *pl, const Mode12Params &mp, bool generated, float *Yout, int accumulate, hipStream_t st, unsigned char *flag = nullptr)
+{
+    const bool pipelined = env_int("EXAT_PIPELINED", 1) != 0 && !(generated && mp.R > 64);
+    if (generated && pl->d.in_dtype == EXAT_BF16) return run_generated_bf16(pl, mp, pipelined, Yout, st);
+    return run_pieces(pl, mp, generated, pipelined, Yout, accumulate, st, flag);
 }
 
 __global__ void k_clear_flags(unsigned char *flags, int n)
@@ -509,10 +466,9 @@ int exat_plan_create(exat_plan_t *plan, const exat_desc_t *desc)
     const size_t qb = (size_t)desc->K * pl->PLpad * pl->Mpad * 4;
     pl->ub = ub; pl->vb = vb; pl->qb = qb; pl->ab = (size_t)3 * pl->Ipad * 64 * 2;
     if (hipMalloc((void **)&pl->Asplit, pl->ab) != hipSuccess ||
-        hipMalloc(&pl->Upack, ub) != hipSuccess || hipMalloc(&pl->Ufrag, ub + MP_UPAD) != hipSuccess ||
-        (desc->in_dtype == EXAT_BF16 && (hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess ||
+        hipMalloc(&pl->Upack, ub) != hipSuccess ||
+        (desc->in_dtype == EXAT_BF16 && (hipMalloc(&pl->Ufrag, ub + MP_UPAD) != hipSuccess || hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess ||
                                          hipMalloc(&pl->Vfragz, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess)) ||
-        (desc->in_dtype != EXAT_BF16 && hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess) ||
         (desc->in_dtype != EXAT_BF16 && (hipMalloc(&pl->Ump, (size_t)pl->PLpad * pl->Ipad * 6 + MP_UPAD) != hipSuccess ||
                                          hipMalloc(&pl->Vmp, (size_t)desc->P * pl->Mpad * pl->Jpad * 6) != hipSuccess)) ||
         (desc->in_dtype == EXAT_F32_SPLIT && (hipMalloc(&pl->Usp, (size_t)pl->PLpad * pl->Ipad * 4 + MP_UPAD) != hipSuccess ||
@@ -574,9 +530,7 @@ int exat_set_factors(exat_plan_t pl, const float *U, int64_t ldU, const float *V
             hipLaunchKernelGGL(k_pack_v_mp<2>, dim3(grid_for(nv8)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (u32x4 *)pl->Vsp, pl->MT, nj16, (uint32_t *)nullptr);
         }
         hipLaunchKernelGGL(k_pack_u<float>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (float *)pl->Upack, pl->PLpad, pl->Ipad);
-        hipLaunchKernelGGL(k_pack_u_frag<float>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (float *)pl->Ufrag, pl->PLpad / 32, pl->Ipad / 8);
         hipLaunchKernelGGL(k_pack_v<float>, dim3(grid_for(nv)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, pl->Vpack, pl->Mpad, pl->Jpad);
-        hipLaunchKernelGGL(k_pack_v_direct, dim3(grid_for(nv)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (float *)pl->Vfrag, pl->Mpad, pl->Jpad);
         hipLaunchKernelGGL(k_pack_w<float>, dim3(grid_for(nw)), dim3(256), 0, st, W, ldW, d.P, d.N, d.K, pl->Wpack, pl->Npad);
     }
     if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;

@@ -7,13 +7,12 @@ namespace exat {
 struct Mode12Params {
     const void *U;   // packed [PLpad][Ipad] of T, zero padded
     const float *V;  // packed [P][Mpad][Jpad] fp32, zero padded (bf16-rounded values for bf16 plans)
-    const float *Vd; // fp32 plans: V in the order mode2_direct consumes (k_pack_v_direct), else unused
     float *Q;        // [k1-k0][PLpad][Mpad] fp32
     // materialised source: element (i,j,k) at X[(i-xo_i) + (j-xo_j)*x_sj + (k-xo_k)*x_sk]
     const void *X;
     int64_t x_sj, x_sk, xo_i, xo_j, xo_k;
     int x_vec;  // 16-byte loads of X are aligned
-    // materialised source held as separate blocks (k_mode12_v3 with TAB): xtab[bi + tab_nbi*(bj + tab_nbj*bk)] is the
+    // materialised source held as separate blocks: xtab[bi + tab_nbi*(bj + tab_nbj*bk)] is the
     // column-major x_dI x dj x dk block (bi, bj, bk) of X (dj, dk shorter in the last block of an axis); X is unused
     const void *const *xtab;
     int64_t x_dI, x_dJ, x_dK;

@@ -30,7 +30,8 @@
 // fp32, 1550 rows 39.1 -> 18.5 ms and 1000^3 bf16, 2400 rows 25.8 -> 8.3 ms (generic kernel before: 1000 is no multiple of a
 // stage); 1024^3 in two fp16 pieces, 2048 rows 14.2 -> 12.0 ms.
 #pragma once
-#include "exat_mode12_v3.h"
+#include "exat_gen.h"
+#include "exat_mode12.h"
 
 namespace exat {
 
@@ -108,7 +109,7 @@ struct Mode12MpCfg {
     static constexpr int XPT = 512 / (64 * NW);                 // runs of 8 values of the X tile per thread
     static constexpr int ROWB = 80, XBUF = COLS * ROWB, SLOT = NP * XBUF;
     static constexpr int NSLOT = NP == 1 ? 8 : (NP == 3 && NW == 4 ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
-    static constexpr int LDS_BYTES = NSLOT * SLOT;
+    static constexpr int lds_bytes(bool gen, int ks) { return NSLOT * SLOT + (gen ? 8 * ks * 2048 : 0); }
     static constexpr int DU = NP == 1 ? 2 : 1;   // register sets of U fragments
     static constexpr int DX = NP == 1 ? 4 : 1;   // register sets of the X tile in flight
     static constexpr int XD = NP == 1 ? 4 : 2;   // register sets of X fragments read from LDS
@@ -220,13 +221,19 @@ typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
 // PTR = false: a fibre of X is addressed by a wave-uniform base and a 32-bit offset of the lane (128 fibres of X are less than
 // 2^31 bytes apart), and the box begins and ends at multiples of 4 in i.  PTR = true: any box; a fibre is addressed by a 64-bit
 // pointer of the lane, which may come from the table of blocks of a slab.
-template <int NP, int NW, int NWC, bool PTR>
-__global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp)
+// MP_GEN (NP = 3): the tile is generated on chip, the low-rank part by the 16x16x32 matrix instruction as in k_mode12_v3 (a wave
+// makes the 16 NSJ fibres it owns, 32 values of i per stage, in aligned quads of i, the unit of the noise).  Everything happens
+// within the stage: the A pieces of 16 rows are requested a few fragments before they are used, the products B[j,r] C[k,r] of a
+// chunk wait in a lane-private piece of LDS, so the only state between stages are the fibres' keys.
+enum { MP_LEAN = 0, MP_PTR = 1, MP_GEN = 2 };
+template <int NP, int NW, int NWC, int SRC, int KS = 1>
+__global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp, const GenSplitParams gs)
 {
     typedef Mode12MpCfg<NP, NW, NWC> cfg;
     typedef std::conditional_t<NP == 1, __bf16, float> T;
     typedef mp_terms<NP> terms;
-    constexpr bool F16 = NP == 2;
+    constexpr bool F16 = NP == 2, PTR = SRC == MP_PTR, GEN = SRC == MP_GEN;
+    static_assert(!GEN || NP == 3, "");
     constexpr int NWR = cfg::NWR, RT = cfg::RT, CT = cfg::CT, EI = cfg::EI, COLS = cfg::COLS, ROWB = cfg::ROWB, XBUF = cfg::XBUF;
     constexpr int SLOT = cfg::SLOT, NSLOT = cfg::NSLOT, H = cfg::H, DU = cfg::DU, DX = cfg::DX, XD = cfg::XD, NF = 2 * CT;
     constexpr int XPT = cfg::XPT, XC = COLS / XPT, XW = NP == 1 ? 1 : 2;   // run u of a thread belongs to fibre col + u*XC
@@ -238,7 +245,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
     const int nk = (int)(p.k1 - p.k0);
     const int bid = blockIdx.x, xcd = bid & 7, t = bid >> 3;
     // the row groups of one slice sit next to each other on one XCD and share the X tiles through its L2
-    const int g = t % p.G, kidx = (t / p.G) * 8 + xcd;
+    // (generated: nothing of X is shared, neighbours take the same rows and share U instead)
+    const int nkx = (nk + 7) >> 3;
+    const int g = GEN ? t / nkx : t % p.G, kidx = (GEN ? t % nkx : t / p.G) * 8 + xcd;
     if (kidx >= nk) return;
     const int64_t k = p.k0 + kidx;
     int t0 = 0, nt = 2 * NWR;   // this group's row tiles: t0 .. t0 + nt - 1
@@ -279,8 +288,47 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         const T *xp[XPT];                // PTR: the lane's pointer for i = ia0 (in the current block)
         int64_t tab_end = 0, tab_in[XPT];   // table: first i beyond the current block; offset of the fibre inside a block
         const void *const *tabrow[XPT];
+        constexpr int NSJ = 8 / NW;      // GEN: 16-fibre tiles of this wave
+        const int l16 = lane & 15, q16 = lane >> 4;
+        uint32_t ckey[NSJ];
+        float amp[NSJ];
+        unsigned char *bcl = smem + NSLOT * SLOT + (wave * NSJ * KS * 2 * 64 + lane) * 16;   // + ((sj*KS + ks)*2 + piece) * 1024
         auto chunk_state = [&]() __attribute__((always_inline)) {
             const int64_t jb = pj > p.j0 ? pj : p.j0;
+            if constexpr (GEN) {
+                // the fibres' keys, and the generator's B operand bc[j, r] = B[j,r] C[k,r] in pieces
+#pragma unroll
+                for (int sj = 0; sj < NSJ; sj++) {
+                    const int64_t j = pj + 16 * (wave * NSJ + sj) + l16;
+                    const bool jok = j >= p.j0 && j < p.j1;
+                    const int64_t jj = jok ? j : p.j0;
+                    ckey[sj] = fibre_key(p.skey, (uint32_t)jj, (uint32_t)k);
+                    amp[sj] = jok ? p.amp2_ln2 : 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ks++) {
+                        bf16x8 bh, bm;
+                        float bv[8], cv[8];   // clamped loads, all in flight together; masked values
+#pragma unroll
+                        for (int e = 0; e < 8; e++) {
+                            const int r = 32 * ks + 8 * q16 + e, rr = r < p.R ? r : p.R - 1;
+                            bv[e] = p.B[jj + p.ldB * rr];
+                            cv[e] = p.C[k + p.ldC * rr];
+                        }
+#pragma unroll
+                        for (int e = 0; e < 8; e++) asm volatile("" : "+v"(bv[e]), "+v"(cv[e]));
+#pragma unroll
+                        for (int e = 0; e < 8; e++) {
+                            const float bc = (jok && 32 * ks + 8 * q16 + e < p.R) ? bv[e] * cv[e] : 0.0f;
+                            __bf16 h, m;
+                            gen_piece<float>::split(bc, h, m);
+                            bh[e] = h; bm[e] = m;
+                        }
+                        *(bf16x8 *)(bcl + ((sj * KS + ks) * 2 + 0) * 1024) = bh;
+                        *(bf16x8 *)(bcl + ((sj * KS + ks) * 2 + 1) * 1024) = bm;
+                    }
+                }
+                return;
+            }
             tab_end = 0;
             jin = pj >= p.j0 && pj + COLS <= p.j1;
 #pragma unroll
@@ -300,6 +348,56 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             if constexpr (!PTR) xu = (const T *)p.X + (ia0 + (int64_t)ps * EI - p.xo_i) + (jb - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
         };
         chunk_state();
+        // GEN: A pieces (h, m) of rows 16*si .. of the tile that is made next
+        auto request_a = [&](int si, bf16x8 (&af)[2 * KS]) __attribute__((always_inline)) {
+            const int64_t ib = ia0 + (int64_t)ps * EI + 16 * si;
+#pragma unroll
+            for (int v = 0; v < 2; v++)
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++) {
+                    const char *b = (const char *)(gs.Asp + ((int64_t)v * gs.Irows + ib) * gs.Rpad + 32 * ks);
+                    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, 32 * KS * 32 * KS, 0x00020000);
+                    af[v * KS + ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, (l16 * gs.Rpad + 8 * q16) * 2, 0, 0));
+                }
+        };
+        // GEN: rows 16*si .. 16*si+15 of this wave's fibres, low rank + noise, split and written to the slot at `base`
+        auto make_rows = [&](int si, const bf16x8 (&af)[2 * KS], unsigned char *base) __attribute__((always_inline)) {
+            const int64_t ib = ia0 + (int64_t)ps * EI;
+            const int i = 16 * si + 4 * q16;
+#pragma unroll
+            for (int sj = 0; sj < NSJ; sj++) {
+                f32x4v c = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++) {
+                    const bf16x8 bh = *(const bf16x8 *)(bcl + ((sj * KS + ks) * 2 + 0) * 1024), bm = *(const bf16x8 *)(bcl + ((sj * KS + ks) * 2 + 1) * 1024);
+                    c = gen_piece<float>::mfma(af[KS + ks], bh, c);
+                    c = gen_piece<float>::mfma(af[ks], bm, c);
+                    c = gen_piece<float>::mfma(af[ks], bh, c);
+                }
+                float z[4], x[4];
+                noise_quad(ckey[sj], (uint32_t)((ib + i) >> 2), amp[sj], z);
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[e] = c[e] + z[e];
+                if (!(ps >= s_lo && ps < s_hi)) {   // zero outside the box
+#pragma unroll
+                    for (int e = 0; e < 4; e++) x[e] = (ib + i + e >= p.i0 && ib + i + e < p.i1) ? x[e] : 0.0f;
+                }
+                uint32_t w0[NP], w1[NP];
+                xmax = fmaxf(fmaxf(xmax, fabsf(x[0])), fabsf(x[1]));
+                xmax = fmaxf(fmaxf(xmax, fabsf(x[2])), fabsf(x[3]));
+                mp_split2<NP, F16>(x[0], x[1], w0);
+                mp_split2<NP, F16>(x[2], x[3], w1);
+#pragma unroll
+                for (int q = 0; q < NP; q++) *(u32x2 *)(base + q * XBUF + (16 * (wave * NSJ + sj) + l16) * ROWB + i * 2) = u32x2{w0[q], w1[q]};
+            }
+        };
+        auto next_tile = [&]() __attribute__((always_inline)) {
+            if (++ps == nst) {
+                ps = 0;
+                if (pj + COLS < p.j1) pj += COLS;
+                chunk_state();
+            }
+        };
         // requests this thread's runs of the next tile; goes on to the tile after it if `go` is set
         auto request_x = [&](u32x4 (&dst)[XPT][XW], bool go) __attribute__((always_inline)) {
             const int64_t ib = ia0 + (int64_t)ps * EI;
@@ -399,7 +497,18 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 
         // tiles 0 .. H-1 into the ring.  (What a chunk hands to the next across its mode 2 lies in the ring; nothing is in flight in
         // registers then, which mode 2 needs.)
-        if (jc == mp.ja0) {
+        if (GEN && jc == mp.ja0) {
+            for (int d = 0; d < H; d++) {
+#pragma unroll
+                for (int si = 0; si < 2; si++) {
+                    bf16x8 af[2 * KS];
+                    request_a(si, af);
+                    make_rows(si, af, smem + d * SLOT);
+                }
+                next_tile();
+            }
+            __syncthreads();
+        } else if (jc == mp.ja0) {
             u32x4 x0[H][XPT][XW];
 #pragma unroll
             for (int d = 0; d < H; d++) request_x(x0[d], true);
@@ -439,6 +548,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             };
 #pragma unroll
             for (int f = 0; f < XD - 1 && f < NF; f++) load_bx(f);
+            bf16x8 af[GEN ? 2 * KS : 1];   // GEN: requested in front of the stage's first fragment and behind fragment FQ0
+            constexpr int FQ0 = NF > 2 ? NF / 4 : 0, FQ1 = NF > 2 ? NF - 3 : 1;   // the two halves of the tile are made behind these
+            if constexpr (GEN) request_a(0, af);
             static_for<NF>([&](auto fc) {
                 constexpr int f = decltype(fc)::value, g2 = f / CT, ct = f % CT;
                 if constexpr (f + XD - 1 < NF) load_bx(f + XD - 1);
@@ -453,7 +565,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
                     for (int rt = 0; rt < RA; rt++) load_u(rt, s + DU, g2, ufr[US][g2][rt]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (f >= FSP && f < FSP + NSP) {
+                if constexpr (GEN) {
+                    if constexpr (f == FQ0) { make_rows(0, af, oth); request_a(1, af); }
+                    if constexpr (f == FQ1) {
+                        make_rows(1, af, oth);
+                        asm volatile("" : "+v"(xmax));
+                        next_tile();
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                } else if constexpr (f >= FSP && f < FSP + NSP) {
                     static_for<NPAIR / NSP>([&](auto ec) {
                         constexpr int e = (f - FSP) * (NPAIR / NSP) + decltype(ec)::value;
                         split_pair(e % 4, xr[XS][e / 4]);
@@ -476,7 +596,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         auto run = [&](auto rac) __attribute__((always_inline)) {
             constexpr int RA = decltype(rac)::value;
 #pragma unroll
-            for (int d = 0; d < DX; d++) request_x(xr[(H + d) % DX], true);
+            for (int d = 0; d < DX && !GEN; d++) request_x(xr[(H + d) % DX], true);
 #pragma unroll
             for (int d = 0; d < DU; d++)
 #pragma unroll

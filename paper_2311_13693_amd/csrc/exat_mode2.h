@@ -19,13 +19,11 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 //   VM_BF16  bf16 matrix cores, Z split into two bf16 pieces (error 2^-17), V_p (bf16) from Vf in fragment
 //            order, [P][Jpad/16][2][64 lanes][8], lane l of fragment (p, j16, mt) holding
 //            V_p[m = 32*mt + l%32, j = 16*j16 + 8*(l/32) .. +7];
-//   VM_F16X2 fp16 matrix cores, Z and V_p each split into two fp16 pieces (Vf: high pieces, Vf2: low pieces,
-//            same fragment order), the three significant cross terms accumulated in fp32 (error 2^-22).
 // VB: V fragments (of 8 columns) requested together on the fp32 path; 16 = a whole chunk, fewer where registers are short.
-enum { VM_F32 = 0, VM_BF16 = 1, VM_F16X2 = 2 };
+enum { VM_F32 = 0, VM_BF16 = 1 };
 template <int RT, int CT, int MTC, int VM, int VB = 16>
 __device__ __forceinline__ void mode2_chunk(const Mode12Params &p, const void *Vf, float *Zs, const f32x16 (&acc)[RT][CT],
-                                            int wrow0, int kidx, int64_t jc, bool first_chunk, int lane, const void *Vf2 = nullptr)
+                                            int wrow0, int kidx, int64_t jc, bool first_chunk, int lane)
 {
     constexpr int COLS = 32 * CT, ZST = COLS + 4;
     constexpr int MP = 32 * MTC;  // = p.Mpad; a constant here so that the 32 Q accesses of a tile differ by immediates
@@ -75,40 +73,7 @@ __device__ __forceinline__ void mode2_chunk(const Mode12Params &p, const void *V
                 for (int mt = 0; mt < MTC; mt++)
 #pragma unroll
                     for (int e = 0; e < 16; e++) qa[mt][e] = 0.0f;
-                if constexpr (VM == VM_F16X2) {
-                    const int64_t fo = (((int64_t)pp * (p.Jpad / 16) + jc / 16) * 2) * 64 + lane;
-                    const f16x8 *vh = (const f16x8 *)Vf + fo, *vl = (const f16x8 *)Vf2 + fo;
-                    constexpr int GB = 4;  // 16-column groups per batch of V fragments
-#pragma unroll
-                    for (int g0 = 0; g0 < COLS / 16; g0 += GB) {
-                        f16x8 bh[GB][MTC], bl[GB][MTC];
-#pragma unroll
-                        for (int g = 0; g < GB; g++)
-#pragma unroll
-                            for (int mt = 0; mt < MTC; mt++) {
-                                bh[g][mt] = vh[((g0 + g) * 2 + mt) * 64];
-                                bl[g][mt] = vl[((g0 + g) * 2 + mt) * 64];
-                            }
-                        __builtin_amdgcn_sched_barrier(0);  // keeps the requests together, ahead of the first MFMA
-#pragma unroll
-                        for (int g = 0; g < GB; g++) {
-                            const f32x4 z0 = *(const f32x4 *)(Zs + l32 * ZST + 16 * (g0 + g) + 8 * hi);
-                            const f32x4 z1 = *(const f32x4 *)(Zs + l32 * ZST + 16 * (g0 + g) + 8 * hi + 4);
-                            f16x8 zh, zl;
-#pragma unroll
-                            for (int e = 0; e < 4; e++) {
-                                zh[e] = (_Float16)z0[e]; zl[e] = (_Float16)(z0[e] - (float)zh[e]);
-                                zh[4 + e] = (_Float16)z1[e]; zl[4 + e] = (_Float16)(z1[e] - (float)zh[4 + e]);
-                            }
-#pragma unroll
-                            for (int mt = 0; mt < MTC; mt++) {
-                                qa[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(zl, bh[g][mt], qa[mt], 0, 0, 0);
-                                qa[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(zh, bl[g][mt], qa[mt], 0, 0, 0);
-                                qa[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(zh, bh[g][mt], qa[mt], 0, 0, 0);
-                            }
-                        }
-                    }
-                } else if constexpr (VM == VM_BF16) {
+                if constexpr (VM == VM_BF16) {
                     // bf16 matrix cores: Z = zh + zl (bf16 pieces), V_p in fragment order
                     const bf16x8 *vf = (const bf16x8 *)Vf + (((int64_t)pp * (p.Jpad / 16) + jc / 16) * 2) * 64 + lane;
                     bf16x8 bv[COLS / 16][MTC];
@@ -169,78 +134,6 @@ __device__ __forceinline__ void mode2_chunk(const Mode12Params &p, const void *V
                     *(Qt + (8 * (e >> 2) + (e & 3)) * MP + 32 * mt) = qsum[mt][e];
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-        }
-    }
-}
-
-// Mode 2 straight from the accumulators, for kernels that ran mode 1 with the MFMA operands swapped, so that a
-// tile's accumulator holds Z^T (rows: 32 fibres j, columns: 32 stacked rows q).  Register 4b+r of lane l is then
-// Z^T[j = 8b + 4(l/32) + r][q = l%32], which is exactly what the 32x32x2 MFMA wants as its second operand for
-// the pair of contraction indices (8b + r, 8b + 4 + r): Q^T[m, q] += sum_j V_p[m, j] Z^T[j, q] takes 16 MFMAs per
-// tile with no trip through LDS.  V comes in the matching order (k_pack_v_direct): [p][mt][j/32][b][lane][r] holds
-// V_p[32 mt + l%32][32 (j/32) + 8b + 4(l/32) + r].  Requires L % 32 == 0 (a tile of 32 rows q lies in one
-// replica) and fp32 data.  Q keeps its layout [k][q][m]: a lane owns one row q and writes 16-byte pieces of it.
-// The RT * MTC output tiles are taken one after the other in steps of one column tile ct (16 MFMAs); the V
-// fragments of a step are requested three steps ahead (a ring of four register sets), so that after the first
-// step the requests are always in flight behind the matrix instructions, also across the stores of a finished tile.
-// Q between the chunks: the rows a wave adds to are its own for the whole launch, so the running sums stay in a
-// wave-private piece of LDS (qlds: RT * MTC * 4 pieces of 64 lanes x 16 bytes, each lane reading back exactly what it
-// wrote: no bank conflicts, no barrier) and only the last chunk's result goes to memory; Q is written once and never read.
-template <int RT, int CT, int MTC>
-__device__ __forceinline__ void mode2_direct(const Mode12Params &p, const float *Vd, const f32x16 (&acc)[RT][CT], int wrow0, int kidx,
-                                             int64_t jc, bool first_chunk, bool last_chunk, f32x4 *qlds, int lane)
-{
-    constexpr int MP = 32 * MTC;   // = p.Mpad
-    constexpr int NS = RT * MTC * CT, AHEAD = 3;
-    const int l32 = lane & 31, hi = lane >> 5;
-    const int64_t nj32 = p.Jpad / 32;
-    f32x4 v[AHEAD + 1][4];
-    f32x4 qold[4];
-    f32x16 d;
-    // step s = ((rt * MTC + mt) * CT + ct); a row tile beyond the stacked rows is skipped (wave-uniform)
-    auto load_step = [&](int s) {
-        const int rt = s / (MTC * CT), mt = (s / CT) % MTC, ct = s % CT;
-        const int q0 = wrow0 + rt * 32;
-        if (q0 < p.PL) {
-            const int pr = q0 / p.L;
-            const f32x4 *vf = (const f32x4 *)Vd + (((int64_t)pr * MTC + mt) * nj32 + jc / 32) * (4 * 64) + lane;
-#pragma unroll
-            for (int b = 0; b < 4; b++) v[s % (AHEAD + 1)][b] = vf[(ct * 4 + b) * 64];
-        }
-    };
-#pragma unroll
-    for (int s = 0; s < AHEAD && s < NS; s++) load_step(s);
-#pragma unroll
-    for (int s = 0; s < NS; s++) {
-        const int rt = s / (MTC * CT), mt = (s / CT) % MTC, ct = s % CT;
-        const int q0 = wrow0 + rt * 32;
-        // this lane's 16 values of row q of Q (4 pieces of 4 consecutive m)
-        float *Qt = p.Q + ((int64_t)kidx * p.PLpad + q0 + l32) * MP + 32 * mt + 4 * hi;   // + 8*b
-        if (s + AHEAD < NS) load_step(s + AHEAD);
-        if (ct == 0 && q0 < p.PL) {
-#pragma unroll
-            for (int b = 0; b < 4; b++) qold[b] = first_chunk ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : qlds[(((rt * MTC + mt) * 4) + b) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 16; e++) d[e] = 0.0f;
-        }
-        __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the MFMAs
-        if (q0 < p.PL) {
-#pragma unroll
-            for (int b = 0; b < 4; b++)
-#pragma unroll
-                for (int r = 0; r < 4; r++)
-                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(v[s % (AHEAD + 1)][b][r], acc[rt][ct][4 * b + r], d, 0, 0, 0);
-            if (ct == CT - 1) {
-                // d: register 4b+r of lane l is Q^T[m = 32 mt + 8b + 4(l/32) + r][q = q0 + l%32]
-#pragma unroll
-                for (int b = 0; b < 4; b++) {
-                    f32x4 o;
-#pragma unroll
-                    for (int r = 0; r < 4; r++) o[r] = d[4 * b + r] + qold[b][r];
-                    if (last_chunk) *(f32x4 *)(Qt + 8 * b) = o;
-                    else qlds[(((rt * MTC + mt) * 4) + b) * 64 + lane] = o;
-                }
-            }
         }
     }
 }
