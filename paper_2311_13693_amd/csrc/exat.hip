@@ -30,6 +30,7 @@ struct exat_plan_s {
     exat_desc_t d;
     int PL, PLpad, Mpad, MT, Npad;
     int64_t Ipad, Jpad;
+    void *arena = nullptr;  // the allocation that holds the arrays below up to Q, the range words and Asplit
     void *Upack = nullptr;
     void *Ufrag = nullptr;  // bf16 plans: U in MFMA fragment order (k_pack_u_frag), same size as Upack
     void *Vfragz = nullptr; // bf16 plans: V in the fragment order of mode2_direct_bf16 (k_pack_v_frag with perm = 1)
@@ -61,7 +62,6 @@ struct exat_plan_s {
     int64_t timed_calls = 0;
     hipEvent_t evr[kTimeRing][3] = {};
     __bf16 *Asplit = nullptr;  // the two 16-bit pieces of the generator's A factor (bf16 or fp16 bit patterns), [2][Ipad][64]
-    size_t ub = 0, vb = 0, qb = 0, ab = 0;  // byte sizes of Upack, Vpack, Q, Asplit
 };
 
 namespace {
@@ -242,6 +242,19 @@ int choose_groups(int T4, int64_t nk, int nw)
     return best;
 }
 
+template <int NT, int MP, int NW, bool LONGK>
+int launch_mode3_inst(const Mode3Params &m3, dim3 grid, size_t lds, hipStream_t st)
+{
+    auto kern = k_mode3<NT, MP, NW, LONGK>;
+    static bool attr_done = false;
+    if (lds > 64 * 1024 && !attr_done) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return EXAT_ERR_HIP;
+        attr_done = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(64 * NW), lds, st, m3);
+    return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
+}
+
 // mode 3 over the slices of a call whose mode-1/2 launches left 2^kshift partial Q per slice
 int run_mode3(exat_plan_s *pl, const Mode12Params &mp, int kshift, float *Yout, int accumulate, unsigned char *flag, hipStream_t st)
 {
@@ -251,17 +264,22 @@ int run_mode3(exat_plan_s *pl, const Mode12Params &mp, int kshift, float *Yout, 
     m3.L = pl->d.L; m3.M = pl->d.M; m3.N = pl->d.N; m3.PL = pl->PL; m3.PLpad = pl->PLpad >> kshift; m3.Mpad = pl->Mpad;
     m3.Npad = pl->Npad;
     m3.K = pl->d.K; m3.k0 = mp.k0; m3.k1 = mp.k1; m3.accumulate = accumulate; m3.flag = flag;
-    const int64_t ntile = ((int64_t)pl->PL * pl->Mpad + 31) / 32;
-    dim3 grid((unsigned)ntile, (unsigned)((pl->Npad + 63) / 64));
-    const bool longk = ((m3.k1 - m3.k0) << kshift) > 512LL * M3_WAVES - 8;   // a wave's slab (rounded up to even) may exceed 512
-    if (pl->Npad % 64 == 0) {
-        if (longk) hipLaunchKernelGGL((k_mode3<2, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-        else hipLaunchKernelGGL((k_mode3<2, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-    } else {  // 32-column tiles, so that no launch carries an idle second tile
-        grid.y = (unsigned)(pl->Npad / 32);
-        if (longk) hipLaunchKernelGGL((k_mode3<1, true>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-        else hipLaunchKernelGGL((k_mode3<1, false>), grid, dim3(64 * M3_WAVES), 0, st, m3);
-    }
+    // 64-column tiles of n unless that would carry an idle second tile.  Below two workgroups of one m tile per compute unit a
+    // workgroup gets 16 waves, else it takes both m tiles (64 values of m) where there are two.
+    const int nt = pl->Npad % 64 == 0 ? 2 : 1, ny = pl->Npad / (32 * nt);
+    const int64_t ntile = (int64_t)pl->PL * pl->MT, nkk = (m3.k1 - m3.k0) << kshift;
+    const bool many = ntile * ny < 512 && nkk >= 64 && nkk <= 8000;   // (8000: no slab of 16 waves is longer than 512)
+    const int mp2 = !many && pl->MT == 2, nw = many ? 16 : 4;
+    const bool longk = !many && nkk > 512LL * nw - 2 * nw;   // a wave's slab (rounded up to even) may exceed 512
+    const dim3 grid((unsigned)((ntile / (1 + mp2) + 7) / 8 * 8), (unsigned)ny);
+    const size_t lds = (size_t)nw * nt * (1 + mp2) * (longk ? 8192 : 4096);
+    int rc;
+    if (many) rc = nt == 2 ? launch_mode3_inst<2, 1, 16, false>(m3, grid, lds, st) : launch_mode3_inst<1, 1, 16, false>(m3, grid, lds, st);
+    else if (longk && mp2) rc = nt == 2 ? launch_mode3_inst<2, 2, 4, true>(m3, grid, lds, st) : launch_mode3_inst<1, 2, 4, true>(m3, grid, lds, st);
+    else if (longk) rc = nt == 2 ? launch_mode3_inst<2, 1, 4, true>(m3, grid, lds, st) : launch_mode3_inst<1, 1, 4, true>(m3, grid, lds, st);
+    else if (mp2) rc = nt == 2 ? launch_mode3_inst<2, 2, 4, false>(m3, grid, lds, st) : launch_mode3_inst<1, 2, 4, false>(m3, grid, lds, st);
+    else rc = nt == 2 ? launch_mode3_inst<2, 1, 4, false>(m3, grid, lds, st) : launch_mode3_inst<1, 1, 4, false>(m3, grid, lds, st);
+    if (rc != EXAT_OK) return rc;
     if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
     if (pl->timing) {
         if (hipEventRecord(pl->evr[pl->timed_calls % exat_plan_s::kTimeRing][2], st) != hipSuccess) return EXAT_ERR_HIP;
@@ -464,21 +482,25 @@ int exat_plan_create(exat_plan_t *plan, const exat_desc_t *desc)
     const size_t vb = (size_t)desc->P * pl->Mpad * pl->Jpad * 4;
     const size_t wb = (size_t)desc->P * desc->K * pl->Npad * 4;
     const size_t qb = (size_t)desc->K * pl->PLpad * pl->Mpad * 4;
-    pl->ub = ub; pl->vb = vb; pl->qb = qb; pl->ab = (size_t)3 * pl->Ipad * 64 * 2;
-    if (hipMalloc((void **)&pl->Asplit, pl->ab) != hipSuccess ||
-        hipMalloc(&pl->Upack, ub) != hipSuccess ||
-        (desc->in_dtype == EXAT_BF16 && (hipMalloc(&pl->Ufrag, ub + MP_UPAD) != hipSuccess || hipMalloc(&pl->Vfrag, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess ||
-                                         hipMalloc(&pl->Vfragz, (size_t)desc->P * pl->Jpad * 64 * 2) != hipSuccess)) ||
-        (desc->in_dtype != EXAT_BF16 && (hipMalloc(&pl->Ump, (size_t)pl->PLpad * pl->Ipad * 6 + MP_UPAD) != hipSuccess ||
-                                         hipMalloc(&pl->Vmp, (size_t)desc->P * pl->Mpad * pl->Jpad * 6) != hipSuccess)) ||
-        (desc->in_dtype == EXAT_F32_SPLIT && (hipMalloc(&pl->Usp, (size_t)pl->PLpad * pl->Ipad * 4 + MP_UPAD) != hipSuccess ||
-                                              hipMalloc(&pl->Vsp, (size_t)desc->P * pl->Mpad * pl->Jpad * 4) != hipSuccess)) ||
-        hipMalloc((void **)&pl->ranges, MPF_WORDS * sizeof(uint32_t)) != hipSuccess || hipMalloc((void **)&pl->Vpack, vb) != hipSuccess ||
-        hipMalloc((void **)&pl->Wpack, wb) != hipSuccess || hipMalloc((void **)&pl->Q, qb) != hipSuccess) {
+    // one allocation, cut into the plan's arrays
+    const bool bf = desc->in_dtype == EXAT_BF16, split = desc->in_dtype == EXAT_F32_SPLIT;
+    const size_t un = (size_t)pl->PLpad * pl->Ipad, vn = (size_t)desc->P * pl->Mpad * pl->Jpad, vf = (size_t)desc->P * pl->Jpad * 64 * 2;
+    const struct { void **ptr; size_t bytes; } cut[] = {
+        {(void **)&pl->ranges, MPF_WORDS * sizeof(uint32_t)}, {(void **)&pl->Asplit, (size_t)3 * pl->Ipad * 64 * 2}, {&pl->Upack, ub},
+        {&pl->Ufrag, bf ? ub + MP_UPAD : 0}, {&pl->Vfrag, bf ? vf : 0}, {&pl->Vfragz, bf ? vf : 0}, {&pl->Ump, bf ? 0 : un * 6 + MP_UPAD},
+        {&pl->Vmp, bf ? 0 : vn * 6}, {&pl->Usp, split ? un * 4 + MP_UPAD : 0}, {&pl->Vsp, split ? vn * 4 : 0}, {(void **)&pl->Vpack, vb},
+        {(void **)&pl->Wpack, wb}, {(void **)&pl->Q, qb}};
+    size_t total = 0;
+    for (const auto &c : cut) total += (c.bytes + 255) & ~(size_t)255;
+    if (hipMalloc(&pl->arena, total) != hipSuccess) {
         (void)hipGetLastError();
+        pl->arena = nullptr;
         exat_plan_destroy(pl);
         return EXAT_ERR_ALLOC;
     }
+    char *at = (char *)pl->arena;
+    for (const auto &c : cut)
+        if (c.bytes) { *c.ptr = at; at += (c.bytes + 255) & ~(size_t)255; }
     pl->nblocks = cdiv(desc->I, desc->dI) * cdiv(desc->J, desc->dJ) * cdiv(desc->K, desc->dK);
     pl->ysize = (int64_t)desc->P * desc->L * desc->M * desc->N;
     *plan = pl;
@@ -496,9 +518,7 @@ int exat_plan_destroy(exat_plan_t pl)
         if (pl->copy_stream) (void)hipStreamDestroy(pl->copy_stream);
     }
     if (!pl) return EXAT_OK;
-    (void)hipFree(pl->Upack); (void)hipFree(pl->Ufrag); (void)hipFree(pl->Vfrag); (void)hipFree(pl->Vfragz);
-    (void)hipFree(pl->Ump); (void)hipFree(pl->Vmp); (void)hipFree(pl->Usp); (void)hipFree(pl->Vsp); (void)hipFree(pl->ranges); (void)hipFree(pl->Vpack); (void)hipFree(pl->Wpack); (void)hipFree(pl->Q);
-    (void)hipFree(pl->slots); (void)hipFree(pl->used_dev); (void)hipFree(pl->Asplit); (void)hipFree((void *)pl->xtab);
+    (void)hipFree(pl->arena); (void)hipFree(pl->slots); (void)hipFree(pl->used_dev); (void)hipFree((void *)pl->xtab);
     for (auto &tr : pl->evr)
         for (hipEvent_t e : tr) if (e) (void)hipEventDestroy(e);
     delete pl;

@@ -1,6 +1,8 @@
 // Small kernels around the fused mode-1/2 kernel: operand packing (stacking, padding,
 // bf16 rounding), the mode-3 contraction, the block merge and the stand-alone block generator.
 #pragma once
+#include <type_traits>
+
 #include "exat_common.h"
 
 namespace exat {
@@ -64,41 +66,47 @@ struct Mode3Params {
     unsigned char *flag;  // if not null, set to 1 by the launch (block streaming: "this slot holds a partial result")
 };
 
-// One workgroup per 32 (q, m) positions x <= 64 columns n; its M3_WAVES waves split the k range into contiguous
-// slabs (the outputs are few and the k range long, so k is where the parallelism is) and wave 0 adds the partial
-// sums in wave order, which keeps the result independent of timing.
-constexpr int M3_WAVES = 4;
+// One workgroup per MP x 32 (q, m) positions of one stacked row x <= 64 columns n; its NW waves split the k range into
+// contiguous slabs (the outputs are few and the k range long, so k is where the parallelism is) and their partial
+// sums are added in wave order, which keeps the result independent of timing.
+// Bound by the loads: Q once from memory, W_p by every workgroup from the caches.  A workgroup that takes all 64 values of m
+// (MP = 2) reads W_p half as often; few workgroups with many waves each (NW = 16) shorten the chain of dependent loads of a
+// small call.  SPEED_NOTE
 
 // NT = 32-column tiles of n per workgroup (1 or 2).  LONGK: a wave's slab of k may exceed KFLUSH values, so the
 // fp32 MFMA accumulators are flushed into fp64 sums every KFLUSH values; without it the accumulators themselves
 // are the slab's result and no fp64 registers are alive during the loop.
-template <int NT, bool LONGK>
-__global__ __launch_bounds__(64 * M3_WAVES, LONGK ? 1 : 2) void k_mode3(const Mode3Params p)
+template <int NT, int MP, int NW, bool LONGK>
+__global__ __launch_bounds__(64 * NW, NW > 4 ? NW / 4 : (LONGK ? 1 : 2)) void k_mode3(const Mode3Params p)
 {
     constexpr int KFLUSH = 512;
-    __shared__ float part[M3_WAVES - 1][NT][16][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
+    typedef std::conditional_t<LONGK, double, float> part_t;
+    extern __shared__ __align__(16) unsigned char m3_smem[];
+    part_t *part = (part_t *)m3_smem;   // [NW][MP][NT][16][64]
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
     if (p.flag != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.flag = 1;
     if (p.ranges != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < MPF_CALL_WORDS) p.ranges[threadIdx.x] = 0;
-    const int64_t pos0 = (int64_t)blockIdx.x * 32;
+    // Workgroup ids go round-robin over the 8 XCDs: each takes a contiguous range of the stacked rows, so that the rows l of one
+    // replica, whose results are neighbours in Y, meet in one L2 (and read the same W_p through it).
+    const int64_t per = (gridDim.x + 7) >> 3, tile = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3), pos0 = tile * 32 * MP;
     if (pos0 >= (int64_t)p.PL * p.Mpad) return;  // whole workgroup
     const int q = (int)(pos0 / p.Mpad), m0 = (int)(pos0 % p.Mpad);
     if (m0 >= p.M) return;                       // a tile made of padding columns only (whole workgroup)
     const int pr = q / p.L, l = q % p.L;
     const int n0 = blockIdx.y * 32 * NT;
     const int64_t nkall = (p.k1 - p.k0) << p.kshift, qs = (int64_t)p.PLpad * p.Mpad;
-    const int64_t slab = (((nkall + M3_WAVES - 1) / M3_WAVES) + 1) & ~(int64_t)1;  // even: lanes 32..63 take odd k
+    const int64_t slab = (((nkall + NW - 1) / NW) + 1) & ~(int64_t)1;  // even: lanes 32..63 take odd k
     const int64_t kbeg = wave * slab;
     const int64_t nk = (kbeg >= nkall) ? 0 : ((kbeg + slab < nkall) ? slab : nkall - kbeg);
-    const float *qp = p.Q + kbeg * qs + pos0 + l32;                                    // + kk*qs
-    const float *wp = p.W + ((int64_t)pr * p.K + p.k0) * p.Npad + n0 + l32;     // + ((kbeg + kk) >> kshift)*Npad (+32 for tile 1)
-    double totl[LONGK ? NT : 1][16];   // LONGK only
-    f32x16 acc[NT];
+    const float *qp = p.Q + kbeg * qs + pos0 + l32;                               // + kk*qs (+32 for tile 1)
+    const float *wp = p.W + ((int64_t)pr * p.K + p.k0) * p.Npad + n0 + l32;       // + ((kbeg + kk) >> kshift)*Npad (+32 for tile 1)
+    double totl[LONGK ? MP * NT : 1][16];   // LONGK only
+    f32x16 acc[MP][NT];
 #pragma unroll
-    for (int t = 0; t < NT; t++)
+    for (int t = 0; t < MP * NT; t++)
 #pragma unroll
         for (int e = 0; e < 16; e++) {
-            acc[t][e] = 0.0f;
+            acc[t / NT][t % NT][e] = 0.0f;
             if (LONGK) totl[t][e] = 0.0;
         }
     for (int64_t kc = 0; kc < nk; kc += LONGK ? KFLUSH : nk) {
@@ -106,81 +114,84 @@ __global__ __launch_bounds__(64 * M3_WAVES, LONGK ? 1 : 2) void k_mode3(const Mo
         // 16 values of k per batch, two register sets: the loads of the next batch are issued before the MFMAs
         // of the current one (the kernel runs at well under one wave per SIMD, so nothing else hides the latency)
         constexpr int KB = 16, NS = KB / 2;
-        float a0[NS], b00[NS], b10[NS], a1[NS], b01[NS], b11[NS];  // b1* unused when NT == 1
-        auto load_batch = [&](float *a, float *b0, float *b1, int64_t kk) {
+        float a[2][MP][NS], b[2][NT][NS];
+        const float *ql = qp + hi * qs;
+        auto load_batch = [&](int set, int64_t kk) __attribute__((always_inline)) {
+            if (kk + KB <= kend) {   // no per-lane condition, wave-uniform offsets
+#pragma unroll
+                for (int t = 0; t < NS; t++) {
+                    const float *a0 = ql + (kk + 2 * t) * qs;
+                    const float *b0 = wp + (p.kshift ? ((kbeg + kk + 2 * t + hi) >> p.kshift) * p.Npad : (kbeg + kk + 2 * t) * p.Npad + hi * p.Npad);
+#pragma unroll
+                    for (int m = 0; m < MP; m++) a[set][m][t] = a0[32 * m];
+#pragma unroll
+                    for (int n = 0; n < NT; n++) b[set][n][t] = b0[32 * n];
+                }
+                return;
+            }
 #pragma unroll
             for (int t = 0; t < NS; t++) {
                 const int64_t kx = kk + 2 * t + hi;
                 const bool ok = kx < kend;
-                a[t] = ok ? qp[kx * qs] : 0.0f;
                 const int64_t kw = ((kbeg + kx) >> p.kshift) * p.Npad;
-                b0[t] = ok ? wp[kw] : 0.0f;
-                if (NT == 2) b1[t] = ok ? wp[kw + 32] : 0.0f;
-            }
-        };
-        auto mma_batch = [&](const float *a, const float *b0, const float *b1) {
 #pragma unroll
-            for (int t = 0; t < NS; t++) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b0[t], acc[0], 0, 0, 0);
-                if (NT == 2) acc[NT - 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b1[t], acc[1], 0, 0, 0);
+                for (int m = 0; m < MP; m++) a[set][m][t] = ok ? qp[kx * qs + 32 * m] : 0.0f;
+#pragma unroll
+                for (int n = 0; n < NT; n++) b[set][n][t] = ok ? wp[kw + 32 * n] : 0.0f;
             }
         };
-        load_batch(a0, b00, b10, kc);
+        auto mma_batch = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < NS; t++)
+#pragma unroll
+                for (int m = 0; m < MP; m++)
+#pragma unroll
+                    for (int n = 0; n < NT; n++) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[set][m][t], b[set][n][t], acc[m][n], 0, 0, 0);
+        };
+        load_batch(0, kc);
         for (int64_t kk = kc; kk < kend; kk += 2 * KB) {
-            load_batch(a1, b01, b11, kk + KB);       // zeros beyond kend
+            load_batch(1, kk + KB);       // zeros beyond kend
             __builtin_amdgcn_sched_barrier(0);
-            mma_batch(a0, b00, b10);
-            load_batch(a0, b00, b10, kk + 2 * KB);
+            mma_batch(0);
+            load_batch(0, kk + 2 * KB);
             __builtin_amdgcn_sched_barrier(0);
-            mma_batch(a1, b01, b11);
+            mma_batch(1);
         }
         if (LONGK) {
 #pragma unroll
-            for (int t = 0; t < NT; t++)
+            for (int t = 0; t < MP * NT; t++)
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
-                    totl[t][e] += (double)acc[t][e];
-                    acc[t][e] = 0.0f;
+                    totl[t][e] += (double)acc[t / NT][t % NT][e];
+                    acc[t / NT][t % NT][e] = 0.0f;
                 }
         }
     }
-    double tot[NT][16];
 #pragma unroll
-    for (int t = 0; t < NT; t++)
+    for (int t = 0; t < MP * NT; t++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) tot[t][e] = LONGK ? totl[t][e] : (double)acc[t][e];
-    if (wave > 0) {
-#pragma unroll
-        for (int t = 0; t < NT; t++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) part[wave - 1][t][e][lane] = (float)tot[t][e];
-    }
+        for (int e = 0; e < 16; e++) {
+            if constexpr (LONGK) part[((wave * MP * NT + t) * 16 + e) * 64 + lane] = totl[t][e];
+            else part[((wave * MP * NT + t) * 16 + e) * 64 + lane] = acc[t / NT][t % NT][e];
+        }
     __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int w = 0; w < M3_WAVES - 1; w++)
-#pragma unroll
-        for (int t = 0; t < NT; t++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) tot[t][e] += (double)part[w][t][e][lane];
+    // The waves' partial sums in wave order, in fp64; wave w finishes the elements w, w + NW, ... of every tile.
     // C layout: element 4b+r of the accumulator is row (position) 8b + 4*hi + r, column n = l32
 #pragma unroll
-    for (int t = 0; t < NT; t++) {
-        const int n = n0 + 32 * t + l32;
-        if (n < p.N) {
+    for (int t = 0; t < MP * NT; t++)
 #pragma unroll
-            for (int b4 = 0; b4 < 4; b4++)
+        for (int ee = 0; ee < 16 / NW; ee++) {
+            const int e = wave + NW * ee;
+            double s = 0.0;
 #pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int m = m0 + 8 * b4 + 4 * hi + r;
-                    if (m < p.M) {
-                        float *dst = p.Y + l + (int64_t)p.L * (m + (int64_t)p.M * (n + (int64_t)p.N * pr));
-                        const float v = (float)tot[t][4 * b4 + r];
-                        *dst = p.accumulate ? *dst + v : v;
-                    }
-                }
+            for (int w = 0; w < NW; w++) s += (double)part[((w * MP * NT + t) * 16 + e) * 64 + lane];
+            const int n = n0 + 32 * (t % NT) + l32, m = m0 + 32 * (t / NT) + 8 * (e >> 2) + 4 * hi + (e & 3);
+            if (n < p.N && m < p.M) {
+                float *dst = p.Y + l + (int64_t)p.L * (m + (int64_t)p.M * (n + (int64_t)p.N * pr));
+                const float v = (float)s;
+                *dst = p.accumulate ? *dst + v : v;
+            }
         }
-    }
 }
 
 // Block merge (Fig. 2a): Y = sum over partial slots in ascending slot order (fp64 running sum).

@@ -154,3 +154,14 @@ def test_value_ranges(case, P):
     X2, _, _, _ = _problem(I, J, K, L, M, N, P, dtype, seed=6)
     if case in ("x_tiny", "x_huge", "x_inf", "x_max", "x_zero", "one_huge", "bf16_inf"):
         assert _err(plan.compress(X2), _ref(X2, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+# mode 3: slabs of k per wave (4 or 16 waves), their remainders, the flush of long slabs into fp64 sums; one and two tiles of m, n
+@pytest.mark.parametrize("K", [1, 15, 63, 64, 65, 129, 513, 2041, 2060, 8001])
+@pytest.mark.parametrize("P,L,M,N", [(2, 3, 20, 33), (2, 9, 50, 20), (40, 16, 33, 64), (2, 300, 33, 40)])
+def test_mode3_slabs(K, P, L, M, N):
+    I, J = 8, 9
+    print("case", K, P, L, M, N, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, "f32")
+    plan = _plan(I, J, K, L, M, N, P, "f32", U, V, W)
+    assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL
