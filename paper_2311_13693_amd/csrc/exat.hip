@@ -206,7 +206,7 @@ int launch_mp_inst(const Mode12Params &mp, const MpParams &q, const GenSplitPara
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return EXAT_ERR_HIP;
         attr_done = true;
     }
-    const int64_t grid = 8LL * ((nk + 7) / 8) * mp.G;
+    const int64_t grid = q.nblk ? (int64_t)q.nblk * mp.G * q.bs : 8LL * ((nk + 7) / 8) * mp.G;
     if (grid > 2147483647LL) return EXAT_ERR_SHAPE;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, mp, q, gs);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
@@ -228,7 +228,7 @@ int launch_mp(const Mode12Params &mp, const MpParams &q, const GenSplitParams &g
 }
 
 // Number of row groups of k_mode12_mp for T4 quads of row tiles and nk slices: a workgroup holds two to four quads, the
-// groups take the quads as evenly as they go, and a compute unit runs one workgroup at a time.
+// groups take the quads as evenly as they go, and a compute unit runs one workgroup of eight waves or two of four at a time.
 int choose_groups(int T4, int64_t nk, int nw)
 {
     int best = 1;
@@ -240,6 +240,16 @@ int choose_groups(int T4, int64_t nk, int nw)
         if (G == (T4 + mx - 1) / mx || c < 0.97 * cost) { best = G; cost = c; }
     }
     return best;
+}
+
+// Runs of about 32 slices (a workgroup per compute unit of an XCD), as many as give every XCD the same number of (run, row group)
+// pairs.
+void slice_runs(int G, int64_t nk, int *nblk, int *bs)
+{
+    int mul = 8;   // the fewest runs whose pairs can be dealt evenly to 8 XCDs: 8 / gcd(G, 8)
+    while (mul > 1 && G % (16 / mul) == 0) mul /= 2;
+    *nblk = (int)(mul * cdiv(nk, 32 * mul));
+    *bs = (int)cdiv(nk, *nblk);
 }
 
 template <int NT, int MP, int NW, bool LONGK>
@@ -311,8 +321,10 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         // fp32 path's pieces (no range limit) for the rest
         const bool split = pl->d.in_dtype == EXAT_F32_SPLIT && !generated && mp.x_vec && (mp.i0 % 32 == 0) && ((mp.i1 - mp.i0) % 32 == 0);
         const int T = (pl->PL + 31) / 32;
-        // up to 4 row tiles: 8 waves, four of which share a tile's fibres; up to 8: two 4-wave workgroups per compute unit; else
-        // groups of 8 to 16 tiles, one 8-wave workgroup per compute unit
+        // Up to 4 row tiles: 8 waves, four of which share a tile's fibres (with a tile per wave half of them would have nothing to
+        // do).  Up to 8: two 4-wave workgroups per compute unit, one's mode 2 under the other's stages (512^3, 256 rows: 0.40 ms with
+        // one 8-wave workgroup of one tile per wave, 0.35 ms so).  Else groups of 8 to 16 tiles, one 8-wave workgroup per compute unit:
+        // with two of four each would read and split every X tile (the stage took longer).
         const int nwc = T <= 4 ? 4 : 1, nw = T > 4 && T <= 8 ? 4 : 8;
         kshift = nwc == 4 ? 2 : 0;
         MpParams q;
@@ -325,6 +337,13 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         q.ja0 = mp.j0 & ~(int64_t)15;
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
+        q.nblk = q.bs = 0;
+        // Row groups of different size drift apart and then neither share X tiles nor leave room for U in the L2 (2400 rows, 1000^3
+        // bf16: 37 GB fetched past the L2 in 7.7 ms): slices in runs, one group per XCD at a time.  Both orders measured, slice by
+        // slice -> runs: 1000^3 fp32, 1550 rows 17.9 -> 16.3 ms; 700^3, 2624 rows 11.6 -> 10.7; 1000^3 bf16, 2400 rows 7.48 -> 7.08;
+        // 300^3 1.156 -> 1.140; but 250 x 250 x 64 0.154 -> 0.156 (the set-up of a workgroup weighs more).  Equal groups stay in step and
+        // gain nothing (1024^3 in four groups 20.8 -> 21.1), two or three groups lose as often as they gain.
+        if (!generated && mp.G >= 4 && q.T4 % mp.G != 0 && mp.i1 - mp.i0 >= 288) slice_runs(mp.G, nk, &q.nblk, &q.bs);
         rc = bf ? launch_mp<1>(mp, q, gs, false, nw, nwc, (int)nk, st) : (split ? launch_mp<2>(mp, q, gs, false, nw, nwc, (int)nk, st) : launch_mp<3>(mp, q, gs, generated, nw, nwc, (int)nk, st));
         if (rc != EXAT_OK) return rc;
         mp.guard = q.flags;

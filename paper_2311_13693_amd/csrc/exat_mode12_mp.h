@@ -17,18 +17,20 @@
 // products when a value lay outside (mp_out_of_range).
 //
 // Decomposition as in k_mode12: a workgroup owns one slice k and a group of stacked rows, walks the slice in chunks of 128
-// fibres with the whole i extent reduced before mode 2.  Eight waves:
-//   NWC = 1  every wave holds up to two 32-row tiles x 128 fibres.  The row tiles are dealt to the G groups in quads, as
-//            evenly as they go (a quad is one tile per SIMD), and inside a group tile t goes to wave t mod 8; a wave with one
+// fibres with the whole i extent reduced before mode 2.
+//   NWC = 1  (NW = 8; NW = 4 for 5 to 8 row tiles, two workgroups per compute unit) every wave holds up to two 32-row tiles x 128 fibres.  The row tiles are dealt to the G groups in quads, as
+//            evenly as they go (a quad is one tile per SIMD), and inside a group tile t goes to wave t mod NW; a wave with one
 //            tile runs a stage loop of its own.
-//   NWC = 2, 4 (at most 8 or 4 row tiles in all)  NWC waves share a row tile and take 128/NWC fibres each; each leaves its
+//   NWC = 4  (at most 4 row tiles in all)  four waves share a row tile and take 32 fibres each; each leaves its
 //            own partial Q, which mode 3 adds up as if it were a slice of its own (Mode3Params::kshift).
 // X goes HBM -> registers -> (split) -> LDS; U comes in fragment order straight from L2 into registers.  The X tiles sit in a
 // ring of NSLOT LDS slots: a stage reads tile s and writes tile s + H, H = NSLOT/2, and the workgroup meets at a barrier
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
-// Measured (one call, before -> now): 512^3 fp32, 512 stacked rows 1.05 -> 0.67 ms (fp32 matrix instruction before); 1000^3
-// fp32, 1550 rows 39.1 -> 18.5 ms and 1000^3 bf16, 2400 rows 25.8 -> 8.3 ms (generic kernel before: 1000 is no multiple of a
-// stage); 1024^3 in two fp16 pieces, 2048 rows 14.2 -> 12.0 ms.
+// Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 21 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
+// (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.1 -> 18.4 ms and
+// 1000^3 bf16, 2400 rows 25.8 -> 7.6 ms (generic kernel before: 1000 is no multiple of a stage); 1024^3 in two fp16 pieces, 2048
+// rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
+// about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
 #include "exat_gen.h"
 #include "exat_mode12.h"
@@ -45,6 +47,7 @@ struct MpParams {
                        // V_p[m = 32*mt + l%32, j = 16*j16 + 4*(l/32) + e%4 + 8*(e/4)]
     int vmt;           // 32-row tiles of m in Vf
     int T4;            // quads of row tiles (NWC = 1)
+    int nblk, bs;      // runs of slices (nblk * G is a multiple of 8) and the longest run's length, or 0
     int64_t ja0;       // first fibre of the first chunk (a multiple of 16, <= j0)
     uint32_t *flags;   // MPF_* words, or null
 };
@@ -244,11 +247,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
     const int wr = wave % NWR, wc = wave / NWR;
     const int nk = (int)(p.k1 - p.k0);
     const int bid = blockIdx.x, xcd = bid & 7, t = bid >> 3;
-    // the row groups of one slice sit next to each other on one XCD and share the X tiles through its L2
-    // (generated: nothing of X is shared, neighbours take the same rows and share U instead)
+    // Workgroup ids go round-robin over the 8 XCDs.  The row groups of one slice sit next to each other on one XCD and share the X
+    // tiles through its L2 (generated: nothing of X is shared, neighbours take the same rows and share U instead).  With mp.nblk
+    // the slices are dealt in that many runs of at most mp.bs: an XCD takes a run with one row group, which is then all of U that its
+    // L2 holds, and the other row groups of the run are on other XCDs at about the same time (X comes from the cache behind the L2s);
+    // the group an XCD takes moves on from run to run, so that larger and smaller groups are spread evenly.
     const int nkx = (nk + 7) >> 3;
-    const int g = GEN ? t / nkx : t % p.G, kidx = (GEN ? t % nkx : t / p.G) * 8 + xcd;
-    if (kidx >= nk) return;
+    int g = GEN ? t / nkx : t % p.G, kidx = (GEN ? t % nkx : t / p.G) * 8 + xcd, kend = nk;
+    if (mp.nblk) {
+        const int b = 8 * (t / mp.bs) + xcd, blk = b / p.G;
+        g = (b + (int)((int64_t)blk * p.G >> 3)) % p.G;
+        kidx = (int)((int64_t)blk * nk / mp.nblk) + t % mp.bs;
+        kend = (int)((int64_t)(blk + 1) * nk / mp.nblk);
+    }
+    if (kidx >= kend) return;
     const int64_t k = p.k0 + kidx;
     int t0 = 0, nt = 2 * NWR;   // this group's row tiles: t0 .. t0 + nt - 1
     if (NWC == 1) {

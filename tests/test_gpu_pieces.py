@@ -165,3 +165,14 @@ def test_mode3_slabs(K, P, L, M, N):
     X, U, V, W = _problem(I, J, K, L, M, N, P, "f32")
     plan = _plan(I, J, K, L, M, N, P, "f32", U, V, W)
     assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL
+
+
+# uneven row groups (13, 18 and 19 quads of row tiles): slices dealt in runs to the compute dies, with runs that are empty, short and whole
+@pytest.mark.parametrize("K", [1, 9, 70, 257])
+@pytest.mark.parametrize("P,L,dtype", [(31, 50, "f32"), (31, 50, "f32s"), (48, 50, "bf16"), (45, 50, "f32")])
+def test_slice_runs(P, L, dtype, K):
+    I, J, M, N = 288, 130, 9, 7
+    print("case", P, L, dtype, K, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
