@@ -50,7 +50,10 @@ typedef enum {
 } exat_status_t;
 
 /* Type in which the kernels consume the X tile and U, V, W.  Products are always
- * accumulated in fp32 and Y is always fp32.  With EXAT_BF16 the elements of X, U, V, W
+ * accumulated in fp32 and Y is always fp32.  With EXAT_F32 every fp32 operand is used whole: either
+ * by fp32 products or as the sum of three bf16 pieces (exact) in six products, which leaves out at most
+ * 2^-26 of a product; calls with values outside the range in which that holds (infinities, NaN, the
+ * ends of the exponent range) are computed with fp32 products.  With EXAT_BF16 the elements of X, U, V, W
  * are rounded to bf16 (round-to-nearest-even) before use; the intermediates of the
  * mode-1 and mode-2 contractions stay fp32. */
 typedef enum { EXAT_F32 = 0, EXAT_BF16 = 1, EXAT_F32_SPLIT = 2 } exat_dtype_t;
@@ -273,18 +276,18 @@ int exat_stage1_last_timing(exat_stage1_t s, float *ms_mode12, float *ms_mode3);
  * The decomposition stage applies the alternating-least-squares algorithm to each of the P small tensors
  * Y_p (L x M x N) that the compression produced.  exat_cpals runs `sweeps` sweeps of the loop body of Alg. 1
  * (update A, then B, then C; each the least-squares solution with the other two fixed,
- * A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^{-1}, solved by Cholesky factorisation of the R x R normal matrix)
- * for all P replicas at once, one workgroup per replica, in fp32.  There is no convergence test: the caller
+ * A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^{-1}, by elimination without pivoting on the R x R normal matrix)
+ * for all P replicas at once, in fp32.  There is no convergence test: the caller
  * chooses the number of sweeps.
  *   Y      device, P*L*M*N floats in the layout exat_compress writes: Y[l + L*(m + M*(n + N*p))]; not modified
  *   A,B,C  device, in: start values, out: result; per replica column-major L x R, M x R, N x R:
  *          A[l + L*(r + R*p)] etc.
- *   work   device scratch of exat_cpals_workspace_floats(L,M,N,P) floats (two permuted copies of Y), caller-owned
+ *   work   device scratch of exat_cpals_workspace_floats(L,M,N,P) floats (partial products of an update), caller-owned
  * Limits: L, M, N, R <= 64.  The normal matrices must be positive definite (they are for generic data): Alg. 1
  * writes a pseudo-inverse, which this solve does not provide, so a replica whose normal matrix loses rank ends in
  * NaN or meaningless factors.  exat_cpals_checked reports that: `status` (device, P int32, written by the call)
- * counts, per replica, the factor updates whose R x R normal matrix showed a zero, negative or NaN pivot in the
- * Cholesky factorisation (0 = every update was positive definite); the caller restarts such a replica from other
+ * counts, per replica, the factor updates whose R x R normal matrix showed a zero, negative or NaN pivot in its
+ * elimination (the squared pivots of its Cholesky factorisation; 0 = every update was positive definite); the caller restarts such a replica from other
  * start values (or drops it), as the restart loop of Alg. 2 does with replicas that fail.  The arithmetic is that of
  * exat_cpals, bit for bit.  Asynchronous on `stream`.  Errors: NULL, SHAPE, HIP. */
 int64_t exat_cpals_workspace_floats(int32_t L, int32_t M, int32_t N, int32_t P);

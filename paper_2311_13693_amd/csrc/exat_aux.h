@@ -50,10 +50,8 @@ __global__ void k_pack_w(const float *src, int64_t ld, int P, int N, int64_t K, 
 }
 
 // Mode 3: Y[p,l,m,n] (=|+=) sum_{k in [k0,k1)} W_p[n,k] Q[k-k0][p*L+l][m].
-// One wave owns 32 consecutive (q, m) positions of one stacked row q (so one replica) and up
-// to 64 values of n; it runs fp32 MFMAs over k in ascending order, flushing the fp32 partial
-// sums into fp64 totals every KFLUSH values of k so that the summation error does not grow
-// with the extent of K.
+// fp32 MFMAs over k in ascending order; the fp32 partial sums go into fp64 totals every KFLUSH values of k so that the
+// summation error does not grow with the extent of K.
 struct Mode3Params {
     const float *Q;  // [nk << kshift][PLpad][Mpad]
     const float *W;  // [P][K][Npad]
@@ -71,7 +69,9 @@ struct Mode3Params {
 // sums are added in wave order, which keeps the result independent of timing.
 // Bound by the loads: Q once from memory, W_p by every workgroup from the caches.  A workgroup that takes all 64 values of m
 // (MP = 2) reads W_p half as often; few workgroups with many waves each (NW = 16) shorten the chain of dependent loads of a
-// small call.  SPEED_NOTE
+// small call.  Workgroup ids are dealt out so that neighbouring rows share an XCD, and full batches of loads carry no
+// per-lane conditions.  Measured (before -> now): 4096 rows x 64 x 512 slices 0.333 -> 0.285 ms, 1550 rows x 50 x 1000 slices
+// 0.202 -> 0.188 ms; 64 rows x 16 x 512 partial slices 10.2 -> 8.7 us with 16 waves instead of 4.
 
 // NT = 32-column tiles of n per workgroup (1 or 2).  LONGK: a wave's slab of k may exceed KFLUSH values, so the
 // fp32 MFMA accumulators are flushed into fp64 sums every KFLUSH values; without it the accumulators themselves
