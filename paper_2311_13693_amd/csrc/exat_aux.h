@@ -10,44 +10,52 @@ namespace exat {
 // round a value through the plan's element type (identity for fp32)
 template <typename T> __device__ __forceinline__ float round_through(float v) { return (float)elem<T>::from_f32(v); }
 
+// The packing routines are written for block `block` of `nblocks` blocks of 256 threads, so that one launch can hold several.
+
 // Stacked fp32 matrix (rows x cols, leading dimension ld) -> zero-padded [rowspad][colspad] of T.
 template <typename T>
-__global__ void k_pack_u(const float *src, int64_t ld, int rows, int64_t cols, T *dst, int rowspad, int64_t colspad)
+__device__ __forceinline__ void pack_u_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int rows, int64_t cols, T *dst, int rowspad, int64_t colspad)
 {
     const int64_t n = (int64_t)rowspad * colspad;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int64_t r = idx / colspad, c = idx % colspad;
         const float v = (r < rows && c < cols) ? src[r * ld + c] : 0.0f;
         dst[idx] = elem<T>::from_f32(v);
     }
 }
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack_u(const float *src, int64_t ld, int rows, int64_t cols, T *dst, int rowspad, int64_t colspad) { pack_u_part<T>(blockIdx.x, gridDim.x, src, ld, rows, cols, dst, rowspad, colspad); }
 
 // Stacked fp32 V (P*M x J) -> fp32 [P][Mpad][Jpad], zero padded, values rounded through T.
 template <typename T>
-__global__ void k_pack_v(const float *src, int64_t ld, int P, int M, int64_t J, float *dst, int Mpad, int64_t Jpad)
+__device__ __forceinline__ void pack_v_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int P, int M, int64_t J, float *dst, int Mpad, int64_t Jpad)
 {
     const int64_t n = (int64_t)P * Mpad * Jpad;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int64_t j = idx % Jpad, pm = idx / Jpad;
         const int m = (int)(pm % Mpad), pr = (int)(pm / Mpad);
         const float v = (m < M && j < J) ? src[((int64_t)pr * M + m) * ld + j] : 0.0f;
         dst[idx] = round_through<T>(v);
     }
 }
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack_v(const float *src, int64_t ld, int P, int M, int64_t J, float *dst, int Mpad, int64_t Jpad) { pack_v_part<T>(blockIdx.x, gridDim.x, src, ld, P, M, J, dst, Mpad, Jpad); }
 
 // Stacked fp32 W (P*N x K) -> transposed fp32 [P][K][Npad] (n contiguous, zero padded), values
 // rounded through T: the layout the mode-3 MFMA reads its B operand from with coalesced loads.
 template <typename T>
-__global__ void k_pack_w(const float *src, int64_t ld, int P, int N, int64_t K, float *dst, int Npad)
+__device__ __forceinline__ void pack_w_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int P, int N, int64_t K, float *dst, int Npad)
 {
     const int64_t n_all = (int64_t)P * K * Npad;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n_all; idx += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n_all; idx += (int64_t)nblocks * 256) {
         const int n = (int)(idx % Npad);
         const int64_t pk = idx / Npad, k = pk % K, pr = pk / K;
         const float v = (n < N) ? src[(pr * N + n) * ld + k] : 0.0f;
         dst[idx] = round_through<T>(v);
     }
 }
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack_w(const float *src, int64_t ld, int P, int N, int64_t K, float *dst, int Npad) { pack_w_part<T>(blockIdx.x, gridDim.x, src, ld, P, N, K, dst, Npad); }
 
 // Mode 3: Y[p,l,m,n] (=|+=) sum_{k in [k0,k1)} W_p[n,k] Q[k-k0][p*L+l][m].
 // fp32 MFMAs over k in ascending order; the fp32 partial sums go into fp64 totals every KFLUSH values of k so that the

@@ -27,8 +27,8 @@
 // ring of NSLOT LDS slots: a stage reads tile s and writes tile s + H, H = NSLOT/2, and the workgroup meets at a barrier
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
 // Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 21 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
-// (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.1 -> 18.4 ms and
-// 1000^3 bf16, 2400 rows 25.8 -> 7.6 ms (generic kernel before: 1000 is no multiple of a stage); 1024^3 in two fp16 pieces, 2048
+// (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 17.6 ms and 1000^3 bf16, 2400 rows 25.8 -> 7.4 ms (generic
+// kernel before: 1000 is no multiple of a stage); slower only: 128 x 128 x 91 bf16, 304 rows 18.6 -> 29 us; 1024^3 in two fp16 pieces, 2048
 // rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
 // about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
@@ -648,11 +648,11 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 
 // Stacked fp32 U (rows x cols, leading dimension ld) -> MpParams::Uf, zero padded; a thread makes the 8 values of one lane.
 template <int NP>
-__global__ __launch_bounds__(256) void k_pack_u_mp(const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags)
+__device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags)
 {
     float mx = 0.0f;
     const int64_t n = (int64_t)rowtiles * nig * 64;
-    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * 256) {
+    for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
         const int64_t f = idx >> 6, ig = f % nig, r = f / nig * 32 + (l & 31), c = ig * 16 + (l >> 5) * 8;
         float v[8];
@@ -672,14 +672,16 @@ __global__ __launch_bounds__(256) void k_pack_u_mp(const float *src, int64_t ld,
     }
     if (flags) mp_note(flags, MPF_UBIG, MPF_UNORM, MPF_UNZ, mx, MP_UMIN, MP_UMAX);
 }
+template <int NP>
+__global__ __launch_bounds__(256) void k_pack_u_mp(const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags) { pack_u_mp_part<NP>(blockIdx.x, gridDim.x, src, ld, rows, cols, dst, rowtiles, nig, flags); }
 
 // Stacked fp32 V (P*M x J) -> MpParams::Vf with vmt = MT, zero padded.
 template <int NP>
-__global__ __launch_bounds__(256) void k_pack_v_mp(const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags)
+__device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags)
 {
     float mx = 0.0f;
     const int64_t n = (int64_t)P * nj16 * MT * 64;
-    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * 256) {
+    for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
         const int64_t f = idx >> 6, mt = f % MT, j16 = f / MT % nj16, pr = f / (MT * nj16), j = 16 * j16 + 4 * (l >> 5);
         const int m = 32 * (int)mt + (l & 31);
@@ -703,5 +705,7 @@ __global__ __launch_bounds__(256) void k_pack_v_mp(const float *src, int64_t ld,
     }
     if (flags) mp_note(flags, MPF_VBIG, MPF_VNORM, MPF_VNZ, mx, MP_VMIN, MP_VMAX);
 }
+template <int NP>
+__global__ __launch_bounds__(256) void k_pack_v_mp(const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags) { pack_v_mp_part<NP>(blockIdx.x, gridDim.x, src, ld, P, M, J, dst, MT, nj16, flags); }
 
 }  // namespace exat
