@@ -274,11 +274,12 @@ int run_mode3(exat_plan_s *pl, const Mode12Params &mp, int kshift, float *Yout, 
     m3.L = pl->d.L; m3.M = pl->d.M; m3.N = pl->d.N; m3.PL = pl->PL; m3.PLpad = pl->PLpad >> kshift; m3.Mpad = pl->Mpad;
     m3.Npad = pl->Npad;
     m3.K = pl->d.K; m3.k0 = mp.k0; m3.k1 = mp.k1; m3.accumulate = accumulate; m3.flag = flag;
-    // 64-column tiles of n unless that would carry an idle second tile.  Below two workgroups of one m tile per compute unit a
-    // workgroup gets 16 waves, else it takes both m tiles (64 values of m) where there are two.
+    // 64-column tiles of n unless that would carry an idle second tile.  Up to one workgroup of one m tile per compute unit and
+    // with 16 values of k and more per wave a workgroup gets 16 waves (64 tiles, 512 slices: 10.2 -> 8.7 us; 304 tiles, 91 slices took 16 us
+    // with 16 waves, in two rounds that mostly add up), else it takes both m tiles (64 values of m) where there are two.
     const int nt = pl->Npad % 64 == 0 ? 2 : 1, ny = pl->Npad / (32 * nt);
     const int64_t ntile = (int64_t)pl->PL * pl->MT, nkk = (m3.k1 - m3.k0) << kshift;
-    const bool many = ntile * ny < 512 && nkk >= 64 && nkk <= 8000;   // (8000: no slab of 16 waves is longer than 512)
+    const bool many = ntile * ny <= 256 && nkk >= 256 && nkk <= 8000;   // (8000: no slab of 16 waves is longer than 512)
     const int mp2 = !many && pl->MT == 2, nw = many ? 16 : 4;
     const bool longk = !many && nkk > 512LL * nw - 2 * nw;   // a wave's slab (rounded up to even) may exceed 512
     const dim3 grid((unsigned)((ntile / (1 + mp2) + 7) / 8 * 8), (unsigned)ny);
