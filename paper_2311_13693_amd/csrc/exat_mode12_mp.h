@@ -28,7 +28,7 @@
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
 // Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 21 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
 // (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 17.6 ms and 1000^3 bf16, 2400 rows 25.8 -> 7.4 ms (generic
-// kernel before: 1000 is no multiple of a stage); slower only: 128 x 128 x 91 bf16, 304 rows 18.6 -> 29 us; 1024^3 in two fp16 pieces, 2048
+// kernel before: 1000 is no multiple of a stage); slower only: 128 x 128 x 91 bf16, 304 rows 18.6 -> 20.4 us; 1024^3 in two fp16 pieces, 2048
 // rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
 // about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
