@@ -688,8 +688,7 @@ int exat_compress_blocks(exat_plan_t pl, const void *const *Xblk, int32_t bj0, i
     // (16 values for fp32 plans, 32 for bf16 and split-fp16 plans) and whole 128-fibre chunks inside every block,
     // 16-byte aligned blocks.  Any other slab is compressed block by block.
     const int ei = d.in_dtype == EXAT_F32 ? 16 : 32;
-    bool one_launch = d.I % d.dI == 0 && d.dI % ei == 0 && d.dJ % 128 == 0 &&
-                      (d.in_dtype == EXAT_F32_SPLIT || env_int("EXAT_PIPELINED", 1) != 0) && env_int("EXAT_SLAB", 1) != 0;
+    bool one_launch = d.I % d.dI == 0 && d.dI % ei == 0 && d.dJ % 128 == 0 && env_int("EXAT_PIPELINED", 1) != 0 && env_int("EXAT_SLAB", 1) != 0;
     for (int64_t q = 0; q < n && one_launch; q++)
         if ((uintptr_t)Xblk[q] & 15) one_launch = false;
     if (!one_launch) {

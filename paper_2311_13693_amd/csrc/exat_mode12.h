@@ -34,26 +34,38 @@ struct Mode12Cfg {
     static constexpr int LDS_BYTES = STAGE_BYTES > EPI_BYTES ? STAGE_BYTES : EPI_BYTES;
 };
 
-// element (i, j, k) of an X that is held as separate blocks
+// address of element (i, j, k) of an X that is held as separate blocks
 template <typename T>
-__device__ __forceinline__ T x_of_table(const Mode12Params &p, int64_t i, int64_t j, int64_t k)
+__device__ __forceinline__ const T *x_of_table(const Mode12Params &p, int64_t i, int64_t j, int64_t k)
 {
     const int64_t bi = i / p.x_dI, bj = j / p.x_dJ, bk = k / p.x_dK, jb0 = bj * p.x_dJ;
     const int64_t djb = (p.j1 - jb0 < p.x_dJ) ? p.j1 - jb0 : p.x_dJ;
-    return ((const T *)p.xtab[(bk * p.tab_nbj + bj) * p.tab_nbi + bi])[(i - bi * p.x_dI) + p.x_dI * ((j - jb0) + djb * (k - bk * p.x_dK))];
+    return (const T *)p.xtab[(bk * p.tab_nbj + bj) * p.tab_nbi + bi] + (i - bi * p.x_dI) + p.x_dI * ((j - jb0) + djb * (k - bk * p.x_dK));
 }
 
-// Slow, fully guarded staging of the X tile straight into LDS (box edges, unaligned tensors).
+// Slow, fully guarded staging of the X tile straight into LDS (box edges, unaligned tensors, separate blocks).
 template <typename T, int COLS, int ROWB>
 __device__ __forceinline__ void stage_x_guarded(const Mode12Params &p, unsigned char *Xs, int64_t ib, int64_t jc, int64_t k, int tid)
 {
+    if (p.xtab) {   // blocks are 16-byte aligned, their i extent and the box's ends in i multiples of 16: a 16-byte piece lies in one block
+        constexpr int E16 = elem<T>::per16, FPR = 32 / E16;
+#pragma unroll 1
+        for (int pc = tid; pc < COLS * FPR; pc += 256) {
+            const int c = pc / FPR, f = pc % FPR;
+            const int64_t j = jc + c, i = ib + f * E16;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (j >= p.j0 && j < p.j1 && i >= p.i0 && i < p.i1) v = *(const u32x4 *)x_of_table<T>(p, i, j, k);
+            *(u32x4 *)(Xs + c * ROWB + f * 16) = v;
+        }
+        return;
+    }
     const T *Xp = (const T *)p.X;
     for (int pc = tid; pc < COLS * 32; pc += 256) {
         const int c = pc >> 5, e = pc & 31;
         const int64_t j = jc + c, i = ib + e;
         T v = elem<T>::from_f32(0.0f);
         if (j >= p.j0 && j < p.j1 && i >= p.i0 && i < p.i1)
-            v = p.xtab ? x_of_table<T>(p, i, j, k) : Xp[(i - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk];
+            v = Xp[(i - p.xo_i) + (j - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk];
         ((T *)(Xs + c * ROWB))[e] = v;
     }
 }
@@ -174,10 +186,10 @@ __global__ __launch_bounds__(256) void k_mode12(const Mode12Params p)
         const int64_t x_off = (pf * E16 - p.xo_i) + (jc + pr0 - p.xo_j) * p.x_sj + (k - p.xo_k) * p.x_sk;
         const int64_t x_step = (int64_t)(256 / FPR) * p.x_sj;
 
-        // a stage takes the fast path when the whole 32 x COLS tile lies inside the box
+        // a stage takes the fast path when the whole 32 x COLS tile lies inside the box (of an X with one base address)
         auto is_fast = [&](int s) -> bool {
             const int64_t ib = ia0 + (int64_t)s * EI;
-            if (SRC == SRC_MATERIALISED) return p.x_vec && jfull && ib >= p.i0 && ib + EI <= p.i1;
+            if (SRC == SRC_MATERIALISED) return p.x_vec && !p.xtab && jfull && ib >= p.i0 && ib + EI <= p.i1;
             return ib + EI <= p.I;
         };
         // fetches (or generates) the operands of stage s into registers

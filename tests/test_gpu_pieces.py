@@ -176,3 +176,48 @@ def test_slice_runs(P, L, dtype, K):
     X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
     plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
     assert _err(plan.compress(X), _ref(X, U, V, W, L, M, N, P, dtype)) <= TOL
+
+
+# a slab of blocks with values outside the range of the piece sums: the generic kernel behind reads X through the block table too.
+# dI of whole and of half stages, a ragged last block along j and k; the same blocks one by one give the expectation (and the next slab
+# starts with a clean record).  EXAT_PIPELINED=0 takes every slab apart, that of a split plan as well.
+@pytest.mark.parametrize("dtype,dI", [("f32", 32), ("f32", 48), ("bf16", 32), ("f32s", 32)])
+@pytest.mark.parametrize("case", ["x_inf", "one_huge", "x_huge", "x_tiny", "u_huge", "v_tiny"])
+@pytest.mark.parametrize("P", [2, 13])
+def test_slab_value_ranges(dtype, dI, case, P):
+    I, J, K, L, M, N = 96, 300, 6, 40, 50, 20
+    d = (dI, 128, 4)
+    print("case", dtype, dI, case, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    sx, su, sv = RANGES.get(case, (1.0, 1.0, 1.0))
+    X, U, V = X * sx, U * su, V * sv
+    if case == "x_inf":
+        X[3, 200, 17] = float("inf")
+    elif case == "one_huge":
+        X[0, 0, 0] = 1e25
+    cut = lambda X: [X[k:k + 4, j:j + 128, i:i + dI].contiguous() for k in range(0, K, 4) for j in range(0, J, 128) for i in range(0, I, dI)]
+    nb = (I // dI, 3, 2)
+
+    def one_by_one(X):
+        for n, b in enumerate(cut(X)):
+            plan.compress_block(b, n % nb[0], n // nb[0] % nb[1], n // (nb[0] * nb[1]))
+        return plan.finalize()
+
+    def slab(X):
+        plan.compress_blocks(cut(X), 0, nb[1], 0, nb[2])
+        return plan.finalize()
+
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W, d)
+    if dtype == "f32s":   # two fp16 pieces have fp16 range; fp32 products are what the switch asks for
+        os.environ["EXAT_PIPELINED"] = "0"
+    try:
+        G, Y = one_by_one(X), slab(X)
+        assert torch.equal(torch.isnan(Y), torch.isnan(G)) and torch.equal(torch.isinf(Y), torch.isinf(G))
+        fin = torch.isfinite(G)
+        assert torch.equal(Y[~fin].nan_to_num(0), G[~fin].nan_to_num(0))
+        assert float((Y[fin].double() - G[fin].double()).norm()) <= 2 * TOL * float(G[fin].double().norm())
+        X2 = _problem(I, J, K, L, M, N, P, dtype, seed=6)[0]
+        if case[0] == "x" or case == "one_huge":
+            assert _err(slab(X2), _ref(X2, U, V, W, L, M, N, P, dtype)) <= TOL
+    finally:
+        os.environ.pop("EXAT_PIPELINED", None)
