@@ -36,8 +36,9 @@ typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // rows of Y start at mult
 struct CpStep {
     const float *Y;         // per replica Y[l + L(m + M n)]
     float *F[3];            // A, B, C, per replica column-major D x R
-    const float *pin;       // [replica][NSin][d][R]: partial MTTKRP results of the update before this one
+    const float *pin;       // [replica][NSin][d][R]: partial MTTKRP results of the update before this one; replicas `rs` floats apart
     float *pout;            // the same of this update
+    int64_t rs;             // the same for every update, whatever its extent: a replica overwrites its own partial results only
     int D[3];               // L, M, N
     int R, NSin, NS, DS;    // NS slabs of DS values of the outer contraction index
     int prev, mode;         // updated factor of the update before and of this one (0, 1, 2), or -1: none
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
     if (p.prev >= 0) {
         const int D0 = p.D[v];
         // MTTKRP result: the slabs' partial results in slab order
-        const float *src = p.pin + rep * p.NSin * D0 * R;
+        const float *src = p.pin + rep * p.rs;
         const int st = D0 * R;
         constexpr int XB = FE < 4 ? FE : 4;
 #pragma unroll
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
         }
     }
     if (kg == 0) {
-        float *dst = p.pout + (rep * p.NS + slab) * Du * R;
+        float *dst = p.pout + rep * p.rs + (int64_t)slab * Du * R;
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int d = 32 * (tile / RC) + 8 * (e >> 2) + 4 * hi + (e & 3);
@@ -391,7 +392,7 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
     if (sweeps == 0) return EXAT_OK;
     // Slabs per replica: about one workgroup per compute unit, and no more than 16, since every workgroup adds up all slabs.  The
     // partial results are double-buffered (a workgroup that is ahead writes while others still read) unless a replica has
-    // one workgroup only.
+    // one workgroup only: that one has read all of its replica's partial results before it writes there.
     const int maxd = L > M ? (L > N ? L : N) : (M > N ? M : N);
     int NS = 256 / P;
     NS = NS > 16 ? 16 : (NS < 1 ? 1 : NS);
@@ -399,7 +400,7 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
     while (NS > 1 && 2 * NS * one > room) NS--;
     float *part[2] = {work, NS > 1 ? work + (int64_t)P * NS * one : work};
     CpStep c;
-    c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.P = P; c.status = status;
+    c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.P = P; c.rs = NS * one; c.status = status;
     c.NSin = 1; c.prev = -1;
     auto launch = [&](int ns) {
         const dim3 grid((unsigned)P, (unsigned)ns);

@@ -130,3 +130,49 @@ def test_checked_variant_reports_replicas_whose_normal_matrix_is_not_positive_de
     exat.cpals_checked(_dev_tensor(Ys2), L, M, N, P, R, sweeps, A, B, C, status=status)
     torch.cuda.synchronize()
     assert (status.cpu().numpy() == 0).all()
+
+
+def _batch(seed, L, M, N, R, P):
+    """P tensors of rank R plus noise and start values near their factors, in the library's layouts ([p][n][m][l], [p][r][d])"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    F = [rn(P, R, d) for d in (L, M, N)]
+    nm = (F[2].transpose(1, 2)[:, :, None, :] * F[1].transpose(1, 2)[:, None, :, :]).reshape(P, N * M, R)
+    Y = torch.bmm(nm, F[0]).view(P, N, M, L)
+    Y += 0.05 * R ** 0.5 * rn(*Y.shape)
+    return Y, [f + 0.5 * rn(*f.shape) for f in F]
+
+
+def _als64(Y, F, sweeps):
+    """The sweeps in 64 bits, all replicas at once."""
+    Y, (A, B, C) = Y.double(), [f.double().transpose(1, 2).contiguous() for f in F]
+    P, N, M, L = Y.shape
+    R = A.shape[2]
+
+    def solve(mx, X1, X2):
+        G = torch.bmm(X1.transpose(1, 2).contiguous(), X1) * torch.bmm(X2.transpose(1, 2).contiguous(), X2)
+        return torch.linalg.solve(G, mx.transpose(1, 2).contiguous()).transpose(1, 2).contiguous()
+
+    for _ in range(sweeps):
+        T = torch.bmm(Y.transpose(2, 3).reshape(P, N * L, M), B).view(P, N, L, R)
+        A = solve((T * C[:, :, None, :]).sum(1), C, B)
+        S = torch.bmm(Y.reshape(P, N * M, L), A).view(P, N, M, R)
+        B = solve((S * C[:, :, None, :]).sum(1), C, A)
+        C = solve((S * B[:, None, :, :]).sum(2), B, A)
+    return [f.transpose(1, 2).contiguous() for f in (A, B, C)]
+
+
+# more replicas than workgroups that are resident at a time, unequal extents: what one replica's update leaves has to stay clear of what
+# the updates of others have still to read (above 128 replicas each has one workgroup)
+@pytest.mark.parametrize("L,M,N,R,P", [(16, 64, 16, 16, 130), (20, 24, 28, 20, 300), (64, 50, 60, 40, 300), (16, 64, 16, 16, 1000), (64, 9, 33, 9, 1100)])
+def test_many_replicas(L, M, N, R, P):
+    print("case", L, M, N, R, P, flush=True)
+    Y, F = _batch(45, L, M, N, R, P)
+    ref = _als64(Y, F, 2)
+    got = [f.clone() for f in F]
+    exat.cpals(Y, L, M, N, P, R, 2, *got)
+    for f, r in zip(got, ref):
+        worst = ((f.double() - r).flatten(1).norm(dim=1) / r.flatten(1).norm(dim=1)).max().item()
+        print("  worst factor rel_fro=%.3e" % worst, flush=True)
+        assert worst <= TOL
