@@ -221,3 +221,27 @@ def test_slab_value_ranges(dtype, dI, case, P):
             assert _err(slab(X2), _ref(X2, U, V, W, L, M, N, P, dtype)) <= TOL
     finally:
         os.environ.pop("EXAT_PIPELINED", None)
+
+
+# a bf16 chunk is filled up to a multiple of four stages: the stages past the tensor's last one must not bring in what lies behind a row
+# tile's U -- other rows (a NaN there belongs to its own replica only), or, in a plan whose last tile is in use (7680 rows), other memory
+@pytest.mark.parametrize("P,L", [(3, 32), (7, 40), (120, 64)])
+@pytest.mark.parametrize("I", [32, 70, 96, 129])
+def test_bf16_stages_past_the_end(P, L, I):
+    J, K, M, N, dtype = 40, 3, 7, 5, "bf16"
+    print("case", P, L, I, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    bad = torch.full((1 << 20,), float("nan"), device="cuda")   # what the plan's memory may have held before
+    torch.cuda.synchronize()
+    del bad
+    torch.cuda.empty_cache()
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    R = _ref(X, U, V, W, L, M, N, P, dtype)
+    assert _err(plan.compress(X), R) <= TOL
+    U[P // 2 * L + 5, :] = float("nan")   # one row of the middle replica
+    plan.set_factors(U, V, W)
+    Y, R = plan.compress(X).view(P, N, M, L), R.view(P, N, M, L)
+    ok = torch.ones(P, L, dtype=torch.bool, device="cuda")
+    ok[P // 2, 5] = False
+    ok = ok[:, None, None, :].expand_as(Y)
+    assert torch.isnan(Y[~ok]).all() and _err(Y[ok], R[ok]) <= TOL
