@@ -277,7 +277,7 @@ int exat_stage1_last_timing(exat_stage1_t s, float *ms_mode12, float *ms_mode3);
  * Y_p (L x M x N) that the compression produced.  exat_cpals runs `sweeps` sweeps of the loop body of Alg. 1
  * (update A, then B, then C; each the least-squares solution with the other two fixed,
  * A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^{-1}, by elimination without pivoting on the R x R normal matrix)
- * for all P replicas at once, in fp32.  There is no convergence test: the caller
+ * for all P replicas at once; sums in fp32, the elimination and the product with the inverse in fp64.  There is no convergence test: the caller
  * chooses the number of sweeps.
  *   Y      device, P*L*M*N floats in the layout exat_compress writes: Y[l + L*(m + M*(n + N*p))]; not modified
  *   A,B,C  device, in: start values, out: result; per replica column-major L x R, M x R, N x R:

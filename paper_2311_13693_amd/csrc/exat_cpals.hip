@@ -13,12 +13,15 @@
 //      slab of the outer contraction index.
 // The tensor is read where it lies: a lane holds one row of the updated mode, and the order of the contraction indices inside
 // a matrix instruction is free, so the first mode reads 128-byte runs along l and the other two 16 bytes of l per lane.
-// The normal matrix is inverted in place by Gauss-Jordan steps without pivoting (it is positive definite; the diagonal elements
+// The normal matrix is inverted by Gauss-Jordan steps without pivoting (it is positive definite; the diagonal elements
 // met are the squared pivots of its Cholesky factorisation): 256 threads own cyclic blocks of it in registers, a step publishes
-// one row and one column through LDS and has one barrier.
-// fp32 throughout; every sum has a fixed order.
-// Measured (32 tensors of 64^3, rank 32, ten sweeps): 3.06 ms with two launches per update and permuted copies of the tensor, 0.75 ms
-// now; an update takes 23 us, of which finishing the one before 10 (the inversion 5), the product 9 and an empty launch 4.
+// two rows and two columns through LDS and has one barrier.
+// Data, products and sums are fp32, in a fixed order; the inverse and the product with it are fp64.  An inverse rounded to fp32 leaves
+// a residual X G - Mx of cond(G) 2^-24 |Mx|, a triangular solve in fp32 one of 2^-24 |Mx|; measured at rank 64, cond(G) = 3.5e4: inverse
+// in fp32 1.9e-4, Cholesky factor and two substitutions in fp32 1.7e-7, inverse in fp64 7.5e-8.  The steps wait for LDS and barriers,
+// not for arithmetic, so fp64 costs nothing (0.746 -> 0.735 ms, with the hardware's reciprocal in place of a guarded division).
+// Measured (32 tensors of 64^3, rank 32, ten sweeps): 3.07 ms with two launches per update and permuted copies of the tensor, 0.735 ms
+// now.
 #include "../../include/exat.h"
 
 #include <hip/hip_runtime.h>
@@ -31,6 +34,7 @@ constexpr int CP_MAX = 64;   // largest L, M, N and R
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // rows of Y start at multiples of 4 bytes
 
 struct CpStep {
@@ -46,11 +50,13 @@ struct CpStep {
     int32_t *status;        // optional, [replica]: incremented by every update whose normal matrix has a non-positive pivot
 };
 
-// 1/x to within an ulp: the hardware's estimate and one Newton step; the division itself where either would leave the normal range
-__device__ __forceinline__ float recip(float x)
+// 1/x to within an ulp or two: the hardware's estimate (more than 20 bits) and two Newton steps.  The pivots come from fp32 values, far
+// inside the range of fp64; a zero gives NaN.
+__device__ __forceinline__ double recip(double x)
 {
-    const float ax = fabsf(x), r = __builtin_amdgcn_rcpf(x), y = fmaf(fmaf(-x, r, 1.0f), r, r);
-    return (ax > 0x1p-120f && ax < 0x1p120f) ? y : 1.0f / x;
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
 }
 
 // RC = 32-column tiles of the rank, NB = 16-wide blocks of it (R <= 16 NB, NB <= 2 RC)
@@ -60,9 +66,12 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
     constexpr int RS = 32 * RC, RSP = RS + 1;
     __shared__ float Fs[3][CP_MAX * RSP];     // factors as [d][r], zero beyond D and R
     __shared__ float Mx[CP_MAX * RSP];        // MTTKRP result of the update before; scratch of the partial tiles
-    __shared__ float G[RS * RSP];             // normal matrix, then its inverse
-    __shared__ float Gt[RC == 1 ? 4 : 8][1024];   // tiles of the Gram matrices
-    __shared__ float rowb[2][2][64], colb[2][2][64];
+    __shared__ float G[RS * RSP];             // normal matrix
+    constexpr int NGT = RC == 1 ? 4 : 8;
+    __shared__ __align__(16) float Gt[NGT][1024];   // tiles of the Gram matrices, then the inverse of the normal matrix
+    double *Gi = (double *)&Gt[0][0];         // [r][c ^ 16 (r & 1)]: neighbouring rows 32 banks apart
+    static_assert(RS * RS * 8 <= NGT * 4096, "");
+    __shared__ double rowb[2][2][64], colb[2][2][64];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t rep = blockIdx.x;
@@ -208,16 +217,16 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
             G[(32 * (t / RC) + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * RSP + 32 * (t % RC) + (l & 31)] = g1 * g2;
         }
         __syncthreads();
-        // G <- G^{-1}: thread (ty, tx) owns the entries (ty + 16 a, tx + 16 b), extended by the identity beyond R.  A step eliminates
-        // two rows and columns, in the order and with the pivots of two single steps.
+        // Gi <- G^{-1}, in fp64: thread (ty, tx) owns the entries (ty + 16 a, tx + 16 b), extended by the identity beyond R.  A step
+        // eliminates two rows and columns, in the order and with the pivots of two single steps.
         const int ty = tid >> 4, tx = tid & 15;
-        float g[NB][NB];
+        double g[NB][NB];
 #pragma unroll
         for (int a = 0; a < NB; a++)
 #pragma unroll
             for (int b = 0; b < NB; b++) {
                 const int i = ty + 16 * a, c = tx + 16 * b;
-                g[a][b] = (i == c && i >= R) ? 1.0f : G[i * RSP + c];
+                g[a][b] = (i == c && i >= R) ? 1.0 : (double)G[i * RSP + c];
             }
         bool bad = false;   // the same in every thread: all see the same pivots
 #pragma unroll
@@ -234,29 +243,29 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
                     for (int b = 0; b < NB; b++) rowb[par][ty & 1][tx + 16 * b] = g[jb][b];
                 }
                 __syncthreads();
-                const float p00 = colb[par][0][j], p10 = colb[par][0][j + 1], p01 = colb[par][1][j], p11 = colb[par][1][j + 1];
-                const float inv0 = recip(p00), ur = p01 * inv0, lr = p10 * inv0, s = fmaf(-lr, p01, p11), inv1 = recip(s);
-                bad = bad || !(p00 > 0.0f) || (j + 1 < R && !(s > 0.0f));   // zero, negative or NaN: not positive definite in fp32
-                float w0[NB], w1[NB], q0[NB], q1[NB];
+                const double p00 = colb[par][0][j], p10 = colb[par][0][j + 1], p01 = colb[par][1][j], p11 = colb[par][1][j + 1];
+                const double inv0 = recip(p00), ur = p01 * inv0, lr = p10 * inv0, s = fma(-lr, p01, p11), inv1 = recip(s);
+                bad = bad || !(p00 > 0.0) || (j + 1 < R && !(s > 0.0));   // zero, negative or NaN: not positive definite
+                double w0[NB], w1[NB], q0[NB], q1[NB];
 #pragma unroll
                 for (int a = 0; a < NB; a++) {
-                    const float f0 = colb[par][0][ty + 16 * a], f1v = colb[par][1][ty + 16 * a];
-                    w1[a] = fmaf(-f0, ur, f1v) * inv1;
-                    w0[a] = fmaf(-w1[a], p10, f0) * inv0;
+                    const double f0 = colb[par][0][ty + 16 * a], f1v = colb[par][1][ty + 16 * a];
+                    w1[a] = fma(-f0, ur, f1v) * inv1;
+                    w0[a] = fma(-w1[a], p10, f0) * inv0;
                     q0[a] = rowb[par][0][tx + 16 * a]; q1[a] = rowb[par][1][tx + 16 * a];
                 }
 #pragma unroll
                 for (int a = 0; a < NB; a++)
 #pragma unroll
                     for (int b = 0; b < NB; b++) {
-                        float up = fmaf(-w1[a], q1[b], fmaf(-w0[a], q0[b], g[a][b]));
+                        double up = fma(-w1[a], q1[b], fma(-w0[a], q0[b], g[a][b]));
                         if (b == jb) up = (tx & 14) == jt ? ((tx & 1) ? -w1[a] : -w0[a]) : up;
                         if (a == jb) {
-                            const float r1 = fmaf(-lr, q0[b], q1[b]) * inv1, r0 = fmaf(-p01, r1, q0[b]) * inv0;
-                            float rr = (ty & 1) ? r1 : r0;
+                            const double r1 = fma(-lr, q0[b], q1[b]) * inv1, r0 = fma(-p01, r1, q0[b]) * inv0;
+                            double rr = (ty & 1) ? r1 : r0;
                             if (b == jb) {   // the inverse of the 2 x 2 pivot block
-                                const float i01 = -ur * inv1;
-                                const float dd = (tx & 1) ? ((ty & 1) ? inv1 : i01) : ((ty & 1) ? -lr * inv1 : fmaf(-i01, lr, inv0));
+                                const double i01 = -ur * inv1;
+                                const double dd = (tx & 1) ? ((ty & 1) ? inv1 : i01) : ((ty & 1) ? -lr * inv1 : fma(-i01, lr, inv0));
                                 rr = (tx & 14) == jt ? dd : rr;
                             }
                             up = (ty & 14) == jt ? rr : up;
@@ -270,26 +279,31 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
 #pragma unroll
             for (int b = 0; b < NB; b++) {
                 const int i = ty + 16 * a, c = tx + 16 * b;
-                G[i * RSP + c] = (i < R && c < R) ? g[a][b] : 0.0f;
+                Gi[i * RS + (c ^ (16 * (i & 1)))] = (i < R && c < R) ? g[a][b] : 0.0;
             }
         if (bad && tid == 0 && slab == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
         __syncthreads();
-        // X = Mx G^{-1}: tile (rt, ct) to wave (rt RC + ct) mod 4
-        const int rtn = (D0 + 31) / 32;
-        for (int t = w; t < rtn * RC; t += 4) {
-            const int row = 32 * (t / RC) + l32, c = 32 * (t % RC) + l32;
-            f32x16 x;
+        // X = Mx G^{-1}, accumulated in fp64: 16 x 16 tile (rt, ct) to wave (rt NB + ct) mod 4
+        const int rtn = (D0 + 15) / 16, l16 = lane & 15, q16 = lane >> 4;
+        for (int t = w; t < rtn * NB; t += 4) {
+            const int row = 16 * (t / NB) + l16, c = 16 * (t % NB) + l16;
+            f64x4 x = {0.0, 0.0, 0.0, 0.0};
+            for (int s = 0; s < 4 * NB; s++) {
+                const int k = 4 * s + q16;
+                x = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Mx[row * RSP + k], Gi[k * RS + (c ^ (16 * (k & 1)))], x, 0, 0, 0);
+            }
 #pragma unroll
-            for (int e = 0; e < 16; e++) x[e] = 0.0f;
-            for (int s = 0; s < 8 * NB; s++) x = __builtin_amdgcn_mfma_f32_32x32x2f32(Mx[row * RSP + 2 * s + hi], G[(2 * s + hi) * RSP + c], x, 0, 0, 0);
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int d = 32 * (t / RC) + 8 * (e >> 2) + 4 * hi + (e & 3);
-                Fs[v][d * RSP + c] = (d < D0 && c < R) ? x[e] : 0.0f;
-                if (slab == 0 && d < D0 && c < R) p.F[v][rep * D0 * R + d + (int64_t)D0 * c] = x[e];
+            for (int e = 0; e < 4; e++) {
+                const int d = 16 * (t / NB) + 4 * e + q16;
+                const float xf = (float)x[e];
+                Fs[v][d * RSP + c] = (d < D0 && c < R) ? xf : 0.0f;
+                if (slab == 0 && d < D0 && c < R) p.F[v][rep * D0 * R + d + (int64_t)D0 * c] = xf;
             }
         }
-        for (int e = tid + 32 * rtn * RS; e < CP_MAX * RS; e += 256) Fs[v][(e / RS) * RSP + e % RS] = 0.0f;   // the unused row tile
+        // the unused row tiles, and the columns beyond the blocks of the rank
+        for (int e = tid + 16 * rtn * RS; e < CP_MAX * RS; e += 256) Fs[v][(e / RS) * RSP + e % RS] = 0.0f;
+        if (16 * NB < RS)
+            for (int e = tid; e < 16 * rtn * (RS - 16 * NB); e += 256) Fs[v][(e / (RS - 16 * NB)) * RSP + 16 * NB + e % (RS - 16 * NB)] = 0.0f;
     }
     if (p.mode < 0) return;
     __syncthreads();

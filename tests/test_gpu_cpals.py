@@ -176,3 +176,31 @@ def test_many_replicas(L, M, N, R, P):
         worst = ((f.double() - r).flatten(1).norm(dim=1) / r.flatten(1).norm(dim=1)).max().item()
         print("  worst factor rel_fro=%.3e" % worst, flush=True)
         assert worst <= TOL
+
+
+# Collinear factors: the normal matrices have condition numbers of 1e3 to 1e6.  The last update of a sweep is C <- Mx G^-1 with the returned A
+# and B, so it can be judged alone.  Its residual C G - Mx holds the rounding of C, of the products in G and of the sums in Mx, each a few
+# 2^-24 of its entries (all of one sign here, nothing cancels), and no factor of the condition number: 2e-6 of |Mx|.  Against the solution in
+# 64 bits the rounding of G counts with the condition number, 8 2^-24 cond(G).
+@pytest.mark.parametrize("R,mix", [(8, 0.995), (32, 0.98), (32, 0.999), (64, 0.95), (64, 0.99), (64, 0.999)])
+def test_collinear_factors(R, mix):
+    print("case", R, mix, flush=True)
+    P, D = 6, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(46)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    F = [(mix ** 0.5 * rn(P, 1, D) + (1 - mix) ** 0.5 * rn(P, R, D)) for _ in range(3)]
+    nm = (F[2].transpose(1, 2)[:, :, None, :] * F[1].transpose(1, 2)[:, None, :, :]).reshape(P, D * D, R)
+    Y = torch.bmm(nm, F[0]).view(P, D, D, D)
+    A, B, C = [(f + 0.05 * (1 - mix) ** 0.5 * rn(*f.shape)).contiguous() for f in F]
+    exat.cpals(Y, D, D, D, P, R, 1, A, B, C)
+    A, B, C = [f.double().transpose(1, 2).contiguous() for f in (A, B, C)]
+    T = torch.bmm(Y.double().reshape(P, D * D, D), A).view(P, D, D, R)
+    Mx = (T * B[:, None, :, :]).sum(2)
+    G = torch.bmm(A.transpose(1, 2).contiguous(), A) * torch.bmm(B.transpose(1, 2).contiguous(), B)
+    S = torch.linalg.solve(G, Mx.transpose(1, 2).contiguous()).transpose(1, 2)
+    for p in range(P):
+        cond, res, err = torch.linalg.cond(G[p]).item(), ((C[p] @ G[p] - Mx[p]).norm() / Mx[p].norm()).item(), ((C[p] - S[p]).norm() / S[p].norm()).item()
+        print("  cond=%.1e residual=%.2e error=%.2e" % (cond, res, err), flush=True)
+        assert 3e2 < cond < 3e6
+        assert res <= 2e-6 and err <= 8 * 2.0 ** -24 * cond
