@@ -582,8 +582,8 @@ int exat_set_factors(exat_plan_t pl, const float *U, int64_t ldU, const float *V
     if (d.in_dtype == EXAT_BF16) {
         hipLaunchKernelGGL(k_pack_u<__bf16>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (__bf16 *)pl->Upack, pl->PLpad, pl->Ipad);
         hipLaunchKernelGGL(k_pack_u_frag<__bf16>, dim3(grid_for(nu)), dim3(256), 0, st, U, ldU, pl->PL, d.I, (__bf16 *)pl->Ufrag, pl->PLpad / 32, pl->Ipad / 16);
-        hipLaunchKernelGGL(k_pack_v_frag, dim3(grid_for((int64_t)d.P * pl->Jpad * 64)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (__bf16 *)pl->Vfrag, pl->Jpad, 0);
-        hipLaunchKernelGGL(k_pack_v_frag, dim3(grid_for((int64_t)d.P * pl->Jpad * 64)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (__bf16 *)pl->Vfragz, pl->Jpad, 1);
+        hipLaunchKernelGGL(k_pack_v_frag, dim3(grid_for((int64_t)d.P * pl->Jpad * 64)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (__bf16 *)pl->Vfrag, pl->Jpad, 0, (uint32_t *)nullptr);
+        hipLaunchKernelGGL(k_pack_v_frag, dim3(grid_for((int64_t)d.P * pl->Jpad * 64)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, (__bf16 *)pl->Vfragz, pl->Jpad, 1, pl->ranges);
         hipLaunchKernelGGL(k_pack_v<__bf16>, dim3(grid_for(nv)), dim3(256), 0, st, V, ldV, d.P, d.M, d.J, pl->Vpack, pl->Mpad, pl->Jpad);
         hipLaunchKernelGGL(k_pack_w<__bf16>, dim3(grid_for(nw)), dim3(256), 0, st, W, ldW, d.P, d.N, d.K, pl->Wpack, pl->Npad);
     } else {

@@ -50,7 +50,13 @@ struct MpParams {
     uint32_t *flags;   // MPF_* words, or null
 };
 
-// notes the largest magnitude `mx` a lane has seen: one word per wave and condition, written only if it is not set yet
+// the largest of mx, |a|, |b|; NaN if one of them is (one instruction)
+__device__ __forceinline__ float mp_max(float mx, float a, float b)
+{
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, fabsf(a)), fabsf(b));
+}
+
+// notes the largest magnitude `mx` a lane has seen, NaN among them as too large: one word per wave and condition, written only if it is not set yet
 __device__ __forceinline__ void mp_note(uint32_t *f, int big, int norm, int nz, float mx, float vmin, float vmax)
 {
     const bool b = __any(!(mx <= vmax)), n = __any(mx >= vmin), z = __any(mx > 0.0f);
@@ -393,8 +399,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
                     for (int e = 0; e < 4; e++) x[e] = (ib + i + e >= p.i0 && ib + i + e < p.i1) ? x[e] : 0.0f;
                 }
                 uint32_t w0[NP], w1[NP];
-                xmax = fmaxf(fmaxf(xmax, fabsf(x[0])), fabsf(x[1]));
-                xmax = fmaxf(fmaxf(xmax, fabsf(x[2])), fabsf(x[3]));
+                xmax = mp_max(xmax, x[0], x[1]);
+                xmax = mp_max(xmax, x[2], x[3]);
                 mp_split2<NP, F16>(x[0], x[1], w0);
                 mp_split2<NP, F16>(x[2], x[3], w1);
 #pragma unroll
@@ -485,7 +491,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             if constexpr (NP > 1) {
                 const uint32_t ua = src[e >> 1][2 * (e & 1)], ub = src[e >> 1][2 * (e & 1) + 1];
                 const float a = __builtin_bit_cast(float, ua), b = __builtin_bit_cast(float, ub);
-                if (NP == 3) xmax = fmaxf(fmaxf(xmax, fabsf(a)), fabsf(b));
+                if (NP == 3) xmax = mp_max(xmax, a, b);
                 mp_split2<NP, F16, true>(a, b, xw[e]);
             }
         };
@@ -631,7 +637,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 #pragma unroll
                 for (int ct = 0; ct < CT; ct++)
 #pragma unroll
-                    for (int e = 0; e < 16; e += 2) zmax = fmaxf(fmaxf(zmax, fabsf(acc[rt][ct][e])), fabsf(acc[rt][ct][e + 1]));
+                    for (int e = 0; e < 16; e += 2) zmax = mp_max(zmax, acc[rt][ct][e], acc[rt][ct][e + 1]);
         }
         const bool first_chunk = (jc == mp.ja0);
         float *Qk = p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
@@ -661,7 +667,7 @@ __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks,
         u32x4 o[NP];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            mx = fmaxf(fmaxf(mx, fabsf(v[2 * e])), fabsf(v[2 * e + 1]));
+            mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll
@@ -694,7 +700,7 @@ __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks,
         u32x4 o[NP];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            mx = fmaxf(fmaxf(mx, fabsf(v[2 * e])), fabsf(v[2 * e + 1]));
+            mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll

@@ -346,7 +346,7 @@ __global__ void k_pack_u_frag(const float *src, int64_t ld, int rows, int64_t co
 // Stacked fp32 V (P*M x J) -> bf16 B fragments of the 32x32x16 MFMA, [P][Jpad/16][2][64 lanes][8], zero padded:
 // lane l of fragment (p, j16, mt) holds V_p[m = 32*mt + l%32, j = 16*j16 + 8*(l/32) .. +7].
 // perm: the column order of mode2_direct_bf16 (UFragParams::Vz) instead.
-__global__ void k_pack_v_frag(const float *src, int64_t ld, int P, int M, int64_t J, __bf16 *dst, int64_t Jpad, int perm)
+__global__ void k_pack_v_frag(const float *src, int64_t ld, int P, int M, int64_t J, __bf16 *dst, int64_t Jpad, int perm, uint32_t *flags)
 {
     const int64_t n = (int64_t)P * Jpad * 64;
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
@@ -356,6 +356,8 @@ __global__ void k_pack_v_frag(const float *src, int64_t ld, int P, int M, int64_
         const int64_t j = perm ? 16 * j16 + 4 * (l >> 5) + (e & 3) + 8 * (e >> 2) : 16 * j16 + 8 * (l >> 5) + e;
         const float v = (m < M && j < J) ? src[(pr * M + m) * ld + j] : 0.0f;
         dst[idx] = (__bf16)v;
+        // k_mode12_mp multiplies V with pieces of Z, some of them zero: not what an infinity times Z is
+        if (flags && !(fabsf((float)(__bf16)v) < __builtin_inff())) flags[MPF_VBIG] = 1;
     }
 }
 

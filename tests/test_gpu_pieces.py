@@ -245,3 +245,62 @@ def test_bf16_stages_past_the_end(P, L, I):
     ok[P // 2, 5] = False
     ok = ok[:, None, None, :].expand_as(Y)
     assert torch.isnan(Y[~ok]).all() and _err(Y[ok], R[ok]) <= TOL
+
+
+def _same_as_generic(call, P):
+    """call() on the route the library takes and with fp32 products throughout: the same infinities and NaN, the same values elsewhere"""
+    Y = call()
+    os.environ["EXAT_PIPELINED"] = "0"
+    try:
+        G = call()
+    finally:
+        os.environ.pop("EXAT_PIPELINED")
+    assert torch.equal(torch.isnan(Y), torch.isnan(G)) and torch.equal(torch.isinf(Y), torch.isinf(G))
+    fin = torch.isfinite(G)
+    assert torch.equal(Y[~fin].nan_to_num(0), G[~fin].nan_to_num(0))
+    if P == 13:
+        assert torch.equal(Y[fin], G[fin])
+    else:   # several wave columns: see test_value_ranges
+        assert float((Y[fin].double() - G[fin].double()).norm()) <= TOL * float(G[fin].double().norm())
+    return G
+
+
+# NaN and infinities in each operand are noted like any value outside the range
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P", [2, 7, 13])
+@pytest.mark.parametrize("case", ["x_nan", "u_nan", "v_nan", "u_inf", "v_inf"])
+def test_non_finite_operands(dtype, case, P):
+    I, J, K, L, M, N = 70, 140, 6, 40, 50, 20
+    print("case", dtype, case, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    bad = float(case[2:])
+    if case[0] == "x":
+        X[3, 100, 17] = bad
+    elif case[0] == "u":
+        U[L + 3, 44] = bad
+    else:
+        V[M + 7, 111] = bad
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    G = _same_as_generic(lambda: plan.compress(X), P)
+    if case != "x_nan":   # one row of U or V: the other replicas are what they are without it
+        G = G.view(P, N, M, L)
+        bad_p = (~torch.isfinite(G)).flatten(1).any(1)
+        assert bad_p.tolist() == [p == 1 for p in range(P)]
+
+
+# generated in fp32: the factors are taken as fp16 pieces, and what lies beyond fp16 becomes an infinity or a NaN of the tile
+@pytest.mark.parametrize("R", [5, 40])
+@pytest.mark.parametrize("P", [2, 7, 13])
+@pytest.mark.parametrize("scale", [(1e5, 1.0, 1.0), (1.0, 1e4, 30.0), (1e30, 1e-20, 1.0)])
+def test_generated_factor_range(P, R, scale):
+    I, J, K, L, M, N = 70, 140, 6, 40, 50, 20
+    print("case", P, R, scale, flush=True)
+    _, U, V, W = _problem(I, J, K, L, M, N, P, "f32")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    A, B, C = [s * torch.randn(R, n, generator=g, device="cuda") for s, n in zip(scale, (I, J, K))]
+    gen = exat.make_gen(A, B, C, 77, 0.01)
+    plan = _plan(I, J, K, L, M, N, P, "f32", U, V, W)
+    G = _same_as_generic(lambda: plan.compress_gen(gen), P)
+    X = torch.matmul((C.double()[:, :, None] * B.double()[:, None, :]).reshape(R, -1).T.contiguous(), A.double()).view(K, J, I)
+    assert _err(G, _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL   # the noise is below rounding here
