@@ -532,8 +532,8 @@ int exat_plan_create(exat_plan_t *plan, const exat_desc_t *desc)
     const size_t un = (size_t)pl->PLpad * pl->Ipad, vn = (size_t)desc->P * pl->Mpad * pl->Jpad, vf = (size_t)desc->P * pl->Jpad * 64 * 2;
     const struct { void **ptr; size_t bytes; } cut[] = {
         {(void **)&pl->ranges, MPF_WORDS * sizeof(uint32_t)}, {(void **)&pl->Asplit, (size_t)3 * pl->Ipad * 64 * 2}, {&pl->Upack, ub},
-        {&pl->Ufrag, bf ? ub : 0}, {&pl->Vfrag, bf ? vf : 0}, {&pl->Vfragz, bf ? vf : 0}, {&pl->Ump, bf ? 0 : un * 6},
-        {&pl->Vmp, bf ? 0 : vn * 6}, {&pl->Usp, split ? un * 4 : 0}, {&pl->Vsp, split ? vn * 4 : 0}, {(void **)&pl->Vpack, vb},
+        {&pl->Ufrag, bf ? ub : 0}, {&pl->Vfrag, bf ? vf : 0}, {&pl->Vfragz, bf ? vf : 0}, {&pl->Ump, bf ? 0 : un * 6 + MP_UPAD},
+        {&pl->Vmp, bf ? 0 : vn * 6}, {&pl->Usp, split ? un * 4 + MP_UPAD : 0}, {&pl->Vsp, split ? vn * 4 : 0}, {(void **)&pl->Vpack, vb},
         {(void **)&pl->Wpack, wb}, {(void **)&pl->Q, qb}};
     size_t total = 0;
     for (const auto &c : cut) total += (c.bytes + 255) & ~(size_t)255;

@@ -37,6 +37,8 @@
 
 namespace exat {
 
+constexpr size_t MP_UPAD = 8 << 10;   // NP > 1: the U fragments of the stage past the last one (2 x NP x 1024 bytes) are requested
+
 struct MpParams {
     const void *Uf;    // [PLpad/32][nig][NP][64 lanes][8]: lane l of fragment (rt, ig, piece) holds row 32*rt + l%32,
                        // i = 16*ig + 8*(l/32) .. +7
@@ -122,6 +124,7 @@ struct Mode12MpCfg {
     static constexpr int XD = NP == 1 ? 4 : 2;   // register sets of X fragments read from LDS
     static constexpr int UNR = DX;               // stages per pass of the stage loop (register sets are addressed statically)
     static_assert(H <= 2 || H % UNR == 0 || UNR % H == 0, "");
+    static_assert(UNR > 1 || 2 * DU * NP * 1024 <= MP_UPAD, "");
     static_assert(UNR % DU == 0 && UNR % DX == 0 && (UNR % H == 0 || H % UNR == 0), "");
 };
 
@@ -504,13 +507,14 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
                 *(u32x4 *)(base + c * XBUF + xs_w + u * XC * ROWB) = v;
             }
         };
-        // U fragments of stage s.  A stage past the box's last one multiplies zeros of X (the chunk is filled up to UNR stages) or nothing:
-        // its fragments are zeros too, which a descriptor of no bytes gives without a read (what follows in memory are other rows, or not U).
+        // U fragments of stage s.  Where a chunk is filled up to UNR stages, those past the box's last one multiply zeros of X: their
+        // fragments are zeros too, which a descriptor of no bytes gives without a read (what follows in memory are other rows, or not U).
+        // With UNR = 1 only the request of stage s+DU goes past the end, and nothing uses it (Uf is padded by MP_UPAD bytes).
         auto load_u = [&](int rt, int s, int g2, u32x4 *dst) __attribute__((always_inline)) {
             const char *b = (const char *)mp.Uf + (int64_t)((wrow0 >> 5) + rt * NWR) * u_tile + ((ia0 >> 4) + 2 * (int64_t)s + g2) * (NP * 1024);
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, s < nstage ? NP * 1024 : 0, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, UNR == 1 || s < nstage ? NP * 1024 : 0, 0x00020000);
 #pragma unroll
-            for (int c = 0; c < NP; c++) dst[c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + c * 1024, 0, 0));
+            for (int c = 0; c < NP; c++) dst[c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, c * 1024, 0));
         };
 
         // tiles 0 .. H-1 into the ring.  (What a chunk hands to the next across its mode 2 lies in the ring; nothing is in flight in
