@@ -52,8 +52,12 @@ typedef enum {
 /* Type in which the kernels consume the X tile and U, V, W.  Products are always
  * accumulated in fp32 and Y is always fp32.  With EXAT_F32 every fp32 operand is used whole: either
  * by fp32 products or as the sum of three bf16 pieces (exact) in six products, which leaves out at most
- * 2^-26 of a product; calls with values outside the range in which that holds (infinities, NaN, the
- * ends of the exponent range) are computed with fp32 products.  With EXAT_BF16 the elements of X, U, V, W
+ * 2^-26 of a product; calls with values outside the range in which that holds are computed with fp32 products.
+ * Inside are: |X| <= 2^80, |U| <= 2^40, |V| <= 2^20 (no infinities, no NaN); elements of U and V that are 0 or
+ * at least 2^-96, the largest of V at least 2^-20; slices of X whose non-zero values reach 2^-96 and of the mode-1
+ * result U X whose rows, where they are not 0, reach 2^-80 (in a slice that does, smaller elements are held to 2^-126
+ * absolutely).  Generated sources up to R = 64 form the low-rank part from two fp16 pieces of A and of B C each: 22 bits, or
+ * 2^-25 absolutely of a value below 1/4; values above 65504 are among those computed with fp32 products.  With EXAT_BF16 the elements of X, U, V, W
  * are rounded to bf16 (round-to-nearest-even) before use; the intermediates of the
  * mode-1 and mode-2 contractions stay fp32. */
 typedef enum { EXAT_F32 = 0, EXAT_BF16 = 1, EXAT_F32_SPLIT = 2 } exat_dtype_t;

@@ -12,8 +12,8 @@
 // of it.
 //
 // Pieces of a value outside a range are not what the sum above says: an infinity has no finite residual, and the low pieces
-// of values near the smallest normal number are lost.  The kernel therefore notes the range of what it multiplies
-// (MpParams::flags) and a launch of the generic kernel behind it, which otherwise ends at once, computes the call with fp32
+// of values near the smallest normal number are lost.  The kernel and the packing of U and V therefore note what lies outside
+// (MpParams::flags; the ranges are in exat_common.h) and a launch of the generic kernel behind it, which otherwise ends at once, computes the call with fp32
 // products when a value lay outside (mp_out_of_range).
 //
 // Decomposition as in k_mode12: a workgroup owns one slice k and a group of stacked rows, walks the slice in chunks of 128
@@ -58,16 +58,13 @@ __device__ __forceinline__ float mp_max(float mx, float a, float b)
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, fabsf(a)), fabsf(b));
 }
 
-// notes the largest magnitude `mx` a lane has seen, NaN among them as too large: one word per wave and condition, written only if it is not set yet
-__device__ __forceinline__ void mp_note(uint32_t *f, int big, int norm, int nz, float mx, float vmin, float vmax)
+// sets a word if the condition holds in any lane (written once per wave at most, and only if it is not set yet)
+__device__ __forceinline__ void mp_note(uint32_t *f, int word, bool lane)
 {
-    const bool b = __any(!(mx <= vmax)), n = __any(mx >= vmin), z = __any(mx > 0.0f);
-    if ((threadIdx.x & 63) == 0) {
-        if (b && !f[big]) f[big] = 1;
-        if (n && !f[norm]) f[norm] = 1;
-        if (z && !n && !f[nz]) f[nz] = 1;
-    }
+    if (__any(lane) && (threadIdx.x & 63) == 0 && !f[word]) f[word] = 1;
 }
+// an element of U or V that is not 0 and too small, or too large, or NaN
+__device__ __forceinline__ bool mp_bad(float v, float vmax) { return !(fabsf(v) <= vmax) || (v != 0.0f && fabsf(v) < MP_EMIN); }
 
 template <int NP> struct mp_terms;   // (X or Z piece, U or V piece) of the products, smallest first
 template <> struct mp_terms<1> { static constexpr int N = 1, X[1] = {0}, U[1] = {0}; };
@@ -287,7 +284,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 
     u32x4 ufr[DU][2][RT][NP];
     u32x4 xr[DX][XPT][XW];
-    float xmax = 0.0f, zmax = 0.0f;
+    float xmax = 0.0f;
+    unsigned zseen = 0;   // of the lane's rows of Z: bit rt: reaches MP_ZMIN, bit 2 + rt: not 0, bit 4: too large or NaN
 
     // ---- the producing side: tiles follow each other through all chunks.  State of the tile that is requested next: chunk
     //      start pj, stage ps, the lane's addresses in that chunk ----
@@ -637,11 +635,14 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 
         if (NP != 2 && mp.flags) {
 #pragma unroll
-            for (int rt = 0; rt < RT; rt++)
+            for (int rt = 0; rt < RT; rt++) {   // (rows of a tile the wave does not have are 0)
+                float m = 0.0f;
 #pragma unroll
                 for (int ct = 0; ct < CT; ct++)
 #pragma unroll
-                    for (int e = 0; e < 16; e += 2) zmax = mp_max(zmax, acc[rt][ct][e], acc[rt][ct][e + 1]);
+                    for (int e = 0; e < 16; e += 2) m = mp_max(m, acc[rt][ct][e], acc[rt][ct][e + 1]);
+                zseen |= (m >= MP_ZMIN ? 1u << rt : 0u) | (m > 0.0f ? 4u << rt : 0u) | (m <= MP_ZMAX ? 0u : 16u);
+            }
         }
         const bool first_chunk = (jc == mp.ja0);
         float *Qk = p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
@@ -651,8 +652,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         else mode2_mp<NP, RT, CT, 1, 32 * NWR>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63);
     }
     if (NP != 2 && mp.flags) {
-        if (NP == 3) mp_note(mp.flags, MPF_XBIG, MPF_XNORM, MPF_XNZ, xmax, MP_XMIN, MP_XMAX);
-        mp_note(mp.flags, MPF_ZBIG, MPF_ZNORM, MPF_ZNZ, zmax, MP_ZMIN, MP_ZMAX);
+        const bool xn = __any(xmax >= MP_EMIN);
+        if (NP == 3) mp_note(mp.flags, MPF_X, !(xmax <= MP_XMAX) || (xmax > 0.0f && !xn));
+        mp_note(mp.flags, MPF_Z, (zseen & 16) || ((zseen >> 2) & ~zseen & 3));
     }
 }
 
@@ -660,7 +662,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 template <int NP>
 __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags)
 {
-    float mx = 0.0f;
+    bool bad = false;
     const int64_t n = (int64_t)rowtiles * nig * 64;
     for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
@@ -671,7 +673,7 @@ __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks,
         u32x4 o[NP];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
+            bad = bad || mp_bad(v[2 * e], MP_UMAX) || mp_bad(v[2 * e + 1], MP_UMAX);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll
@@ -680,7 +682,7 @@ __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks,
 #pragma unroll
         for (int q = 0; q < NP; q++) dst[(f * NP + q) * 64 + l] = o[q];
     }
-    if (flags) mp_note(flags, MPF_UBIG, MPF_UNORM, MPF_UNZ, mx, MP_UMIN, MP_UMAX);
+    if (flags) mp_note(flags, MPF_U, bad);
 }
 template <int NP>
 __global__ __launch_bounds__(256) void k_pack_u_mp(const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags) { pack_u_mp_part<NP>(blockIdx.x, gridDim.x, src, ld, rows, cols, dst, rowtiles, nig, flags); }
@@ -690,6 +692,7 @@ template <int NP>
 __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags)
 {
     float mx = 0.0f;
+    bool bad = false;
     const int64_t n = (int64_t)P * nj16 * MT * 64;
     for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
@@ -705,6 +708,7 @@ __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks,
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
+            bad = bad || mp_bad(v[2 * e], MP_VMAX) || mp_bad(v[2 * e + 1], MP_VMAX);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll
@@ -713,7 +717,11 @@ __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks,
 #pragma unroll
         for (int q = 0; q < NP; q++) dst[(f * NP + q) * 64 + l] = o[q];
     }
-    if (flags) mp_note(flags, MPF_VBIG, MPF_VNORM, MPF_VNZ, mx, MP_VMIN, MP_VMAX);
+    if (flags) {
+        mp_note(flags, MPF_V, bad);
+        mp_note(flags, MPF_VNORM, mx >= MP_VMIN);
+        mp_note(flags, MPF_VNZ, mx > 0.0f);
+    }
 }
 template <int NP>
 __global__ __launch_bounds__(256) void k_pack_v_mp(const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags) { pack_v_mp_part<NP>(blockIdx.x, gridDim.x, src, ld, P, M, J, dst, MT, nj16, flags); }

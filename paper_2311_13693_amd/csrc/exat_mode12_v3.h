@@ -357,7 +357,7 @@ __global__ void k_pack_v_frag(const float *src, int64_t ld, int P, int M, int64_
         const float v = (m < M && j < J) ? src[(pr * M + m) * ld + j] : 0.0f;
         dst[idx] = (__bf16)v;
         // k_mode12_mp multiplies V with pieces of Z, some of them zero: not what an infinity times Z is
-        if (flags && !(fabsf((float)(__bf16)v) < __builtin_inff())) flags[MPF_VBIG] = 1;
+        if (flags && !(fabsf((float)(__bf16)v) < __builtin_inff())) flags[MPF_V] = 1;
     }
 }
 

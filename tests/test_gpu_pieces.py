@@ -304,3 +304,43 @@ def test_generated_factor_range(P, R, scale):
     G = _same_as_generic(lambda: plan.compress_gen(gen), P)
     X = torch.matmul((C.double()[:, :, None] * B.double()[:, None, :]).reshape(R, -1).T.contiguous(), A.double()).view(K, J, I)
     assert _err(G, _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL   # the noise is below rounding here
+
+
+# a small part of an operand beside ordinary values, and an output made of that part alone: one replica's U or V, a slice of X that one row of
+# W picks.  Small enough that pieces would lose bits (1e-36: error 1e-4 and more), or not (1e-15).
+@pytest.mark.parametrize("P", [2, 7, 13])
+@pytest.mark.parametrize("scale", [1e-36, 1e-15])
+@pytest.mark.parametrize("part", ["u", "v", "x"])
+def test_small_part_beside_ordinary(part, scale, P):
+    I, J, K, L, M, N = 70, 140, 6, 40, 50, 20
+    print("case", part, scale, P, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, "f32")
+    if part == "u":
+        U[L:2 * L] *= scale
+    elif part == "v":
+        V[M:2 * M] *= scale
+    else:
+        X[3] *= scale
+        W[N + 4] = 0
+        W[N + 4, 3] = 1
+    plan = _plan(I, J, K, L, M, N, P, "f32", U, V, W)
+    Y, R = plan.compress(X).view(P, N, -1), _ref(X, U, V, W, L, M, N, P, "f32").view(P, N, -1)
+    sel = (1, 4) if part == "x" else (1,)
+    assert _err(Y[sel], R[sel]) <= TOL and _err(Y, R) <= TOL
+
+
+# scales that the pieces hold: the call is not computed a second time (the generic kernel adds up in another order)
+@pytest.mark.parametrize("sx,su", [(1e-24, 1.0), (1e-15, 1.0), (1e20, 1.0), (1.0, 1e-20), (1.0, 1e10), (1e-12, 1e-7)])
+def test_scales_inside_the_range(sx, su):
+    I, J, K, L, M, N, P = 70, 140, 6, 40, 50, 20, 13
+    print("case", sx, su, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, "f32")
+    X, U = X * sx, U * su
+    plan = _plan(I, J, K, L, M, N, P, "f32", U, V, W)
+    Y = plan.compress(X)
+    os.environ["EXAT_PIPELINED"] = "0"
+    try:
+        G = plan.compress(X)
+    finally:
+        os.environ.pop("EXAT_PIPELINED")
+    assert _err(Y, _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL and not torch.equal(Y, G)
