@@ -272,7 +272,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         t0 = 4 * (g * per + (g < more ? g : more));
         nt = 4 * (per + (g < more ? 1 : 0));
     }
-    const int wrow0 = 32 * (t0 + wr);   // first row of this wave's tile 0; tile 1 is NWR tiles further
+    // first row of this wave's tile 0; tile 1 is NWR tiles further.  In a group of one quad the waves of eight beyond it take tile 0 of the
+    // group along and leave no result (they make their share of X).
+    const bool own = wr < nt;
+    const int wrow0 = 32 * (t0 + (own ? wr : 0));
     const bool two = wr + NWR < nt && wrow0 + 32 * NWR < p.PL;
     const int64_t ia0 = p.i0 & ~(int64_t)(EI - 1);
     const int nstage = (int)((p.i1 - ia0 + EI - 1) / EI);
@@ -647,7 +650,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         const bool first_chunk = (jc == mp.ja0);
         float *Qk = p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
         const int64_t jw = jc + wc * CT * 32;
-        const int ntile = two ? 2 : 1;
+        const int ntile = two ? 2 : (own ? 1 : 0);
         if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63);
         else mode2_mp<NP, RT, CT, 1, 32 * NWR>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63);
     }
