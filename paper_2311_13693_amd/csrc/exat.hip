@@ -828,10 +828,19 @@ int exat_gen_block(const exat_desc_t *desc, const exat_gen_t *gen, int32_t bi, i
     gp.j0 = (int64_t)bj * d.dJ; gp.j1 = gp.j0 + blk_ext(d.J, d.dJ, bj);
     gp.k0 = (int64_t)bk * d.dK; gp.k1 = gp.k0 + blk_ext(d.K, d.dK, bk);
     const int64_t nq = ((gp.i1 - 1) >> 2) - (gp.i0 >> 2) + 1;
-    const int64_t nb = cdiv(nq, GB_Q) * cdiv(gp.j1 - gp.j0, GB_J * GB_W) * (gp.k1 - gp.k0);
+    hipStream_t st = (hipStream_t)stream;
+    const int64_t dj = gp.j1 - gp.j0, dk = gp.k1 - gp.k0, nqb = cdiv(nq, GB_Q), njb = cdiv(dj, GB_J * GB_W), nb = nqb * njb * dk;
+    if (4 * nq * dj <= GB_Q * nqb * GB_J * GB_W * njb) {   // at most a quarter of k_gen_box's lanes would be busy
+        int lq = 0;
+        while (lq < 6 && (1 << lq) < nq) lq++;
+        const int64_t nt = cdiv(cdiv(dj * dk, GB_J * (64 >> lq)) * cdiv(nq, 1 << lq), 4);
+        const dim3 grid((unsigned)(nt > (1 << 22) ? (1 << 22) : nt));
+        if (d.in_dtype == EXAT_BF16) hipLaunchKernelGGL(k_gen_thin<__bf16>, grid, dim3(256), 0, st, gp, lq, (__bf16 *)out);
+        else hipLaunchKernelGGL(k_gen_thin<float>, grid, dim3(256), 0, st, gp, lq, (float *)out);
+        return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
+    }
     const dim3 grid((unsigned)(nb > (1 << 22) ? (1 << 22) : nb));
     const size_t lds = (size_t)GB_W * gp.R * GB_J * sizeof(float);   // at most 32 KiB (R <= 256)
-    hipStream_t st = (hipStream_t)stream;
     if (d.in_dtype == EXAT_BF16) hipLaunchKernelGGL(k_gen_box<__bf16>, grid, dim3(64 * GB_W), lds, st, gp, (__bf16 *)out);
     else hipLaunchKernelGGL(k_gen_box<float>, grid, dim3(64 * GB_W), lds, st, gp, (float *)out);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;

@@ -299,4 +299,83 @@ __global__ __launch_bounds__(64 * GB_W) void k_gen_box(const GenParams p, T *out
     }
 }
 
+// The same for blocks thin in i or in j, which would leave most lanes of k_gen_box without a quad or most waves without a fibre.  A
+// wave takes 2^lq quads, the smallest power of two that holds a fibre (at most 64), of (64 >> lq) GB_J fibres; the fibres are numbered over
+// j and k together, and neighbouring lanes write neighbouring fibres.  A lane's fibres are its own, so their products B[j,r] C[k,r] are
+// formed in registers, for two r at a time (one at a time waits for the loads: R = 64 takes three times as long).
+// Taken up to a quarter of k_gen_box's lanes busy.  2^24 elements, fp32, one quad per thread as it once was, k_gen_box, this one, in us:
+//   dI = 4 of long fibres in j  R = 5  47, 569, 25   R = 64  362, 2031, 94        64 x 32 x 8192 (a quarter)  R = 5  88, 43, 25   R = 64  952, 137, 97
+//   dI = 32                     R = 5  59, 77, 25    R = 64  532, 247, 93         500 x 4 x 8388              R = 5  88, 64, 30   R = 64  940, 289, 124
+// In full blocks k_gen_box takes 13.
+template <typename T>
+__global__ __launch_bounds__(256) void k_gen_thin(const GenParams p, int lq, T *out)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, FW = 64 >> lq, grp = lane >> lq;
+    const int64_t q0 = p.i0 >> 2, nq = ((p.i1 - 1) >> 2) - q0 + 1;
+    const int64_t di = p.i1 - p.i0, dj = p.j1 - p.j0, nf = dj * (p.k1 - p.k0), nqb = (nq + (1 << lq) - 1) >> lq, nw = (nf + GB_J * FW - 1) / (GB_J * FW) * nqb;
+    const int sj = (int)(FW % dj), sk = (int)(FW / dj);
+    typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+    typedef T out4 __attribute__((ext_vector_type(4)));
+    typedef out4 out4_u __attribute__((aligned(sizeof(T))));
+    for (int64_t wv = (int64_t)blockIdx.x * 4 + w; wv < nw; wv += (int64_t)gridDim.x * 4) {
+        const int64_t iq = q0 + (wv % nqb << lq) + (lane & ((1 << lq) - 1)), i = 4 * iq;
+        const bool whole = i >= p.i0 && i + 4 <= p.i1;
+        const int64_t t0 = wv / nqb * (GB_J * FW) + grp;   // fibre u of the lane is t0 + u FW
+        int j[GB_J], k[GB_J];
+        j[0] = (int)(t0 % dj); k[0] = (int)(t0 / dj);
+#pragma unroll
+        for (int u = 1; u < GB_J; u++) {
+            j[u] = j[u - 1] + sj; k[u] = k[u - 1] + sk;
+            if (j[u] >= dj) { j[u] -= (int)dj; k[u]++; }
+        }
+        float x[GB_J][4];
+#pragma unroll
+        for (int u = 0; u < GB_J; u++) {
+            if (t0 + u * FW >= nf) { j[u] = 0; k[u] = 0; }   // past the box: made and not written
+#pragma unroll
+            for (int e = 0; e < 4; e++) x[u][e] = 0.0f;
+        }
+#pragma unroll 2
+        for (int r = 0; r < p.R; r++) {
+            f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
+            const float *ap = p.A + p.ldA * r, *bp = p.B + p.j0 + p.ldB * r, *cp = p.C + p.k0 + p.ldC * r;
+            if (whole) a = *(const f32x4_a4 *)(ap + i);
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (i + e >= p.i0 && i + e < p.i1) a[e] = ap[i + e];
+            }
+            float bc[GB_J];
+#pragma unroll
+            for (int u = 0; u < GB_J; u++) bc[u] = bp[j[u]] * cp[k[u]];
+#pragma unroll
+            for (int u = 0; u < GB_J; u++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[u][e] = __builtin_fmaf(a[e], bc[u], x[u][e]);
+        }
+        if (p.amp2_ln2 != 0.0f) {
+#pragma unroll
+            for (int u = 0; u < GB_J; u++) {
+                float z[4];
+                noise_quad(fibre_key(p.skey, (uint32_t)(p.j0 + j[u]), (uint32_t)(p.k0 + k[u])), (uint32_t)iq, p.amp2_ln2, z);
+#pragma unroll
+                for (int e = 0; e < 4; e++) x[u][e] += z[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < GB_J; u++) {
+            if (t0 + u * FW >= nf) continue;
+            T *dst = out + (i - p.i0) + di * (t0 + u * FW);
+            if (whole) {
+                const out4 v = {elem<T>::from_f32(x[u][0]), elem<T>::from_f32(x[u][1]), elem<T>::from_f32(x[u][2]), elem<T>::from_f32(x[u][3])};
+                *(out4_u *)dst = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (i + e >= p.i0 && i + e < p.i1) dst[e] = elem<T>::from_f32(x[u][e]);
+            }
+        }
+    }
+}
+
 }  // namespace exat
