@@ -63,8 +63,11 @@ __device__ __forceinline__ void mp_note(uint32_t *f, int word, bool lane)
 {
     if (__any(lane) && (threadIdx.x & 63) == 0 && !f[word]) f[word] = 1;
 }
-// an element of U or V that is not 0 and too small, or too large, or NaN
-__device__ __forceinline__ bool mp_bad(float v, float vmax) { return !(fabsf(v) <= vmax) || (v != 0.0f && fabsf(v) < MP_EMIN); }
+// the smallest magnitude that is not 0, as its bits without the sign minus one (0 becomes the largest value)
+__device__ __forceinline__ unsigned mp_bits(float v) { return (__builtin_bit_cast(unsigned, v) << 1) - 1u; }
+__device__ __forceinline__ unsigned mp_min(unsigned mn, float a, float b) { return min(min(mn, mp_bits(a)), mp_bits(b)); }
+// elements of U or V of these extremes: one that is not 0 and too small, or too large, or NaN
+__device__ __forceinline__ bool mp_bad(unsigned mn, float mx, float vmax) { return mn < mp_bits(MP_EMIN) || !(mx <= vmax); }
 
 template <int NP> struct mp_terms;   // (X or Z piece, U or V piece) of the products, smallest first
 template <> struct mp_terms<1> { static constexpr int N = 1, X[1] = {0}, U[1] = {0}; };
@@ -665,7 +668,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
 template <int NP>
 __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags)
 {
-    bool bad = false;
+    float mx = 0.0f;
+    unsigned mn = ~0u;
     const int64_t n = (int64_t)rowtiles * nig * 64;
     for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
@@ -676,7 +680,8 @@ __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks,
         u32x4 o[NP];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            bad = bad || mp_bad(v[2 * e], MP_UMAX) || mp_bad(v[2 * e + 1], MP_UMAX);
+            mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
+            mn = mp_min(mn, v[2 * e], v[2 * e + 1]);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll
@@ -685,7 +690,7 @@ __device__ __forceinline__ void pack_u_mp_part(unsigned block, unsigned nblocks,
 #pragma unroll
         for (int q = 0; q < NP; q++) dst[(f * NP + q) * 64 + l] = o[q];
     }
-    if (flags) mp_note(flags, MPF_U, bad);
+    if (flags) mp_note(flags, MPF_U, mp_bad(mn, mx, MP_UMAX));
 }
 template <int NP>
 __global__ __launch_bounds__(256) void k_pack_u_mp(const float *src, int64_t ld, int rows, int64_t cols, u32x4 *dst, int rowtiles, int64_t nig, uint32_t *flags) { pack_u_mp_part<NP>(blockIdx.x, gridDim.x, src, ld, rows, cols, dst, rowtiles, nig, flags); }
@@ -695,7 +700,7 @@ template <int NP>
 __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks, const float *src, int64_t ld, int P, int M, int64_t J, u32x4 *dst, int MT, int64_t nj16, uint32_t *flags)
 {
     float mx = 0.0f;
-    bool bad = false;
+    unsigned mn = ~0u;
     const int64_t n = (int64_t)P * nj16 * MT * 64;
     for (int64_t idx = (int64_t)block * 256 + threadIdx.x; idx < n; idx += (int64_t)nblocks * 256) {
         const int l = (int)(idx & 63);
@@ -711,7 +716,7 @@ __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks,
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             mx = mp_max(mx, v[2 * e], v[2 * e + 1]);
-            bad = bad || mp_bad(v[2 * e], MP_VMAX) || mp_bad(v[2 * e + 1], MP_VMAX);
+            mn = mp_min(mn, v[2 * e], v[2 * e + 1]);
             uint32_t w[NP];
             mp_split2<NP, NP == 2>(v[2 * e], v[2 * e + 1], w);
 #pragma unroll
@@ -721,9 +726,10 @@ __device__ __forceinline__ void pack_v_mp_part(unsigned block, unsigned nblocks,
         for (int q = 0; q < NP; q++) dst[(f * NP + q) * 64 + l] = o[q];
     }
     if (flags) {
-        mp_note(flags, MPF_V, bad);
-        mp_note(flags, MPF_VNORM, mx >= MP_VMIN);
-        mp_note(flags, MPF_VNZ, mx > 0.0f);
+        mp_note(flags, MPF_V, mp_bad(mn, mx, MP_VMAX));
+        const bool n = __any(mx >= MP_VMIN);   // (then MPF_VNZ says nothing more, and most waves read one word only)
+        mp_note(flags, MPF_VNORM, n);
+        mp_note(flags, MPF_VNZ, mx > 0.0f && !n);
     }
 }
 template <int NP>
