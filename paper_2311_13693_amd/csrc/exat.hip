@@ -340,7 +340,7 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
         q.nblk = q.bs = 0;
         // Row groups of different size drift apart and then neither share X tiles nor leave room for U in the L2 (2400 rows, 1000^3
-        // bf16: 37 GB fetched past the L2 in 7.7 ms): slices in runs, one group per XCD at a time.  Both orders measured, slice by
+        // bf16: 37 GB fetched past the L2 in 7.7 ms slice by slice, 17 GB in 7.2 ms in runs): slices in runs, one group per XCD at a time.  Both orders measured, slice by
         // slice -> runs: 1000^3 fp32, 1550 rows 17.9 -> 16.3 ms; 700^3, 2624 rows 11.6 -> 10.7; 1000^3 bf16, 2400 rows 7.48 -> 7.08;
         // 300^3 1.156 -> 1.140; but 250 x 250 x 64 0.154 -> 0.156 (the set-up of a workgroup weighs more).  Equal groups stay in step and
         // gain nothing (1024^3 in four groups 20.8 -> 21.1), two or three groups lose as often as they gain.

@@ -13,14 +13,14 @@
 //
 // Pieces of a value outside a range are not what the sum above says: an infinity has no finite residual, and the low pieces
 // of values near the smallest normal number are lost.  The kernel and the packing of U and V therefore note what lies outside
-// (MpParams::flags; the ranges are in exat_common.h) and a launch of the generic kernel behind it, which otherwise ends at once, computes the call with fp32
-// products when a value lay outside (mp_out_of_range).
+// (MpParams::flags; the ranges are in exat_common.h) and a launch of the generic kernel behind it, which otherwise ends at once,
+// computes the call with fp32 products when a value lay outside (mp_out_of_range).
 //
 // Decomposition as in k_mode12: a workgroup owns one slice k and a group of stacked rows, walks the slice in chunks of 128
 // fibres with the whole i extent reduced before mode 2.
-//   NWC = 1  (NW = 8; NW = 4 for 5 to 8 row tiles, two workgroups per compute unit) every wave holds up to two 32-row tiles x 128 fibres.  The row tiles are dealt to the G groups in quads, as
-//            evenly as they go (a quad is one tile per SIMD), and inside a group tile t goes to wave t mod NW; a wave with one
-//            tile runs a stage loop of its own.
+//   NWC = 1  (NW = 8; NW = 4 for 5 to 8 row tiles, two workgroups per compute unit) every wave holds up to two 32-row tiles x 128
+//            fibres.  The row tiles are dealt to the G groups in quads, as evenly as they go (a quad is one tile per SIMD), and inside
+//            a group tile t goes to wave t mod NW; a wave with one tile runs a stage loop of its own.
 //   NWC = 4  (at most 4 row tiles in all)  four waves share a row tile and take 32 fibres each; each leaves its
 //            own partial Q, which mode 3 adds up as if it were a slice of its own (Mode3Params::kshift).
 // X goes HBM -> registers -> (split) -> LDS; U comes in fragment order straight from L2 into registers.  The X tiles sit in a
@@ -28,8 +28,8 @@
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
 // Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 21 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
 // (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 17.6 ms and 1000^3 bf16, 2400 rows 25.8 -> 7.4 ms (generic
-// kernel before: 1000 is no multiple of a stage); slower only: 128 x 128 x 91 bf16, 304 rows 18.6 -> 20.4 us; 1024^3 in two fp16 pieces, 2048
-// rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
+// kernel before: 1000 is no multiple of a stage); slower only, by the range check's launch: 128 x 128 x 91 bf16, 304 rows 18.3 -> 20.6 us;
+// 1024^3 in two fp16 pieces, 2048 rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
 // about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
 #include "exat_gen.h"
