@@ -4,17 +4,18 @@
 // step lengths.  Declarations and contracts in include/exat.h.
 //
 // The stacked matrix is the array the compression was set up with; it is only read, never factored or copied.
-// One iteration is two launches, each a tall-and-skinny product on the fp32 matrix cores (32x32x2):
-//   k_ls_up    q = U p      one workgroup per 32 rows of U and 32 right-hand sides; p = s + beta p_old is formed
-//                           on the fly
-//   k_ls_down  s = U^T r    one workgroup per 32 columns of U and 32 right-hand sides; r = r_old - alpha q is
-//                           formed on the fly, and the workgroup updates its block of x
-// The eight waves of a workgroup split the contraction range and add their tiles in wave order.
-// A small problem has too few output tiles to fill the chip; then several workgroups share a tile, each takes part
-// of the contraction range, and k_ls_join adds their partial products in a fixed order.
+// One iteration is two launches, each a tall-and-skinny product on the fp32 matrix cores (16x16x4):
+//   k_ls_up    q = U p      p = s + beta p_old is formed on the fly
+//   k_ls_down  s = U^T r    r = r_old - alpha q is formed on the fly, and the workgroup updates its block of x
+// A workgroup of 8 waves owns a tile of the result with its whole contraction range, which its waves split; they add their tiles
+// in wave order through LDS.  A launch of this kind costs 4 to 5 us whatever it does, and a small system is little more than launches:
+// so no tile's sum is split among workgroups (the two launches that joined the parts cost what the products did), nothing but LDS is
+// waited for at a barrier, and nothing is requested that is not used (requests beyond the end of the range: +15 %).
+// 2048 x 1024, 32 right-hand sides, 40 iterations: 1.25 ms with split tiles and joins, 0.64 ms now (up 6.5, down 9.8 us; a workgroup of
+// k_ls_down reads 384 KB, at about 100 GB/s); 10000 x 4000, 64 right-hand sides: 18.2 -> 5.7 ms.
 // Every workgroup also writes its share of the new p (r) into the other of two buffers, so no launch reads what
 // it writes.  The squared column norms that alpha and beta need are left as per-workgroup partial sums and added
-// in workgroup order by whoever needs them: no atomics, every sum has a fixed order.
+// in a fixed order by whoever needs them: no atomics, every sum has a fixed order.
 // In fp32 the iteration must not run on past convergence (the step lengths become ratios of rounding noise and the
 // iterates drift away again), so a column whose normal-equation residual has fallen to `tol` times its start value
 // is frozen: its alpha and beta are zero from then on, which every workgroup decides alike from the same sums.
@@ -26,319 +27,382 @@
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // rows of U and the workspace start at multiples of 4 bytes
 
 constexpr int LS_MAXR = 64;
+constexpr int LS_NW = 8;  // waves per workgroup; they split the contraction range
 
+// The work arrays (x, s, p, q, r) hold four consecutive rows of a column together, [row / 4][column][row % 4], which is what a lane
+// holds of a 16x16 result and what it needs of the second operand of four matrix instructions: 16 bytes per access.  Rows are padded
+// with zeros to a multiple of 32, columns to a multiple of 16.
 struct LsParams {
     const float *U;       // rows x I, row-major, leading dimension ldU
-    int64_t ldU;
+    unsigned ldU;         // rows * ldU <= 2^30
+    unsigned last4;       // index of the last four elements of U (0 if there are fewer)
     int rows, I, R;
-    int Rp, rowsP, IP;    // R, rows and I rounded up to multiples of 32; the work arrays are padded with zeros
-    int nbA, nbB;         // workgroups of k_ls_up (rowsP / 32) and k_ls_down (IP / 32)
-    int vec4;             // rows of U may be read 16 bytes at a time
+    int Rp, rowsP, IP;    // padded R, rows, I
+    int nbA, nbB;         // row tiles of k_ls_up and k_ls_down
     float tol2;           // a column whose gamma has fallen to tol2 * gamma_0 is left as it is
-    float *x, *s, *p[2];  // IP x Rp, row-major
-    float *q, *r[2];      // rowsP x Rp, row-major
-    float *partA;         // [nbA][64]    column sums of q^2 per workgroup
-    float *partB[3];      // [nbB][64]    column sums of s^2 per workgroup: initial, then two alternating
-    float *join;          // [group][rows][Rp] partial products when several workgroups share an output tile
+    f32x4_a4 *x, *s, *p[2];  // IP x Rp
+    f32x4_a4 *q, *r[2];      // rowsP x Rp
+    float *partA;         // [nbA][Rp]    column sums of q^2 per row tile
+    float *partB;         // [nbB][Rp]    column sums of s^2 per row tile
+    float *gam;           // [3][64]      gamma_0, then gamma_t of even and odd t (gamma: column sums of s^2)
 };
 
-constexpr int LS_MAXJOIN = 512;   // output tiles x groups never exceeds this when there is more than one group
-
-// stacked replica factors A[l + L*(c + R*p)] -> r[row][c], row = p*L + l, padded with zeros
+// stacked replica factors A[l + L*(c + R*p)] -> r, row = p*L + l
 __global__ void k_ls_init(LsParams P, const float *Astack, int L)
 {
     const int64_t n = (int64_t)P.rowsP * P.Rp;
+    float *r = (float *)P.r[0];
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(idx % P.Rp);
-        const int64_t row = idx / P.Rp;
+        const int c = (int)((idx >> 2) % P.Rp);
+        const int64_t row = (idx >> 2) / P.Rp * 4 + (idx & 3);
         float v = 0.0f;
         if (row < P.rows && c < P.R) v = Astack[row % L + (int64_t)L * (c + (int64_t)P.R * (row / L))];
-        P.r[0][idx] = v;
+        r[idx] = v;
     }
 }
 
-constexpr int LS_NW = 8;   // waves per workgroup; they split the contraction range
-
-// Adds the partial tiles of waves 1.. to wave 0's, in wave order.  After it wave 0 holds the workgroup's 32 x 32
-// tile: register v of lane (m, h) is element [8 (v / 4) + 4 h + v % 4][m].
-__device__ __forceinline__ void reduce_waves(f32x16 &acc, float (*red)[16][64], int w, int lane)
+// Tile (b, nt) of this workgroup: consecutive ids go to the XCDs in turn; the tiles of one row tile, which read the same part of U, go
+// to one of them, and to the same one in every launch.
+__device__ __forceinline__ void tile_of(int nct, int &b, int &nt)
 {
-    if (w > 0) {
+    const int id = blockIdx.x, y = id >> 3;
+    nt = y % nct;
+    b = (y / nct) * 8 + (id & 7);
+}
+
+// Column sums of a [n][Rp] array of per-workgroup partial sums for the NC = 16 TR columns from `part` on: a lane gets those of columns
+// (lane % 16) + 16 tr.  Thread groups take the entries in turn, the groups of a wave and then the waves are added in order.  The loads
+// are made by `colsum_load`, the rest by `colsum_add`: what is requested between them is in flight meanwhile.
+// Barrier for what goes through LDS: requests to memory stay in flight across it
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int NC>
+constexpr int LS_CL = NC / 4;   // 128 entries ahead, the rest in a loop
+template <int NC>
+__device__ __forceinline__ void colsum_load(const float *__restrict__ part, int n, int Rp, int tid, float (&v)[LS_CL<NC>])
+{
+    const int c = tid % NC, g = tid / NC, NG = 64 * LS_NW / NC;
 #pragma unroll
-        for (int v = 0; v < 16; v++) red[w - 1][v][lane] = acc[v];
+    for (int i = 0; i < LS_CL<NC>; i++) {
+        const int k = g + i * NG;
+        v[i] = part[(unsigned)((k < n ? k : n - 1) * Rp + c)];
     }
-    __syncthreads();
-    if (w == 0) {
-        for (int ww = 0; ww < LS_NW - 1; ww++)
+}
+template <int NC>
+__device__ __forceinline__ void colsum_add(const float *__restrict__ part, int n, int Rp, int tid, const float (&v)[LS_CL<NC>],
+                                           float (*tmp)[NC], float (&sum)[NC / 16])
+{
+    const int c = tid % NC, g = tid / NC, NG = 64 * LS_NW / NC, lane = tid & 63;
+    float a = 0.0f;
 #pragma unroll
-            for (int v = 0; v < 16; v++) acc[v] += red[ww][v][lane];
+    for (int i = 0; i < LS_CL<NC>; i++) a += (g + i * NG < n) ? v[i] : 0.0f;
+#pragma unroll 8
+    for (int k = g + LS_CL<NC> * NG; k < n; k += NG) a += part[(unsigned)(k * Rp + c)];
+    if (NC == 16) a += __shfl_xor(a, 16);
+    a += __shfl_xor(a, 32);
+    if (lane < NC) tmp[tid >> 6][lane] = a;
+    lds_barrier();
+#pragma unroll
+    for (int tr = 0; tr < NC / 16; tr++) {
+        sum[tr] = 0.0f;
+#pragma unroll
+        for (int w = 0; w < LS_NW; w++) sum[tr] += tmp[w][16 * tr + (lane & 15)];
     }
 }
 
-// Column sums of three [n][64] arrays of per-workgroup partial sums at once (so that their loads are in flight
-// together): wave g adds the entries g, g + LS_NW, ... of column tid % 64, the first 64 threads then add the waves'
-// results in wave order and hold the sums.  All threads of the workgroup must call it.
-__device__ __forceinline__ void colsum3(const float *__restrict__ pa, int na, const float *__restrict__ pb, int nb,
-                                        const float *__restrict__ pc, int nc, float (*tmp)[LS_NW][64], int tid,
-                                        float &ra, float &rb, float &rc)
+// Adds the waves' tiles in wave order, stores the result (rows from row0 on, of which those below `rows` count) and leaves the column
+// sums of squares in part[0 .. NC).  A lane's four values of a 16x16 tile are rows 4 (lane / 16) .. + 3 of column lane % 16.
+template <int TM, int TR>
+__device__ __forceinline__ void reduce_store(const f32x4 (&acc)[TM][TR], f32x4 (*red)[TM * TR][64], f32x4_a4 *out, int Rp, int row0, int col0,
+                                             int rows, float *part, int w, int lane)
 {
-    const int c = tid & 63, g = tid >> 6;
-    const int nmax = na > nb ? (na > nc ? na : nc) : (nb > nc ? nb : nc);
-    float a = 0.0f, b = 0.0f, d = 0.0f;
-#pragma unroll 4
-    for (int i = g; i < nmax; i += LS_NW) {
-        const float va = i < na ? pa[i * 64 + c] : 0.0f;
-        const float vb = i < nb ? pb[i * 64 + c] : 0.0f;
-        const float vc = i < nc ? pc[i * 64 + c] : 0.0f;
-        a += va; b += vb; d += vc;
-    }
-    tmp[0][g][c] = a; tmp[1][g][c] = b; tmp[2][g][c] = d;
-    __syncthreads();
-    ra = rb = rc = 0.0f;
-    if (tid < 64)
-        for (int w = 0; w < LS_NW; w++) { ra += tmp[0][w][c]; rb += tmp[1][w][c]; rc += tmp[2][w][c]; }
-}
-
-// wave 0: stores the tile to out (rows row0.., columns col0.., leading dimension Rp) and the tile's column sums
-// of squares
-__device__ __forceinline__ void store_tile(const f32x16 &acc, float *out, int Rp, int row0, int col0, float *part, int m, int h)
-{
+#pragma unroll
+    for (int tm = 0; tm < TM; tm++)
+#pragma unroll
+        for (int tr = 0; tr < TR; tr++) red[w][tm * TR + tr][lane] = acc[tm][tr];
+    lds_barrier();
+    if (w >= TR) return;
     float ss = 0.0f;
 #pragma unroll
-    for (int v = 0; v < 16; v++) {
-        const int row = row0 + 8 * (v / 4) + 4 * h + (v % 4);
-        out[(int64_t)row * Rp + col0 + m] = acc[v];
-        ss += acc[v] * acc[v];
+    for (int tm = 0; tm < TM; tm++) {
+        f32x4 a = red[0][tm * TR + w][lane];
+#pragma unroll
+        for (int k = 1; k < LS_NW; k++) a += red[k][tm * TR + w][lane];
+        const int row = row0 + 16 * tm + 4 * (lane >> 4);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            a[e] = row + e < rows ? a[e] : 0.0f;
+            ss += a[e] * a[e];
+        }
+        out[(unsigned)((row >> 2) * Rp + col0 + 16 * w + (lane & 15))] = a;
     }
-    if (!part) return;
+    ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
-    if (h == 0) part[col0 + m] = ss;
-    if (Rp == 32 && h == 1) part[32 + m] = 0.0f;
+    if (lane < 16) part[16 * w + lane] = ss;
 }
 
-// Adds the G partial products of the workgroups that shared an output tile, in group order, into `out` and leaves
-// the column sums of squares of the 32 rows of workgroup b in part[b][64].  256 threads: a thread keeps one column.
-__global__ __launch_bounds__(256) void k_ls_join(const float *__restrict__ src, int G, int64_t gstride, float *__restrict__ out,
-                                                 float *__restrict__ part, int Rp)
-{
-    __shared__ float col[8][64];
-    const int tid = threadIdx.x, c = tid & (Rp - 1), r0 = tid / Rp, nr = 256 / Rp;   // nr row groups: 8 or 4
-    const int64_t base = (int64_t)blockIdx.x * 32 * Rp;
-    float ss = 0.0f;
-    for (int r = r0; r < 32; r += nr) {
-        const int64_t off = base + (int64_t)r * Rp + c;
-        float v = 0.0f;
-        for (int g = 0; g < G; g++) v += src[g * gstride + off];
-        out[off] = v;
-        ss += v * v;
-    }
-    col[r0][c] = ss;
-    __syncthreads();
-    if (tid < 64) {
-        float t = 0.0f;
-        if (tid < Rp)
-            for (int g = 0; g < nr; g++) t += col[g][tid];
-        part[(int64_t)blockIdx.x * 64 + tid] = t;
-    }
-}
+// The contraction range in steps of 16, dealt to the waves in pairs (a pair covers whole 128-byte lines of a row of U)
+__device__ __forceinline__ int step_of(int n, int w) { return 2 * (w + LS_NW * (n >> 1)) + (n & 1); }
 
-constexpr int LS_D = 4;   // steps whose operands a wave loads in one batch; two batches are in flight
-
-// q = U p_t with p_t = s + beta_t p_{t-1} (p_0 = s); beta_t = gamma_t / gamma_{t-1}, gamma = column sums of s^2.
-// Workgroup (b, nt): rows 32 b .. 32 b + 31 of U, columns 32 nt .. 32 nt + 31 of p.
-__global__ __launch_bounds__(64 * LS_NW) void k_ls_up(LsParams P, int t, int cur, int prev)
+// q = U p_t with p_t = s + beta_t p_{t-1} (p_0 = s); beta_t = gamma_t / gamma_{t-1}.  Tile: rows 16 TM b .. of U, columns 16 TR nt .. of
+// p.  QUAD: U has at least four elements; otherwise they are read one by one.
+template <int TM, int TR, bool QUAD>
+__global__ __launch_bounds__(64 * LS_NW) void k_ls_up(const LsParams P, int t)
 {
-    __shared__ float red[LS_NW - 1][16][64];
-    __shared__ float beta_s[64];
-    __shared__ float tmp[3][LS_NW][64];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, m = lane & 31, h = lane >> 5;
-    const int b = blockIdx.x, col0 = 32 * blockIdx.y;
-    const float *__restrict__ s = P.s, *__restrict__ pold = P.p[(t + 1) & 1];
-    float *__restrict__ pnew = P.p[t & 1];
-    const int row = 32 * b + m;
-    const bool rok = row < P.rows;
-    const float *urow = P.U + (int64_t)(rok ? row : P.rows - 1) * P.ldU;
-    // 8 values of k per step (lane half h takes 4 consecutive ones); wave w takes steps w, w + LS_NW, ..., LS_D
-    // of them per batch
-    struct Ops { float u[4], sv[4], pv[4]; };
-    Ops oa[LS_D], ob[LS_D];
-    auto load_batch = [&](Ops *o, int k0) {
+    constexpr int NC = 16 * TR;
+    __shared__ f32x4 red[LS_NW][TM * TR][64];
+    __shared__ float tmp[LS_NW][NC];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q16 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b, nt;
+    tile_of(P.Rp / NC, b, nt);
+    if (b >= P.nbA) return;
+    const int col0 = NC * nt;
+    const f32x4_a4 *__restrict__ s = P.s + col0, *__restrict__ pold = (t > 0 ? P.p[(t + 1) & 1] : P.s) + col0;
+    float cs[LS_CL<NC>], g0[TR], gz[TR];
+    colsum_load<NC>(P.partB + col0, P.nbB, P.Rp, tid, cs);
 #pragma unroll
-        for (int d = 0; d < LS_D; d++) {
-            const int k = k0 + d * 8 * LS_NW + 4 * h;
-            if (k - 4 * h < P.IP) {
-                if (P.vec4 && k + 3 < P.I) {
-                    const float4 v = *(const float4 *)(urow + k);
-                    o[d].u[0] = v.x; o[d].u[1] = v.y; o[d].u[2] = v.z; o[d].u[3] = v.w;
-                } else {
+    for (int tr = 0; tr < TR; tr++) {
+        g0[tr] = P.gam[64 * (1 + ((t + 1) & 1)) + col0 + 16 * tr + l16];
+        gz[tr] = P.gam[col0 + 16 * tr + l16];
+    }
+    unsigned uo[TM];
 #pragma unroll
-                    for (int e = 0; e < 4; e++) o[d].u[e] = (k + e < P.I) ? urow[k + e] : 0.0f;
-                }
+    for (int tm = 0; tm < TM; tm++) {
+        const int row = 16 * (TM * b + tm) + l16;
+        uo[tm] = (unsigned)(row < P.rows ? row : P.rows - 1) * P.ldU;
+    }
+    const int nst = (P.I + 15) / 16;
+    struct Ops { f32x4 u[TM], sv[TR], pv[TR]; };
+    // a lane holds four consecutive k, 16 step + 4 (lane / 16) + e; requests beyond the range are made at its end and not used
+    auto load = [&](Ops &o, int n) __attribute__((always_inline)) {
+        int st = step_of(n, w);
+        st = st < nst ? st : nst - 1;
+        const unsigned k = 16 * st + 4 * q16;
+#pragma unroll
+        for (int tm = 0; tm < TM; tm++) {
+            if (QUAD) {
+                const unsigned a = uo[tm] + k;
+                o.u[tm] = *(const f32x4_a4 *)(P.U + (a < P.last4 ? a : P.last4));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++) o.u[tm][e] = P.U[uo[tm] + (k + e < (unsigned)P.I ? k + e : 0u)];
+            }
+        }
+#pragma unroll
+        for (int tr = 0; tr < TR; tr++) {
+            const unsigned v = (k >> 2) * (unsigned)P.Rp + 16 * tr + l16;
+            o.sv[tr] = s[v];
+            o.pv[tr] = pold[v];
+        }
+    };
+    f32x4 acc[TM][TR];
+#pragma unroll
+    for (int tm = 0; tm < TM; tm++)
+#pragma unroll
+        for (int tr = 0; tr < TR; tr++) acc[tm][tr] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto mac = [&](Ops &o, int n, const float (&bet)[TR]) __attribute__((always_inline)) {
+        const int st = step_of(n, w);
+        if (st >= nst) return;
+        if (16 * st + 16 > P.I) {   // the end of the rows: what follows a row is not part of it
+            const unsigned k = 16 * st + 4 * q16;
+#pragma unroll
+            for (int tm = 0; tm < TM; tm++) {
+                const f32x4 v = o.u[tm];
+                const unsigned a = uo[tm] + k, sh = QUAD && a > P.last4 ? a - P.last4 : 0u;
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
-                    const unsigned off = (unsigned)(k + e) * (unsigned)P.Rp + (unsigned)(col0 + m);   // < 2^30
-                    o[d].sv[e] = s[off];
-                    o[d].pv[e] = t > 0 ? pold[off] : 0.0f;
+                    float x = v[e];
+                    if (e < 3) x = sh == 1 ? v[(e + 1) & 3] : x;
+                    if (e < 2) x = sh == 2 ? v[(e + 2) & 3] : x;
+                    if (e < 1) x = sh == 3 ? v[(e + 3) & 3] : x;
+                    o.u[tm][e] = k + e < (unsigned)P.I ? x : 0.0f;
                 }
             }
         }
-    };
-    auto mac_batch = [&](const Ops *o, int k0, float bet, f32x16 &acc) {
 #pragma unroll
-        for (int d = 0; d < LS_D; d++) {
-            if (k0 + d * 8 * LS_NW < P.IP) {
+        for (int e = 0; e < 4; e++)
 #pragma unroll
-                for (int e = 0; e < 4; e++)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(rok ? o[d].u[e] : 0.0f, o[d].sv[e] + bet * o[d].pv[e], acc, 0, 0, 0);
+            for (int tr = 0; tr < TR; tr++) {
+                const float pe = o.sv[tr][e] + bet[tr] * o.pv[tr][e];
+#pragma unroll
+                for (int tm = 0; tm < TM; tm++) acc[tm][tr] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.u[tm][e], pe, acc[tm][tr], 0, 0, 0);
             }
-        }
     };
-    constexpr int BK = LS_D * 8 * LS_NW;   // values of k per batch of the workgroup
-    const int GK = BK * (int)gridDim.z;    // the groups of an output tile take the batches in turn
-    const int kw = 8 * w + BK * (int)blockIdx.z;
-    load_batch(oa, kw);                    // in flight while the step length is worked out
-    load_batch(ob, kw + GK);
-    if (t > 0) {
-        float g1, g0, gz;
-        colsum3(P.partB[cur], P.nbB, P.partB[prev], P.nbB, P.partB[0], P.nbB, tmp, tid, g1, g0, gz);
-        if (tid < 64) beta_s[tid] = (g0 > 0.0f && g1 > P.tol2 * gz) ? g1 / g0 : 0.0f;
-    } else if (tid < 64)
-        beta_s[tid] = 0.0f;
-    __syncthreads();
-    const float bet = beta_s[col0 + m];
-    f32x16 acc;
+    Ops oa, ob;
+    load(oa, 0);
+    load(ob, 1);
+    // this workgroup's share of p_t in its columns: `share` elements of 16 bytes, a multiple of the number of columns
+    const int n4 = P.IP / 4 * NC, share = ((P.IP / 4 + P.nbA - 1) / P.nbA) * NC;
+    const int i0 = b * share + tid, iend = n4 < (b + 1) * share ? n4 : (b + 1) * share;
+    auto at = [&](int i) { return (unsigned)(i / NC) * (unsigned)P.Rp + (unsigned)(i % NC); };
+    const unsigned ip = at(i0 < n4 ? i0 : n4 - 1);
+    const f32x4 s0 = s[ip], p0 = pold[ip];
+    float g1[TR], bet[TR];
+    colsum_add<NC>(P.partB + col0, P.nbB, P.Rp, tid, cs, tmp, g1);
 #pragma unroll
-    for (int v = 0; v < 16; v++) acc[v] = 0.0f;
-    for (int k0 = kw; k0 < P.IP; k0 += 2 * GK) {
-        mac_batch(oa, k0, bet, acc);
-        load_batch(oa, k0 + 2 * GK);
-        mac_batch(ob, k0 + GK, bet, acc);
-        load_batch(ob, k0 + 3 * GK);
+    for (int tr = 0; tr < TR; tr++) {
+        bet[tr] = (t > 0 && g0[tr] > 0.0f && g1[tr] > P.tol2 * gz[tr]) ? g1[tr] / g0[tr] : 0.0f;
+        if (b == 0 && tid < 16) {
+            P.gam[64 * (1 + (t & 1)) + col0 + 16 * tr + l16] = g1[tr];
+            if (t == 0) P.gam[col0 + 16 * tr + l16] = g1[tr];
+        }
     }
-    // this workgroup's share of p_t
-    const int64_t n = (int64_t)P.IP * P.Rp;
-    const int64_t wg = b + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z), nwg = (int64_t)gridDim.x * gridDim.y * gridDim.z;
-#pragma unroll 4
-    for (int64_t idx = wg * (64 * LS_NW) + tid; idx < n; idx += nwg * (64 * LS_NW)) {
-        float v = s[idx];
-        if (t > 0) v += beta_s[idx & (P.Rp - 1)] * pold[idx];
-        pnew[idx] = v;
+    int n = 0;
+    for (; LS_NW * (n + 2) < nst; n += 2) {
+        mac(oa, n, bet);
+        load(oa, n + 2);
+        mac(ob, n + 1, bet);
+        load(ob, n + 3);
     }
-    reduce_waves(acc, red, w, lane);
-    if (w == 0) {
-        if (gridDim.z == 1) store_tile(acc, P.q, P.Rp, 32 * b, col0, P.partA + (int64_t)b * 64, m, h);
-        else store_tile(acc, P.join + (int64_t)blockIdx.z * P.rowsP * P.Rp, P.Rp, 32 * b, col0, nullptr, m, h);
+    mac(oa, n, bet);
+    mac(ob, n + 1, bet);
+    reduce_store<TM, TR>(acc, red, P.q, P.Rp, 16 * TM * b, col0, P.rows, P.partA + (int64_t)b * P.Rp + col0, w, lane);
+    {
+        const float bc = TR == 2 && (lane & 16) ? bet[TR - 1] : bet[0];
+        f32x4_a4 *__restrict__ pnew = P.p[t & 1] + col0;
+        if (i0 < iend) pnew[ip] = s0 + bc * p0;
+        for (int i = i0 + 64 * LS_NW; i < iend; i += 64 * LS_NW) pnew[at(i)] = s[at(i)] + bc * pold[at(i)];
     }
 }
 
 // s = U^T r_{t+1} with r_{t+1} = r_t - alpha_t q_t, x += alpha_t p_t; alpha_t = gamma_t / (column sums of q_t^2).
-// t = -1 is the start: r is taken as it stands, x is cleared.
-// Workgroup (b, nt): columns 32 b .. 32 b + 31 of U, columns 32 nt .. 32 nt + 31 of r.
-__global__ __launch_bounds__(64 * LS_NW) void k_ls_down(LsParams P, int t, int cur, int nxt)
+// t = -1 is the start: r is taken as it stands, x is cleared.  Tile: columns 16 TM b .. of U, columns 16 TR nt .. of r.
+template <int TM, int TR>
+__global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
 {
-    __shared__ float red[LS_NW - 1][16][64];
-    __shared__ float alpha_s[64];
-    __shared__ float tmp[3][LS_NW][64];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, m = lane & 31, h = lane >> 5;
-    const int b = blockIdx.x, col0 = 32 * blockIdx.y;
-    const float *__restrict__ rold = P.r[t < 0 ? 0 : (t + 1) & 1], *__restrict__ q = P.q;
-    float *__restrict__ rnew = P.r[t < 0 ? 1 : t & 1];
-    const int i = 32 * b + m;
-    const bool iok = i < P.I;
-    const unsigned ucol = (unsigned)(iok ? i : P.I - 1), ldu = (unsigned)P.ldU;   // rows * ldU < 2^30
-    // 8 rows of U per step (lane half h takes every second one); wave w takes steps w, w + LS_NW, ..., LS_D of them
-    // per batch
-    struct Ops { float u[4], rv[4], qv[4]; };
-    Ops oa[LS_D], ob[LS_D];
-    auto load_batch = [&](Ops *o, int k0) {
+    constexpr int NC = 16 * TR;
+    __shared__ f32x4 red[LS_NW][TM * TR][64];
+    __shared__ float tmp[LS_NW][NC];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q16 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b, nt;
+    tile_of(P.Rp / NC, b, nt);
+    if (b >= P.nbB) return;
+    const int col0 = NC * nt;
+    const f32x4_a4 *__restrict__ rold = P.r[t < 0 ? 0 : (t + 1) & 1] + col0, *__restrict__ q = (t < 0 ? P.r[0] : P.q) + col0;
+    float cs[LS_CL<NC>] = {}, g[TR], gz[TR];
+    if (t >= 0) colsum_load<NC>(P.partA + col0, P.nbA, P.Rp, tid, cs);
 #pragma unroll
-        for (int d = 0; d < LS_D; d++) {
-            if (k0 + d * 8 * LS_NW < P.rowsP) {
+    for (int tr = 0; tr < TR; tr++) {
+        g[tr] = P.gam[64 * (1 + (t & 1)) + col0 + 16 * tr + l16];
+        gz[tr] = P.gam[col0 + 16 * tr + l16];
+    }
+    unsigned uc[TM];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int pl = k0 + d * 8 * LS_NW + 2 * e + h;
-                    const float v = P.U[(unsigned)(pl < P.rows ? pl : P.rows - 1) * ldu + ucol];
-                    o[d].u[e] = (iok && pl < P.rows) ? v : 0.0f;
-                    const unsigned off = (unsigned)pl * (unsigned)P.Rp + (unsigned)(col0 + m);   // < 2^30
-                    o[d].rv[e] = rold[off];
-                    o[d].qv[e] = t >= 0 ? q[off] : 0.0f;
-                }
-            }
+    for (int tm = 0; tm < TM; tm++) {
+        const int i = 16 * (TM * b + tm) + l16;
+        uc[tm] = (unsigned)(i < P.I ? i : P.I - 1);
+    }
+    const int nst = (P.rows + 15) / 16;
+    struct Ops { float u[TM][4]; f32x4 rv[TR], qv[TR]; };
+    // a lane holds the rows 16 step + 4 (lane / 16) + e of U; beyond the last one r is zero and any row will do
+    auto load = [&](Ops &o, int n) __attribute__((always_inline)) {
+        int st = step_of(n, w);
+        st = st < nst ? st : nst - 1;
+        const int k = 16 * st + 4 * q16;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const unsigned ro = (unsigned)(k + e < P.rows ? k + e : P.rows - 1) * P.ldU;
+#pragma unroll
+            for (int tm = 0; tm < TM; tm++) o.u[tm][e] = P.U[ro + uc[tm]];
+        }
+#pragma unroll
+        for (int tr = 0; tr < TR; tr++) {
+            const unsigned v = (unsigned)(k >> 2) * (unsigned)P.Rp + 16 * tr + l16;
+            o.rv[tr] = rold[v];
+            o.qv[tr] = q[v];
         }
     };
-    auto mac_batch = [&](const Ops *o, int k0, float al, f32x16 &acc) {
+    f32x4 acc[TM][TR];
 #pragma unroll
-        for (int d = 0; d < LS_D; d++) {
-            if (k0 + d * 8 * LS_NW < P.rowsP) {
+    for (int tm = 0; tm < TM; tm++)
 #pragma unroll
-                for (int e = 0; e < 4; e++)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(o[d].u[e], o[d].rv[e] - al * o[d].qv[e], acc, 0, 0, 0);
+        for (int tr = 0; tr < TR; tr++) acc[tm][tr] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto mac = [&](const Ops &o, int n, const float (&al)[TR]) __attribute__((always_inline)) {
+        if (step_of(n, w) >= nst) return;
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+            for (int tr = 0; tr < TR; tr++) {
+                const float re = o.rv[tr][e] - al[tr] * o.qv[tr][e];
+#pragma unroll
+                for (int tm = 0; tm < TM; tm++) acc[tm][tr] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.u[tm][e], re, acc[tm][tr], 0, 0, 0);
             }
-        }
     };
-    constexpr int BK = LS_D * 8 * LS_NW;   // rows of U per batch of the workgroup
-    const int GK = BK * (int)gridDim.z;    // the groups of an output tile take the batches in turn
-    const int kw = 8 * w + BK * (int)blockIdx.z;
-    load_batch(oa, kw);                    // in flight while the step length is worked out
-    load_batch(ob, kw + GK);
+    Ops oa, ob;
+    load(oa, 0);
+    load(ob, 1);
+    // this workgroup's share of r_{t+1} in its columns, and its block of x
+    const int n4 = P.rowsP / 4 * NC, share = ((P.rowsP / 4 + P.nbB - 1) / P.nbB) * NC;
+    const int i0 = b * share + tid, iend = n4 < (b + 1) * share ? n4 : (b + 1) * share;
+    auto at = [&](int i) { return (unsigned)(i / NC) * (unsigned)P.Rp + (unsigned)(i % NC); };
+    const unsigned ir = at(i0 < n4 ? i0 : n4 - 1);
+    const f32x4 r0 = rold[ir], q0 = q[ir];
+    constexpr int NX = 4 * TM * NC;
+    const unsigned ix = (unsigned)(4 * TM * b) * (unsigned)P.Rp + col0 + at(tid % NX);
+    const f32x4 x0 = P.x[ix], p0 = P.p[t & 1][ix];
+    float al[TR];
+#pragma unroll
+    for (int tr = 0; tr < TR; tr++) al[tr] = 0.0f;
     if (t >= 0) {
-        float g, gz, d;
-        colsum3(P.partB[cur], P.nbB, P.partB[0], P.nbB, P.partA, P.nbA, tmp, tid, g, gz, d);
-        if (tid < 64) alpha_s[tid] = (d > 0.0f && g > P.tol2 * gz) ? g / d : 0.0f;
-    } else if (tid < 64)
-        alpha_s[tid] = 0.0f;
-    __syncthreads();
-    const float al = alpha_s[col0 + m];
-    f32x16 acc;
+        float d[TR];
+        colsum_add<NC>(P.partA + col0, P.nbA, P.Rp, tid, cs, tmp, d);
 #pragma unroll
-    for (int v = 0; v < 16; v++) acc[v] = 0.0f;
-    for (int k0 = kw; k0 < P.rowsP; k0 += 2 * GK) {
-        mac_batch(oa, k0, al, acc);
-        load_batch(oa, k0 + 2 * GK);
-        mac_batch(ob, k0 + GK, al, acc);
-        load_batch(ob, k0 + 3 * GK);
+        for (int tr = 0; tr < TR; tr++) al[tr] = (d[tr] > 0.0f && g[tr] > P.tol2 * gz[tr]) ? g[tr] / d[tr] : 0.0f;
     }
-    const int64_t n = (int64_t)P.rowsP * P.Rp;
-    const int64_t wg = b + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z), nwg = (int64_t)gridDim.x * gridDim.y * gridDim.z;
-#pragma unroll 4
-    for (int64_t idx = wg * (64 * LS_NW) + tid; idx < n; idx += nwg * (64 * LS_NW)) {
-        float v = rold[idx];
-        if (t >= 0) v -= alpha_s[idx & (P.Rp - 1)] * q[idx];
-        rnew[idx] = v;
+    int n = 0;
+    for (; LS_NW * (n + 2) < nst; n += 2) {
+        mac(oa, n, al);
+        load(oa, n + 2);
+        mac(ob, n + 1, al);
+        load(ob, n + 3);
     }
-    // the 32 x 32 block of x that belongs to this workgroup's columns of U and of r
-    const float *__restrict__ pt = P.p[t & 1];
-#pragma unroll 2
-    for (int e = tid; e < 32 * 32 && blockIdx.z == 0; e += 64 * LS_NW) {
-        const int64_t off = (int64_t)(32 * b + e / 32) * P.Rp + col0 + e % 32;
-        P.x[off] = t >= 0 ? P.x[off] + alpha_s[col0 + e % 32] * pt[off] : 0.0f;
-    }
-    reduce_waves(acc, red, w, lane);
-    if (w == 0) {
-        if (gridDim.z == 1) store_tile(acc, P.s, P.Rp, 32 * b, col0, P.partB[nxt] + (int64_t)b * 64, m, h);
-        else store_tile(acc, P.join + (int64_t)blockIdx.z * P.IP * P.Rp, P.Rp, 32 * b, col0, nullptr, m, h);
+    mac(oa, n, al);
+    mac(ob, n + 1, al);
+    reduce_store<TM, TR>(acc, red, P.s, P.Rp, 16 * TM * b, col0, P.I, P.partB + (int64_t)b * P.Rp + col0, w, lane);
+    {
+        const float ac = TR == 2 && (lane & 16) ? al[TR - 1] : al[0];
+        f32x4_a4 *__restrict__ rnew = P.r[t < 0 ? 1 : t & 1] + col0;
+        if (i0 < iend) rnew[ir] = r0 - ac * q0;
+        for (int i = i0 + 64 * LS_NW; i < iend; i += 64 * LS_NW) rnew[at(i)] = rold[at(i)] - ac * q[at(i)];
+        if (tid < NX) P.x[ix] = t >= 0 ? x0 + ac * p0 : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 }
 
-// X[i + I*c] = x[i][c]; relres[c] = sqrt(gamma_last / gamma_0), the norm of column c of U^T (A - U X) relative to
-// that of U^T A
-__global__ void k_ls_finish(LsParams P, int last, float *X, float *relres)
+// X[i + I*c] = x(i, c); relres[c] = sqrt(gamma_last / gamma_0), the norm of column c of U^T (A - U X) relative to
+// that of U^T A; gamma_last is still in parts
+__global__ __launch_bounds__(256) void k_ls_finish(LsParams P, int iters, float *X, float *relres)
 {
+    __shared__ float tmp[4][64];
     const int64_t n = (int64_t)P.I * P.R;
+    const float *x = (const float *)P.x;
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
         const int64_t c = idx / P.I, i = idx % P.I;
-        X[idx] = P.x[i * P.Rp + c];
+        X[idx] = x[((i >> 2) * P.Rp + c) * 4 + (i & 3)];
     }
-    if (relres && blockIdx.x == 0 && (int)threadIdx.x < P.R) {
-        float g1 = 0.0f, g0 = 0.0f;
-        for (int i = 0; i < P.nbB; i++) {
-            g1 += P.partB[last][i * 64 + threadIdx.x];
-            g0 += P.partB[0][i * 64 + threadIdx.x];
+    if (relres && blockIdx.x == 0) {
+        const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
+        float a = 0.0f;
+        if (c < P.R) {
+#pragma unroll 4
+            for (int i = g; i < P.nbB; i += 4) a += P.partB[(int64_t)i * P.Rp + c];
         }
-        relres[threadIdx.x] = g0 > 0.0f ? sqrtf(g1 / g0) : 0.0f;
+        tmp[g][c] = a;
+        __syncthreads();
+        if (g == 0 && c < P.R) {
+            const float g1 = tmp[0][c] + tmp[1][c] + tmp[2][c] + tmp[3][c], g0 = iters > 0 ? P.gam[c] : g1;
+            relres[c] = g0 > 0.0f ? sqrtf(g1 / g0) : 0.0f;
+        }
     }
 }
 
@@ -349,6 +413,26 @@ bool shape_ok(int32_t P, int32_t L, int32_t I, int32_t R)
     return P >= 1 && L >= 1 && I >= 1 && R >= 1 && R <= LS_MAXR && (int64_t)P * L <= (1 << 22) && I <= (1 << 22);
 }
 
+// Tile of a product with `m` rows of the result and Rp right-hand sides, in units of 16.  What a tile costs is its reads, its rows of U
+// and two vectors per right-hand side, and 256 compute units take the tiles in turn.  40 iterations, 2048 x 1024, R = 32: 0.64 ms with
+// the smallest tile; 10000 x 4000, R = 64: 9.8 ms with it, 6.9 with 2 x 1, 5.7 with 2 x 2 (64 rows or 64 right-hand sides: slower
+// again; 16 x 32 never has the lowest cost).  More tiles than 2048 are made 32 rows high: the workspace has room for that many partial sums.
+struct Tile { int tm, tr; };
+Tile choose_tile(int m, int Rp)
+{
+    const Tile all[] = {{1, 1}, {2, 1}, {2, 2}};
+    Tile best = all[0];
+    int64_t bc = 0;
+    for (const Tile &t : all) {
+        if (Rp % (16 * t.tr)) continue;
+        const int64_t nb = (m + 16 * t.tm - 1) / (16 * t.tm), nwg = nb * (Rp / (16 * t.tr));
+        if (t.tm == 1 && nb > 2048) continue;
+        const int64_t cost = ((nwg + 255) / 256) * (16 * t.tm + 32 * t.tr);
+        if (bc == 0 || cost < bc) { best = t; bc = cost; }
+    }
+    return best;
+}
+
 }  // namespace
 
 extern "C" {
@@ -356,8 +440,9 @@ extern "C" {
 int64_t exat_ls_workspace_floats(int32_t P, int32_t L, int32_t I, int32_t R)
 {
     if (!shape_ok(P, L, I, R)) return 0;
+    // the vectors, and room for the partial sums of either tile height (16 rows up to 2048 tiles, else 32)
     const int64_t rowsP = up32(P * L), IP = up32(I), Rp = up32(R);
-    return 4 * IP * Rp + 3 * rowsP * Rp + (rowsP / 32) * 64 + 3 * (IP / 32) * 64 + LS_MAXJOIN * 1024;
+    return 4 * IP * Rp + 3 * rowsP * Rp + (rowsP / 32) * 64 + 3 * (IP / 32) * 64 + 512 * 1024;
 }
 
 int exat_ls(const float *U, int64_t ldU, int32_t P, int32_t L, int32_t I, const float *Astack, int32_t R, int32_t iters,
@@ -368,52 +453,45 @@ int exat_ls(const float *U, int64_t ldU, int32_t P, int32_t L, int32_t I, const 
     if ((int64_t)P * L * ldU > ((int64_t)1 << 30)) return EXAT_ERR_SHAPE;   // the kernels index U with 32 bits
     hipStream_t st = (hipStream_t)stream;
     LsParams p;
-    p.U = U; p.ldU = ldU; p.rows = P * L; p.I = I; p.R = R;
-    p.Rp = up32(R); p.rowsP = up32(p.rows); p.IP = up32(I);
-    p.nbA = p.rowsP / 32; p.nbB = p.IP / 32;
+    p.U = U; p.ldU = (unsigned)ldU; p.rows = P * L; p.I = I; p.R = R;
+    p.Rp = 16 * ((R + 15) / 16); p.rowsP = up32(p.rows); p.IP = up32(I);
     p.tol2 = tol * tol;
-    p.vec4 = (ldU % 4 == 0 && ((uintptr_t)U & 15) == 0) ? 1 : 0;
+    const int64_t nel = (int64_t)(p.rows - 1) * ldU + I;
+    p.last4 = (unsigned)(nel >= 4 ? nel - 4 : 0);
+    const Tile ta = choose_tile(p.rows, p.Rp), tb = choose_tile(p.I, p.Rp);
+    p.nbA = (p.rows + 16 * ta.tm - 1) / (16 * ta.tm); p.nbB = (p.I + 16 * tb.tm - 1) / (16 * tb.tm);
     const int64_t nx = (int64_t)p.IP * p.Rp, nr = (int64_t)p.rowsP * p.Rp;
     float *w = work;
-    p.x = w; w += nx; p.s = w; w += nx; p.p[0] = w; w += nx; p.p[1] = w; w += nx;
-    p.q = w; w += nr; p.r[0] = w; w += nr; p.r[1] = w; w += nr;
-    p.partA = w; w += (int64_t)p.nbA * 64;
-    for (int t = 0; t < 3; t++) { p.partB[t] = w; w += (int64_t)p.nbB * 64; }
-    p.join = w;
-    const unsigned nct = (unsigned)(p.Rp / 32);   // column tiles of 32 right-hand sides
-    // A single workgroup draws little bandwidth from memory, so small problems are spread further: up to 16 groups of
-    // workgroups share an output tile (one per batch of the contraction range at most), each leaves a partial
-    // product, and k_ls_join adds them in group order.
-    auto groups = [&](int64_t tiles, int64_t len) {
-        const int64_t bk = (int64_t)LS_D * 8 * LS_NW, batches = (len + bk - 1) / bk;
-        int64_t g = LS_MAXJOIN / tiles;
-        if (g > 16) g = 16;
-        if (g > batches) g = batches;
-        return (unsigned)(g < 1 ? 1 : g);
+    auto take = [&](int64_t n) { f32x4_a4 *a = (f32x4_a4 *)w; w += n; return a; };
+    p.x = take(nx); p.s = take(nx); p.p[0] = take(nx); p.p[1] = take(nx);
+    p.q = take(nr); p.r[0] = take(nr); p.r[1] = take(nr);
+    p.partA = w; w += (int64_t)p.nbA * p.Rp;
+    p.partB = w; w += (int64_t)p.nbB * p.Rp;
+    p.gam = w;
+    auto grid = [&](int nb, int tr) { return dim3((unsigned)((nb + 7) / 8 * 8 * (p.Rp / (16 * tr)))); };
+    auto up = [&](int t) {
+        const dim3 g = grid(p.nbA, ta.tr), blk(64 * LS_NW);
+        if (nel < 4) hipLaunchKernelGGL((k_ls_up<1, 1, false>), g, blk, 0, st, p, t);   // three rows at most: the smallest tile
+        else if (ta.tm == 1 && ta.tr == 1) hipLaunchKernelGGL((k_ls_up<1, 1, true>), g, blk, 0, st, p, t);
+        else if (ta.tr == 1) hipLaunchKernelGGL((k_ls_up<2, 1, true>), g, blk, 0, st, p, t);
+        else hipLaunchKernelGGL((k_ls_up<2, 2, true>), g, blk, 0, st, p, t);
     };
-    const unsigned ga = groups((int64_t)p.nbA * nct, p.IP), gb = groups((int64_t)p.nbB * nct, p.rowsP);
-    auto down = [&](int t, int cur, int nxt) {
-        hipLaunchKernelGGL(k_ls_down, dim3((unsigned)p.nbB, nct, gb), dim3(64 * LS_NW), 0, st, p, t, cur, nxt);
-        if (gb > 1)
-            hipLaunchKernelGGL(k_ls_join, dim3((unsigned)p.nbB), dim3(256), 0, st, (const float *)p.join, (int)gb, nx, p.s, p.partB[nxt], p.Rp);
+    auto down = [&](int t) {
+        const dim3 g = grid(p.nbB, tb.tr), blk(64 * LS_NW);
+        if (tb.tm == 1 && tb.tr == 1) hipLaunchKernelGGL((k_ls_down<1, 1>), g, blk, 0, st, p, t);
+        else if (tb.tr == 1) hipLaunchKernelGGL((k_ls_down<2, 1>), g, blk, 0, st, p, t);
+        else hipLaunchKernelGGL((k_ls_down<2, 2>), g, blk, 0, st, p, t);
     };
-    auto up = [&](int t, int cur, int prev) {
-        hipLaunchKernelGGL(k_ls_up, dim3((unsigned)p.nbA, nct, ga), dim3(64 * LS_NW), 0, st, p, t, cur, prev);
-        if (ga > 1)
-            hipLaunchKernelGGL(k_ls_join, dim3((unsigned)p.nbA), dim3(256), 0, st, (const float *)p.join, (int)ga, nr, p.q, p.partA, p.Rp);
-    };
-    // gamma_t (the column sums of s_t^2) lives in partB[cur(t)]: gamma_0 stays in buffer 0 for the final ratio
-    auto cur_of = [](int t) { return t == 0 ? 0 : 1 + ((t - 1) & 1); };
     const unsigned g_init = (unsigned)((nr + 255) / 256 < 4096 ? (nr + 255) / 256 : 4096);
     hipLaunchKernelGGL(k_ls_init, dim3(g_init), dim3(256), 0, st, p, Astack, (int)L);
-    down(-1, 0, 0);
+    down(-1);
     for (int t = 0; t < iters; t++) {
-        up(t, cur_of(t), t > 0 ? cur_of(t - 1) : 0);
-        down(t, cur_of(t), cur_of(t + 1));
+        up(t);
+        down(t);
     }
     const int64_t nout = (int64_t)I * R;
     const unsigned g_fin = (unsigned)((nout + 255) / 256 < 4096 ? (nout + 255) / 256 : 4096);
-    hipLaunchKernelGGL(k_ls_finish, dim3(g_fin), dim3(256), 0, st, p, cur_of(iters), X, relres);
+    hipLaunchKernelGGL(k_ls_finish, dim3(g_fin), dim3(256), 0, st, p, (int)iters, X, relres);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 

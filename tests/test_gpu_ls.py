@@ -128,3 +128,53 @@ def test_unaligned_matrix_pointer():
     torch.cuda.synchronize()
     got = X.cpu().numpy().astype(np.float64).reshape((I, R), order="F")
     assert _rel(got, oracle.stacked_ls(Us, A)) <= TOL
+
+
+def _cgls(U, A, iters):
+    """The iteration itself in fp64."""
+    X, R = np.zeros((U.shape[1], A.shape[1])), A.copy()
+    S = U.T @ R
+    Pd, g = S.copy(), (S * S).sum(0)
+    for _ in range(iters):
+        Q = U @ Pd
+        al = g / (Q * Q).sum(0)
+        X, R = X + al * Pd, R - al * Q
+        S = U.T @ R
+        g, g0 = (S * S).sum(0), g
+        Pd = S + (g / g0) * Pd
+    return X
+
+
+@pytest.mark.parametrize("rows,I,R,ld,off", [
+    (1, 3, 1, 3, 0), (3, 1, 1, 1, 1),              # fewer than four elements of U
+    (1, 4, 2, 4, 1), (2, 2, 17, 2, 0),             # exactly four: the last request is moved back to them
+    (48, 17, 16, 17, 1), (33, 18, 33, 18, 3), (50, 19, 48, 22, 2),   # rows that end 1, 2, 3 values into a request, off 16 bytes
+    (256, 128, 32, 128, 0), (257, 130, 32, 130, 0),                   # whole steps of all waves; one more
+    (4096, 40, 16, 40, 0), (4097, 41, 16, 41, 0),  # 256 tiles of 16 rows; taller tiles
+    (1100, 1025, 64, 1025, 1), (2049, 2049, 64, 2052, 0),             # taller, then wider tiles in both products
+    (70000, 5, 64, 5, 0),                          # many row tiles: partial norms beyond the first requests
+])
+def test_tiles_and_ends(rows, I, R, ld, off):
+    """A few steps from X = 0 against the same iteration in fp64.  The systems are random and have full rank or are cut off long before
+    they matter; an iterate is a sum of at most three directions, each with fp32 rounding (2^-24 sqrt(n) and the conditioning of
+    the step lengths): 1e-5.  The workspace starts 4 bytes off, too, and what surrounds it is checked."""
+    print("case", rows, I, R, ld, off, flush=True)
+    rng = np.random.default_rng(rows + I)
+    iters = min(3, I)
+    Us = rng.standard_normal((rows, I)).astype(np.float32) * rows ** -0.5
+    A = rng.standard_normal((rows, R)).astype(np.float32)
+    buf = torch.full((rows * ld + off + 8,), float("nan"), dtype=torch.float32).cuda()
+    Ud = buf[off:off + rows * ld].view(rows, ld)[:, :I]
+    Ud.copy_(torch.from_numpy(Us))
+    n = exat.lib().exat_ls_workspace_floats(1, rows, I, R)
+    work = torch.full((n + 2,), 7.5, dtype=torch.float32).cuda()
+    X, _ = exat.ls(Ud, 1, rows, I, torch.from_numpy(np.ascontiguousarray(A.T)).cuda(), R, iters, 0.0, work=work[1:n + 1])
+    torch.cuda.synchronize()
+    got = X.cpu().numpy().astype(np.float64).reshape((I, R), order="F")
+    # one row or one unknown: the first step is exact and the second divides rounding noise
+    if min(rows, I) <= 2:
+        iters = 1
+        got = exat.ls(Ud, 1, rows, I, torch.from_numpy(np.ascontiguousarray(A.T)).cuda(), R, 1, 0.0)[0]
+        got = got.cpu().numpy().astype(np.float64).reshape((I, R), order="F")
+    assert _rel(got, _cgls(Us.astype(np.float64), A.astype(np.float64), iters)) <= TOL
+    assert float(work[0]) == 7.5 and float(work[n + 1]) == 7.5
