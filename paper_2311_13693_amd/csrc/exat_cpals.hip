@@ -1,27 +1,31 @@
 // Batched CP-ALS on the P proxy tensors (paper Alg. 1; Sec. 3 "Decomposition").  Declarations and contracts in
 // include/exat.h.
 //
-// The P problems are independent and small (L, M, N, R <= 64), so latency is what bounds them: the tensors stay in the caches,
-// a sweep is 3 * 2 L M N R flops per replica (1.6 GFLOP at 32 replicas of 64^3, rank 32: 10 us at the fp32 matrix rate) and the
-// rest are short serial steps.  One update, e.g. of A, is one launch, k_cpals_step, of NS workgroups per replica:
-//   1. the update before it is finished: the workgroup adds the NS partial MTTKRP results in slab order, forms the normal matrix
-//      G = (F2^T F2) * (F1^T F1) (Gram matrices on the fp32 matrix cores), inverts it and multiplies, X = Mx G^{-1}.  Every
-//      workgroup of the replica does that for itself (it needs the new factor at once and there is nothing to wait for); the
-//      first one writes the factor to memory.
-//   2. its share of this update's MTTKRP, Mx[d0,r] = sum_{d2} sum_{d1} Y[d0,d1,d2] F1[d1,r] F2[d2,r]: a product of the
-//      unfolded tensor with the Khatri-Rao matrix, whose entries are formed in registers, on the fp32 matrix cores, over a
-//      slab of the outer contraction index.
+// The P problems are independent and small (L, M, N, R <= 64), so latency is what bounds them: a sweep is 3 * 2 L M N R flops per
+// replica (1.6 GFLOP at 32 replicas of 64^3, rank 32: 10 us at the fp32 matrix rate) and the rest are short serial steps.  One
+// update, e.g. of A, is one launch, k_cpals_step, of NS + 1 workgroups per replica:
+//   1. the update before it is finished: the workgroup adds the NS partial MTTKRP results in slab order and multiplies with the inverse
+//      of the normal matrix, X = Mx G^{-1}.  Every workgroup of the replica does that for itself (it needs the new factor at once and
+//      there is nothing to wait for); the first slab's writes the factor to memory.
+//   2. NS workgroups compute their share of this update's MTTKRP, Mx[d0,r] = sum_{d2} (sum_{d1} Y[d0,d1,d2] F1[d1,r]) F2[d2,r], over a
+//      slab of the outer contraction index, the inner sum on the bf16 matrix cores with both operands as three bf16 pieces (six of the
+//      nine products; what is left out is at most 2^-26 of a product).  F1 is split once; the sum over d1 has to lie in the range of fp32.
+//   3. Meanwhile one workgroup forms this update's normal matrix G = (F2^T F2) * (F1^T F1) (Gram matrices on the fp32 matrix cores; G
+//      does not depend on the MTTKRP) and inverts it for the next launch.
 // The tensor is read where it lies: a lane holds one row of the updated mode, and the order of the contraction indices inside
 // a matrix instruction is free, so the first mode reads 128-byte runs along l and the other two 16 bytes of l per lane.
-// The normal matrix is inverted by Gauss-Jordan steps without pivoting (it is positive definite; the diagonal elements
-// met are the squared pivots of its Cholesky factorisation): 256 threads own cyclic blocks of it in registers, a step publishes
-// two rows and two columns through LDS and has one barrier.
+// The normal matrix is inverted by Gauss-Jordan steps without pivoting (it is positive definite; the pivots met are the squared ones of
+// its Cholesky factorisation): 256 threads own cyclic blocks of it in registers, a step eliminates four rows and columns, which go through
+// LDS, and has one barrier.
 // Data, products and sums are fp32, in a fixed order; the inverse and the product with it are fp64.  An inverse rounded to fp32 leaves
 // a residual X G - Mx of cond(G) 2^-24 |Mx|, a triangular solve in fp32 one of 2^-24 |Mx|; measured at rank 64, cond(G) = 3.5e4: inverse
-// in fp32 1.9e-4, Cholesky factor and two substitutions in fp32 1.7e-7, inverse in fp64 7.5e-8.  The steps wait for LDS and barriers,
-// not for arithmetic, so fp64 costs nothing (0.746 -> 0.735 ms, with the hardware's reciprocal in place of a guarded division).
-// Measured (32 tensors of 64^3, rank 32, ten sweeps): 3.07 ms with two launches per update and permuted copies of the tensor, 0.735 ms
-// now.
+// in fp32 1.9e-4, Cholesky factor and two substitutions in fp32 1.7e-7, inverse in fp64 6.5e-8.  The steps wait for LDS and barriers,
+// not for arithmetic, so fp64 costs nothing.
+// Measured (32 tensors of 64^3, rank 32, ten sweeps, 31 launches): 0.735 ms with the inverse in line in every workgroup, fp32 matrix
+// instructions (6 us a launch) and four waves; 0.62 with a workgroup of its own for the inverse, 0.55 with eight waves and 32-bit
+// offsets, 0.49 with bf16 pieces, 0.42 with the requests in the order of their use and none under a condition, and with four pivots
+// per step (7.2 -> 5 us).  A launch is now bound by two chains of about 11 us: partial results, product, Gram matrices (4 us), inverse;
+// and the tensor's way from the last-level cache (33.5 MB, more than the L2 holds).  Rank 64: 1.34 -> 0.78 ms; 16^3, rank 8: 0.35 -> 0.24.
 #include "../../include/exat.h"
 
 #include <hip/hip_runtime.h>
@@ -31,10 +35,17 @@
 namespace {
 
 constexpr int CP_MAX = 64;   // largest L, M, N and R
+constexpr int CP_NS = 8;     // largest number of slabs
+constexpr int CP_NW = 8;     // waves per workgroup
+constexpr int CP_NT = 64 * CP_NW;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef double f64_a4 __attribute__((aligned(4)));    // the workspace starts at a multiple of 4 bytes
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // rows of Y start at multiples of 4 bytes
 
 struct CpStep {
@@ -48,7 +59,17 @@ struct CpStep {
     int prev, mode;         // updated factor of the update before and of this one (0, 1, 2), or -1: none
     int P;
     int32_t *status;        // optional, [replica]: incremented by every update whose normal matrix has a non-positive pivot
+    const f64_a4 *gin;      // [replica][16 NB][16 NB]: inverse of the normal matrix of the update before this one
+    f64_a4 *gout;           // the same of this update
 };
+
+// Barrier for what goes through LDS: requests to memory stay in flight across it
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 // 1/x to within an ulp or two: the hardware's estimate (more than 20 bits) and two Newton steps.  The pivots come from fp32 values, far
 // inside the range of fp64; a zero gives NaN.
@@ -59,239 +80,292 @@ __device__ __forceinline__ double recip(double x)
     return fma(fma(-x, y, 1.0), y, y);
 }
 
-// RC = 32-column tiles of the rank, NB = 16-wide blocks of it (R <= 16 NB, NB <= 2 RC)
+// Inverse of the normal matrix G = (F2^T F2) * (F1^T F1) of the factors Fa and Fb, as g[a][b] = element (ty + 16 a, tx + 16 b) of thread
+// 16 ty + tx, zero beyond R.  All 256 threads call it; `bad` is set if a pivot is not positive.
 template <int RC, int NB>
-__global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
+__device__ __forceinline__ bool invert_normal(const float *Fa, const float *Fb, float (*Gt)[1024], float *G, double (*rowb)[64][4], double (*colb)[64][4],
+                                              int R, int tid, int w, double (&g)[NB][NB])
+{
+    constexpr int RS = 32 * RC, RSP = RS + 1;
+    const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+    // Gram matrices, one 32 x 32 tile of one of them (one tile only: a quarter of its contraction) per job, jobs to the waves in turn
+    constexpr int KH = CP_NW / (2 * RC * RC);
+    {
+        const int t = w / (2 * KH), kh = w % KH;
+        const float *F = ((w / KH) & 1 ? Fb : Fa) + kh * (CP_MAX / KH) * RSP + hi * RSP;
+        const int ri = 32 * (t / RC) + l32, ci = 32 * (t % RC) + l32;
+        f32x16 gt[2];
+#pragma unroll
+        for (int e = 0; e < 16; e++) gt[0][e] = gt[1][e] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < CP_MAX / 2 / KH; s++)
+            gt[s & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(F[2 * s * RSP + ri], F[2 * s * RSP + ci], gt[s & 1], 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; e++) Gt[w][e * 64 + lane] = gt[0][e] + gt[1][e];
+    }
+    lds_barrier();
+    for (int e = tid; e < RC * RC * 1024; e += CP_NT) {
+        const int t = e >> 10, x = e & 1023, r = x >> 6, l = x & 63;
+        float g1 = Gt[2 * KH * t][x], g2 = Gt[2 * KH * t + KH][x];
+#pragma unroll
+        for (int k = 1; k < KH; k++) { g1 += Gt[2 * KH * t + k][x]; g2 += Gt[2 * KH * t + KH + k][x]; }
+        G[(32 * (t / RC) + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * RSP + 32 * (t % RC) + (l & 31)] = g1 * g2;
+    }
+    lds_barrier();
+    // Gi <- G^{-1}, in fp64: thread (ty, tx) owns the entries (ty + 16 a, tx + 16 b), extended by the identity beyond R.  A step
+    // eliminates four rows and columns, in the order and with the pivots of four single steps.  Four waves do it, the others keep step.
+    const bool act = w < 4;
+    const int ty = (tid >> 4) & 15, tx = tid & 15;
+#pragma unroll
+    for (int a = 0; a < NB; a++)
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const int i = ty + 16 * a, c = tx + 16 * b;
+            g[a][b] = (i == c && i >= R) ? 1.0 : (double)G[i * RSP + c];
+        }
+    bool bad = false;   // the same in every thread: all see the same pivots
+    double er[4], ec[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        er[k] = (ty & 3) == k ? -1.0 : 0.0;
+        ec[k] = (tx & 3) == k ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int jb = 0; jb < NB; jb++)
+        for (int jt = 0; jt < 16; jt += 4) {
+            const int j = 16 * jb + jt, par = (jt >> 2) & 1;
+            if (j >= R) break;
+            const bool rin = (ty & 12) == jt, cin = (tx & 12) == jt;
+            if (act && cin) {
+#pragma unroll
+                for (int a = 0; a < NB; a++) colb[par][ty + 16 * a][tx & 3] = g[a][jb];
+            }
+            if (act && rin) {
+#pragma unroll
+                for (int b = 0; b < NB; b++) rowb[par][tx + 16 * b][ty & 3] = g[jb][b];
+            }
+            lds_barrier();
+            if (!act) continue;
+            // the pivot block is symmetric up to rounding: its upper triangle
+            const double a00 = rowb[par][j][0], a01 = rowb[par][j + 1][0], a11 = rowb[par][j + 1][1], b00 = rowb[par][j + 2][0],
+                         b01 = rowb[par][j + 3][0], b10 = rowb[par][j + 2][1], b11 = rowb[par][j + 3][1], d00 = rowb[par][j + 2][2],
+                         d01 = rowb[par][j + 3][2], d11 = rowb[par][j + 3][3];
+            double f[NB][4], q[NB][4];
+#pragma unroll
+            for (int a = 0; a < NB; a++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    f[a][k] = colb[par][ty + 16 * a][k];
+                    q[a][k] = rowb[par][tx + 16 * a][k];
+                }
+            // its inverse, by every thread for itself, in 2 x 2 blocks: [A B; B^T D], T = A^-1 B, S = D - B^T T, U = T S^-1,
+            // [A^-1 + U T^T, -U; -U^T, S^-1].  The squared Cholesky pivots are a00, det A / a00, s00 and det S / s00.
+            const double da = fma(a00, a11, -a01 * a01), ia = recip(da), x00 = a11 * ia, x01 = -a01 * ia, x11 = a00 * ia;
+            const double t00 = fma(x00, b00, x01 * b10), t01 = fma(x00, b01, x01 * b11), t10 = fma(x01, b00, x11 * b10), t11 = fma(x01, b01, x11 * b11);
+            const double s00 = fma(-b00, t00, fma(-b10, t10, d00)), s01 = fma(-b00, t01, fma(-b10, t11, d01)), s11 = fma(-b01, t01, fma(-b11, t11, d11));
+            const double ds = fma(s00, s11, -s01 * s01), is = recip(ds), y00 = s11 * is, y01 = -s01 * is, y11 = s00 * is;
+            const double u00 = fma(t00, y00, t01 * y01), u01 = fma(t00, y01, t01 * y11), u10 = fma(t10, y00, t11 * y01), u11 = fma(t10, y01, t11 * y11);
+            const double z00 = fma(u00, t00, fma(u01, t01, x00)), z01 = fma(u00, t10, fma(u01, t11, x01)), z11 = fma(u10, t10, fma(u11, t11, x11));
+            const double pv[4][4] = {{z00, z01, -u00, -u01}, {z01, z11, -u10, -u11}, {-u00, -u10, y00, y01}, {-u01, -u11, y01, y11}};
+            // zero, negative or NaN: not positive definite
+            bad = bad || !(a00 > 0.0) || (j + 1 < R && !(da > 0.0)) || (j + 2 < R && !(s00 > 0.0)) || (j + 3 < R && !(ds > 0.0));
+            // rows outside the block: g - F P^-1 Q, in its columns -F P^-1; its rows: P^-1 Q and P^-1.  With minus the identity for F in its
+            // rows, the identity for Q in its columns and zero for g in both this is one formula.
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                f[jb][k] = rin ? er[k] : f[jb][k];
+                q[jb][k] = cin ? ec[k] : q[jb][k];
+            }
+#pragma unroll
+            for (int a = 0; a < NB; a++) {
+                double wv[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    wv[k] = fma(f[a][3], pv[3][k], fma(f[a][2], pv[2][k], fma(f[a][1], pv[1][k], f[a][0] * pv[0][k])));
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    double base = g[a][b];
+                    if (a == jb) base = rin ? 0.0 : base;
+                    if (b == jb) base = cin ? 0.0 : base;
+                    g[a][b] = fma(-wv[3], q[b][3], fma(-wv[2], q[b][2], fma(-wv[1], q[b][1], fma(-wv[0], q[b][0], base))));
+                }
+            }
+        }
+#pragma unroll
+    for (int a = 0; a < NB; a++)
+#pragma unroll
+        for (int b = 0; b < NB; b++)
+            if (ty + 16 * a >= R || tx + 16 * b >= R) g[a][b] = 0.0;
+    return bad;
+}
+
+// Element i of an array whose start is the same in all lanes: one 32-bit offset per lane, no 64-bit address arithmetic on the vector unit
+__device__ __forceinline__ float at(const float *base, int i) { return *(const float *)((const char *)base + 4u * (unsigned)i); }
+
+// eight fp32 values as three bf16 pieces each, x = h + m + l (exact: three times eight significand bits), in operand order
+__device__ __forceinline__ void split8(const float *x, u32x4 (&w)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            typedef float f2 __attribute__((ext_vector_type(2)));
+            w[q][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf16x2));   // one packed conversion
+            if (q < 2) {   // the residual of a rounding to bf16 is exact in fp32
+                a -= __builtin_bit_cast(float, w[q][i] << 16);
+                b -= __builtin_bit_cast(float, w[q][i] & 0xffff0000u);
+            }
+        }
+    }
+}
+__device__ __forceinline__ f32x16 mma(const u32x4 &a, const u32x4 &b, const f32x16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// RC = 32-column tiles of the rank, NB = 16-wide blocks of it (R <= 16 NB, NB <= 2 RC)
+// U: the factor that is updated (in the launch behind the last update: 0).
+template <int RC, int NB, bool OWN, int U>
+__global__ __launch_bounds__(CP_NT) void k_cpals_step(const CpStep p)
 {
     constexpr int RS = 32 * RC, RSP = RS + 1;
     __shared__ float Fs[3][CP_MAX * RSP];     // factors as [d][r], zero beyond D and R
-    __shared__ float Mx[CP_MAX * RSP];        // MTTKRP result of the update before; scratch of the partial tiles
+    __shared__ float Mx[CP_MAX * RSP];        // MTTKRP result of the update before
     __shared__ float G[RS * RSP];             // normal matrix
-    constexpr int NGT = RC == 1 ? 4 : 8;
-    __shared__ __align__(16) float Gt[NGT][1024];   // tiles of the Gram matrices, then the inverse of the normal matrix
+    __shared__ __align__(16) float Gt[CP_NW][1024];   // tiles of the Gram matrices, the inverse of the normal matrix, partial tiles
     double *Gi = (double *)&Gt[0][0];         // [r][c ^ 16 (r & 1)]: neighbouring rows 32 banks apart
-    static_assert(RS * RS * 8 <= NGT * 4096, "");
-    __shared__ double rowb[2][2][64], colb[2][2][64];
+    static_assert(RS * RS * 8 <= CP_NW * 4096, "");
+    __shared__ __align__(16) double rowb[2][64][4], colb[2][64][4];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t rep = blockIdx.x;
-    const int slab = blockIdx.y, R = p.R;
+    // unless every workgroup inverts for itself (OWN), the first one of a replica does nothing else
+    const bool inv = !OWN && p.mode >= 0 && blockIdx.y == 0;
+    const int slab = !OWN && p.mode >= 0 ? (int)blockIdx.y - 1 : (int)blockIdx.y, R = p.R;
+    constexpr int RB = 16 * NB;
+    auto put_gi = [&](int i, int c, double x) { Gi[i * RS + (c ^ (16 * (i & 1)))] = x; };
 
     // ---- this workgroup's share of the MTTKRP.  Mode 0: rows l, inner m, outer n; mode 1: rows m, inner l, outer n; mode 2:
     //      rows n, inner l, outer m.  Tile (rt, ct) of the result to wave w mod ntile; the waves of a tile take the values of
     //      the outer index in turn ----
-    const int u = p.mode >= 0 ? p.mode : 0, Du = p.D[u], i1 = u == 0 ? 1 : 0, i2 = u == 2 ? 1 : 2, D1 = p.D[i1], D2 = p.D[i2];
-    const int rtn = (Du + 31) / 32, ntile = rtn * RC, kgn = 4 / ntile, kg = w / ntile, tile = w % ntile;
+    constexpr int i1 = U == 0 ? 1 : 0, i2 = U == 2 ? 1 : 2;
+    const int Du = p.D[U], D1 = p.D[i1], D2 = p.D[i2];
+    const int rtn = (Du + 31) / 32, ntile = rtn * RC, kgn = CP_NW / ntile, kg = w / ntile, tile = w % ntile;
     const int row = 32 * (tile / RC) + l32, c = 32 * (tile % RC) + l32;
-    // element (row, d1, d2) of the tensor: a wave-uniform pointer to (0, d1, d2) and the lane's 32-bit offset (a replica has at most
-    // 2^18 elements)
-    const int LM = p.D[0] * p.D[1], su = u == 0 ? 1 : (u == 1 ? p.D[0] : LM), s2 = u == 2 ? p.D[0] : LM;
-    const float *yu = p.Y + rep * LM * p.D[2];
-    const unsigned ro = (unsigned)((row < Du ? row : Du - 1) * su);
+    // element (row, d1, d2) of the tensor: the replica's buffer (2^18 elements at most), a lane's part of the offset, a wave-uniform part.
+    // Every request is made, with the offset NONE where there is nothing to read (it reads nothing then): a request under a condition
+    // makes the compiler wait for all that are outstanding.
+    constexpr int NONE = 1 << 24;
+    const int L4 = 4 * p.D[0], LM = p.D[0] * p.D[1], su = U == 0 ? 1 : (U == 1 ? p.D[0] : LM), s2 = U == 2 ? L4 : 4 * LM;
+    const auto yb = __builtin_amdgcn_make_buffer_rsrc((void *)(p.Y + rep * LM * p.D[2]), 0, p.mode >= 0 && !inv ? 4 * LM * p.D[2] : 0, 0x00020000);
+    const int ro = 4 * (row < Du ? row : Du - 1) * su, roh = ro + (U == 0 ? L4 : 16) * hi;
     constexpr int NSTEP = CP_MAX / 2;
-    const int nq = (D1 + 7) / 8;           // groups of 8 inner indices
+    const int nj = (D1 + 15) / 16;         // groups of 16 inner indices
     const int d2a = slab * p.DS, d2b = d2a + p.DS < D2 ? d2a + p.DS : D2;
+    auto ld = [&](int vo, int so) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(yb, vo, so, 0)); };
     auto load = [&](int d2, f32x4 (&a)[NSTEP / 4]) __attribute__((always_inline)) {
-        const float *y = yu + d2 * s2;
+        const int so = d2 < d2b ? d2 * s2 : NONE;
 #pragma unroll
         for (int q = 0; q < NSTEP / 4; q++) {
-            if (q < nq) {
-                if (u == 0) {
+            if constexpr (U == 0) {
 #pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const int d = 8 * q + 2 * e;   // lane half hi: d + hi; beyond D1 the factor is zero and any element will do
-                        if (d + 1 < D1) a[q][e] = (y + d * p.D[0])[ro + (unsigned)(hi * p.D[0])];
-                        else a[q][e] = (y + (D1 - 1) * p.D[0])[ro];
-                    }
-                } else if (8 * q + 8 <= D1)
-                    a[q] = *(const f32x4_a4 *)((y + 8 * q) + (ro + 4u * hi));
-                else {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const int d = 8 * q + 4 * hi + e;
-                        a[q][e] = y[ro + (unsigned)(d < D1 ? d : D1 - 1)];
-                    }
+                for (int e = 0; e < 4; e++) {
+                    const int d = 8 * q + 2 * e;   // lane half hi: d + hi; beyond D1 the factor is zero
+                    a[q][e] = ld(d + 1 < D1 ? roh : ro, d < D1 ? so + d * L4 : NONE);
                 }
-            }
+            } else   // four values of l at 8 q + 4 hi: beyond D1 there are the row's neighbours, which `mac` takes out
+                a[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(yb, roh, 8 * q < D1 ? so + 32 * q : NONE, 0));
         }
     };
-    // the wave's first PF values of the outer index are requested ahead of everything else: most of its share comes in while the
-    // update before is finished
-    constexpr int PF = 4;
+    constexpr int PF = 2;
     f32x4 ya[PF][NSTEP / 4];
-    if (p.mode >= 0) {
+    // Requests in the order of their use: the factors that are fixed in the update before this one (without one: in this update), that
+    // update's inverse and the slabs' partial results, then the wave's first PF values of the outer index, most of whose way is gone
+    // when the update before is finished.  All of them are made at clamped addresses and masked afterwards.
+    const int v = U == 0 && p.prev < 0 ? 0 : (U + 2) % 3;
+    const int f1 = v == 0 ? 1 : 0, f2 = v == 2 ? 1 : 2, D0 = p.D[v], st = D0 * R;
+    constexpr int FE = CP_MAX * RS / CP_NT, GE = RB * RB < CP_NT ? 1 : RB * RB / CP_NT;
+    const float *psrc = p.pin + rep * p.rs;
+    auto poff = [&](int x) {
+        const int e = tid + CP_NT * x, d = e / RS, r = e % RS;
+        return (d < D0 ? d : D0 - 1) * R + (r < R ? r : R - 1);
+    };
+    float tf[2][FE], tp[FE][CP_NS];
+    double gl[GE];
 #pragma unroll
-        for (int i = 0; i < PF; i++)
-            if (d2a + kg + i * kgn < d2b) load(d2a + kg + i * kgn, ya[i]);
-    }
-
-    // The factors that are fixed in the update before this one (without one: in this update).  All loads below are made at clamped
-    // addresses and masked afterwards, so that they are in flight together.
-    const int v = p.prev >= 0 ? p.prev : p.mode;
-    const int f1 = v == 0 ? 1 : 0, f2 = v == 2 ? 1 : 2;
-    constexpr int FE = CP_MAX * RS / 256;
-    {
-        float t[2][FE];
+    for (int q = 0; q < 2; q++) {
+        const int f = q ? f2 : f1, D = p.D[f];
+        const float *src = p.F[f] + rep * D * R;
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
-            const int f = q ? f2 : f1, D = p.D[f];
-            const float *src = p.F[f] + rep * D * R;
-#pragma unroll
-            for (int x = 0; x < FE; x++) {
-                const int e = tid + 256 * x, d = e % CP_MAX, r = e / CP_MAX;
-                t[q][x] = src[(d < D ? d : D - 1) + D * (r < R ? r : R - 1)];
-            }
+        for (int x = 0; x < FE; x++) {
+            const int e = tid + CP_NT * x, d = e % CP_MAX, r = e / CP_MAX;
+            tf[q][x] = at(src, (d < D ? d : D - 1) + D * (r < R ? r : R - 1));
         }
+    }
+    if constexpr (!OWN) {
+        const f64_a4 *src = p.gin + rep * (RB * RB);
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
-            const int f = q ? f2 : f1, D = p.D[f];
+        for (int x = 0; x < GE; x++) gl[x] = src[(tid + CP_NT * x) % (RB * RB)];
+    }
 #pragma unroll
-            for (int x = 0; x < FE; x++) {
-                const int e = tid + 256 * x, d = e % CP_MAX, r = e / CP_MAX;
-                Fs[f][d * RSP + r] = (d < D && r < R) ? t[q][x] : 0.0f;
-            }
+    for (int x = 0; x < FE; x++)
+#pragma unroll
+        for (int sl = 0; sl < CP_NS; sl++) tp[x][sl] = at(psrc + (sl < p.NSin ? sl : p.NSin - 1) * st, poff(x));
+#pragma unroll
+    for (int i = 0; i < PF; i++) load(d2a + kg + i * kgn, ya[i]);
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int f = q ? f2 : f1, D = p.D[f];
+#pragma unroll
+        for (int x = 0; x < FE; x++) {
+            const int e = tid + CP_NT * x, d = e % CP_MAX, r = e / CP_MAX;
+            Fs[f][d * RSP + r] = (d < D && r < R) ? tf[q][x] : 0.0f;
         }
     }
 
     if (p.prev >= 0) {
-        const int D0 = p.D[v];
         // MTTKRP result: the slabs' partial results in slab order
-        const float *src = p.pin + rep * p.rs;
-        const int st = D0 * R;
-        constexpr int XB = FE < 4 ? FE : 4;
 #pragma unroll
-        for (int x0 = 0; x0 < FE; x0 += XB) {
-            const float *q[XB];
-            float x[XB];
+        for (int x = 0; x < FE; x++) {
+            float sum = 0.0f;
 #pragma unroll
-            for (int i = 0; i < XB; i++) {
-                const int e = tid + 256 * (x0 + i), d = e / RS, r = e % RS;
-                q[i] = src + (d < D0 ? d : D0 - 1) * R + (r < R ? r : R - 1);
-                x[i] = 0.0f;
-            }
-            int sl = 0;
-            for (; sl + 8 <= p.NSin; sl += 8) {
-                float t[XB][8];
-#pragma unroll
-                for (int i = 0; i < XB; i++)
-#pragma unroll
-                    for (int u = 0; u < 8; u++) t[i][u] = q[i][(sl + u) * st];
-#pragma unroll
-                for (int i = 0; i < XB; i++)
-#pragma unroll
-                    for (int u = 0; u < 8; u++) x[i] += t[i][u];
-            }
-            for (; sl < p.NSin; sl++)
-#pragma unroll
-                for (int i = 0; i < XB; i++) x[i] += q[i][sl * st];
-#pragma unroll
-            for (int i = 0; i < XB; i++) {
-                const int e = tid + 256 * (x0 + i), d = e / RS, r = e % RS;
-                Mx[d * RSP + r] = (d < D0 && r < R) ? x[i] : 0.0f;
-            }
+            for (int sl = 0; sl < CP_NS; sl++) sum += sl < p.NSin ? tp[x][sl] : 0.0f;
+            const int e = tid + CP_NT * x, d = e / RS, r = e % RS;
+            Mx[d * RSP + r] = (d < D0 && r < R) ? sum : 0.0f;
         }
-        __syncthreads();
-        // Gram matrices, one 32 x 32 tile of one of them (one tile only: half of its contraction) per job, jobs to the waves in turn
-        constexpr int KH = RC == 1 ? 2 : 1, NJ = RC * RC * 2 * KH;
+        if constexpr (OWN) {
+            lds_barrier();
+            double gi[NB][NB];
+            const bool bad = invert_normal<RC, NB>(Fs[f1], Fs[f2], Gt, G, rowb, colb, R, tid, w, gi);
+            if (bad && tid == 0 && slab == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
+            lds_barrier();
 #pragma unroll
-        for (int j = w; j < NJ; j += 4) {
-            const int t = j / (2 * KH), m = (j / KH) & 1, kh = j % KH;
-            const float *F = Fs[m ? f2 : f1];
-            const int ri = 32 * (t / RC) + l32, ci = 32 * (t % RC) + l32;
-            f32x16 g[2];
+            for (int a = 0; a < NB; a++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) g[0][e] = g[1][e] = 0.0f;
+                for (int b = 0; b < NB; b++)
+                    if (tid < 256) put_gi((tid >> 4) + 16 * a, (tid & 15) + 16 * b, gi[a][b]);
+        } else {
 #pragma unroll
-            for (int s = 0; s < CP_MAX / 2 / KH; s++) {
-                const int d = (2 * (s + kh * (CP_MAX / 2 / KH)) + hi) * RSP;
-                g[s & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(F[d + ri], F[d + ci], g[s & 1], 0, 0, 0);
-            }
-#pragma unroll
-            for (int e = 0; e < 16; e++) Gt[j][e * 64 + lane] = g[0][e] + g[1][e];
+            for (int x = 0; x < GE; x++)
+                if (tid < RB * RB) put_gi((tid + CP_NT * x) / RB, (tid + CP_NT * x) % RB, gl[x]);
         }
-        __syncthreads();
-        for (int e = tid; e < RC * RC * 1024; e += 256) {
-            const int t = e >> 10, x = e & 1023, r = x >> 6, l = x & 63;
-            float g1 = Gt[2 * KH * t][x], g2 = Gt[2 * KH * t + KH][x];
-            if (KH == 2) { g1 += Gt[2 * KH * t + 1][x]; g2 += Gt[2 * KH * t + KH + 1][x]; }
-            G[(32 * (t / RC) + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * RSP + 32 * (t % RC) + (l & 31)] = g1 * g2;
-        }
-        __syncthreads();
-        // Gi <- G^{-1}, in fp64: thread (ty, tx) owns the entries (ty + 16 a, tx + 16 b), extended by the identity beyond R.  A step
-        // eliminates two rows and columns, in the order and with the pivots of two single steps.
-        const int ty = tid >> 4, tx = tid & 15;
-        double g[NB][NB];
-#pragma unroll
-        for (int a = 0; a < NB; a++)
-#pragma unroll
-            for (int b = 0; b < NB; b++) {
-                const int i = ty + 16 * a, c = tx + 16 * b;
-                g[a][b] = (i == c && i >= R) ? 1.0 : (double)G[i * RSP + c];
-            }
-        bool bad = false;   // the same in every thread: all see the same pivots
-#pragma unroll
-        for (int jb = 0; jb < NB; jb++)
-            for (int jt = 0; jt < 16; jt += 2) {
-                const int j = 16 * jb + jt, par = (jt >> 1) & 1;
-                if (j >= R) break;
-                if ((tx & 14) == jt) {
-#pragma unroll
-                    for (int a = 0; a < NB; a++) colb[par][tx & 1][ty + 16 * a] = g[a][jb];
-                }
-                if ((ty & 14) == jt) {
-#pragma unroll
-                    for (int b = 0; b < NB; b++) rowb[par][ty & 1][tx + 16 * b] = g[jb][b];
-                }
-                __syncthreads();
-                const double p00 = colb[par][0][j], p10 = colb[par][0][j + 1], p01 = colb[par][1][j], p11 = colb[par][1][j + 1];
-                const double inv0 = recip(p00), ur = p01 * inv0, lr = p10 * inv0, s = fma(-lr, p01, p11), inv1 = recip(s);
-                bad = bad || !(p00 > 0.0) || (j + 1 < R && !(s > 0.0));   // zero, negative or NaN: not positive definite
-                double w0[NB], w1[NB], q0[NB], q1[NB];
-#pragma unroll
-                for (int a = 0; a < NB; a++) {
-                    const double f0 = colb[par][0][ty + 16 * a], f1v = colb[par][1][ty + 16 * a];
-                    w1[a] = fma(-f0, ur, f1v) * inv1;
-                    w0[a] = fma(-w1[a], p10, f0) * inv0;
-                    q0[a] = rowb[par][0][tx + 16 * a]; q1[a] = rowb[par][1][tx + 16 * a];
-                }
-#pragma unroll
-                for (int a = 0; a < NB; a++)
-#pragma unroll
-                    for (int b = 0; b < NB; b++) {
-                        double up = fma(-w1[a], q1[b], fma(-w0[a], q0[b], g[a][b]));
-                        if (b == jb) up = (tx & 14) == jt ? ((tx & 1) ? -w1[a] : -w0[a]) : up;
-                        if (a == jb) {
-                            const double r1 = fma(-lr, q0[b], q1[b]) * inv1, r0 = fma(-p01, r1, q0[b]) * inv0;
-                            double rr = (ty & 1) ? r1 : r0;
-                            if (b == jb) {   // the inverse of the 2 x 2 pivot block
-                                const double i01 = -ur * inv1;
-                                const double dd = (tx & 1) ? ((ty & 1) ? inv1 : i01) : ((ty & 1) ? -lr * inv1 : fma(-i01, lr, inv0));
-                                rr = (tx & 14) == jt ? dd : rr;
-                            }
-                            up = (ty & 14) == jt ? rr : up;
-                        }
-                        g[a][b] = up;
-                    }
-            }
-        __syncthreads();
-#pragma unroll
-        for (int a = 0; a < NB; a++)
-#pragma unroll
-            for (int b = 0; b < NB; b++) {
-                const int i = ty + 16 * a, c = tx + 16 * b;
-                Gi[i * RS + (c ^ (16 * (i & 1)))] = (i < R && c < R) ? g[a][b] : 0.0;
-            }
-        if (bad && tid == 0 && slab == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
-        __syncthreads();
+        lds_barrier();
         // X = Mx G^{-1}, accumulated in fp64: 16 x 16 tile (rt, ct) to wave (rt NB + ct) mod 4
         const int rtn = (D0 + 15) / 16, l16 = lane & 15, q16 = lane >> 4;
-        for (int t = w; t < rtn * NB; t += 4) {
+        for (int t = w; t < rtn * NB; t += CP_NW) {
             const int row = 16 * (t / NB) + l16, c = 16 * (t % NB) + l16;
-            f64x4 x = {0.0, 0.0, 0.0, 0.0};
+            float mx[4 * NB];
+            double gx[4 * NB];
+#pragma unroll
             for (int s = 0; s < 4 * NB; s++) {
                 const int k = 4 * s + q16;
-                x = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Mx[row * RSP + k], Gi[k * RS + (c ^ (16 * (k & 1)))], x, 0, 0, 0);
+                mx[s] = Mx[row * RSP + k];
+                gx[s] = Gi[k * RS + (c ^ (16 * (k & 1)))];
             }
+            f64x4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4 * NB; s++) x = __builtin_amdgcn_mfma_f64_16x16x4f64((double)mx[s], gx[s], x, 0, 0, 0);
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 const int d = 16 * (t / NB) + 4 * e + q16;
@@ -301,61 +375,90 @@ __global__ __launch_bounds__(256) void k_cpals_step(const CpStep p)
             }
         }
         // the unused row tiles, and the columns beyond the blocks of the rank
-        for (int e = tid + 16 * rtn * RS; e < CP_MAX * RS; e += 256) Fs[v][(e / RS) * RSP + e % RS] = 0.0f;
+        for (int e = tid + 16 * rtn * RS; e < CP_MAX * RS; e += CP_NT) Fs[v][(e / RS) * RSP + e % RS] = 0.0f;
         if (16 * NB < RS)
-            for (int e = tid; e < 16 * rtn * (RS - 16 * NB); e += 256) Fs[v][(e / (RS - 16 * NB)) * RSP + 16 * NB + e % (RS - 16 * NB)] = 0.0f;
+            for (int e = tid; e < 16 * rtn * (RS - 16 * NB); e += CP_NT) Fs[v][(e / (RS - 16 * NB)) * RSP + 16 * NB + e % (RS - 16 * NB)] = 0.0f;
     }
     if (p.mode < 0) return;
-    __syncthreads();
+    lds_barrier();
+    if (!OWN && inv) {
+        double gi[NB][NB];
+        const bool bad = invert_normal<RC, NB>(Fs[i1], Fs[i2], Gt, G, rowb, colb, R, tid, w, gi);
+        if (bad && tid == 0 && p.status) p.status[rep] += 1;   // launches on one stream: nothing else touches this word now
+        f64_a4 *dst = p.gout + rep * (RB * RB);
+#pragma unroll
+        for (int a = 0; a < NB; a++)
+#pragma unroll
+            for (int b = 0; b < NB; b++)
+                if (tid < 256) dst[((tid >> 4) + 16 * a) * RB + (tid & 15) + 16 * b] = gi[a][b];
+        return;
+    }
 
     // inner index of step s, lane half hi: mode 0: 2s + hi; else 8 (s/4) + 4 hi + s%4 (a lane's 16 bytes)
     float b1[NSTEP];
+    const float *b1s = Fs[i1] + c + (U == 0 ? hi : 4 * hi) * RSP;
+    if constexpr (U == 0) {
 #pragma unroll
-    for (int s = 0; s < NSTEP; s++) {
-        const int d = u == 0 ? 2 * s + hi : 8 * (s >> 2) + 4 * hi + (s & 3);
-        b1[s] = Fs[i1][d * RSP + c];
+        for (int s = 0; s < NSTEP; s++) b1[s] = b1s[2 * s * RSP];
+    } else {
+#pragma unroll
+        for (int s = 0; s < NSTEP; s++) b1[s] = b1s[(8 * (s >> 2) + (s & 3)) * RSP];
     }
-    f32x16 acc[2];
+    u32x4 bp[CP_MAX / 16][3];
 #pragma unroll
-    for (int e = 0; e < 16; e++) acc[0][e] = acc[1][e] = 0.0f;
+    for (int j = 0; j < CP_MAX / 16; j++) split8(&b1[8 * j], bp[j]);
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.0f;
+    // one value of the outer index: the product over the inner one, smallest terms first, then its factor
     auto mac = [&](int d2, const f32x4 (&a)[NSTEP / 4]) __attribute__((always_inline)) {
         const float f2 = Fs[i2][d2 * RSP + c];
+        f32x16 t;
 #pragma unroll
-        for (int q = 0; q < NSTEP / 4; q++) {
-            if (q < nq) {
+        for (int e = 0; e < 16; e++) t[e] = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 4; e++) acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][e], b1[4 * q + e] * f2, acc[e & 1], 0, 0, 0);
+        for (int j = 0; j < CP_MAX / 16; j++) {
+            if (j < nj) {
+                u32x4 ap[3];
+                float av[8] = {a[2 * j][0], a[2 * j][1], a[2 * j][2], a[2 * j][3], a[2 * j + 1][0], a[2 * j + 1][1], a[2 * j + 1][2], a[2 * j + 1][3]};
+                if (U != 0 && 16 * j + 16 > D1) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) av[e] = 16 * j + 8 * (e >> 2) + 4 * hi + (e & 3) < D1 ? av[e] : 0.0f;
+                }
+                split8(av, ap);
+                t = mma(ap[2], bp[j][0], t);
+                t = mma(ap[0], bp[j][2], t);
+                t = mma(ap[1], bp[j][1], t);
+                t = mma(ap[1], bp[j][0], t);
+                t = mma(ap[0], bp[j][1], t);
+                t = mma(ap[0], bp[j][0], t);
             }
         }
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[e] += f2 * t[e];
     };
     for (int d2 = d2a + kg; d2 < d2b; d2 += PF * kgn) {
 #pragma unroll
         for (int i = 0; i < PF; i++) {
             if (d2 + i * kgn < d2b) mac(d2 + i * kgn, ya[i]);
-            if (d2 + (i + PF) * kgn < d2b) load(d2 + (i + PF) * kgn, ya[i]);
+            load(d2 + (i + PF) * kgn, ya[i]);
         }
     }
+    // the waves of a tile add up in wave order; the inverse is not needed any more
+    if (kg > 0) {
 #pragma unroll
-    for (int e = 0; e < 16; e++) acc[0][e] += acc[1][e];
-    // the waves of a tile add up in wave order
-    for (int k = 1; k < kgn; k++) {
-        __syncthreads();
-        if (kg == k) {
-#pragma unroll
-            for (int e = 0; e < 16; e++) Mx[(tile * 16 + e) * 64 + lane] = acc[0][e];
-        }
-        __syncthreads();
-        if (kg == 0) {
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[0][e] += Mx[(tile * 16 + e) * 64 + lane];
-        }
+        for (int e = 0; e < 16; e++) Gt[(kg - 1) * ntile + tile][e * 64 + lane] = acc[e];
     }
+    lds_barrier();
     if (kg == 0) {
+        for (int k = 0; k < kgn - 1; k++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[e] += Gt[k * ntile + tile][e * 64 + lane];
         float *dst = p.pout + rep * p.rs + (int64_t)slab * Du * R;
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int d = 32 * (tile / RC) + 8 * (e >> 2) + 4 * hi + (e & 3);
-            if (d < Du && c < R) dst[d * R + c] = acc[0][e];
+            if (d < Du && c < R) dst[d * R + c] = acc[e];
         }
     }
 }
@@ -404,23 +507,36 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
         if (hipGetLastError() != hipSuccess) return EXAT_ERR_HIP;
     }
     if (sweeps == 0) return EXAT_OK;
-    // Slabs per replica: about one workgroup per compute unit, and no more than 16, since every workgroup adds up all slabs.  The
-    // partial results are double-buffered (a workgroup that is ahead writes while others still read) unless a replica has
-    // one workgroup only: that one has read all of its replica's partial results before it writes there.
+    // Slabs per replica: one workgroup per compute unit with the one that inverts (two do not fit), and no more than CP_NS: the partial
+    // results of all slabs are requested at once, and beyond eight the inverse takes longer than a slab (8 tensors of 64^3, rank 32:
+    // 0.375 ms with 16 and with 8; 16 of 32^3, rank 16: 0.278, 0.261).  The partial results and the
+    // inverses are double-buffered: a workgroup that is ahead writes while others still read.
+    // Every workgroup inverts for itself where a replica has a single one (more than 128 replicas; one workgroup that does both keeps
+    // the compute unit as busy as two and finishes the update before once: 1000 tensors of 16^3, rank 16: 1.69 -> 1.26 ms, 130 of 64^3, rank
+    // 32: 1.37 -> 1.27; at rank 64 the other way round, 300 of 64^3: 5.08, 5.56), which then has read its partial results before it writes
+    // there; and for tiny tensors of high rank, where the workspace has no room for the inverses.
     const int maxd = L > M ? (L > N ? L : N) : (M > N ? M : N);
-    int NS = 256 / P;
-    NS = NS > 16 ? 16 : (NS < 1 ? 1 : NS);
+    int NS = 256 / P - 1;
+    NS = NS > CP_NS ? CP_NS : (NS < 1 ? 1 : NS);
     const int64_t room = (int64_t)slabs_for(maxd, P) * CP_MAX * CP_MAX, one = (int64_t)maxd * R;
     while (NS > 1 && 2 * NS * one > room) NS--;
-    float *part[2] = {work, NS > 1 ? work + (int64_t)P * NS * one : work};
+    const int64_t RB = R <= 16 ? 16 : (R <= 32 ? 32 : 64);
+    const bool own = (P > 128 && R <= 32) || 2 * NS * one + 4 * RB * RB > 2 * (int64_t)L * M * N + room;
+    float *part[2] = {work, own && NS == 1 ? work : work + (int64_t)P * NS * one};
+    f64_a4 *ginv[2] = {(f64_a4 *)(work + 2 * P * NS * one), (f64_a4 *)(work + 2 * P * NS * one) + P * RB * RB};
     CpStep c;
     c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.P = P; c.rs = NS * one; c.status = status;
     c.NSin = 1; c.prev = -1;
-    auto launch = [&](int ns) {
-        const dim3 grid((unsigned)P, (unsigned)ns);
-        if (R <= 16) hipLaunchKernelGGL((k_cpals_step<1, 1>), grid, dim3(256), 0, st, c);
-        else if (R <= 32) hipLaunchKernelGGL((k_cpals_step<1, 2>), grid, dim3(256), 0, st, c);
-        else hipLaunchKernelGGL((k_cpals_step<2, 4>), grid, dim3(256), 0, st, c);
+    auto launch = [&](int ns, bool inverse) {
+        const dim3 grid((unsigned)P, (unsigned)(ns + (inverse && !own ? 1 : 0)));
+        const int u = c.mode < 0 ? 0 : c.mode;
+        auto go = [&](auto k0, auto k1, auto k2) { hipLaunchKernelGGL(u == 0 ? k0 : u == 1 ? k1 : k2, grid, dim3(CP_NT), 0, st, c); };
+        if (own && R <= 16) go(k_cpals_step<1, 1, true, 0>, k_cpals_step<1, 1, true, 1>, k_cpals_step<1, 1, true, 2>);
+        else if (own && R <= 32) go(k_cpals_step<1, 2, true, 0>, k_cpals_step<1, 2, true, 1>, k_cpals_step<1, 2, true, 2>);
+        else if (own) go(k_cpals_step<2, 4, true, 0>, k_cpals_step<2, 4, true, 1>, k_cpals_step<2, 4, true, 2>);
+        else if (R <= 16) go(k_cpals_step<1, 1, false, 0>, k_cpals_step<1, 1, false, 1>, k_cpals_step<1, 1, false, 2>);
+        else if (R <= 32) go(k_cpals_step<1, 2, false, 0>, k_cpals_step<1, 2, false, 1>, k_cpals_step<1, 2, false, 2>);
+        else go(k_cpals_step<2, 4, false, 0>, k_cpals_step<2, 4, false, 1>, k_cpals_step<2, 4, false, 2>);
     };
     // A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^-1, then B <- Y_(2) (C kr A) [..]^-1, then C <- Y_(3) (B kr A) [..]^-1: the launch of an
     // update finishes the one before it
@@ -431,11 +547,13 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
         c.DS = (D2 + ns - 1) / ns;
         c.NS = (D2 + c.DS - 1) / c.DS;
         c.pin = part[(t + 1) & 1]; c.pout = part[t & 1];
-        launch(c.NS);
+        c.gin = ginv[(t + 1) & 1]; c.gout = ginv[t & 1];
+        launch(c.NS, true);
         c.NSin = c.NS; c.prev = c.mode;
     }
     c.pin = part[(3 * sweeps + 1) & 1]; c.pout = nullptr; c.mode = -1; c.NS = 1;
-    launch(1);
+    c.gin = ginv[(3 * sweeps + 1) & 1]; c.gout = nullptr;
+    launch(1, false);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
