@@ -259,8 +259,17 @@ template <int N, int I_, typename F> __device__ __forceinline__ void s1_static_f
 }
 template <int N, typename F> __device__ __forceinline__ void s1_static_for(F &&f) { s1_static_for_(f, std::integral_constant<int, 0>(), std::integral_constant<int, N>()); }
 
+// Barrier for what goes through LDS: requests to memory stay in flight across it
+__device__ __forceinline__ void s1_lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), D = steps of X a wave keeps in flight, RAGGED: I is no
-// multiple of 32 (what a request reads past the end of a column is set to zero).
+// multiple of 32 (a request past the end of a column goes past the end of the buffer, which reads nothing and gives zero: zeroing
+// what has arrived made every request wait for its data, 1000 x 500 x 800, A1 = 64: 0.68 -> 0.42 ms).
 //
 // Mode 1.  A wave owns 64 columns of the workgroup's 256-column tile and walks down them in steps of 32 rows.  A step's
 // 8 KiB are requested with eight 16-byte-per-lane loads that run ALONG the columns (eight lanes cover the 128 bytes of one
@@ -274,6 +283,11 @@ template <int N, typename F> __device__ __forceinline__ void s1_static_for(F &&f
 // hold Z^T (rows: columns j, columns: rows a).  Nothing in the step loop waits for another wave: no barrier, no branch
 // (steps past the end of a tile are made harmless instead: they multiply a valid step of the same columns with the
 // all-zero U fragment).
+// With more than 64 rows a there is one wave per SIMD and nobody to fill its waits (PIPE): a half-step's matrix instructions then have
+// the splitting of the next half-step between them, a fixed share behind each, while the one after that is read from LDS (one slot per
+// wave; a wave's LDS accesses stay in order).  1024 x 1024 x 1000, A1 = 128: 1.10 -> 0.99 ms, 1000^3, A1 = 100: 1.07 -> 1.04 (4000-byte columns:
+// every request straddles two lines); with X from the caches 0.73 ms, without mode 2 0.95.  Three or four steps in flight are slower (1.07, 1.11),
+// and so are two workgroups of 64 rows side by side (1.36: they drift apart and X is read from memory twice).
 // Mode 2, at the end of a tile, is on the matrix cores as well: the waves put their Z^T tiles into LDS in operand order
 // (registers 8t .. 8t+7 of a transposed accumulator are the 16 columns 16t .. 16t+15 in the order Vd is packed in), and the
 // RT x MT blocks of the slice's B1 x A1 result are dealt out to the four waves (block b = mt RT + rt to wave b mod 4), each
@@ -283,7 +297,8 @@ template <int RT, int MT, int D, bool RAGGED, int WPC = 1>
 __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams p)
 {
     extern __shared__ float smem[];
-    constexpr int DL = 2;                           // LDS slots per wave
+    constexpr bool PIPE = WPC == 1;                 // one wave per SIMD: the steps overlap inside the wave
+    constexpr int DL = PIPE ? 1 : 2;                // LDS slots per wave
     constexpr int UN = D % DL == 0 ? D : D * DL;    // steps per unrolled group: ring slots are compile-time constants
     constexpr int SLOT = 64 * SM_GI;                // floats per slot: 64 columns x 32 rows
     constexpr int NBW = (RT * MT + SM_NW - 1) / SM_NW;   // result blocks per wave
@@ -326,32 +341,30 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
 
     // requests of padded step n = tile * ngp + g: X of the step itself if it exists, else of the last step of the tile
     // (or of the last tile), which is then multiplied with the zero fragment
-    auto request_x = [&](int n, s1_f32x4 (&dst)[8]) {
+    struct XReq { int soff, vo; };
+    auto locate_x = [&](int n) {
         int tile = n / ngp, g = n - tile * ngp;
         tile = tile < ntile ? tile : ntile - 1;
         g = g < ng ? g : ng - 1;
-        const int soff = (int)((((int64_t)tile * SM_TJ + 64 * w) * p.I + (int64_t)SM_GI * g) * 4);
-#pragma unroll
-        for (int m = 0; m < 8; m++) {
-            s1_f32x4 v = __builtin_bit_cast(s1_f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane, soff + (int)(8 * m * p.I * 4), 0));
-            if (RAGGED) {
-                const bool in = (int64_t)SM_GI * g + 4 * (lane & 7) < p.I;   // I is a multiple of 4: a piece is inside or outside
-#pragma unroll
-                for (int e = 0; e < 4; e++) v[e] = in ? v[e] : 0.0f;
-            }
-            dst[m] = v;
-        }
+        // I is a multiple of 4: a piece is inside a column or outside, where the offset is past the end of the buffer
+        return XReq{(int)((((int64_t)tile * SM_TJ + 64 * w) * p.I + (int64_t)SM_GI * g) * 4),
+                    RAGGED && SM_GI * g + 4 * (lane & 7) >= (int)p.I ? INT32_MIN : x_lane};
     };
-    auto request_u = [&](int n, s1_bf16x8 (&dst)[2][RT]) {
+    auto load_x = [&](const XReq &r, int m) {
+        return __builtin_bit_cast(s1_f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, r.vo, r.soff + (int)(8 * m * p.I * 4), 0));
+    };
+    auto request_x = [&](int n, s1_f32x4 (&dst)[8]) {
+        const XReq r = locate_x(n);
+#pragma unroll
+        for (int m = 0; m < 8; m++) dst[m] = load_x(r, m);
+    };
+    auto request_u = [&](int n, int h, s1_bf16x8 (&dst)[RT]) {
         const int tile = n / ngp, g = n - tile * ngp;
+        int ks = 2 * g + h;
+        ks = (g < ng && ks < nks) ? ks : nks;      // the zero fragment for what lies past the end
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            int ks = 2 * g + h;
-            ks = (g < ng && ks < nks) ? ks : nks;      // the zero fragment for what lies past the end
-#pragma unroll
-            for (int rt = 0; rt < RT; rt++)
-                dst[h][rt] = __builtin_bit_cast(s1_bf16x8, __builtin_amdgcn_raw_buffer_load_b128(urs, f_lane, (rt * (nks + 1) + ks) * 1024, 0));
-        }
+        for (int rt = 0; rt < RT; rt++)
+            dst[rt] = __builtin_bit_cast(s1_bf16x8, __builtin_amdgcn_raw_buffer_load_b128(urs, f_lane, (rt * (nks + 1) + ks) * 1024, 0));
     };
     // x = h + m + l with h, m, l the three 8-bit slices of the significand, each a bf16 value (truncation: the residuals
     // are exact); two values per register
@@ -372,7 +385,20 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
     };
     // mode 2 on the finished tile
     auto finish_tile = [&](int tile) {
-        __syncthreads();   // every wave is done with its slots: the Z^T fragments take the LDS over
+        // V fragments of column block jb for the wave's blocks, requested VD - 1 blocks ahead, the first ones before anything else: they are
+        // queued behind the requests of X.  The accumulators of mode 1 are free meanwhile.
+        constexpr int VD = PIPE ? 4 : 2;
+        s1_bf16x8 vr[VD][NBW];
+        auto request_v = [&](int jb, s1_bf16x8 (&dst)[NBW]) {
+#pragma unroll
+            for (int i = 0; i < NBW; i++) {
+                const int blk = w + SM_NW * i, mt = blk / RT;    // past the last block: a request past the buffer, zeros
+                dst[i] = __builtin_bit_cast(s1_bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrs, f_lane, (mt * 16 * ntile + 16 * tile + jb) * 1024, 0));
+            }
+        };
+#pragma unroll
+        for (int jb = 0; jb < VD - 1; jb++) request_v(jb, vr[jb]);
+        s1_lds_barrier();   // every wave is done with its slots: the Z^T fragments take the LDS over
 #pragma unroll
         for (int rt = 0; rt < RT; rt++)
 #pragma unroll
@@ -387,26 +413,10 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
                     *(s1_f32x4 *)dst = lo;
                     *(s1_f32x4 *)(dst + 256) = up;
                 }
-#pragma unroll
-        for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-            for (int ct = 0; ct < SM_CT; ct++)
-#pragma unroll
-                for (int e = 0; e < 16; e++) acc[rt][ct][e] = 0.0f;
-        __syncthreads();
-        // V fragments of column block jb for the wave's blocks, requested one block ahead
-        s1_bf16x8 vr[2][NBW];
-        auto request_v = [&](int jb, s1_bf16x8 (&dst)[NBW]) {
-#pragma unroll
-            for (int i = 0; i < NBW; i++) {
-                const int blk = w + SM_NW * i, mt = blk / RT;    // past the last block: a request past the buffer, zeros
-                dst[i] = __builtin_bit_cast(s1_bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrs, f_lane, (mt * 16 * ntile + 16 * tile + jb) * 1024, 0));
-            }
-        };
-        request_v(0, vr[0]);
+        s1_lds_barrier();
 #pragma unroll
         for (int jb = 0; jb < 16; jb++) {
-            if (jb + 1 < 16) request_v(jb + 1, vr[(jb + 1) & 1]);
+            if (jb + VD - 1 < 16) request_v(jb + VD - 1, vr[(jb + VD - 1) % VD]);
             s1_bf16x8 zh, zm, zl;
             if constexpr (ONE_RT) {
                 const int rt = w % RT;
@@ -418,11 +428,11 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
             if constexpr (ONE_RT) {
                 // pieces outside, blocks inside: consecutive MFMAs go to different accumulators
 #pragma unroll
-                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zl, qacc[i], 0, 0, 0);
+                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zl, qacc[i], 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zm, qacc[i], 0, 0, 0);
+                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zm, qacc[i], 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zh, qacc[i], 0, 0, 0);
+                for (int i = 0; i < NBW; i++) qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zh, qacc[i], 0, 0, 0);
             } else {
 #pragma unroll
                 for (int i = 0; i < NBW; i++) {
@@ -431,52 +441,122 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
                     s1_f32x4 x[2];
                     x[0] = *(const s1_f32x4 *)src; x[1] = *(const s1_f32x4 *)(src + 256);
                     split3(x, zh, zm, zl);
-                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zl, qacc[i], 0, 0, 0);
-                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zm, qacc[i], 0, 0, 0);
-                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb & 1][i], zh, qacc[i], 0, 0, 0);
+                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zl, qacc[i], 0, 0, 0);
+                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zm, qacc[i], 0, 0, 0);
+                    qacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[jb % VD][i], zh, qacc[i], 0, 0, 0);
                 }
             }
         }
-        __syncthreads();   // the slots take the LDS back
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+            for (int ct = 0; ct < SM_CT; ct++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[rt][ct][e] = 0.0f;
+        s1_lds_barrier();   // the slots take the LDS back
     };
 
     s1_static_for<D>([&](auto dc) {
         constexpr int d = decltype(dc)::value;
-        request_x(d, xr[d]);
-        request_u(d, ur[d]);
+        request_x(PIPE ? d + 1 : d, xr[d]);
+        request_u(d, 0, ur[d][0]);
+        request_u(d, 1, ur[d][1]);
     });
+    // PIPE: pieces l, m, h of the two column tiles for the half-steps h = 0, 1 of a step, and what they are made from
+    s1_u32x4 xp[PIPE ? 2 : 1][3][SM_CT];
+    s1_f32x4 raw[PIPE ? 2 : 1][SM_CT][2];
+    // a third of the splitting of two values: their upper pieces, their middle ones, their lower ones.  The residuals take the place of
+    // the values.
+    auto split_share = [&]<int S>(s1_f32x4 (&x)[SM_CT][2], s1_u32x4 (&xp)[3][SM_CT]) __attribute__((always_inline)) {
+        constexpr int ct = S / 12, q = S % 12 / 3, part = S % 3;
+        float &x0 = ((float *)&x[ct][q >> 1])[2 * (q & 1)], &x1 = ((float *)&x[ct][q >> 1])[2 * (q & 1) + 1];
+        const unsigned b0 = __builtin_bit_cast(unsigned, x0), b1 = __builtin_bit_cast(unsigned, x1);
+        xp[2 - part][ct][q] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+        if constexpr (part < 2) {
+            x0 -= __builtin_bit_cast(float, b0 & 0xffff0000u);
+            x1 -= __builtin_bit_cast(float, b1 & 0xffff0000u);
+        }
+    };
+    if constexpr (PIPE) {   // step 0 through LDS, its first half in pieces
+        s1_f32x4 x0[8];
+        request_x(0, x0);
+#pragma unroll
+        for (int m = 0; m < 8; m++) *(s1_f32x4 *)(xs + swz(8 * m + (lane >> 3), lane & 7)) = x0[m];
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int ct = 0; ct < SM_CT; ct++)
+#pragma unroll
+                for (int v = 0; v < 2; v++) raw[h][ct][v] = *(const s1_f32x4 *)(xs + swz(32 * ct + l32, 4 * h + 2 * hi + v));
+        s1_static_for<12 * SM_CT>([&](auto sc) { split_share.template operator()<decltype(sc)::value>(raw[0], xp[0]); });
+    }
     for (int tile = 0; tile < ntile; tile++) {
         for (int g0 = 0; g0 < ngp; g0 += UN) {
             s1_static_for<UN>([&](auto dc) {
                 constexpr int dd = decltype(dc)::value, d = dd % D, sl = dd % DL;
                 const int n = tile * ngp + g0 + dd;
-                float *slot = xs + sl * SLOT;
-                // the step that has arrived goes to the wave's LDS slot, and its registers out again for step n + D
+                if constexpr (PIPE) {
+                    // Half-step 2 n + h: its matrix instructions, each with a share of the splitting of the next half-step behind it; the
+                    // one after that is read from LDS meanwhile, and step n + 1 goes there before.  D >= 2 steps of X are on their way.
+                    float *slot = xs;   // all of step n has been read from it
+                    s1_static_for<2>([&](auto hc) {
+                        constexpr int h = decltype(hc)::value;
+                        XReq r;
+                        if constexpr (h == 0) {
 #pragma unroll
-                for (int m = 0; m < 8; m++) *(s1_f32x4 *)(slot + swz(8 * m + (lane >> 3), lane & 7)) = xr[d][m];
-                request_x(n + D, xr[d]);
-#pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    s1_bf16x8 xp[3][SM_CT];   // pieces l, m, h of the two column tiles
-#pragma unroll
-                    for (int ct = 0; ct < SM_CT; ct++) {
-                        const int j = 32 * ct + l32;
-                        s1_f32x4 x[2];
-                        x[0] = *(const s1_f32x4 *)(slot + swz(j, 4 * h + 2 * hi));
-                        x[1] = *(const s1_f32x4 *)(slot + swz(j, 4 * h + 2 * hi + 1));
-                        split3(x, xp[2][ct], xp[1][ct], xp[0][ct]);
-                    }
-                    // smallest pieces first; consecutive MFMAs go to different accumulators (one that adds to the result of
-                    // the instruction before it waits for that result)
-#pragma unroll
-                    for (int pc = 0; pc < 3; pc++)
+                            for (int m = 0; m < 8; m++) *(s1_f32x4 *)(slot + swz(8 * m + (lane >> 3), lane & 7)) = xr[d][m];
+                            r = locate_x(n + 1 + D);
+                        }
 #pragma unroll
                         for (int ct = 0; ct < SM_CT; ct++)
 #pragma unroll
-                            for (int rt = 0; rt < RT; rt++)
-                                acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[pc][ct], ur[d][h][rt], acc[rt][ct], 0, 0, 0);
+                            for (int v = 0; v < 2; v++) raw[h][ct][v] = *(const s1_f32x4 *)(slot + swz(32 * ct + l32, 4 * h + 2 * hi + v));
+                        __builtin_amdgcn_sched_barrier(0);
+                        // smallest pieces first; consecutive MFMAs go to different accumulators
+                        constexpr int NM = 3 * SM_CT * RT, NS = 3 * 4 * SM_CT;   // matrix instructions, shares
+                        s1_static_for<NM>([&](auto ic) {
+                            constexpr int i = decltype(ic)::value, pc = i / (SM_CT * RT), ct = i / RT % SM_CT, rt = i % RT;
+                            acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(s1_bf16x8, xp[h][pc][ct]), ur[d][h][rt], acc[rt][ct], 0, 0, 0);
+                            s1_static_for<NS>([&](auto sc) {
+                                constexpr int s = decltype(sc)::value;
+                                if constexpr (s * NM / NS == i) split_share.template operator()<s>(raw[1 - h], xp[1 - h]);
+                            });
+                            if constexpr (h == 0 && i % (NM / 8) == 0 && i / (NM / 8) < 8) xr[d][i / (NM / 8)] = load_x(r, i / (NM / 8));
+                            if constexpr (h == 1 && i == NM / 2) request_u(n + D, 0, ur[d][0]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        });
+                    });
+                    request_u(n + D, 1, ur[d][1]);
+                } else {
+                    float *slot = xs + sl * SLOT;
+                    // the step that has arrived goes to the wave's LDS slot, and its registers out again for step n + D
+#pragma unroll
+                    for (int m = 0; m < 8; m++) *(s1_f32x4 *)(slot + swz(8 * m + (lane >> 3), lane & 7)) = xr[d][m];
+                    request_x(n + D, xr[d]);
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {
+                        s1_bf16x8 xp[3][SM_CT];   // pieces l, m, h of the two column tiles
+#pragma unroll
+                        for (int ct = 0; ct < SM_CT; ct++) {
+                            const int j = 32 * ct + l32;
+                            s1_f32x4 x[2];
+                            x[0] = *(const s1_f32x4 *)(slot + swz(j, 4 * h + 2 * hi));
+                            x[1] = *(const s1_f32x4 *)(slot + swz(j, 4 * h + 2 * hi + 1));
+                            split3(x, xp[2][ct], xp[1][ct], xp[0][ct]);
+                        }
+                        // smallest pieces first; consecutive MFMAs go to different accumulators (one that adds to the result of
+                        // the instruction before it waits for that result)
+#pragma unroll
+                        for (int pc = 0; pc < 3; pc++)
+#pragma unroll
+                            for (int ct = 0; ct < SM_CT; ct++)
+#pragma unroll
+                                for (int rt = 0; rt < RT; rt++)
+                                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[pc][ct], ur[d][h][rt], acc[rt][ct], 0, 0, 0);
+                    }
+                    request_u(n + D, 0, ur[d][0]);
+                    request_u(n + D, 1, ur[d][1]);
                 }
-                request_u(n + D, ur[d]);
             });
         }
         finish_tile(tile);

@@ -215,3 +215,33 @@ def test_first_stage_from_host_memory(monkeypatch):
     got = a.cpu().numpy().astype(np.float64).reshape(st.dims, order="F")
     assert _rel(got, oracle.first_stage(X, *mats)) <= TOL
     st.close()
+
+
+# More than 64 rows a: steps of 32 rows that overlap inside a wave.  One step and less, an odd number of steps (a padded one behind them),
+# pieces past the end of a column, one column, tiles of 256 columns one short, full and one over.
+@pytest.mark.parametrize("I,J,A1,B1", [(4, 1, 65, 1), (32, 255, 128, 33), (36, 256, 96, 128), (64, 257, 100, 64), (100, 40, 128, 100),
+                                       (132, 520, 128, 128), (192, 300, 70, 90), (60, 513, 97, 5), (1000, 30, 100, 100)])
+def test_first_stage_overlapped_steps(I, J, A1, B1):
+    print("case", I, J, A1, B1, flush=True)
+    rng = np.random.default_rng(I + J)
+    K, C1 = 3, 2
+
+    def sign(rows, cols):   # CSR, up to four entries +-1/2 per column
+        r = np.concatenate([rng.choice(rows, min(4, rows), replace=False) for _ in range(cols)])
+        c = np.repeat(np.arange(cols), min(4, rows))
+        o = np.lexsort((c, r))
+        v = rng.choice([-0.5, 0.5], r.size).astype(np.float32)
+        return np.concatenate([[0], np.cumsum(np.bincount(r, minlength=rows))]).astype(np.int64), c[o].astype(np.int32), v[o]
+    mats = [sign(A1, I), sign(B1, J), sign(C1, K)]
+    X = rng.standard_normal((I, J, K)).astype(np.float32)
+    st = exat.Stage1(I, J, K, *mats)
+    got = st.apply(gu.to_dev_x(X)).cpu().numpy().astype(np.float64).reshape(A1, B1, C1, order="F")
+    st.close()
+    dense = []
+    for (rp, ci, v), n in zip(mats, (I, J, K)):
+        d = np.zeros((len(rp) - 1, n))
+        d[np.repeat(np.arange(len(rp) - 1), np.diff(rp)), ci] = v
+        dense.append(d)
+    ref = np.einsum("ai,bj,ck,ijk->abc", *dense, X.astype(np.float64), optimize=True)
+    # sums of at most 4 I J K / (A1 B1 C1) exact products of fp32 values with +-1/8, in fp32
+    assert np.abs(got - ref).max() <= 2e-6 * np.sqrt((ref ** 2).mean()) + 1e-6 * np.abs(X).max()
