@@ -194,16 +194,17 @@ int launch_v4_gen_bf16(const Mode12Params &mp, const GenSplitParams &gs, const U
     return boxed ? launch_v4_inst<true>(mp, gs, uf, nk, st) : launch_v4_inst<false>(mp, gs, uf, nk, st);
 }
 
-template <int NP, int NW, int NWC, int SRC, int KS = 1>
+template <int NP, int NW, int NWC, int SRC, int KS = 1, bool QL = false>
 int launch_mp_inst(const Mode12Params &mp, const MpParams &q, const GenSplitParams &gs, int nk, hipStream_t st)
 {
-    typedef Mode12MpCfg<NP, NW, NWC> cfg;
-    auto kern = k_mode12_mp<NP, NW, NWC, SRC, KS>;
-    constexpr int lds = cfg::lds_bytes(SRC == MP_GEN, KS);
-    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    typedef Mode12MpCfg<NP, NW, NWC, QL> cfg;
+    auto kern = k_mode12_mp<NP, NW, NWC, SRC, KS, QL>;
+    constexpr int ring = cfg::lds_bytes(SRC == MP_GEN, KS), most = QL ? 160 * 1024 : ring;
+    static_assert(ring <= 160 * 1024, "LDS of a compute unit");
+    const int lds = ring + (QL ? 2 * 32 * NW * q.qs * 4 : 0);
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return EXAT_ERR_HIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess) return EXAT_ERR_HIP;
         attr_done = true;
     }
     const int64_t grid = q.nblk ? (int64_t)q.nblk * mp.G * q.bs : 8LL * ((nk + 7) / 8) * mp.G;
@@ -218,6 +219,8 @@ int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, const GenSplitParam
         if (generated) return gs.Rpad == 32 ? launch_mp_inst<NP, NW, NWC, MP_GEN, 1>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_GEN, 2>(mp, q, gs, nk, st);
     // the lean build unless X is a set of blocks, the box has odd ends in i, or the fibres are millions of values long
     const bool ptr = mp.xtab || mp.i0 % 4 != 0 || mp.i1 % 4 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
+    if constexpr (NP != 2 && NW == 8 && NWC == 1)
+        if (q.qs) return ptr ? launch_mp_inst<NP, NW, NWC, MP_PTR, 1, true>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_LEAN, 1, true>(mp, q, gs, nk, st);
     return ptr ? launch_mp_inst<NP, NW, NWC, MP_PTR>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_LEAN>(mp, q, gs, nk, st);
 }
 template <int NP>
@@ -338,6 +341,12 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         q.ja0 = mp.j0 & ~(int64_t)15;
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
+        // Q in LDS where the workgroup has its own compute unit, more than one chunk adds to it and 512 rows of it fit beside the ring
+        // (up to 50 columns m for fp32, 60 for bf16; generated sources need the room for their operands, two fp16 pieces have
+        // longer rows in the configurations they are used in)
+        q.qs = 0;
+        if (!split && !generated && nw == 8 && nwc == 1 && mp.j1 - q.ja0 > 128)
+            q.qs = mp_qrow(pl->d.M, 512, 160 * 1024 - (bf ? Mode12MpCfg<1, 8, 1, true>::lds_bytes(false, 1) : Mode12MpCfg<3, 8, 1, true>::lds_bytes(false, 1)));
         q.nblk = q.bs = 0;
         // Row groups of different size drift apart and then neither share X tiles nor leave room for U in the L2 (2400 rows, 1000^3
         // bf16: 37 GB fetched past the L2 in 7.7 ms slice by slice, 17 GB in 7.2 ms in runs): slices in runs, one group per XCD at a time.  Both orders measured, slice by

@@ -50,6 +50,7 @@ struct MpParams {
     int nblk, bs;      // runs of slices (nblk * G is a multiple of 8) and the longest run's length, or 0
     int64_t ja0;       // first fibre of the first chunk (a multiple of 16, <= j0)
     uint32_t *flags;   // MPF_* words, or null
+    int qs;            // QL: floats per row of Q in LDS, even (see mp_qrow)
 };
 
 // the largest of mx, |a|, |b|; NaN if one of them is (one instruction)
@@ -112,12 +113,17 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
     }
 }
 
-template <int NP, int NW, int NWC>
+// QL: the workgroup's rows of Q stay in LDS, behind the ring, until its last chunk (rows of MpParams::qs floats).  The Q of the 32
+// workgroups of an XCD is as large as its L2, and with the chunks' other traffic every chunk read it from memory, in front of a wait
+// nothing covers.  The ring is half as long for it, a barrier after every second stage (bf16) or every stage (fp32).  Before -> now:
+// 1000^3 bf16, 2400 rows 7.24 -> 6.46 ms; fp32: 1000^3, 1550 rows 16.6 -> 16.2 ms, 500^3 blocks of it 20.9 -> 20.1, 512^3, 512 rows 658 -> 644
+// us, 250^3 263 -> 257, 64 x 1000 x 300, 820 rows 720 -> 650; the same sums in the same order.
+template <int NP, int NW, int NWC, bool QL = false>
 struct Mode12MpCfg {
     static constexpr int NWR = NW / NWC, RT = 2, CT = 4 / NWC, COLS = 128, EI = 32;
     static constexpr int XPT = 512 / (64 * NW);                 // runs of 8 values of the X tile per thread
     static constexpr int ROWB = 80, XBUF = COLS * ROWB, SLOT = NP * XBUF;
-    static constexpr int NSLOT = NP == 1 ? 8 : (NP == 3 && NW == 4 ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
+    static constexpr int NSLOT = NP == 1 ? (QL ? 4 : 8) : (NP == 3 && (NW == 4 || QL) ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
     static constexpr int lds_bytes(bool gen, int ks) { return NSLOT * SLOT + (gen ? 8 * ks * 2048 : 0); }
     static constexpr int DU = NP == 1 ? 2 : 1;   // register sets of U fragments
     static constexpr int DX = NP == 1 ? 4 : 1;   // register sets of the X tile in flight
@@ -128,13 +134,35 @@ struct Mode12MpCfg {
     static_assert(UNR % DU == 0 && UNR % DX == 0 && (UNR % H == 0 || H % UNR == 0), "");
 };
 
+// Floats per row of Q in LDS, where `lds` bytes are left for `rows` rows: an odd multiple of 4 or, where that is too much, the number
+// of columns made even (neighbouring rows then start in different banks either way); 0 if there is no room.  Rows are read and written
+// 8 bytes at a time: `mp_q_ld`, `mp_q_st` of columns c .. c+3, of which those beyond the row are zero.
+inline int mp_qrow(int M, int rows, int lds)
+{
+    const int a = 4 * (((M + 3) / 4) | 1), b = 2 * (((M + 1) / 2) | 1), most = lds / (4 * rows);
+    return a <= most ? a : (b <= most ? b : 0);
+}
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f32x4 mp_q_ld(const float *row, int c, int qs)
+{
+    f32x2 a = {0.0f, 0.0f}, b = {0.0f, 0.0f};
+    if (c < qs) a = *(const f32x2 *)(row + c);
+    if (c + 2 < qs) b = *(const f32x2 *)(row + c + 2);
+    return f32x4{a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ void mp_q_st(float *row, int c, int qs, const f32x4 &v)
+{
+    if (c < qs) *(f32x2 *)(row + c) = f32x2{v[0], v[1]};
+    if (c + 2 < qs) *(f32x2 *)(row + c + 2) = f32x2{v[2], v[3]};
+}
+
 // Mode 2 from the accumulators (acc holds Z^T: rows 32 fibres j, columns 32 stacked rows q; see mode2_direct_bf16 for the
 // order of the contraction slots), Z split into pieces like X, V packed in pieces.  A tile whose rows belong to several
 // replicas is multiplied with each one's V, and a lane keeps the product of its row's replica.  Q[row][m] += Q^T[m][row];
 // Qk points to the rows of this slice (and wave column).
-template <int NP, int RT, int CT, int MTC, int RSTRIDE>
+template <int NP, int RT, int CT, int MTC, int RSTRIDE, bool QL>
 __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &mp, float *Qk, f32x16 (&acc)[RT][CT], int wrow0, int ntile,
-                                         int64_t jc, bool first_chunk, int lane)
+                                         int64_t jc, bool first_chunk, int lane, float *ql)
 {
     constexpr bool F16 = NP == 2;
     constexpr int MP = 32 * MTC, NZ = NP == 2 ? 2 : 3, NV = NP;
@@ -149,7 +177,7 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
             const int q = q0 + l32;
             const int qlast = (q0 + 31 < p.PL - 1) ? q0 + 31 : p.PL - 1;
             const int pfirst = q0 / p.L, plast = qlast / p.L;
-            float *Qt = Qk + (int64_t)q * MP + 4 * hi;   // + 32*mt + 8*b
+            float *Qt = QL ? ql + (rt * RSTRIDE + l32) * mp.qs : Qk + (int64_t)q * MP + 4 * hi;   // + 32*mt + 8*b (+ 4*hi)
             for (int pp = pfirst; pp <= plast; pp++) {
                 const bool mine = q >= pp * p.L && q < (pp + 1) * p.L && q < p.PL;
                 // Step st = 2 ct + t multiplies 16 fibres: Z split into pieces (during the step before) times the fragments of V,
@@ -191,7 +219,7 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
 #pragma unroll
                             for (int b = 0; b < 4; b++) {
                                 qold[m][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                                if (!first_chunk && mine) qold[m][b] = *(const f32x4 *)(Qt + 32 * m + 8 * b);
+                                if (!first_chunk && mine) qold[m][b] = QL ? mp_q_ld(Qt, 32 * m + 8 * b + 4 * hi, mp.qs) : *(const f32x4 *)(Qt + 32 * m + 8 * b);
                             }
                     }
                     __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the MFMAs
@@ -214,7 +242,8 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
                             f32x4 o;
 #pragma unroll
                             for (int r = 0; r < 4; r++) o[r] = d[m][4 * b + r] + qold[m][b][r];
-                            *(f32x4 *)(Qt + 32 * m + 8 * b) = o;
+                            if (QL) mp_q_st(Qt, 32 * m + 8 * b + 4 * hi, mp.qs, o);
+                            else *(f32x4 *)(Qt + 32 * m + 8 * b) = o;
                         }
                 }
             }
@@ -236,10 +265,10 @@ typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
 // within the stage: the A pieces of 16 rows are requested a few fragments before they are used, the products B[j,r] C[k,r] of a
 // chunk wait in a lane-private piece of LDS, so the only state between stages are the fibres' keys.
 enum { MP_LEAN = 0, MP_PTR = 1, MP_GEN = 2 };
-template <int NP, int NW, int NWC, int SRC, int KS = 1>
+template <int NP, int NW, int NWC, int SRC, int KS = 1, bool QL = false>
 __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, const MpParams mp, const GenSplitParams gs)
 {
-    typedef Mode12MpCfg<NP, NW, NWC> cfg;
+    typedef Mode12MpCfg<NP, NW, NWC, QL> cfg;
     typedef std::conditional_t<NP == 1, __bf16, float> T;
     typedef mp_terms<NP> terms;
     constexpr bool F16 = NP == 2, PTR = SRC == MP_PTR, GEN = SRC == MP_GEN;
@@ -654,8 +683,23 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         float *Qk = p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
         const int64_t jw = jc + wc * CT * 32;
         const int ntile = two ? 2 : (own ? 1 : 0);
-        if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63);
-        else mode2_mp<NP, RT, CT, 1, 32 * NWR>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63);
+        float *ql = (float *)(smem + NSLOT * SLOT) + 32 * wr * mp.qs;
+        if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
+        else mode2_mp<NP, RT, CT, 1, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
+        if constexpr (QL) {   // behind the last chunk: the wave's rows go to memory
+            if (jc + COLS >= p.j1) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int m4 = 8 * p.MT;
+                for (int rt = 0; rt < ntile; rt++)
+                    for (int e = tid & 63; e < 32 * m4; e += 64) {
+                        const int r = rt * 32 * NWR + e / m4, c = 4 * (e % m4);
+                        const f32x4 v = mp_q_ld(ql + r * mp.qs, c, mp.qs);
+                        if (wrow0 + r < p.PL) *(f32x4 *)(Qk + (int64_t)(wrow0 + r) * p.Mpad + c) = v;
+                    }
+            }
+        }
     }
     if (NP != 2 && mp.flags) {
         const bool xn = __any(xmax >= MP_EMIN);

@@ -344,3 +344,20 @@ def test_scales_inside_the_range(sx, su):
     finally:
         os.environ.pop("EXAT_PIPELINED")
     assert _err(Y, _ref(X, U, V, W, L, M, N, P, "f32")) <= TOL and not torch.equal(Y, G)
+
+
+# Rows of Q that stay in LDS over the chunks: row lengths that are odd multiples of 4, that are not (46 to 50 columns for fp32), the longest
+# ones and the first ones without room; two chunks and more, a last chunk of one fibre; rows that fill the last group, or not; odd ends in i.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M", [1, 4, 5, 32, 33, 44, 45, 47, 48, 49, 50, 51, 52, 53, 60, 61])
+@pytest.mark.parametrize("I,J,P,L", [(33, 257, 11, 47), (64, 129, 16, 32)])
+def test_rows_in_lds(dtype, M, I, J, P, L):
+    K, N = 9, 3
+    print("case", dtype, M, I, J, P, L, flush=True)
+    X, U, V, W = _problem(I, J, K, L, M, N, P, dtype)
+    plan = _plan(I, J, K, L, M, N, P, dtype, U, V, W)
+    R = _ref(X, U, V, W, L, M, N, P, dtype)
+    Y = plan.new_y()
+    for _ in range(2):   # and again over what the first call left
+        Y.fill_(float("nan"))
+        assert _err(plan.compress(X, Y), R) <= TOL
