@@ -219,7 +219,7 @@ int launch_mp_nwc(const Mode12Params &mp, const MpParams &q, const GenSplitParam
         if (generated) return gs.Rpad == 32 ? launch_mp_inst<NP, NW, NWC, MP_GEN, 1>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_GEN, 2>(mp, q, gs, nk, st);
     // the lean build unless X is a set of blocks, the box has odd ends in i, or the fibres are millions of values long
     const bool ptr = mp.xtab || mp.i0 % 4 != 0 || mp.i1 % 4 != 0 || mp.x_sj > (1LL << 31) / (128 * (NP == 1 ? 2 : 4)) - 64;
-    if constexpr (NP != 2 && NW == 8 && NWC == 1)
+    if constexpr (NP != 2 && NW == 8)
         if (q.qs) return ptr ? launch_mp_inst<NP, NW, NWC, MP_PTR, 1, true>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_LEAN, 1, true>(mp, q, gs, nk, st);
     return ptr ? launch_mp_inst<NP, NW, NWC, MP_PTR>(mp, q, gs, nk, st) : launch_mp_inst<NP, NW, NWC, MP_LEAN>(mp, q, gs, nk, st);
 }
@@ -341,12 +341,15 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         q.ja0 = mp.j0 & ~(int64_t)15;
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
-        // Q in LDS where the workgroup has its own compute unit, more than one chunk adds to it and 512 rows of it fit beside the ring
-        // (up to 50 columns m for fp32, 60 for bf16; generated sources need the room for their operands, two fp16 pieces have
-        // longer rows in the configurations they are used in)
+        // Q in LDS where the workgroup has its own compute unit, 512 rows of it fit beside the ring and more than one chunk adds to it (up
+        // to 50 columns m for fp32, 60 for bf16) or four wave columns do (beside the whole ring, short calls need it: 20 and 40);
+        // generated sources need the room for their operands, two fp16 pieces have longer rows in the configurations they are used in
+        auto room = [&](auto c1, auto c3) { return 160 * 1024 - (bf ? decltype(c1)::lds_bytes(false, 1) : decltype(c3)::lds_bytes(false, 1)); };
         q.qs = 0;
+        if (!split && !generated && nwc == 4) q.qs = mp_qrow(pl->d.M, 512, room(Mode12MpCfg<1, 8, 4, true>(), Mode12MpCfg<3, 8, 4, true>()));
         if (!split && !generated && nw == 8 && nwc == 1 && mp.j1 - q.ja0 > 128)
-            q.qs = mp_qrow(pl->d.M, 512, 160 * 1024 - (bf ? Mode12MpCfg<1, 8, 1, true>::lds_bytes(false, 1) : Mode12MpCfg<3, 8, 1, true>::lds_bytes(false, 1)));
+            q.qs = mp_qrow(pl->d.M, 512, room(Mode12MpCfg<1, 8, 1, true>(), Mode12MpCfg<3, 8, 1, true>()));
+        if (q.qs) kshift = 0;
         q.nblk = q.bs = 0;
         // Row groups of different size drift apart and then neither share X tiles nor leave room for U in the L2 (2400 rows, 1000^3
         // bf16: 37 GB fetched past the L2 in 7.7 ms slice by slice, 17 GB in 7.2 ms in runs): slices in runs, one group per XCD at a time.  Both orders measured, slice by

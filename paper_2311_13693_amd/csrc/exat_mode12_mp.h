@@ -22,13 +22,13 @@
 //            fibres.  The row tiles are dealt to the G groups in quads, as evenly as they go (a quad is one tile per SIMD), and inside
 //            a group tile t goes to wave t mod NW; a wave with one tile runs a stage loop of its own.
 //   NWC = 4  (at most 4 row tiles in all)  four waves share a row tile and take 32 fibres each; each leaves its
-//            own partial Q, which mode 3 adds up as if it were a slice of its own (Mode3Params::kshift).
+//            own partial Q, which mode 3 adds up as if it were a slice of its own (Mode3Params::kshift), or which are added up in LDS (QL).
 // X goes HBM -> registers -> (split) -> LDS; U comes in fragment order straight from L2 into registers.  The X tiles sit in a
 // ring of NSLOT LDS slots: a stage reads tile s and writes tile s + H, H = NSLOT/2, and the workgroup meets at a barrier
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
-// Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 21 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
-// (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 17.6 ms and 1000^3 bf16, 2400 rows 25.8 -> 7.4 ms (generic
-// kernel before: 1000 is no multiple of a stage); slower only, by the range check's launch: 128 x 128 x 91 bf16, 304 rows 18.3 -> 20.6 us;
+// Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 17 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
+// (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 16.2 ms and 1000^3 bf16, 2400 rows 25.8 -> 6.5 ms (generic
+// kernel before: 1000 is no multiple of a stage);
 // 1024^3 in two fp16 pieces, 2048 rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
 // about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
@@ -118,12 +118,14 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
 // nothing covers.  The ring is half as long for it, a barrier after every second stage (bf16) or every stage (fp32).  Before -> now:
 // 1000^3 bf16, 2400 rows 7.24 -> 6.46 ms; fp32: 1000^3, 1550 rows 16.6 -> 16.2 ms, 500^3 blocks of it 20.9 -> 20.1, 512^3, 512 rows 658 -> 644
 // us, 250^3 263 -> 257, 64 x 1000 x 300, 820 rows 720 -> 650; the same sums in the same order.
+// With NWC = 4 the wave columns' partial rows are added there too, behind the last chunk, and mode 3 reads a quarter: 128^3 fp32, 64 rows
+// 22.3 -> 17.1 us, bf16 18.9 -> 14.7; 512^3 bf16, 128 rows 153 -> 104 us.
 template <int NP, int NW, int NWC, bool QL = false>
 struct Mode12MpCfg {
     static constexpr int NWR = NW / NWC, RT = 2, CT = 4 / NWC, COLS = 128, EI = 32;
     static constexpr int XPT = 512 / (64 * NW);                 // runs of 8 values of the X tile per thread
     static constexpr int ROWB = 80, XBUF = COLS * ROWB, SLOT = NP * XBUF;
-    static constexpr int NSLOT = NP == 1 ? (QL ? 4 : 8) : (NP == 3 && (NW == 4 || QL) ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
+    static constexpr int NSLOT = NP == 1 ? (QL && NWC == 1 ? 4 : 8) : (NP == 3 && (NW == 4 || (QL && NWC == 1)) ? 2 : 4), H = NSLOT / 2;   // two 4-wave workgroups share the LDS
     static constexpr int lds_bytes(bool gen, int ks) { return NSLOT * SLOT + (gen ? 8 * ks * 2048 : 0); }
     static constexpr int DU = NP == 1 ? 2 : 1;   // register sets of U fragments
     static constexpr int DX = NP == 1 ? 4 : 1;   // register sets of the X tile in flight
@@ -680,13 +682,26 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             }
         }
         const bool first_chunk = (jc == mp.ja0);
-        float *Qk = p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
+        float *Qk = QL ? p.Q + (int64_t)kidx * p.PLpad * p.Mpad : p.Q + ((int64_t)kidx * NWC + wc) * (p.PLpad / NWC) * p.Mpad;
         const int64_t jw = jc + wc * CT * 32;
         const int ntile = two ? 2 : (own ? 1 : 0);
-        float *ql = (float *)(smem + NSLOT * SLOT) + 32 * wr * mp.qs;
+        float *ql = (float *)(smem + NSLOT * SLOT) + (64 * NWR * wc + 32 * wr) * mp.qs;
         if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
         else mode2_mp<NP, RT, CT, 1, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
-        if constexpr (QL) {   // behind the last chunk: the wave's rows go to memory
+        if constexpr (QL && NWC > 1) {   // behind the last chunk: the wave columns' rows are added up on their way to memory
+            if (jc + COLS >= p.j1) {
+                __syncthreads();
+                const float *qb = (const float *)(smem + NSLOT * SLOT);
+                const int m4 = 8 * p.MT, rows = p.PL < 64 * NWR ? p.PL : 64 * NWR;
+                for (int e = tid; e < rows * m4; e += 64 * NW) {
+                    const int r = e / m4, c = 4 * (e % m4);
+                    f32x4 v = mp_q_ld(qb + r * mp.qs, c, mp.qs);
+#pragma unroll
+                    for (int w = 1; w < NWC; w++) v += mp_q_ld(qb + (64 * NWR * w + r) * mp.qs, c, mp.qs);
+                    *(f32x4 *)(Qk + (int64_t)r * p.Mpad + c) = v;
+                }
+            }
+        } else if constexpr (QL) {   // behind the last chunk: the wave's rows go to memory
             if (jc + COLS >= p.j1) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();

@@ -348,9 +348,10 @@ def test_scales_inside_the_range(sx, su):
 
 # Rows of Q that stay in LDS over the chunks: row lengths that are odd multiples of 4, that are not (46 to 50 columns for fp32), the longest
 # ones and the first ones without room; two chunks and more, a last chunk of one fibre; rows that fill the last group, or not; odd ends in i.
+# Up to 128 rows the wave columns' partial rows are added there (up to 20 columns for fp32, 40 for bf16), also of a single chunk.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("M", [1, 4, 5, 32, 33, 44, 45, 47, 48, 49, 50, 51, 52, 53, 60, 61])
-@pytest.mark.parametrize("I,J,P,L", [(33, 257, 11, 47), (64, 129, 16, 32)])
+@pytest.mark.parametrize("M", [1, 4, 5, 19, 20, 21, 32, 33, 37, 40, 41, 44, 45, 47, 48, 49, 50, 51, 52, 53, 60, 61])
+@pytest.mark.parametrize("I,J,P,L", [(33, 257, 11, 47), (64, 129, 16, 32), (64, 129, 4, 31), (33, 257, 3, 11), (128, 100, 8, 16), (40, 1, 1, 1)])
 def test_rows_in_lds(dtype, M, I, J, P, L):
     K, N = 9, 3
     print("case", dtype, M, I, J, P, L, flush=True)
