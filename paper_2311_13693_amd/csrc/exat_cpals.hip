@@ -24,7 +24,8 @@
 // Measured (32 tensors of 64^3, rank 32, ten sweeps, 31 launches): 0.735 ms with the inverse in line in every workgroup, fp32 matrix
 // instructions (6 us a launch) and four waves; 0.62 with a workgroup of its own for the inverse, 0.55 with eight waves and 32-bit
 // offsets, 0.49 with bf16 pieces, 0.42 with the requests in the order of their use and none under a condition, and with four pivots
-// per step (7.2 -> 5 us).  A launch is now bound by two chains of about 11 us: partial results, product, Gram matrices (4 us), inverse;
+// per step (7.2 -> 5 us), 0.385 with a descriptor per outer value in place of scalar offsets (60 to 89 scalars were spilled in the update of
+// A).  A launch is now bound by two chains of about 11 us: partial results, product, Gram matrices (4 us), inverse;
 // and the tensor's way from the last-level cache (33.5 MB, more than the L2 holds).  Rank 64: 1.34 -> 0.78 ms; 16^3, rank 8: 0.35 -> 0.24.
 #include "../../include/exat.h"
 
@@ -253,29 +254,33 @@ __global__ __launch_bounds__(CP_NT) void k_cpals_step(const CpStep p)
     const int Du = p.D[U], D1 = p.D[i1], D2 = p.D[i2];
     const int rtn = (Du + 31) / 32, ntile = rtn * RC, kgn = CP_NW / ntile, kg = w / ntile, tile = w % ntile;
     const int row = 32 * (tile / RC) + l32, c = 32 * (tile % RC) + l32;
-    // element (row, d1, d2) of the tensor: the replica's buffer (2^18 elements at most), a lane's part of the offset, a wave-uniform part.
-    // Every request is made, with the offset NONE where there is nothing to read (it reads nothing then): a request under a condition
-    // makes the compiler wait for all that are outstanding.
-    constexpr int NONE = 1 << 24;
-    const int L4 = 4 * p.D[0], LM = p.D[0] * p.D[1], su = U == 0 ? 1 : (U == 1 ? p.D[0] : LM), s2 = U == 2 ? L4 : 4 * LM;
-    const auto yb = __builtin_amdgcn_make_buffer_rsrc((void *)(p.Y + rep * LM * p.D[2]), 0, p.mode >= 0 && !inv ? 4 * LM * p.D[2] : 0, 0x00020000);
-    const int ro = 4 * (row < Du ? row : Du - 1) * su, roh = ro + (U == 0 ? L4 : 16) * hi;
+    // Element (row, d1, d2) of the tensor: each value d2 of the outer index is a buffer of its own, from its first element to the end of the
+    // replica (mode 0: of the slice, where the inner index ends too), and a lane's offset.  Every request is made, in a buffer of no bytes or
+    // at the offset NONE where there is nothing to read (it reads nothing then): a request under a condition makes the compiler wait for all
+    // that are outstanding.  The range check is relied on for the lane's offset alone, the scalar offset is zero everywhere.
+    constexpr int NONE = 1 << 30;
+    const bool none = p.mode < 0 || inv;
+    const int L4 = 4 * p.D[0], LM = p.D[0] * p.D[1], su = U == 0 ? 1 : (U == 1 ? p.D[0] : LM), s2 = U == 2 ? p.D[0] : LM;
+    const float *yr = p.Y + rep * LM * p.D[2];
+    const int roh = 4 * (row < Du ? row : Du - 1) * su + (U == 0 ? L4 : 16) * hi;
     constexpr int NSTEP = CP_MAX / 2;
     const int nj = (D1 + 15) / 16;         // groups of 16 inner indices
-    const int d2a = slab * p.DS, d2b = d2a + p.DS < D2 ? d2a + p.DS : D2;
-    auto ld = [&](int vo, int so) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(yb, vo, so, 0)); };
+    const int d2a = none ? 0 : slab * p.DS, d2e = d2a + p.DS < D2 ? d2a + p.DS : D2, d2b = none ? 0 : d2e;
     auto load = [&](int d2, f32x4 (&a)[NSTEP / 4]) __attribute__((always_inline)) {
-        const int so = d2 < d2b ? d2 * s2 : NONE;
+        const int f = d2 < d2b ? d2 * s2 : 0, bytes = U == 0 ? 4 * LM : 4 * (LM * p.D[2] - f);
+        const auto yb = __builtin_amdgcn_make_buffer_rsrc((void *)(yr + f), 0, d2 < d2b ? bytes : 0, 0x00020000);
+        int vo = roh;
+        if (U == 0) asm("" : "+v"(vo));    // the offsets of a slice are made here, one after the other: 32 registers otherwise
 #pragma unroll
         for (int q = 0; q < NSTEP / 4; q++) {
             if constexpr (U == 0) {
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int d = 8 * q + 2 * e;   // lane half hi: d + hi; beyond D1 the factor is zero
-                    a[q][e] = ld(d + 1 < D1 ? roh : ro, d < D1 ? so + d * L4 : NONE);
+                for (int e = 0; e < 4; e++) {   // inner index 8 q + 2 e + hi: beyond D1 past the slice
+                    a[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(yb, vo, 0, 0));
+                    vo += 2 * L4;
                 }
             } else   // four values of l at 8 q + 4 hi: beyond D1 there are the row's neighbours, which `mac` takes out
-                a[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(yb, roh, 8 * q < D1 ? so + 32 * q : NONE, 0));
+                a[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(yb, 8 * q < D1 ? vo + 32 * q : NONE, 0, 0));
         }
     };
     constexpr int PF = 2;

@@ -230,3 +230,27 @@ def test_slabs_and_workspace(L, M, N, R, P):
     worst = ((torch.bmm(C, G) - Mx).abs() / (torch.bmm(C.abs(), G.abs()) + Ma))[ok].max().item()
     print("  %d of %d replicas, residual %.2e" % (int(ok.sum()), P, worst), flush=True)
     assert worst <= 2e-6
+
+
+# What is requested beyond the tensors' ends (or not at all: the workgroups that invert, slabs past the last value) must read nothing: the
+# tensors lie inside one allocation of NaN that reaches 2^24 bytes and more beyond them on both sides, and then inside one of zeros: the same
+# bits.  Extents that end inside a request of each mode, one slab and several, with an inverse of its own and not.
+@pytest.mark.parametrize("L,M,N,R,P", [(64, 64, 64, 32, 2), (63, 61, 62, 16, 3), (5, 3, 7, 2, 4), (1, 1, 1, 1, 2), (9, 33, 18, 33, 52), (33, 10, 41, 64, 90),
+                                       (17, 15, 13, 16, 130), (31, 9, 50, 20, 140), (8, 8, 8, 40, 600)])
+def test_reads_end_with_the_tensors(L, M, N, R, P):
+    print("case", L, M, N, R, P, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L + P)
+    n, guard = P * L * M * N, (1 << 22) + (1 << 18)
+    data = torch.randn(n, generator=g, device="cuda")
+    start = [torch.randn(P, R, d, generator=g, device="cuda") for d in (L, M, N)]
+    got = []
+    for around in (0.0, float("nan")):
+        buf = torch.full((n + 2 * guard + 1,), around, device="cuda")
+        Y = buf[guard + 1:guard + 1 + n]
+        Y.copy_(data)
+        F = [f.clone() for f in start]
+        exat.cpals(Y, L, M, N, P, R, 2, *F)
+        torch.cuda.synchronize()
+        got.append(torch.cat([f.flatten() for f in F]).view(torch.int32))
+    assert torch.equal(*got)
