@@ -10,8 +10,9 @@
 // A workgroup of 8 waves owns a tile of the result with its whole contraction range, which its waves split; they add their tiles
 // in wave order through LDS.  A launch of this kind costs 4 to 5 us whatever it does, and a small system is little more than launches:
 // so no tile's sum is split among workgroups (the two launches that joined the parts cost what the products did), nothing but LDS is
-// waited for at a barrier, and nothing is requested that is not used (requests beyond the end of the range: +15 %).
-// 2048 x 1024, 32 right-hand sides, 40 iterations: 1.25 ms with split tiles and joins, 0.64 ms now (up 6.5, down 9.8 us; a workgroup of
+// waited for at a barrier, and nothing is requested that is not used (requests beyond the end of the range: +15 %).  In tall systems
+// k_ls_down has too few tiles for that: several workgroups share one, and k_ls_join adds their parts (choose_split).
+// 2048 x 1024, 32 right-hand sides, 40 iterations: 1.25 ms with split tiles and joins, 0.62 ms now (up 6.5, down 9.2 us; a workgroup of
 // k_ls_down reads 384 KB, at about 100 GB/s); 10000 x 4000, 64 right-hand sides: 18.2 -> 5.7 ms.
 // Every workgroup also writes its share of the new p (r) into the other of two buffers, so no launch reads what
 // it writes.  The squared column norms that alpha and beta need are left as per-workgroup partial sums and added
@@ -42,12 +43,12 @@ struct LsParams {
     unsigned last4;       // index of the last four elements of U (0 if there are fewer)
     int rows, I, R;
     int Rp, rowsP, IP;    // padded R, rows, I
-    int nbA, nbB;         // row tiles of k_ls_up and k_ls_down
+    int nbA, nbB;         // row tiles of k_ls_up and k_ls_down, or (for who reads them) partial sums in partA and partB
     float tol2;           // a column whose gamma has fallen to tol2 * gamma_0 is left as it is
     f32x4_a4 *x, *s, *p[2];  // IP x Rp
     f32x4_a4 *q, *r[2];      // rowsP x Rp
     float *partA;         // [nbA][Rp]    column sums of q^2 per row tile
-    float *partB;         // [nbB][Rp]    column sums of s^2 per row tile
+    float *partB;         // [nbB][Rp]    column sums of s^2 per row tile, or per 32 rows (k_ls_join)
     float *gam;           // [3][64]      gamma_0, then gamma_t of even and odd t (gamma: column sums of s^2)
 };
 
@@ -74,9 +75,6 @@ __device__ __forceinline__ void tile_of(int nct, int &b, int &nt)
     b = (y / nct) * 8 + (id & 7);
 }
 
-// Column sums of a [n][Rp] array of per-workgroup partial sums for the NC = 16 TR columns from `part` on: a lane gets those of columns
-// (lane % 16) + 16 tr.  Thread groups take the entries in turn, the groups of a wave and then the waves are added in order.  The loads
-// are made by `colsum_load`, the rest by `colsum_add`: what is requested between them is in flight meanwhile.
 // Barrier for what goes through LDS: requests to memory stay in flight across it
 __device__ __forceinline__ void lds_barrier()
 {
@@ -85,6 +83,9 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Column sums of a [n][Rp] array of per-workgroup partial sums for the NC = 16 TR columns from `part` on: a lane gets those of columns
+// (lane % 16) + 16 tr.  Thread groups take the entries in turn, the groups of a wave and then the waves are added in order.  The loads
+// are made by `colsum_load`, the rest by `colsum_add`: what is requested between them is in flight meanwhile.
 template <int NC>
 constexpr int LS_CL = NC / 4;   // 128 entries ahead, the rest in a loop
 template <int NC>
@@ -121,7 +122,7 @@ __device__ __forceinline__ void colsum_add(const float *__restrict__ part, int n
 
 // Adds the waves' tiles in wave order, stores the result (rows from row0 on, of which those below `rows` count) and leaves the column
 // sums of squares in part[0 .. NC).  A lane's four values of a 16x16 tile are rows 4 (lane / 16) .. + 3 of column lane % 16.
-template <int TM, int TR>
+template <int TM, int TR, bool SUMS = true>
 __device__ __forceinline__ void reduce_store(const f32x4 (&acc)[TM][TR], f32x4 (*red)[TM * TR][64], f32x4_a4 *out, int Rp, int row0, int col0,
                                              int rows, float *part, int w, int lane)
 {
@@ -145,13 +146,14 @@ __device__ __forceinline__ void reduce_store(const f32x4 (&acc)[TM][TR], f32x4 (
         }
         out[(unsigned)((row >> 2) * Rp + col0 + 16 * w + (lane & 15))] = a;
     }
+    if (!SUMS) return;
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
     if (lane < 16) part[16 * w + lane] = ss;
 }
 
-// The contraction range in steps of 16, dealt to the waves in pairs (a pair covers whole 128-byte lines of a row of U)
-__device__ __forceinline__ int step_of(int n, int w) { return 2 * (w + LS_NW * (n >> 1)) + (n & 1); }
+// The contraction range in steps of 16, dealt to nw waves in pairs (a pair covers whole 128-byte lines of a row of U)
+__device__ __forceinline__ int step_of(int n, int w, int nw = LS_NW) { return 2 * (w + nw * (n >> 1)) + (n & 1); }
 
 // q = U p_t with p_t = s + beta_t p_{t-1} (p_0 = s); beta_t = gamma_t / gamma_{t-1}.  Tile: rows 16 TM b .. of U, columns 16 TR nt .. of
 // p.  QUAD: U has at least four elements; otherwise they are read one by one.
@@ -277,8 +279,9 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_up(const LsParams P, int t)
 
 // s = U^T r_{t+1} with r_{t+1} = r_t - alpha_t q_t, x += alpha_t p_t; alpha_t = gamma_t / (column sums of q_t^2).
 // t = -1 is the start: r is taken as it stands, x is cleared.  Tile: columns 16 TM b .. of U, columns 16 TR nt .. of r.
-template <int TM, int TR>
-__global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
+// SPLIT: the GB workgroups of grid y share a tile's rows of U and leave partial tiles (join: GB x IP x Rp), which k_ls_join adds.
+template <int TM, int TR, bool SPLIT>
+__global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t, int share_by, f32x4_a4 *join)
 {
     constexpr int NC = 16 * TR;
     __shared__ f32x4 red[LS_NW][TM * TR][64];
@@ -288,13 +291,14 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
     int b, nt;
     tile_of(P.Rp / NC, b, nt);
     if (b >= P.nbB) return;
+    const int GB = SPLIT ? share_by : 1, g = SPLIT ? (int)blockIdx.y : 0, wg = w + LS_NW * g, nwg = LS_NW * GB;
     const int col0 = NC * nt;
     const f32x4_a4 *__restrict__ rold = P.r[t < 0 ? 0 : (t + 1) & 1] + col0, *__restrict__ q = (t < 0 ? P.r[0] : P.q) + col0;
-    float cs[LS_CL<NC>] = {}, g[TR], gz[TR];
+    float cs[LS_CL<NC>] = {}, gt[TR], gz[TR];
     if (t >= 0) colsum_load<NC>(P.partA + col0, P.nbA, P.Rp, tid, cs);
 #pragma unroll
     for (int tr = 0; tr < TR; tr++) {
-        g[tr] = P.gam[64 * (1 + (t & 1)) + col0 + 16 * tr + l16];
+        gt[tr] = P.gam[64 * (1 + (t & 1)) + col0 + 16 * tr + l16];
         gz[tr] = P.gam[col0 + 16 * tr + l16];
     }
     unsigned uc[TM];
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
     struct Ops { float u[TM][4]; f32x4 rv[TR], qv[TR]; };
     // a lane holds the rows 16 step + 4 (lane / 16) + e of U; beyond the last one r is zero and any row will do
     auto load = [&](Ops &o, int n) __attribute__((always_inline)) {
-        int st = step_of(n, w);
+        int st = step_of(n, wg, nwg);
         st = st < nst ? st : nst - 1;
         const int k = 16 * st + 4 * q16;
 #pragma unroll
@@ -329,7 +333,7 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
 #pragma unroll
         for (int tr = 0; tr < TR; tr++) acc[tm][tr] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     auto mac = [&](const Ops &o, int n, const float (&al)[TR]) __attribute__((always_inline)) {
-        if (step_of(n, w) >= nst) return;
+        if (step_of(n, wg, nwg) >= nst) return;
 #pragma unroll
         for (int e = 0; e < 4; e++)
 #pragma unroll
@@ -343,8 +347,8 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
     load(oa, 0);
     load(ob, 1);
     // this workgroup's share of r_{t+1} in its columns, and its block of x
-    const int n4 = P.rowsP / 4 * NC, share = ((P.rowsP / 4 + P.nbB - 1) / P.nbB) * NC;
-    const int i0 = b * share + tid, iend = n4 < (b + 1) * share ? n4 : (b + 1) * share;
+    const int n4 = P.rowsP / 4 * NC, ns = P.nbB * GB, bs = b * GB + g, share = ((P.rowsP / 4 + ns - 1) / ns) * NC;
+    const int i0 = bs * share + tid, iend = n4 < (bs + 1) * share ? n4 : (bs + 1) * share;
     auto at = [&](int i) { return (unsigned)(i / NC) * (unsigned)P.Rp + (unsigned)(i % NC); };
     const unsigned ir = at(i0 < n4 ? i0 : n4 - 1);
     const f32x4 r0 = rold[ir], q0 = q[ir];
@@ -358,10 +362,10 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
         float d[TR];
         colsum_add<NC>(P.partA + col0, P.nbA, P.Rp, tid, cs, tmp, d);
 #pragma unroll
-        for (int tr = 0; tr < TR; tr++) al[tr] = (d[tr] > 0.0f && g[tr] > P.tol2 * gz[tr]) ? g[tr] / d[tr] : 0.0f;
+        for (int tr = 0; tr < TR; tr++) al[tr] = (d[tr] > 0.0f && gt[tr] > P.tol2 * gz[tr]) ? gt[tr] / d[tr] : 0.0f;
     }
     int n = 0;
-    for (; LS_NW * (n + 2) < nst; n += 2) {
+    for (; nwg * (n + 2) < nst; n += 2) {
         mac(oa, n, al);
         load(oa, n + 2);
         mac(ob, n + 1, al);
@@ -369,13 +373,39 @@ __global__ __launch_bounds__(64 * LS_NW) void k_ls_down(const LsParams P, int t)
     }
     mac(oa, n, al);
     mac(ob, n + 1, al);
-    reduce_store<TM, TR>(acc, red, P.s, P.Rp, 16 * TM * b, col0, P.I, P.partB + (int64_t)b * P.Rp + col0, w, lane);
+    f32x4_a4 *out = SPLIT ? join + (int64_t)g * (P.IP / 4) * P.Rp : P.s;
+    reduce_store<TM, TR, !SPLIT>(acc, red, out, P.Rp, 16 * TM * b, col0, P.I, P.partB + (int64_t)b * P.Rp + col0, w, lane);
     {
         const float ac = TR == 2 && (lane & 16) ? al[TR - 1] : al[0];
         f32x4_a4 *__restrict__ rnew = P.r[t < 0 ? 1 : t & 1] + col0;
         if (i0 < iend) rnew[ir] = r0 - ac * q0;
         for (int i = i0 + 64 * LS_NW; i < iend; i += 64 * LS_NW) rnew[at(i)] = rold[at(i)] - ac * q[at(i)];
-        if (tid < NX) P.x[ix] = t >= 0 ? x0 + ac * p0 : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (tid < NX && g == 0) P.x[ix] = t >= 0 ? x0 + ac * p0 : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+
+// Adds the GB partial tiles of s in group order and leaves the column sums of squares of 32 rows per workgroup in partB.  8 Rp threads.
+__global__ __launch_bounds__(8 * LS_MAXR) void k_ls_join(const LsParams P, int GB, const f32x4_a4 *join)
+{
+    __shared__ float col[8][LS_MAXR];
+    const int c = threadIdx.x % P.Rp, y = threadIdx.x / P.Rp, row = 32 * blockIdx.x + 4 * y;
+    const int64_t e = (int64_t)(row >> 2) * P.Rp + c, gs = (int64_t)(P.IP / 4) * P.Rp;
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 8
+    for (int g = 0; g < GB; g++) v += join[g * gs + e];
+    float ss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        v[i] = row + i < P.I ? v[i] : 0.0f;
+        ss += v[i] * v[i];
+    }
+    P.s[e] = v;
+    col[y][c] = ss;
+    __syncthreads();
+    if (y == 0) {
+        float a = 0.0f;
+        for (int k = 0; k < 8; k++) a += col[k][c];
+        P.partB[(int64_t)blockIdx.x * P.Rp + c] = a;
     }
 }
 
@@ -418,12 +448,12 @@ bool shape_ok(int32_t P, int32_t L, int32_t I, int32_t R)
 // the smallest tile; 10000 x 4000, R = 64: 9.8 ms with it, 6.9 with 2 x 1, 5.7 with 2 x 2 (64 rows or 64 right-hand sides: slower
 // again; 16 x 32 never has the lowest cost).  More tiles than 2048 are made 32 rows high: the workspace has room for that many partial sums.
 struct Tile { int tm, tr; };
+constexpr Tile LS_TILES[] = {{1, 1}, {2, 1}, {2, 2}};
 Tile choose_tile(int m, int Rp)
 {
-    const Tile all[] = {{1, 1}, {2, 1}, {2, 2}};
-    Tile best = all[0];
+    Tile best = LS_TILES[0];
     int64_t bc = 0;
-    for (const Tile &t : all) {
+    for (const Tile &t : LS_TILES) {
         if (Rp % (16 * t.tr)) continue;
         const int64_t nb = (m + 16 * t.tm - 1) / (16 * t.tm), nwg = nb * (Rp / (16 * t.tr));
         if (t.tm == 1 && nb > 2048) continue;
@@ -431,6 +461,33 @@ Tile choose_tile(int m, int Rp)
         if (bc == 0 || cost < bc) { best = t; bc = cost; }
     }
     return best;
+}
+
+// Tall systems have few tiles of k_ls_down with many rows of U each, which a workgroup reads at about 100 GB/s: the workgroups that share
+// a tile, 1 if none do, and then the tile's size.  In ns: a workgroup's reads, all of them at 10 TB/s (caches), the addition of the waves'
+// tiles, and for a shared one the launch that joins the parts.  The estimate is rough, so a tile is shared where it saves a third.  10
+// iterations, one workgroup per tile -> this rule: 2^20 x 64, R = 32 58.7 -> 9.2 ms (46.9 with 16 x 32 rows at a time and four launches); 65536 x
+// 256, R = 16 2.57 -> 0.49; 16384 x 1024, R = 64 0.90 -> 0.69; 4096 x 256, R = 16 207 -> 134 us.  Where a third is not expected it gains or
+// loses a few percent: 4800 x 2000, R = 32 354 -> 364 us, R = 16 316 -> 298.  The sums are shorter, too: at 2^20 rows the error of one
+// workgroup per tile is 6e-6 after three steps, of this rule 0.9e-6.
+int choose_split(int rows, int I, int Rp, int64_t room, Tile &tile)
+{
+    const int64_t IPRp = (int64_t)up32(I) * Rp;
+    auto cost = [&](const Tile &t, int G, int64_t &nwg) {
+        const int64_t bytes = (int64_t)rows * (64 * t.tm + 128 * t.tr);
+        nwg = (int64_t)((I + 16 * t.tm - 1) / (16 * t.tm)) * (Rp / (16 * t.tr)) * G;
+        return bytes / (100 * G) + nwg / G * bytes / 10000 + 500 * t.tm * t.tr + (G > 1 ? 5000 + 100 * G + G * IPRp / 500 : 0);
+    };
+    int64_t nwg, best = cost(tile, 1, nwg) * 2 / 3;
+    int GB = 1;
+    for (const Tile &t : LS_TILES) {
+        if (Rp % (16 * t.tr)) continue;
+        for (int G = 2; G <= 64 && G * IPRp <= room; G *= 2) {
+            const int64_t c = cost(t, G, nwg);
+            if (nwg <= 256 && c < best) { best = c; GB = G; tile = t; }
+        }
+    }
+    return GB;
 }
 
 }  // namespace
@@ -458,16 +515,25 @@ int exat_ls(const float *U, int64_t ldU, int32_t P, int32_t L, int32_t I, const 
     p.tol2 = tol * tol;
     const int64_t nel = (int64_t)(p.rows - 1) * ldU + I;
     p.last4 = (unsigned)(nel >= 4 ? nel - 4 : 0);
-    const Tile ta = choose_tile(p.rows, p.Rp), tb = choose_tile(p.I, p.Rp);
-    p.nbA = (p.rows + 16 * ta.tm - 1) / (16 * ta.tm); p.nbB = (p.I + 16 * tb.tm - 1) / (16 * tb.tm);
+    const Tile ta = choose_tile(p.rows, p.Rp);
+    Tile tb = choose_tile(p.I, p.Rp);
+    p.nbA = (p.rows + 16 * ta.tm - 1) / (16 * ta.tm);
+    const int64_t small = (int64_t)p.nbA * p.Rp + (p.IP / 16) * p.Rp + 3 * 64;
+    const int GB = choose_split(p.rows, p.I, p.Rp, (p.rowsP / 32) * 64 + 3 * (p.IP / 32) * 64 + 512 * 1024 - small, tb);
+    p.nbB = (p.I + 16 * tb.tm - 1) / (16 * tb.tm);
+    const bool split = GB > 1;
+    const int nB = split ? p.IP / 32 : p.nbB;   // partial sums in partB
     const int64_t nx = (int64_t)p.IP * p.Rp, nr = (int64_t)p.rowsP * p.Rp;
     float *w = work;
     auto take = [&](int64_t n) { f32x4_a4 *a = (f32x4_a4 *)w; w += n; return a; };
     p.x = take(nx); p.s = take(nx); p.p[0] = take(nx); p.p[1] = take(nx);
     p.q = take(nr); p.r[0] = take(nr); p.r[1] = take(nr);
     p.partA = w; w += (int64_t)p.nbA * p.Rp;
-    p.partB = w; w += (int64_t)p.nbB * p.Rp;
-    p.gam = w;
+    p.partB = w; w += (int64_t)nB * p.Rp;
+    p.gam = w; w += 3 * 64;
+    f32x4_a4 *join = (f32x4_a4 *)w;
+    const LsParams pd = p;
+    p.nbB = nB;
     auto grid = [&](int nb, int tr) { return dim3((unsigned)((nb + 7) / 8 * 8 * (p.Rp / (16 * tr)))); };
     auto up = [&](int t) {
         const dim3 g = grid(p.nbA, ta.tr), blk(64 * LS_NW);
@@ -477,10 +543,14 @@ int exat_ls(const float *U, int64_t ldU, int32_t P, int32_t L, int32_t I, const 
         else hipLaunchKernelGGL((k_ls_up<2, 2, true>), g, blk, 0, st, p, t);
     };
     auto down = [&](int t) {
-        const dim3 g = grid(p.nbB, tb.tr), blk(64 * LS_NW);
-        if (tb.tm == 1 && tb.tr == 1) hipLaunchKernelGGL((k_ls_down<1, 1>), g, blk, 0, st, p, t);
-        else if (tb.tr == 1) hipLaunchKernelGGL((k_ls_down<2, 1>), g, blk, 0, st, p, t);
-        else hipLaunchKernelGGL((k_ls_down<2, 2>), g, blk, 0, st, p, t);
+        dim3 g = grid(pd.nbB, tb.tr);
+        const dim3 blk(64 * LS_NW);
+        g.y = (unsigned)GB;
+        auto go = [&](auto whole, auto part) { hipLaunchKernelGGL(split ? part : whole, g, blk, 0, st, pd, t, GB, join); };
+        if (tb.tm == 1 && tb.tr == 1) go(k_ls_down<1, 1, false>, k_ls_down<1, 1, true>);
+        else if (tb.tr == 1) go(k_ls_down<2, 1, false>, k_ls_down<2, 1, true>);
+        else go(k_ls_down<2, 2, false>, k_ls_down<2, 2, true>);
+        if (split) hipLaunchKernelGGL(k_ls_join, dim3((unsigned)nB), dim3(8 * p.Rp), 0, st, p, GB, (const f32x4_a4 *)join);
     };
     const unsigned g_init = (unsigned)((nr + 255) / 256 < 4096 ? (nr + 255) / 256 : 4096);
     hipLaunchKernelGGL(k_ls_init, dim3(g_init), dim3(256), 0, st, p, Astack, (int)L);

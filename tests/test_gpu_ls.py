@@ -178,3 +178,30 @@ def test_tiles_and_ends(rows, I, R, ld, off):
         got = got.cpu().numpy().astype(np.float64).reshape((I, R), order="F")
     assert _rel(got, _cgls(Us.astype(np.float64), A.astype(np.float64), iters)) <= TOL
     assert float(work[0]) == 7.5 and float(work[n + 1]) == 7.5
+
+
+@pytest.mark.parametrize("rows,I,R,ld,off", [
+    (4096, 17, 5, 17, 0), (8209, 64, 64, 64, 0), (16391, 33, 48, 34, 1),   # tiles of k_ls_down that several workgroups share
+    (12345, 300, 32, 300, 0), (20000, 700, 64, 700, 0), (1 << 20, 5, 16, 5, 0), (1 << 20, 16, 32, 16, 0),
+])
+def test_tall_systems(rows, I, R, ld, off):
+    """Three steps against the same iteration in fp64.  A sum over the rows is a chain of at most 2^9 additions per accumulator (rows of 2^20
+    in 64 parts, eight waves, four rows per instruction), each rounded by 2^-24: 2^4.5 2^-24 = 1.4e-6 for one sum, 4e-6 for the few that
+    follow each other here; with one workgroup per tile 5e-6 and 6e-6 at 2^20 rows."""
+    print("case", rows, I, R, ld, off, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + I)
+    buf = torch.full((rows * ld + off + 8,), float("nan"), device="cuda")
+    Ud = buf[off:off + rows * ld].view(rows, ld)[:, :I]
+    Ud.copy_(torch.randn(rows, I, generator=g, device="cuda") * rows ** -0.5)
+    A = torch.randn(R, rows, generator=g, device="cuda")
+    n = exat.lib().exat_ls_workspace_floats(1, rows, I, R)
+    work = torch.full((n + 2,), 7.5, dtype=torch.float32).cuda()
+    X, _ = exat.ls(Ud, 1, rows, I, A, R, 3, 0.0, work=work[1:n + 1])
+    again, _ = exat.ls(Ud, 1, rows, I, A, R, 3, 0.0, work=work[1:n + 1])
+    assert torch.equal(X, again)   # fixed order of all sums
+    ref = _cgls(Ud.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.float64).T, 3)
+    err = _rel(X.cpu().numpy().astype(np.float64).reshape((I, R), order="F"), ref)
+    print("  error %.2e" % err, flush=True)
+    assert err <= 4e-6
+    assert float(work[0]) == 7.5 and float(work[n + 1]) == 7.5
