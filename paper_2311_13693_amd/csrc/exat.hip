@@ -245,6 +245,25 @@ int choose_groups(int T4, int64_t nk, int nw)
     return best;
 }
 
+// Whether rows of Q that fit stay in LDS over the chunks.  They save a read of Q per chunk and halve the ring of X tiles.  2600 calls
+// of 33 to 512 values in i, 129 to 768 in j, 40 to 400 slices and 384 to 2048 rows, both builds in turn (speed with over without): with
+// more than 32 columns of Q the saving is the larger part (fp32 1.06, never below 1; bf16 1.05), except for
+// bf16 in two chunks of fewer than six stages in one round of workgroups that fills the chip (1.0, down to 0.95) and in chunks of two
+// stages where half the compute units are idle.  With up to 32 columns Q is half as large: fp32 gains (1.03) but
+// in two chunks of small slices of a single group (0.94 to 0.98); bf16 needs 57000 values a slice (512 rows, 100 by 300: 0.95; 192
+// by 300: 1.02) or, from three stages on, idle compute units (1.02) or many rows (1280 rows, 1.04).  Where i ends inside a piece of
+// four the read of the last stage waits: bf16 gains (1.05, five stages 1.2) unless that is the third of four stages (0.85 to 0.98).
+bool mp_keep_q(const Mode12Params &mp, const MpParams &q, bool bf, int64_t nk)
+{
+    const int64_t nj = mp.j1 - q.ja0, ni = mp.i1 - (mp.i0 & ~(int64_t)31), nstage = cdiv(ni, 32);
+    if (nj <= 128) return false;
+    const bool full = nk * mp.G > 128;
+    if (!bf) return mp.MT == 2 || !full || mp.G > 1 || nj > 256 || ni * nj >= 16000;
+    if (mp.i0 % 4 != 0 || mp.i1 % 4 != 0) return nstage != 3;
+    if (mp.MT == 2) return full ? nj > 256 || nstage >= 6 || nk * mp.G <= 200 || nk * mp.G > 256 : nstage >= 3;
+    return ni * nj >= 57000 || (nstage >= 3 && (!full || (q.T4 >= 10 && ni * nj >= 20000)));
+}
+
 // Runs of about 32 slices (a workgroup per compute unit of an XCD), as many as give every XCD the same number of (run, row group)
 // pairs.
 void slice_runs(int G, int64_t nk, int *nblk, int *bs)
@@ -342,12 +361,13 @@ int run_pieces(exat_plan_s *pl, Mode12Params mp, bool generated, bool pipelined,
         if (q.ja0 + 128 * cdiv(mp.j1 - q.ja0, 128) > pl->Jpad) q.ja0 = mp.j0 & ~(int64_t)127;
         mp.G = nwc > 1 ? 1 : choose_groups(q.T4, nk, nw);
         // Q in LDS where the workgroup has its own compute unit, 512 rows of it fit beside the ring and more than one chunk adds to it (up
-        // to 50 columns m for fp32, 60 for bf16) or four wave columns do (beside the whole ring, short calls need it: 20 and 40);
-        // generated sources need the room for their operands, two fp16 pieces have longer rows in the configurations they are used in
+        // to 50 columns m for fp32, 60 for bf16; see mp_keep_q) or four wave columns do (beside the whole ring, short calls need it: 20
+        // and 40); generated sources need the room for their operands, two fp16 pieces have longer rows in the configurations they are
+        // used in
         auto room = [&](auto c1, auto c3) { return 160 * 1024 - (bf ? decltype(c1)::lds_bytes(false, 1) : decltype(c3)::lds_bytes(false, 1)); };
         q.qs = 0;
         if (!split && !generated && nwc == 4) q.qs = mp_qrow(pl->d.M, 512, room(Mode12MpCfg<1, 8, 4, true>(), Mode12MpCfg<3, 8, 4, true>()));
-        if (!split && !generated && nw == 8 && nwc == 1 && mp.j1 - q.ja0 > 128)
+        if (!split && !generated && nw == 8 && nwc == 1 && mp_keep_q(mp, q, bf, nk))
             q.qs = mp_qrow(pl->d.M, 512, room(Mode12MpCfg<1, 8, 1, true>(), Mode12MpCfg<3, 8, 1, true>()));
         if (q.qs) kshift = 0;
         q.nblk = q.bs = 0;

@@ -113,7 +113,8 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
     }
 }
 
-// QL: the workgroup's rows of Q stay in LDS, behind the ring, until its last chunk (rows of MpParams::qs floats).  The Q of the 32
+// QL: the workgroup's rows of Q stay in LDS, behind the ring, until its last chunk (rows of MpParams::qs floats), which adds them to its own
+// and writes the sum to memory (through LDS as well: 2 to 5 % of a call of two or three chunks).  The Q of the 32
 // workgroups of an XCD is as large as its L2, and with the chunks' other traffic every chunk read it from memory, in front of a wait
 // nothing covers.  The ring is half as long for it, a barrier after every second stage (bf16) or every stage (fp32).  Before -> now:
 // 1000^3 bf16, 2400 rows 7.24 -> 6.46 ms; fp32: 1000^3, 1550 rows 16.6 -> 16.2 ms, 500^3 blocks of it 20.9 -> 20.1, 512^3, 512 rows 658 -> 644
@@ -164,9 +165,9 @@ __device__ __forceinline__ void mp_q_st(float *row, int c, int qs, const f32x4 &
 // Qk points to the rows of this slice (and wave column).
 template <int NP, int RT, int CT, int MTC, int RSTRIDE, bool QL>
 __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &mp, float *Qk, f32x16 (&acc)[RT][CT], int wrow0, int ntile,
-                                         int64_t jc, bool first_chunk, int lane, float *ql)
+                                         int64_t jc, bool first_chunk, int lane, float *ql, bool keep)
 {
-    constexpr bool F16 = NP == 2;
+    constexpr bool F16 = NP == 2, LATE = QL && CT == 4;   // LATE: old rows of Q are read where they are needed (one wave column)
     constexpr int MP = 32 * MTC, NZ = NP == 2 ? 2 : 3, NV = NP;
     typedef std::conditional_t<NP == 1, mp_terms_z1, mp_terms<NP>> terms;
 #pragma unroll
@@ -221,7 +222,7 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
 #pragma unroll
                             for (int b = 0; b < 4; b++) {
                                 qold[m][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                                if (!first_chunk && mine) qold[m][b] = QL ? mp_q_ld(Qt, 32 * m + 8 * b + 4 * hi, mp.qs) : *(const f32x4 *)(Qt + 32 * m + 8 * b);
+                                if (!LATE && !first_chunk && mine) qold[m][b] = QL ? mp_q_ld(Qt, 32 * m + 8 * b + 4 * hi, mp.qs) : *(const f32x4 *)(Qt + 32 * m + 8 * b);
                             }
                     }
                     __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the MFMAs
@@ -242,9 +243,11 @@ __device__ __forceinline__ void mode2_mp(const Mode12Params &p, const MpParams &
 #pragma unroll
                         for (int b = 0; b < 4; b++) {
                             f32x4 o;
+                            if (LATE && !first_chunk) qold[m][b] = mp_q_ld(Qt, 32 * m + 8 * b + 4 * hi, mp.qs);
 #pragma unroll
                             for (int r = 0; r < 4; r++) o[r] = d[m][4 * b + r] + qold[m][b][r];
-                            if (QL) mp_q_st(Qt, 32 * m + 8 * b + 4 * hi, mp.qs, o);
+                            if (QL && (keep || !LATE)) mp_q_st(Qt, 32 * m + 8 * b + 4 * hi, mp.qs, o);
+                            else if (QL) *(f32x4 *)(Qk + (int64_t)q * MP + 4 * hi + 32 * m + 8 * b) = o;
                             else *(f32x4 *)(Qt + 32 * m + 8 * b) = o;
                         }
                 }
@@ -686,8 +689,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
         const int64_t jw = jc + wc * CT * 32;
         const int ntile = two ? 2 : (own ? 1 : 0);
         float *ql = (float *)(smem + NSLOT * SLOT) + (64 * NWR * wc + 32 * wr) * mp.qs;
-        if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
-        else mode2_mp<NP, RT, CT, 1, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql);
+        const bool keep = jc + COLS < p.j1;   // (one wave column:) the last chunk's rows go to memory
+        if (p.MT == 2) mode2_mp<NP, RT, CT, 2, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql, keep);
+        else mode2_mp<NP, RT, CT, 1, 32 * NWR, QL>(p, mp, Qk, acc, wrow0, ntile, jw, first_chunk, tid & 63, ql, keep);
         if constexpr (QL && NWC > 1) {   // behind the last chunk: the wave columns' rows are added up on their way to memory
             if (jc + COLS >= p.j1) {
                 __syncthreads();
@@ -700,19 +704,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
                     for (int w = 1; w < NWC; w++) v += mp_q_ld(qb + (64 * NWR * w + r) * mp.qs, c, mp.qs);
                     *(f32x4 *)(Qk + (int64_t)r * p.Mpad + c) = v;
                 }
-            }
-        } else if constexpr (QL) {   // behind the last chunk: the wave's rows go to memory
-            if (jc + COLS >= p.j1) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const int m4 = 8 * p.MT;
-                for (int rt = 0; rt < ntile; rt++)
-                    for (int e = tid & 63; e < 32 * m4; e += 64) {
-                        const int r = rt * 32 * NWR + e / m4, c = 4 * (e % m4);
-                        const f32x4 v = mp_q_ld(ql + r * mp.qs, c, mp.qs);
-                        if (wrow0 + r < p.PL) *(f32x4 *)(Qk + (int64_t)(wrow0 + r) * p.Mpad + c) = v;
-                    }
             }
         }
     }
