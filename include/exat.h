@@ -282,7 +282,10 @@ int exat_stage1_last_timing(exat_stage1_t s, float *ms_mode12, float *ms_mode3);
  * (update A, then B, then C; each the least-squares solution with the other two fixed,
  * A <- Y_(1) (C kr B) [(C^T C) * (B^T B)]^{-1}, by elimination without pivoting on the R x R normal matrix)
  * for all P replicas at once; sums in fp32, the elimination and the product with the inverse in fp64.  There is no convergence test: the caller
- * chooses the number of sweeps.
+ * chooses the number of sweeps.  The products of Y with a factor take both as the sums of three bf16 pieces (six of the nine products,
+ * at most 2^-26 of a product is left out).  Range: the normal matrices (F1^T F1) * (F2^T F2) and the products of the
+ * unfolded Y with C kr B etc., which are formed in fp32, have to be in its range, as with fp32 products; values of Y below 2^-110 lose bits,
+ * above 3.39e38 they give NaN.
  *   Y      device, P*L*M*N floats in the layout exat_compress writes: Y[l + L*(m + M*(n + N*p))]; not modified
  *   A,B,C  device, in: start values, out: result; per replica column-major L x R, M x R, N x R:
  *          A[l + L*(r + R*p)] etc.

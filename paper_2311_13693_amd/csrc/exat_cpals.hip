@@ -9,7 +9,10 @@
 //      there is nothing to wait for); the first slab's writes the factor to memory.
 //   2. NS workgroups compute their share of this update's MTTKRP, Mx[d0,r] = sum_{d2} (sum_{d1} Y[d0,d1,d2] F1[d1,r]) F2[d2,r], over a
 //      slab of the outer contraction index, the inner sum on the bf16 matrix cores with both operands as three bf16 pieces (six of the
-//      nine products; what is left out is at most 2^-26 of a product).  F1 is split once; the sum over d1 has to lie in the range of fp32.
+//      nine products; what is left out is at most 2^-26 of a product).  F1 is split once.  The inner sum and the pieces need no range record:
+//      with Y of the size of A B C, |Y F1| = |F1 F2| |F1 F3| is a root of the product of two normal matrices, so what would leave the range
+//      of fp32, or have pieces below the smallest bf16 value (2^-133; a piece is at least 2^-17 of its value), meets a normal matrix that
+//      has left it before.  8450 scalings of Y and the start factors by 10^-36 to 10^36: all that worked with fp32 products still do.
 //   3. Meanwhile one workgroup forms this update's normal matrix G = (F2^T F2) * (F1^T F1) (Gram matrices on the fp32 matrix cores; G
 //      does not depend on the MTTKRP) and inverts it for the next launch.
 // The tensor is read where it lies: a lane holds one row of the updated mode, and the order of the contraction indices inside
@@ -203,7 +206,8 @@ __device__ __forceinline__ bool invert_normal(const float *Fa, const float *Fb, 
 // Element i of an array whose start is the same in all lanes: one 32-bit offset per lane, no 64-bit address arithmetic on the vector unit
 __device__ __forceinline__ float at(const float *base, int i) { return *(const float *)((const char *)base + 4u * (unsigned)i); }
 
-// eight fp32 values as three bf16 pieces each, x = h + m + l (exact: three times eight significand bits), in operand order
+// eight fp32 values as three bf16 pieces each, x = h + m + l, in operand order: exact (three times eight significand bits) from 2^-110,
+// where the last bit of l is the smallest bf16 value, up to the largest bf16 value, 3.39e38, above which h is infinite
 __device__ __forceinline__ void split8(const float *x, u32x4 (&w)[3])
 {
 #pragma unroll

@@ -254,3 +254,29 @@ def test_reads_end_with_the_tensors(L, M, N, R, P):
         torch.cuda.synchronize()
         got.append(torch.cat([f.flatten() for f in F]).view(torch.int32))
     assert torch.equal(*got)
+
+
+# The range of Y and the factors: while every normal matrix, (F1^T F1) * (F2^T F2) in fp32, and its right-hand side are, so are the bf16
+# pieces and the inner sums Y F1 (with Y of the size of A B C, |Y F1| = |F1 F2| |F1 F3|, a root of the product of two normal matrices).
+# Powers of two pass through every operation unchanged: B0 2^b, C0 2^c and Y 2^y give A 2^(y-b-c), B 2^b and C 2^c, bit for bit.
+@pytest.mark.parametrize("P", [3, 140])   # with workgroups that invert, and without
+@pytest.mark.parametrize("y,b,c", [(0, 40, -40), (0, -45, 45), (-66, -22, -22), (60, 20, 20), (40, 0, 0), (-50, 0, 0), (30, 40, -10), (-30, 5, -35), (10, -40, 30)])
+def test_scaled_tensors_and_factors(y, b, c, P):
+    print("case", y, b, c, P, flush=True)
+    L, M, N, R = 33, 20, 41, 12
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    F = [torch.randn(P, R, d, generator=g, device="cuda") for d in (L, M, N)]
+    Y = torch.empty(P, N, M, L, device="cuda")
+    for p in range(P):
+        Y[p] = ((F[2][p][:, :, None] * F[1][p][:, None, :]).reshape(R, -1).T.contiguous() @ F[0][p]).view(N, M, L)
+    Y += 0.1 * torch.randn(Y.shape, generator=g, device="cuda")
+    start = [f + 0.5 * torch.randn(f.shape, generator=g, device="cuda") for f in F]
+    out = []
+    for e in ((0, 0, 0), (y, b, c)):
+        G = [start[0].clone(), start[1] * 2.0 ** e[1], start[2] * 2.0 ** e[2]]
+        exat.cpals(Y * 2.0 ** e[0], L, M, N, P, R, 3, *G)
+        out.append([G[0] * 2.0 ** (e[1] + e[2] - e[0]), G[1] * 2.0 ** -e[1], G[2] * 2.0 ** -e[2]])
+    assert bool(torch.isfinite(out[0][0]).all())
+    for s, t in zip(*out):
+        assert torch.equal(s, t)
