@@ -206,11 +206,11 @@ def test_collinear_factors(R, mix):
         assert res <= 2e-6 and err <= 8 * 2.0 ** -24 * cond
 
 
-# Every number of slabs, both double-buffered and not, and (10^3 and 8^3 at rank 40, many replicas) the case without room in the workspace
+# Every number of slabs (1 to 8: min(8, 256 / P - 1), or fewer where the outer extent is not that much longer), both double-buffered and not, and (10^3 and 8^3 at rank 40, many replicas) the case without room in the workspace
 # for the inverses.  The last update of a sweep is C <- Mx G^-1 with the returned A and B: |C G - Mx| against what goes into it, |C| |G| and
 # the absolute products in Mx, each rounded with a few 2^-24: 2e-6.  The workspace has a guard behind it and starts 4 bytes off.
 @pytest.mark.parametrize("L,M,N,R,P", [(33, 18, 17, 16, 1), (17, 31, 49, 20, 30), (64, 64, 64, 33, 52), (15, 16, 1, 5, 70), (9, 20, 41, 32, 127),
-                                       (5, 3, 2, 4, 128), (30, 30, 30, 17, 257), (8, 8, 8, 40, 600), (10, 9, 10, 40, 700), (8, 9, 10, 64, 900)])
+                                       (20, 64, 64, 16, 1), (50, 50, 50, 32, 42), (33, 40, 20, 20, 51), (5, 3, 2, 4, 128), (30, 30, 30, 17, 257), (8, 8, 8, 40, 600), (10, 9, 10, 40, 700), (8, 9, 10, 64, 900)])
 def test_slabs_and_workspace(L, M, N, R, P):
     print("case", L, M, N, R, P, flush=True)
     g = torch.Generator(device="cuda")
@@ -226,7 +226,7 @@ def test_slabs_and_workspace(L, M, N, R, P):
               for y, a, b in ((Y.double(), A, B), (Y.double().abs(), A.abs(), B.abs()))]
     G = torch.bmm(A.transpose(1, 2).contiguous(), A) * torch.bmm(B.transpose(1, 2).contiguous(), B)
     ok = torch.linalg.cond(G) < 1e7   # the others are not positive definite in fp32
-    assert bool(ok.any())
+    assert int(ok.sum()) >= 0.95 * P   # (all of them are, with these start values)
     worst = ((torch.bmm(C, G) - Mx).abs() / (torch.bmm(C.abs(), G.abs()) + Ma))[ok].max().item()
     print("  %d of %d replicas, residual %.2e" % (int(ok.sum()), P, worst), flush=True)
     assert worst <= 2e-6
