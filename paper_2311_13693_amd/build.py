@@ -12,9 +12,9 @@ _PUBLIC = os.path.join(os.path.dirname(HERE), "include", "exat.h")
 UNITS = {
     "exat.hip": ["exat_device.h", "exat_common.h", "exat_mode12.h", "exat_mode2.h", "exat_gen.h",
                  "exat_mode12_v3.h", "exat_mode12_v4.h", "exat_mode12_mp.h", "exat_aux.h"],
-    "exat_stage1.hip": [],
-    "exat_cpals.hip": [],
-    "exat_ls.hip": [],
+    "exat_stage1.hip": ["exat_lds.h"],
+    "exat_cpals.hip": ["exat_lds.h"],
+    "exat_ls.hip": ["exat_lds.h"],
     "exat_probe.hip": [],
 }
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-w",

@@ -31,6 +31,7 @@
 // A).  A launch is now bound by two chains of about 11 us: partial results, product, Gram matrices (4 us), inverse;
 // and the tensor's way from the last-level cache (33.5 MB, more than the L2 holds).  Rank 64: 1.34 -> 0.78 ms; 16^3, rank 8: 0.35 -> 0.24.
 #include "../../include/exat.h"
+#include "exat_lds.h"
 
 #include <hip/hip_runtime.h>
 
@@ -59,21 +60,12 @@ struct CpStep {
     float *pout;            // the same of this update
     int64_t rs;             // the same for every update, whatever its extent: a replica overwrites its own partial results only
     int D[3];               // L, M, N
-    int R, NSin, NS, DS;    // NS slabs of DS values of the outer contraction index
+    int R, NSin, DS;        // slabs of the update before; values of the outer contraction index per slab of this one
     int prev, mode;         // updated factor of the update before and of this one (0, 1, 2), or -1: none
-    int P;
     int32_t *status;        // optional, [replica]: incremented by every update whose normal matrix has a non-positive pivot
     const f64_a4 *gin;      // [replica][16 NB][16 NB]: inverse of the normal matrix of the update before this one
     f64_a4 *gout;           // the same of this update
 };
-
-// Barrier for what goes through LDS: requests to memory stay in flight across it
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // 1/x to within an ulp or two: the hardware's estimate (more than 20 bits) and two Newton steps.  The pivots come from fp32 values, far
 // inside the range of fp64; a zero gives NaN.
@@ -85,7 +77,7 @@ __device__ __forceinline__ double recip(double x)
 }
 
 // Inverse of the normal matrix G = (F2^T F2) * (F1^T F1) of the factors Fa and Fb, as g[a][b] = element (ty + 16 a, tx + 16 b) of thread
-// 16 ty + tx, zero beyond R.  All 256 threads call it; `bad` is set if a pivot is not positive.
+// 16 ty + tx, zero beyond R; the first 256 threads hold it.  All threads call it; `bad` is set if a pivot is not positive.
 template <int RC, int NB>
 __device__ __forceinline__ bool invert_normal(const float *Fa, const float *Fb, float (*Gt)[1024], float *G, double (*rowb)[64][4], double (*colb)[64][4],
                                               int R, int tid, int w, double (&g)[NB][NB])
@@ -360,7 +352,7 @@ __global__ __launch_bounds__(CP_NT) void k_cpals_step(const CpStep p)
                 if (tid < RB * RB) put_gi((tid + CP_NT * x) / RB, (tid + CP_NT * x) % RB, gl[x]);
         }
         lds_barrier();
-        // X = Mx G^{-1}, accumulated in fp64: 16 x 16 tile (rt, ct) to wave (rt NB + ct) mod 4
+        // X = Mx G^{-1}, accumulated in fp64: 16 x 16 tile (rt, ct) to wave (rt NB + ct) mod CP_NW
         const int rtn = (D0 + 15) / 16, l16 = lane & 15, q16 = lane >> 4;
         for (int t = w; t < rtn * NB; t += CP_NW) {
             const int row = 16 * (t / NB) + l16, c = 16 * (t % NB) + l16;
@@ -534,7 +526,7 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
     float *part[2] = {work, own && NS == 1 ? work : work + (int64_t)P * NS * one};
     f64_a4 *ginv[2] = {(f64_a4 *)(work + 2 * P * NS * one), (f64_a4 *)(work + 2 * P * NS * one) + P * RB * RB};
     CpStep c;
-    c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.P = P; c.rs = NS * one; c.status = status;
+    c.Y = Y; c.F[0] = A; c.F[1] = B; c.F[2] = C; c.D[0] = L; c.D[1] = M; c.D[2] = N; c.R = R; c.rs = NS * one; c.status = status;
     c.NSin = 1; c.prev = -1;
     auto launch = [&](int ns, bool inverse) {
         const dim3 grid((unsigned)P, (unsigned)(ns + (inverse && !own ? 1 : 0)));
@@ -554,13 +546,13 @@ int exat_cpals_checked(const float *Y, int32_t L, int32_t M, int32_t N, int32_t 
         const int D2 = c.mode == 2 ? M : N;
         int ns = NS < D2 ? NS : D2;
         c.DS = (D2 + ns - 1) / ns;
-        c.NS = (D2 + c.DS - 1) / c.DS;
+        ns = (D2 + c.DS - 1) / c.DS;
         c.pin = part[(t + 1) & 1]; c.pout = part[t & 1];
         c.gin = ginv[(t + 1) & 1]; c.gout = ginv[t & 1];
-        launch(c.NS, true);
-        c.NSin = c.NS; c.prev = c.mode;
+        launch(ns, true);
+        c.NSin = ns; c.prev = c.mode;
     }
-    c.pin = part[(3 * sweeps + 1) & 1]; c.pout = nullptr; c.mode = -1; c.NS = 1;
+    c.pin = part[(3 * sweeps + 1) & 1]; c.pout = nullptr; c.mode = -1;
     c.gin = ginv[(3 * sweeps + 1) & 1]; c.gout = nullptr;
     launch(1, false);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;

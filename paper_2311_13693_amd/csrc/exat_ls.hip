@@ -21,6 +21,7 @@
 // iterates drift away again), so a column whose normal-equation residual has fallen to `tol` times its start value
 // is frozen: its alpha and beta are zero from then on, which every workgroup decides alike from the same sums.
 #include "../../include/exat.h"
+#include "exat_lds.h"
 
 #include <hip/hip_runtime.h>
 
@@ -73,14 +74,6 @@ __device__ __forceinline__ void tile_of(int nct, int &b, int &nt)
     const int id = blockIdx.x, y = id >> 3;
     nt = y % nct;
     b = (y / nct) * 8 + (id & 7);
-}
-
-// Barrier for what goes through LDS: requests to memory stay in flight across it
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Column sums of a [n][Rp] array of per-workgroup partial sums for the NC = 16 TR columns from `part` on: a lane gets those of columns

@@ -28,7 +28,7 @@
 // after every H-th stage only (between two barriers the slots read and the slots written are disjoint).
 // Measured (one call with mode 3, before -> now): 128^3 fp32, 64 stacked rows 34.9 -> 17 us; 512^3 fp32, 512 rows 1.05 -> 0.66 ms
 // (fp32 matrix instruction before); 1000^3 fp32, 1550 rows 39.2 -> 16.2 ms and 1000^3 bf16, 2400 rows 25.8 -> 6.5 ms (generic
-// kernel before: 1000 is no multiple of a stage);
+// kernel before: 1000 is no multiple of a stage); slower only, by the range check's launch: 128 x 128 x 91 bf16, 304 rows 18.3 -> 20.1 us;
 // 1024^3 in two fp16 pieces, 2048 rows 14.2 -> 12.0 ms; 512^3 generated in fp32 9.9 -> 7.0 ms.  In the stage loop of the fp32 cases the matrix pipe runs at
 // about 1.5 PFLOP/s on random operands, where a large bf16 product of the vendor's library reaches 1.28.
 #pragma once
@@ -118,7 +118,7 @@ __device__ __forceinline__ void mp_split2(float a, float b, uint32_t (&w)[NP])
 // workgroups of an XCD is as large as its L2, and with the chunks' other traffic every chunk read it from memory, in front of a wait
 // nothing covers.  The ring is half as long for it, a barrier after every second stage (bf16) or every stage (fp32).  Before -> now:
 // 1000^3 bf16, 2400 rows 7.24 -> 6.46 ms; fp32: 1000^3, 1550 rows 16.6 -> 16.2 ms, 500^3 blocks of it 20.9 -> 20.1, 512^3, 512 rows 658 -> 644
-// us, 250^3 263 -> 257, 64 x 1000 x 300, 820 rows 720 -> 650; the same sums in the same order.
+// us, 250^3 263 -> 246, 64 x 1000 x 300, 820 rows 674 -> 607; the same sums in the same order.
 // With NWC = 4 the wave columns' partial rows are added there too, behind the last chunk, and mode 3 reads a quarter: 128^3 fp32, 64 rows
 // 22.3 -> 17.1 us, bf16 18.9 -> 14.7; 512^3 bf16, 128 rows 153 -> 104 us.
 template <int NP, int NW, int NWC, bool QL = false>
@@ -137,8 +137,8 @@ struct Mode12MpCfg {
     static_assert(UNR % DU == 0 && UNR % DX == 0 && (UNR % H == 0 || H % UNR == 0), "");
 };
 
-// Floats per row of Q in LDS, where `lds` bytes are left for `rows` rows: an odd multiple of 4 or, where that is too much, the number
-// of columns made even (neighbouring rows then start in different banks either way); 0 if there is no room.  Rows are read and written
+// Floats per row of Q in LDS, where `lds` bytes are left for `rows` rows: an odd multiple of 4 or, where that is too much, an odd
+// multiple of 2 (neighbouring rows start in different banks either way); 0 if there is no room.  Rows are read and written
 // 8 bytes at a time: `mp_q_ld`, `mp_q_st` of columns c .. c+3, of which those beyond the row are zero.
 inline int mp_qrow(int M, int rows, int lds)
 {

@@ -21,6 +21,7 @@
 //                    are what kept it below half of the HBM peak.
 // Every sum has a fixed order, so results are bit-identical from run to run.
 #include "../../include/exat.h"
+#include "exat_lds.h"
 
 #include <hip/hip_runtime.h>
 
@@ -259,14 +260,6 @@ template <int N, int I_, typename F> __device__ __forceinline__ void s1_static_f
 }
 template <int N, typename F> __device__ __forceinline__ void s1_static_for(F &&f) { s1_static_for_(f, std::integral_constant<int, 0>(), std::integral_constant<int, N>()); }
 
-// Barrier for what goes through LDS: requests to memory stay in flight across it
-__device__ __forceinline__ void s1_lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), D = steps of X a wave keeps in flight, RAGGED: I is no
 // multiple of 32 (a request past the end of a column goes past the end of the buffer, which reads nothing and gives zero: zeroing
 // what has arrived made every request wait for its data, 1000 x 500 x 800, A1 = 64: 0.68 -> 0.42 ms).
@@ -327,7 +320,8 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
 #pragma unroll
         for (int e = 0; e < 16; e++) qacc[i][e] = 0.0f;
 
-    // the slice as a buffer: a request past its end (columns past J) returns zeros
+    // The slice as a buffer: a request past its end (columns past J) returns zeros.  The range check counts the scalar offset in and does
+    // not wrap around: measured on gfx950 with scalar offsets up to and beyond the end, inside one allocation.
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)Xk, 0, (int)(p.I * p.J * 4), 0x00020000);
     const int x_lane = (int)(((lane >> 3) * p.I + 4 * (lane & 7)) * 4);        // column lane/8 of a load's eight, piece lane%8
     const int f_lane = lane * 16;
@@ -398,7 +392,7 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
         };
 #pragma unroll
         for (int jb = 0; jb < VD - 1; jb++) request_v(jb, vr[jb]);
-        s1_lds_barrier();   // every wave is done with its slots: the Z^T fragments take the LDS over
+        lds_barrier();   // every wave is done with its slots: the Z^T fragments take the LDS over
 #pragma unroll
         for (int rt = 0; rt < RT; rt++)
 #pragma unroll
@@ -413,7 +407,7 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
                     *(s1_f32x4 *)dst = lo;
                     *(s1_f32x4 *)(dst + 256) = up;
                 }
-        s1_lds_barrier();
+        lds_barrier();
 #pragma unroll
         for (int jb = 0; jb < 16; jb++) {
             if (jb + VD - 1 < 16) request_v(jb + VD - 1, vr[(jb + VD - 1) % VD]);
@@ -453,7 +447,7 @@ __global__ __launch_bounds__(64 * SM_NW, WPC) void k_stage1_mfma(const S1MParams
             for (int ct = 0; ct < SM_CT; ct++)
 #pragma unroll
                 for (int e = 0; e < 16; e++) acc[rt][ct][e] = 0.0f;
-        s1_lds_barrier();   // the slots take the LDS back
+        lds_barrier();   // the slots take the LDS back
     };
 
     s1_static_for<D>([&](auto dc) {
