@@ -28,8 +28,8 @@
 // instructions (6 us a launch) and four waves; 0.62 with a workgroup of its own for the inverse, 0.55 with eight waves and 32-bit
 // offsets, 0.49 with bf16 pieces, 0.42 with the requests in the order of their use and none under a condition, and with four pivots
 // per step (7.2 -> 5 us), 0.385 with a descriptor per outer value in place of scalar offsets (60 to 89 scalars were spilled in the update of
-// A).  A launch is now bound by two chains of about 11 us: partial results, product, Gram matrices (4 us), inverse;
-// and the tensor's way from the last-level cache (33.5 MB, more than the L2 holds).  Rank 64: 1.34 -> 0.78 ms; 16^3, rank 8: 0.35 -> 0.24.
+// A).  A launch is now bound by two chains of about 10 us: partial results, product, Gram matrices (4 us), inverse;
+// and the tensor's way from the last-level cache (33.5 MB, more than the L2 holds).  Rank 64: 1.34 -> 0.82 ms; 16^3, rank 8: 0.35 -> 0.21.
 #include "../../include/exat.h"
 #include "exat_lds.h"
 

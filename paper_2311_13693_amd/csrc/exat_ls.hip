@@ -12,7 +12,7 @@
 // so no tile's sum is split among workgroups (the two launches that joined the parts cost what the products did), nothing but LDS is
 // waited for at a barrier, and nothing is requested that is not used (requests beyond the end of the range: +15 %).  In tall systems
 // k_ls_down has too few tiles for that: several workgroups share one, and k_ls_join adds their parts (choose_split).
-// 2048 x 1024, 32 right-hand sides, 40 iterations: 1.25 ms with split tiles and joins, 0.62 ms now (up 6.5, down 9.2 us; a workgroup of
+// 2048 x 1024, 32 right-hand sides, 40 iterations: 1.25 ms with split tiles and joins, 0.62 ms now (up 6.7, down 9.2 us; a workgroup of
 // k_ls_down reads 384 KB, at about 100 GB/s); 10000 x 4000, 64 right-hand sides: 18.2 -> 5.7 ms.
 // Every workgroup also writes its share of the new p (r) into the other of two buffers, so no launch reads what
 // it writes.  The squared column norms that alpha and beta need are left as per-workgroup partial sums and added
