@@ -250,10 +250,11 @@ int choose_groups(int T4, int64_t nk, int nw)
 // more than 32 columns of Q the saving is the larger part (fp32 1.06, never below 1; bf16 1.05), except for bf16 in two chunks of fewer
 // than six stages in one round of workgroups that fills the chip (1.0, down to 0.95) and in chunks of two stages where half the compute
 // units are idle.  With up to 32 columns Q is half as large: fp32 gains (1.03) but in two chunks of small slices of a single group (0.94
-// to 0.98); bf16 with replicas of at least a row tile gains from 57000 values a slice on (512 rows, 100 by 300: 0.95; 192 by 300: 1.02)
-// or, from three stages on, with idle compute units (1.02) or many rows (1280 rows, 1.04), with smaller replicas (every tile has several,
-// each a pass over its rows of Q) it is as fast at most (16 rows 1.0, 20 rows 0.96 to 1.0).  Where i ends inside a piece of four the
-// read of the last stage waits: bf16 gains (1.05, five stages 1.2) unless that is the third of four stages (0.85 to 0.98).
+// to 0.98); bf16 gains from 57000 values a slice on (512 rows, 100 by 300: 0.95; 192 by 300: 1.02) or, with replicas of at least a row
+// tile and from three stages on, with idle compute units (1.02) or many rows (1280 rows, 1.04).  Where more than two replicas share a
+// row tile (each a pass over its rows of Q) it gains from 120000 values on (replicas of 20 rows: 0.96 to 1.02 below, 0.99 to 1.08
+// above).  Where i ends inside a piece of four the read of the last stage waits: bf16 gains (1.05, five stages 1.2) unless that is the
+// third of four stages (0.85 to 0.98).
 bool mp_keep_q(const Mode12Params &mp, const MpParams &q, bool bf, int64_t nk)
 {
     const int64_t nj = mp.j1 - q.ja0, ni = mp.i1 - (mp.i0 & ~(int64_t)31), nstage = cdiv(ni, 32);
@@ -262,8 +263,8 @@ bool mp_keep_q(const Mode12Params &mp, const MpParams &q, bool bf, int64_t nk)
     if (!bf) return mp.MT == 2 || !full || mp.G > 1 || nj > 256 || ni * nj >= 16000;
     if (mp.i0 % 4 != 0 || mp.i1 % 4 != 0) return nstage != 3;
     if (mp.MT == 2) return full ? nj > 256 || nstage >= 6 || nk * mp.G <= 200 || nk * mp.G > 256 : nstage >= 3;
-    if (mp.L < 32) return false;
-    return ni * nj >= 57000 || (nstage >= 3 && (!full || (q.T4 >= 10 && ni * nj >= 20000)));
+    const int64_t least = mp.L >= 32 || mp.L == 16 ? 57000 : 120000;
+    return ni * nj >= least || (mp.L >= 32 && nstage >= 3 && (!full || (q.T4 >= 10 && ni * nj >= 20000)));
 }
 
 // Runs of about 32 slices (a workgroup per compute unit of an XCD), as many as give every XCD the same number of (run, row group)

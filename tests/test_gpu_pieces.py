@@ -364,12 +364,12 @@ def test_rows_in_lds(dtype, M, I, J, P, L):
         assert _err(plan.compress(X, Y), R) <= TOL
 
 
-# Around the rule for keeping rows of Q in LDS (bf16: three stages, 57000 values a slice, the third of four stages cut inside a piece of four;
+# Around the rule for keeping rows of Q in LDS (bf16: three stages, 57000 or 120000 values a slice, the third of four stages cut inside a piece of four;
 # fp32: 16000 values a slice): two and three chunks, the last of which writes the sums.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M", [32, 50])
 @pytest.mark.parametrize("I,J,K,P,L", [(64, 256, 5, 12, 32), (96, 129, 5, 12, 32), (92, 300, 5, 12, 32), (90, 300, 5, 12, 32), (101, 200, 5, 13, 31),
-                                       (152, 384, 130, 12, 32), (148, 384, 130, 12, 32), (64, 250, 130, 12, 32), (62, 250, 130, 12, 32)])
+                                       (152, 384, 130, 12, 32), (148, 384, 130, 12, 32), (64, 250, 130, 12, 32), (62, 250, 130, 12, 32), (400, 304, 5, 25, 20), (392, 300, 5, 25, 20)])
 def test_rows_in_lds_rule(dtype, M, I, J, K, P, L):
     N = 3
     print("case", dtype, M, I, J, K, P, L, flush=True)
