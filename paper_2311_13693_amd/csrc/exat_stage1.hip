@@ -258,17 +258,21 @@ template <int N, int I_, typename F> __device__ __forceinline__ void s1_static_f
 }
 template <int N, typename F> __device__ __forceinline__ void s1_static_for(F &&f) { s1_static_for_(f, std::integral_constant<int, 0>(), std::integral_constant<int, N>()); }
 
-// LDS of k_stage1_mfma in front of the ring of U: two steps of the tile's columns, or the Z^T fragments of a finished tile
-constexpr int s1_lds_main(int RT) { return 16 * RT * 2 * 1024 > SM_TJ * 2 * SM_GI * 4 ? 16 * RT * 2 * 1024 : SM_TJ * 2 * SM_GI * 4; }
+// LDS of k_stage1_mfma in front of the ring of U: the tile's columns of two steps (eight waves: of one), or the Z^T fragments of a finished tile
+constexpr int s1_lds_main(int RT, int NW)
+{
+    const int zt = 16 * RT * 2 * 1024, cols = SM_TJ * (NW == 8 ? 1 : 2) * SM_GI * 4;
+    return zt > cols ? zt : cols;
+}
 
-// RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), D = steps of X a wave keeps in flight, RAGGED: I is no
+// RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), RAGGED: I is no
 // multiple of 32 (a request past the end of a column goes past the end of the buffer, which reads nothing and gives zero: zeroing
 // what has arrived made every request wait for its data, 1000 x 500 x 800, A1 = 64: 0.68 -> 0.42 ms).
 //
 // Mode 1.  A wave owns 64 columns (four waves) or 32 (eight) of the workgroup's 256-column tile and walks down them in steps of 32 rows.
 // A step is requested with 16-byte-per-lane loads that run ALONG the columns (eight lanes cover the 128 bytes of one
-// column, a load covers eight columns: every request is a whole cache line), D steps ahead.  The U fragments are the same for
-// all waves: each requests its share, D steps ahead too -- a wave's loads come back in issue order, so a request with a shorter
+// column, a load covers eight columns: every request is a whole cache line), two steps ahead.  The U fragments are the same for
+// all waves: each requests its share, two steps ahead too -- a wave's loads come back in issue order, so a request with a shorter
 // lead would wait behind the long ones and cut their lead to its own -- and hands it over through a ring of four steps in LDS, with a
 // barrier after every second step.  (When every wave requested all of U, as many bytes came from the L2 as of X from memory, in the same
 // queue: the kernel's time grew with the sum of both.)  When a step arrives the wave writes it into its private LDS slot (column-major, the
@@ -291,15 +295,15 @@ constexpr int s1_lds_main(int RT) { return 16 * RT * 2 * 1024 > SM_TJ * 2 * SM_G
 // RT x MT blocks of the slice's B1 x A1 result are dealt out to the waves (block b = mt RT + rt to wave b mod NW), each
 // of which adds, over the tile's 16 column blocks, V fragment x split Z^T fragment to the blocks it owns, in registers,
 // for the whole slice.  No two waves add to the same number, so every sum has a fixed order.
-template <int RT, int MT, int D, bool RAGGED, int NW>
+template <int RT, int MT, bool RAGGED, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
 {
     extern __shared__ float smem[];
     constexpr int CT = SM_TJ / (32 * NW), NL = 4 * CT;   // 32-column tiles of a wave, requests of a step
     constexpr bool PIPE = NW == 8;                  // the steps overlap inside the wave
     constexpr int DL = PIPE ? 1 : 2;                // LDS slots per wave
+    constexpr int D = 2;                            // steps of X on their way
     constexpr int UN = 2;                           // steps per unrolled group, between two barriers
-    static_assert(D == 2, "register sets are addressed statically");
     constexpr int UF = 2 * RT, UQ = (UF + NW - 1) / NW;   // U fragments of a step, and of them a wave's share
     constexpr int SLOT = 32 * CT * SM_GI;           // floats per slot: the wave's columns x 32 rows
     constexpr int NBW = (RT * MT + NW - 1) / NW;   // result blocks per wave
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *xs = smem + w * (DL * SLOT);
     // U of the steps 2 i .. 2 i + 3, behind what the columns and mode 2 need: [4][UF][64 lanes][8]
-    unsigned char *uring = (unsigned char *)smem + s1_lds_main(RT) + lane * 16;
+    unsigned char *uring = (unsigned char *)smem + s1_lds_main(RT, NW) + lane * 16;
     float *zt = smem;                               // Z^T fragments of a finished tile: [16 jb][RT][2 halves][64 lanes][4]
     const int64_t k = blockIdx.x;
     const float *Xk = p.X + k * p.I * p.J;
@@ -774,29 +778,29 @@ int launch12(const S1Params &p, dim3 grid, size_t lds, hipStream_t st)
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
-template <int RT, int MT, int D, bool RAGGED, int NW>
+template <int RT, int MT, bool RAGGED, int NW>
 int launch_mfma_inst(const S1MParams &p, unsigned nk, hipStream_t st)
 {
-    const size_t lds = s1_lds_main(RT) + 4 * 2 * RT * 1024;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_stage1_mfma<RT, MT, D, RAGGED, NW>),
+    const size_t lds = s1_lds_main(RT, NW) + 4 * 2 * RT * 1024;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_stage1_mfma<RT, MT, RAGGED, NW>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return EXAT_ERR_HIP;
-    hipLaunchKernelGGL((k_stage1_mfma<RT, MT, D, RAGGED, NW>), dim3(nk), dim3(64 * NW), lds, st, p);
+    hipLaunchKernelGGL((k_stage1_mfma<RT, MT, RAGGED, NW>), dim3(nk), dim3(64 * NW), lds, st, p);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
-template <int RT, int MT, int D, int NW>
+template <int RT, int MT, int NW>
 int launch_mfma(const S1MParams &p, unsigned nk, hipStream_t st)
 {
-    return (p.I % SM_GI) ? launch_mfma_inst<RT, MT, D, true, NW>(p, nk, st) : launch_mfma_inst<RT, MT, D, false, NW>(p, nk, st);
+    return (p.I % SM_GI) ? launch_mfma_inst<RT, MT, true, NW>(p, nk, st) : launch_mfma_inst<RT, MT, false, NW>(p, nk, st);
 }
-template <int RT, int D, int NW>
+template <int RT, int NW>
 int launch_mfma_rt(const S1MParams &p, unsigned nk, hipStream_t st)
 {
     switch ((p.B1 + 31) / 32) {
-    case 1: return launch_mfma<RT, 1, D, NW>(p, nk, st);
-    case 2: return launch_mfma<RT, 2, D, NW>(p, nk, st);
-    case 3: return launch_mfma<RT, 3, D, NW>(p, nk, st);
-    default: return launch_mfma<RT, 4, D, NW>(p, nk, st);
+    case 1: return launch_mfma<RT, 1, NW>(p, nk, st);
+    case 2: return launch_mfma<RT, 2, NW>(p, nk, st);
+    case 3: return launch_mfma<RT, 3, NW>(p, nk, st);
+    default: return launch_mfma<RT, 4, NW>(p, nk, st);
     }
 }
 
@@ -984,10 +988,10 @@ int run_mode12(exat_stage1_s *s, const float *X, int64_t k0, int64_t nk, hipStre
         // eight.  With a slice for every compute unit or fewer there are no two to share one, and eight waves it is (four -> eight: 400 x 600 x 200,
         // A1 = 32 52.9 -> 48.8 us, x 100 51.9 -> 44.0; 800 x 900 x 240, A1 = 64 147 -> 143; but x 300, A1 = 32, 92 -> 103).
         switch ((s->A1 + 31) / 32) {
-        case 1: return nk <= 256 ? launch_mfma_rt<1, 2, 8>(m, (unsigned)nk, st) : launch_mfma_rt<1, 2, 4>(m, (unsigned)nk, st);
-        case 2: return nk <= 256 ? launch_mfma_rt<2, 2, 8>(m, (unsigned)nk, st) : launch_mfma_rt<2, 2, 4>(m, (unsigned)nk, st);
-        case 3: return launch_mfma_rt<3, 2, 8>(m, (unsigned)nk, st);
-        default: return launch_mfma_rt<4, 2, 8>(m, (unsigned)nk, st);
+        case 1: return nk <= 256 ? launch_mfma_rt<1, 8>(m, (unsigned)nk, st) : launch_mfma_rt<1, 4>(m, (unsigned)nk, st);
+        case 2: return nk <= 256 ? launch_mfma_rt<2, 8>(m, (unsigned)nk, st) : launch_mfma_rt<2, 4>(m, (unsigned)nk, st);
+        case 3: return launch_mfma_rt<3, 8>(m, (unsigned)nk, st);
+        default: return launch_mfma_rt<4, 8>(m, (unsigned)nk, st);
         }
     }
     S1Params p;
