@@ -678,6 +678,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             // The tile is split behind the last fragments, a run at a time: its request is a stage old, in a chunk's first stage
             // younger (it follows mode 2).
             constexpr int NPAIR = 4 * XPT, NSP = NF < XPT ? NF : XPT, FSP = CARRY ? FB - NSP : NF - NSP;
+            static_assert(FSP >= 0, "the whole tile is split within the stage");
             const int so1 = so == (NSLOT - 1) * SLOT ? 0 : so + SLOT, sw1 = sw == (NSLOT - 1) * SLOT ? 0 : sw + SLOT;
             const unsigned char *nxt = smem + so1 + xs_r;
             auto meet = [&]() __attribute__((always_inline)) {
