@@ -265,7 +265,7 @@ constexpr int s1_lds_main(int RT, int NW)
     return zt > cols ? zt : cols;
 }
 
-// RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), RAGGED: I is no
+// RT, MT = 32-row tiles of a and of b (A1 <= 32 RT, B1 <= 32 MT), OWN: every wave requests all of U for itself, RAGGED: I is no
 // multiple of 32 (a request past the end of a column goes past the end of the buffer, which reads nothing and gives zero: zeroing
 // what has arrived made every request wait for its data, 1000 x 500 x 800, A1 = 64: 0.68 -> 0.42 ms).
 //
@@ -274,8 +274,9 @@ constexpr int s1_lds_main(int RT, int NW)
 // column, a load covers eight columns: every request is a whole cache line), two steps ahead.  The U fragments are the same for
 // all waves: each requests its share, two steps ahead too -- a wave's loads come back in issue order, so a request with a shorter
 // lead would wait behind the long ones and cut their lead to its own -- and hands it over through a ring of four steps in LDS, with a
-// barrier after every second step.  (When every wave requested all of U, as many bytes came from the L2 as of X from memory, in the same
-// queue: the kernel's time grew with the sum of both.)  When a step arrives the wave writes it into its private LDS slot (column-major, the
+// barrier after every second step.  (When every wave requests all of U, as many bytes come from the L2 as of X from memory, in the same
+// queue: the kernel's time grows with the sum of both.  OWN does so all the same, without ring and barriers: see run_mode12 for where
+// the barriers cost more.)  When a step arrives the wave writes it into its private LDS slot (column-major, the
 // 16-byte pieces of a column XOR-swizzled with the column number so that neither the writes along the columns nor the
 // fragment reads across them collide on a bank), reads it back as MFMA operands (lane l: column l%32 of a 32-column tile,
 // eight consecutive rows), splits each value into three truncated bf16 pieces (8 + 8 + 8 significand bits: the split is
@@ -295,7 +296,7 @@ constexpr int s1_lds_main(int RT, int NW)
 // RT x MT blocks of the slice's B1 x A1 result are dealt out to the waves (block b = mt RT + rt to wave b mod NW), each
 // of which adds, over the tile's 16 column blocks, V fragment x split Z^T fragment to the blocks it owns, in registers,
 // for the whole slice.  No two waves add to the same number, so every sum has a fixed order.
-template <int RT, int MT, bool RAGGED, int NW>
+template <int RT, int MT, bool RAGGED, int NW, bool OWN>
 __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
 {
     extern __shared__ float smem[];
@@ -304,7 +305,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
     constexpr int DL = PIPE ? 1 : 2;                // LDS slots per wave
     constexpr int D = 2;                            // steps of X on their way
     constexpr int UN = 2;                           // steps per unrolled group, between two barriers
-    constexpr int UF = 2 * RT, UQ = (UF + NW - 1) / NW;   // U fragments of a step, and of them a wave's share
+    static_assert(!(OWN && PIPE), "eight waves share U");
+    constexpr int UF = 2 * RT, UQ = OWN ? UF : (UF + NW - 1) / NW;   // U fragments of a step, and of them those that a wave requests
     constexpr int SLOT = 32 * CT * SM_GI;           // floats per slot: the wave's columns x 32 rows
     constexpr int NBW = (RT * MT + NW - 1) / NW;   // result blocks per wave
     constexpr bool ONE_RT = NW % RT == 0;        // all blocks of a wave lie in one row tile rt: its Z fragments are split once
@@ -345,7 +347,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
     auto swz = [](int c, int q) { return c * SM_GI + 4 * (q ^ ((c >> 1) & 7)); };
 
     s1_f32x4 xr[D][NL];             // ring of steps of X as requested: xr[d][m] = this lane's piece of load m
-    s1_bf16x8 ur[D][UQ];           // this wave's share of the U fragments (half-step, row tile) of two steps later
+    s1_bf16x8 ur[D][UQ];           // this wave's U fragments (half-step, row tile): its share of those of two steps later, or (OWN) all of the step
 
     // requests of padded step n = tile * ngp + g: X of the step itself if it exists, else of the last step of the tile
     // (or of the last tile), which is then multiplied with the zero fragment
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
         const int tile = n / ngp, g = n - tile * ngp;
 #pragma unroll
         for (int i = 0; i < UQ; i++) {
-            const int f = (w + NW * i) % UF, rt = f % RT;
+            const int f = OWN ? i : (w + NW * i) % UF, rt = f % RT;
             int ks = 2 * g + f / RT;
             ks = (g < ng && ks < nks) ? ks : nks;      // the zero fragment for what lies past the end
             dst[i] = __builtin_bit_cast(s1_bf16x8, __builtin_amdgcn_raw_buffer_load_b128(urs, lane * 16, (rt * (nks + 1) + ks) * 1024, 0));
@@ -471,16 +473,24 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
         lds_barrier();   // the slots take the LDS back
     };
 
-    s1_bf16x8 u0[D][UQ];
-    s1_static_for<D>([&](auto dc) {
-        constexpr int d = decltype(dc)::value;
-        request_u(d, u0[d]);
-        request_x(PIPE ? d + 1 : d, xr[d]);
-        request_u(D + d, ur[d]);
-    });
-    __builtin_amdgcn_sched_barrier(0);   // all of them ahead of the first wait
-    s1_static_for<D>([&](auto dc) { store_u(decltype(dc)::value, u0[decltype(dc)::value]); });
-    lds_barrier();
+    if constexpr (OWN)
+        s1_static_for<D>([&](auto dc) {
+            constexpr int d = decltype(dc)::value;
+            request_x(d, xr[d]);
+            request_u(d, ur[d]);
+        });
+    else {
+        s1_bf16x8 u0[D][UQ];
+        s1_static_for<D>([&](auto dc) {
+            constexpr int d = decltype(dc)::value;
+            request_u(d, u0[d]);
+            request_x(PIPE ? d + 1 : d, xr[d]);
+            request_u(D + d, ur[d]);
+        });
+        __builtin_amdgcn_sched_barrier(0);   // all of them ahead of the first wait
+        s1_static_for<D>([&](auto dc) { store_u(decltype(dc)::value, u0[decltype(dc)::value]); });
+        lds_barrier();
+    }
     int up = 0;   // ring slot of the U of this pair of steps
     // PIPE: pieces l, m, h of the column tiles and U fragments for the half-steps h = 0, 1 of a step, and what the pieces are made from
     s1_u32x4 xp[PIPE ? 2 : 1][3][CT];
@@ -566,16 +576,18 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
                     });
                 } else {
                     float *slot = xs + sl * SLOT;
-                    load_uf(up + (dd & 1), 0);
+                    if constexpr (!OWN) load_uf(up + (dd & 1), 0);
                     // the step that has arrived goes to the wave's LDS slot, and its registers out again for step n + D
 #pragma unroll
                     for (int m = 0; m < NL; m++) *(s1_f32x4 *)(slot + swz(8 * m + (lane >> 3), lane & 7)) = xr[d][m];
                     request_x(n + D, xr[d]);
-                    store_u((up ^ 2) + (dd & 1), ur[d]);
-                    request_u(n + 2 + D, ur[d]);
+                    if constexpr (!OWN) {
+                        store_u((up ^ 2) + (dd & 1), ur[d]);
+                        request_u(n + 2 + D, ur[d]);
+                    }
 #pragma unroll
                     for (int h = 0; h < 2; h++) {
-                        if (h == 1) load_uf(up + (dd & 1), 1);
+                        if (!OWN && h == 1) load_uf(up + (dd & 1), 1);
                         s1_bf16x8 xp[3][CT];   // pieces l, m, h of the two column tiles
 #pragma unroll
                         for (int ct = 0; ct < CT; ct++) {
@@ -593,9 +605,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_stage1_mfma(const S1MParams p)
                             for (int ct = 0; ct < CT; ct++)
 #pragma unroll
                                 for (int rt = 0; rt < RT; rt++)
-                                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[pc][ct], uf[h][rt], acc[rt][ct], 0, 0, 0);
+                                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[pc][ct], OWN ? ur[d][(h * RT + rt) % UQ] : uf[h][rt], acc[rt][ct], 0, 0, 0);
                     }
-                    if constexpr (dd & 1) {
+                    if constexpr (OWN) request_u(n + D, ur[d]);
+                    else if constexpr (dd & 1) {
                         lds_barrier();
                         up ^= 2;
                     }
@@ -778,29 +791,29 @@ int launch12(const S1Params &p, dim3 grid, size_t lds, hipStream_t st)
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
 
-template <int RT, int MT, bool RAGGED, int NW>
+template <int RT, int MT, bool RAGGED, int NW, bool OWN>
 int launch_mfma_inst(const S1MParams &p, unsigned nk, hipStream_t st)
 {
-    const size_t lds = s1_lds_main(RT, NW) + 4 * 2 * RT * 1024;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_stage1_mfma<RT, MT, RAGGED, NW>),
+    const size_t lds = s1_lds_main(RT, NW) + (OWN ? 0 : 4 * 2 * RT * 1024);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_stage1_mfma<RT, MT, RAGGED, NW, OWN>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return EXAT_ERR_HIP;
-    hipLaunchKernelGGL((k_stage1_mfma<RT, MT, RAGGED, NW>), dim3(nk), dim3(64 * NW), lds, st, p);
+    hipLaunchKernelGGL((k_stage1_mfma<RT, MT, RAGGED, NW, OWN>), dim3(nk), dim3(64 * NW), lds, st, p);
     return hipGetLastError() == hipSuccess ? EXAT_OK : EXAT_ERR_HIP;
 }
-template <int RT, int MT, int NW>
+template <int RT, int MT, int NW, bool OWN>
 int launch_mfma(const S1MParams &p, unsigned nk, hipStream_t st)
 {
-    return (p.I % SM_GI) ? launch_mfma_inst<RT, MT, true, NW>(p, nk, st) : launch_mfma_inst<RT, MT, false, NW>(p, nk, st);
+    return (p.I % SM_GI) ? launch_mfma_inst<RT, MT, true, NW, OWN>(p, nk, st) : launch_mfma_inst<RT, MT, false, NW, OWN>(p, nk, st);
 }
-template <int RT, int NW>
+template <int RT, int NW, bool OWN = false>
 int launch_mfma_rt(const S1MParams &p, unsigned nk, hipStream_t st)
 {
     switch ((p.B1 + 31) / 32) {
-    case 1: return launch_mfma<RT, 1, NW>(p, nk, st);
-    case 2: return launch_mfma<RT, 2, NW>(p, nk, st);
-    case 3: return launch_mfma<RT, 3, NW>(p, nk, st);
-    default: return launch_mfma<RT, 4, NW>(p, nk, st);
+    case 1: return launch_mfma<RT, 1, NW, OWN>(p, nk, st);
+    case 2: return launch_mfma<RT, 2, NW, OWN>(p, nk, st);
+    case 3: return launch_mfma<RT, 3, NW, OWN>(p, nk, st);
+    default: return launch_mfma<RT, 4, NW, OWN>(p, nk, st);
     }
 }
 
@@ -982,14 +995,28 @@ int run_mode12(exat_stage1_s *s, const float *X, int64_t k0, int64_t nk, hipStre
         S1MParams m;
         m.X = X; m.I = s->I; m.J = s->J; m.A1 = s->A1; m.B1 = s->B1; m.Ud = (const __bf16 *)s->Ud; m.Vd = (const __bf16 *)s->Vd;
         m.Q = s->Q; m.k0 = k0;
-        // Two steps in flight per wave measured best at every size (more cost registers and gain nothing: the
-        // waves of a compute unit together keep 64 to 128 KiB on their way).  Up to 64 rows a the registers allow two
-        // workgroups of four waves per compute unit (one of eight waves: 1000^3, A1 = 64 0.78 -> 0.80 ms, 512^3 103 -> 114 us), above that one of
-        // eight.  With a slice for every compute unit or fewer there are no two to share one, and eight waves it is (four -> eight: 400 x 600 x 200,
-        // A1 = 32 52.9 -> 48.8 us, x 100 51.9 -> 44.0; 800 x 900 x 240, A1 = 64 147 -> 143; but x 300, A1 = 32, 92 -> 103).
+        // Above 64 rows a, one workgroup of eight waves per compute unit is all that the registers allow.  Up to 64 rows there are three forms with
+        // the same sums: eight waves, four waves with U through LDS, of which two workgroups share a compute unit, and four waves that each request
+        // all of U.  Speed over that of the last, 29 shapes of slices from 64 x 64 to 1000 x 1000, 60 to 1200 of them, with X another tensor in every
+        // call, from memory | the same one, from the last-level cache if it fits:
+        // - A slice for every compute unit or fewer: there are no two workgroups to share one, and eight waves it is (0.96 to 1.35 | 0.96 to 1.28),
+        //   unless a slice has fewer than six steps, for which their pipeline is not worth filling (0.92 to 0.98 | 0.92 to 1.01).  With more
+        //   slices they reach 0.67 to 1.03.
+        // - More slices: U through LDS keeps U's bytes out of the queue of X, but the waves wait for each other.  X beyond the 256 MB of that cache:
+        //   1.00 to 1.09.  Up to there 0.99 to 1.08 | 0.96 to 1.06, but for slices of up to 128 columns, whose tile leaves two waves or more idle
+        //   (0.91 to 1.09 | 0.88 to 1.01), for small slices (0.94 to 1.05 | 0.94 to 1.04, most below 1), and up to 32 rows a, where U is half as much,
+        //   while most compute units have one workgroup only (257 to 310 slices: 0.97 to 1.05 | 0.91 to 1.02).
+        const int64_t slice = s->I * s->J, steps = (s->J + SM_TJ - 1) / SM_TJ * ((s->I + SM_GI - 1) / SM_GI);
+        const bool beyond = slice * nk > (256LL << 20) / 4;
+        const bool eight = nk <= 256 && steps >= 6;
+        const bool own = nk <= 256 ? steps < 6 : !beyond && (s->J <= 128 || slice < 32 * 1024 || (s->A1 <= 32 && nk <= 320));
         switch ((s->A1 + 31) / 32) {
-        case 1: return nk <= 256 ? launch_mfma_rt<1, 8>(m, (unsigned)nk, st) : launch_mfma_rt<1, 4>(m, (unsigned)nk, st);
-        case 2: return nk <= 256 ? launch_mfma_rt<2, 8>(m, (unsigned)nk, st) : launch_mfma_rt<2, 4>(m, (unsigned)nk, st);
+        case 1:
+            if (eight) return launch_mfma_rt<1, 8>(m, (unsigned)nk, st);
+            return own ? launch_mfma_rt<1, 4, true>(m, (unsigned)nk, st) : launch_mfma_rt<1, 4>(m, (unsigned)nk, st);
+        case 2:
+            if (eight) return launch_mfma_rt<2, 8>(m, (unsigned)nk, st);
+            return own ? launch_mfma_rt<2, 4, true>(m, (unsigned)nk, st) : launch_mfma_rt<2, 4>(m, (unsigned)nk, st);
         case 3: return launch_mfma_rt<3, 8>(m, (unsigned)nk, st);
         default: return launch_mfma_rt<4, 8>(m, (unsigned)nk, st);
         }

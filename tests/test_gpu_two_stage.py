@@ -83,8 +83,8 @@ def test_first_stage_matrix_core_form_agrees_with_sparse_form(monkeypatch):
     assert err <= 1e-6 and err > 0.0   # > 0: the two runs did take different kernels
 
 
-@pytest.mark.parametrize("L,K", [(16, 3), (16, 257), (32, 3), (32, 257), (48, 3), (64, 3)])   # one to four row tiles of a: four waves up to two with
-@pytest.mark.parametrize("I,J", [(4, 40), (32, 256), (36, 257), (64, 255), (100, 513), (160, 33)])   # more than 256 slices, else eight
+@pytest.mark.parametrize("L,K", [(16, 3), (16, 257), (32, 3), (32, 257), (48, 3), (64, 3)])   # one to four row tiles of a
+@pytest.mark.parametrize("I,J", [(4, 40), (32, 256), (36, 257), (64, 255), (100, 513), (160, 33)])   # (100, 513) with eight waves for 3 slices
 def test_first_stage_matrix_core_steps(L, K, I, J):
     """One step of 32 rows, an odd number of steps, several tiles of 256 columns: the ring of U in LDS runs on through the steps that fill
     up a pair and through the tiles, and columns and steps past the end contribute nothing."""
@@ -96,6 +96,43 @@ def test_first_stage_matrix_core_steps(L, K, I, J):
     # three exact pieces: what is left are the roundings of the fp32 sums, far below 1e-6 at these lengths
     assert _rel(got, ref) <= 1e-6
     assert np.abs(got - ref).max() <= 3e-6 * np.abs(ref).max()
+
+
+# A resident call and its slabs from host memory take different forms of the matrix-core kernel, whose sums have the same order: up to 64 rows a
+# slabs of at least six steps run eight waves; resident tensors of more than 256 slices four, with U requested by every wave (own) or through LDS
+# (shared).  Column tiles one column over, steps that end inside 32 rows, one tile of many steps, many tiles of one step, the ends of the rules.
+@pytest.mark.parametrize("L,I,J,K,slab", [
+    (16, 196, 257, 321, 250),    # shared, eight
+    (16, 196, 257, 320, 256),    # own, eight
+    (16, 124, 260, 330, 70),     # own (slices of less than 32768 values), eight
+    (16, 128, 256, 330, 70),     # shared, own (4 steps)
+    (16, 4, 12300, 321, 107),    # shared, eight: 49 tiles of one step
+    (16, 384, 129, 321, 200),    # shared, eight: one tile of 12 steps
+    (16, 400, 128, 330, 110),    # own (128 columns), eight
+    (16, 96, 200, 300, 100),     # own, own (3 steps)
+    (16, 160, 256, 6, 2),        # own, own (5 steps)
+    (16, 192, 256, 6, 2),        # eight, eight
+    (32, 64, 513, 257, 256),     # shared, eight
+    (32, 132, 260, 300, 7),      # shared, eight
+    (32, 128, 255, 257, 129),    # own (slices of less than 32768 values), own
+    (32, 516, 127, 260, 130),    # own, eight
+    (32, 36, 257, 257, 257),     # own, own
+])
+def test_first_stage_forms_agree(monkeypatch, L, I, J, K, slab):
+    print("case", L, I, J, K, slab, flush=True)
+    ts = _ts(I=I, J=J, K=K, L=L, M=20, N=2, index=311)
+    X = _x(29, I, J, K)
+    mats = wl.first_stage_matrices(ts)
+    monkeypatch.setenv("EXAT_STAGE1_SLAB_BYTES", str(slab * I * J * 4))
+    st = exat.Stage1(I, J, K, *mats)
+    flat = torch.from_numpy(X.reshape(-1, order="F"))
+    res = st.apply(flat.cuda()).clone()
+    host = st.apply_host(flat).clone()
+    torch.cuda.synchronize()
+    assert torch.equal(res, host)
+    got = res.cpu().numpy().astype(np.float64).reshape(st.dims, order="F")
+    st.close()
+    assert _rel(got, oracle.first_stage(X, *mats)) <= 1e-6
 
 
 def test_first_stage_general_csr_and_run_to_run():
