@@ -536,8 +536,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mode12_mp(const Mode12Params p, 
             if constexpr (!PTR) {
                 // One request per four values (bf16: eight), without a branch: what lies outside the box is out of range by the lane's offset, and
                 // gives zeros (bf16: see mask_x).  Requests under a condition brought a stretch of scalar code and branches into every stage, and
-                // the waits behind them counted with the shorter of the paths.  Whole calls, before -> now: 1000^3 fp32, 1550 rows 16.61 -> 16.42 ms,
-                // bf16, 2400 rows 6.59 -> 6.44; 250^3 fp32, 800 rows 253 -> 249 us.
+                // the waits behind them counted with the shorter of the paths.  Whole calls, before -> now: 512^3 fp32, 512 rows 652 -> 644 us, 1000^3
+                // bf16, 2400 rows 6.59 -> 6.44 ms; 1000^3 fp32, 1550 rows between nothing and 1.5 %, which is the spread.
                 const int i = x_first(ps);
 #pragma unroll
                 for (int c = 0; c < XW; c++) {
